@@ -88,10 +88,9 @@ enum {
      * exists so that both code paths can be tested and timed. */
     RIB_FLAG_FORCE_ROW_MAX = 1,
     /* Use the wide workgroups (8 waves sharing each streamed tile) whenever the
-     * window has a multiple of 512 tokens, forward and backward.  By default
-     * they are chosen only for windows of 4096 tokens or more with enough work
-     * to fill the chip several times over.  Same results within rounding (tile
-     * boundaries do not enter the arithmetic).  For tests and tuning. */
+     * window has a multiple of 512 tokens, in the bf16 forward; the other kernels
+     * have one workgroup shape.  Same results within rounding (tile boundaries
+     * do not enter the arithmetic).  For tests and tuning. */
     RIB_FLAG_WIDE = 2,
     /* Run on the vector-ALU kernels even where a matrix-core kernel serves the
      * problem.  Same results within rounding; for tests and comparisons. */

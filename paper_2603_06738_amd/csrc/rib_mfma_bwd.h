@@ -1,0 +1,913 @@
+// RIB window attention, backward, on the gfx950 matrix cores (bf16 MFMA, fp32
+// accumulation).  Gradient formulas: include/rib_attn.h (chain rule through paper
+// Sec. 2.2 and Sec. 3.1 Eq. 5-6).
+//
+// Two kernels, both free of atomics so that every output is run-to-run identical:
+//
+//   dq kernel   -- a wave owns 64 queries (MFMA B operands in registers) and the workgroup
+//     streams the unit's keys through LDS.  Per 32x32 block it forms the TRANSPOSED scores
+//     S^T = K_aug Q_aug^T and dP^T = V dO^T (a lane owns a QUERY column), so dS^T is the B
+//     operand of dQ_aug^T += K_aug^T dS^T (contraction over keys).
+//   dkv kernel  -- a wave owns 64 keys and the workgroup streams the queries; S = Q_aug K_aug^T
+//     and dP = dO V^T with a lane owning a KEY column, so P and dS, packed to bf16, are the B
+//     operands of dV^T += dO^T P and dK_aug^T += Q_aug^T dS (contractions over queries).
+//
+//   In both kernels it is Q_aug that carries scale * log2(e), rounded to bf16 exactly as the
+//   forward rounds it, so the recomputed logits are the forward's bit for bit.  P is recomputed
+//   as exp2(S - LSE) and dS = P (dP - delta).  Where the padding of the augmented rows has two
+//   free columns neither subtraction costs a vector instruction: -LSE*log2(e), split into a bf16
+//   high and low part, rides in the last two columns of Q_aug against ones in K_aug, and -delta
+//   rides the same way in the padding of dO against ones in V.  Without free columns (template
+//   flags XS for the scores, XD for dP) they enter as the C operand of the first MFMA (dkv: a
+//   lane's accumulator rows are queries) or as a lane constant added to the result (dq: a lane
+//   is one query).
+//
+//   What bounds them: the matrix pipe (11 MFMAs a 32x32 block in dkv, 9 in dq, 32 clk each) and
+//   the vector ALU (16 exp2, 16 multiplies, 8 or 16 packs and whatever the staging costs, about
+//   340 / 260 clk) nearly balance, and two waves of 256 registers share a SIMD.  So the streamed
+//   tiles are kept as plain rows in LDS, written as 8-byte pieces, and the operands of the
+//   products that contract over tokens are read TRANSPOSED from the same rows
+//   (ds_read_b64_tr_b16): no transposed image, no byte permutes to build one.  One pair of kernels
+//   serves every window of 64 or more tokens: a last partial tile repeats the window's last token
+//   and masks its rows of S (the separate kernels for windows that were not whole 256-token blocks,
+//   with their predicated staging, took 650 us where these take 300 us: 24 x 24 windows, 8 x 96 x 96
+//   tokens, 6 heads, d = 30, r = 18).
+//
+//   The last r columns of dQ_aug / dK_aug are this unit's contribution to dF_q /
+//   dF_k (Sec. 3.1: the RIB features are shared by all windows); they go to a
+//   per-unit fp32 scratch and are summed over windows in a fixed order afterwards.
+#pragma once
+
+#include "rib_common.h"
+
+namespace rib {
+namespace bwd {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+// P and dS go to bf16 by truncation (one byte-permute per pair), which loses half a unit in the
+// last place on average (relative 2^-8 * 0.7213 for log-uniform mantissas).  The loss is made up
+// BEFORE the truncation: this constant is added to the -LSE * log2(e) that rides with every
+// logit, so P (and with it dS = P (dP - delta)) is scaled up by the mean loss and then truncated.
+// Values that are exactly representable (P = 1 of a one-hot row, P = 2^-k of a uniform row) come
+// through unchanged, the others are right on average.
+constexpr float kTruncLog2 = 0.0040593f;   // log2(1 + 2^-8 * 0.7213)
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    bf16x2 v;
+    v[0] = (__bf16)a;
+    v[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ uint32_t scale_pair(uint32_t w, float s) { return pack_bf16(lo_bf16(w) * s, hi_bf16(w) * s); }
+// x as a bf16 pair (hi, lo) with hi + lo == x to ~2^-17 relative
+__device__ __forceinline__ uint32_t split_bf16(float x)
+{
+    bf16x2 v;
+    v[0] = (__bf16)x;
+    v[1] = (__bf16)(x - (float)v[0]);
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ uint32_t trunc_pack(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    uint4 w = {a, b, c, d};
+    return __builtin_bit_cast(bf16x8, w);
+}
+__device__ __forceinline__ f32x16 mfma(const bf16x8 &a, const bf16x8 &b, const f32x16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// The thread id as a value the optimiser cannot trace back: lane constants derived from it are
+// recomputed where they are used instead of being held in registers across the MFMA blocks.
+__device__ __forceinline__ int opaque_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// Two dwords at a 4-byte aligned address.
+struct __attribute__((packed, aligned(4))) dword2 {
+    uint32_t x, y;
+};
+struct __attribute__((packed, aligned(4))) float2u {
+    float x, y;
+};
+struct __attribute__((packed, aligned(4))) float4u {
+    float x, y, z, w;
+};
+
+// A operand of a product that contracts over tokens: 32 columns starting at `c0` (a lane's row is
+// column c0 + lane % 32) of 16 tokens starting at row image `rows`, in the order the 32x32
+// accumulator layout hands its rows to the next MFMA (tokens 4*hf + 0..3, then 8 + 4*hf + 0..3).
+// ds_read_b64_tr_b16 transposes 4 rows x 16 columns per group of 16 lanes: lane a of the group
+// names row a / 4, columns 4 * (a % 4) .. + 3, and receives column a of the four rows.
+// `lane_off` = tr_lane_offset<STRIDE>().
+template <int STRIDE>
+__device__ __forceinline__ int tr_lane_offset(int lane)
+{
+    const int a = lane & 15, chalf = (lane >> 4) & 1, hf = lane >> 5;
+    return (4 * hf + (a >> 2)) * STRIDE + 16 * chalf + 4 * (a & 3);
+}
+typedef s16x4 __attribute__((address_space(3))) *lds_s16x4;
+template <int STRIDE>
+__device__ __forceinline__ bf16x8 read_tr(const bf16_t *rows, int lane_off, int c0)
+{
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(rows + lane_off + c0));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(rows + lane_off + c0 + 8 * STRIDE));
+    return u.v;
+}
+template <int N>
+__device__ __forceinline__ void read_rows(bf16x8 (&dst)[N], const bf16_t *base)
+{
+#pragma unroll
+    for (int t = 0; t < N; ++t) dst[t] = *(const bf16x8 *)(base + 16 * t);
+}
+
+// LDS image of one streamed tile of T tokens: X = augmented rows (content | RIB | zero pad | two
+// extra columns), Y = value-like rows (content | zero pad | two extra columns), then (XS / XD) the
+// tile's -LSE*log2(e) and -delta as floats.  Strides are odd multiples of 16 bytes (conflict-free
+// 16-byte reads).  Three stages rotate: while a tile is multiplied, the next one is complete (its
+// first operands are read ahead of the barrier) and the one after it is being written.
+template <int DQK, int T>
+struct Lay {
+    static constexpr int DVK = 32;
+    static constexpr int XS = DQK + 8, YS = DVK + 8;
+    static constexpr int YR = T * XS, EX = YR + T * YS;
+    static constexpr int STAGE = EX + 4 * T;                        // bf16 elements
+    static constexpr int KS = DQK / 16, VS = DVK / 16;
+    static constexpr int RB = (DQK + 31) / 32;                      // 32-row blocks of dQ_aug^T / dK_aug^T
+    static constexpr int NSTAGE = 3;
+    static constexpr int WAVE_STAT = 64 * (XS + YS);                // one wave's stationary rows (before the first tile)
+    static constexpr size_t bytes(int waves)
+    {
+        return (size_t)(NSTAGE * STAGE > waves * WAVE_STAT ? NSTAGE * STAGE : waves * WAVE_STAT) * sizeof(bf16_t);
+    }
+};
+
+// A window of one image: where its tokens lie, relative to the image's first token.  ALN (window
+// side a multiple of 8): eight consecutive tokens lie in one window row, so a wave's row is scalar
+// arithmetic and a lane adds its column (wrapped once at the image edge).  Otherwise the separable
+// map in LDS (row bases, then wrapped columns), with lookups clamped to the window's last token.
+struct Win {
+    const int *rowb, *colo;
+    uint32_t inv_m;
+    int M, last, y0, x0, H, W;
+    // `n0`: the wave's first token (uniform), this lane's token is n0 + l
+    template <bool ALN>
+    __device__ __forceinline__ uint32_t token(int n0, int l) const
+    {
+        if (ALN) {
+            const int iy = (int)__umulhi((uint32_t)n0, inv_m);
+            int y = y0 + iy;
+            if (y >= H) y -= H;
+            const uint32_t x = (uint32_t)(x0 + n0 - iy * M) + (uint32_t)l, xw = x - (uint32_t)W;
+            return (x < xw ? x : xw) + (uint32_t)(y * W);
+        }
+        const int n = n0 + l, nc = n < last ? n : last;
+        const int iy = (int)__umulhi((uint32_t)nc, inv_m);
+        return (uint32_t)(rowb[iy] + colo[nc - __mul24(iy, M)]);
+    }
+    // any token (per lane)
+    __device__ __forceinline__ uint32_t any(int n) const
+    {
+        const int iy = (int)__umulhi((uint32_t)n, inv_m);
+        int y = y0 + iy;
+        if (y >= H) y -= H;
+        int x = x0 + n - __mul24(iy, M);
+        if (x >= W) x -= W;
+        return (uint32_t)(y * W + x);
+    }
+};
+template <bool ALN>
+__device__ __forceinline__ Win window_of(const Geo &g, int w, int nt, int *lds, int &b)
+{
+    const int wx = w % g.nwx, t = w / g.nwx, wy = t % g.nwy;
+    b = t / g.nwy;
+    Win m;
+    m.y0 = wy * g.M + g.s, m.x0 = wx * g.M + g.s;
+    m.rowb = lds, m.colo = lds + g.M;
+    m.inv_m = g.inv_m, m.M = g.M, m.last = g.N - 1, m.H = g.H, m.W = g.W;
+    if (!ALN) {
+        for (int i = threadIdx.x; i < 2 * g.M; i += nt) {
+            if (i < g.M) {
+                const int y = m.y0 + i;
+                lds[i] = (y >= g.H ? y - g.H : y) * g.W;
+            } else {
+                const int x = m.x0 + i - g.M;
+                lds[i] = x >= g.W ? x - g.W : x;
+            }
+        }
+    }
+    return m;
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs; renumber them so that each XCD works on a
+// contiguous range of (unit, block) and its L2 sees all users of a window's lines.
+__device__ __forceinline__ void block_coords(int nblk, int64_t &u, int &blk)
+{
+    const int G = gridDim.x, per = G >> 3, rem = G & 7, xcd = blockIdx.x & 7;
+    const int logical = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
+    u = logical / nblk;
+    blk = logical - (int)(u * nblk);
+}
+
+// What a lane moves when 8 lanes share a token: the dword pair 2j, 2j+1 of the content row and of
+// the RIB row (a second pair for rows longer than 32 values).  Lanes past the end slide back onto
+// the last pair (they duplicate a neighbour); rows of a single dword (d = 2, r = 2) move alone.
+// TINY compiles those single-dword rows (and r = 0) in; without it d >= 4 and r >= 4.
+struct Piece {
+    int dc, f0, f1;                 // first dword of the content / RIB pieces
+    bool c1, f1d, fnone;            // single-dword content / RIB rows, no RIB at all (uniform)
+};
+template <bool TINY>
+__device__ __forceinline__ Piece piece_of(const Geo &g, int j)
+{
+    const int hp = g.d >> 1, rh = g.r >> 1;
+    Piece p;
+    p.c1 = TINY && hp < 2;
+    p.f1d = TINY && rh < 2;
+    p.fnone = TINY && rh == 0;
+    p.dc = p.c1 ? 0 : (2 * j < hp - 2 ? 2 * j : hp - 2);
+    p.f0 = p.f1d ? 0 : (2 * j < rh - 2 ? 2 * j : rh - 2);
+    p.f1 = p.f1d ? 0 : (16 + 2 * j < rh - 2 ? 16 + 2 * j : rh - 2);
+    return p;
+}
+__device__ __forceinline__ dword2 get8(const char *base, uint32_t off, bool one)
+{
+    dword2 v;
+    if (one) v.x = *(const uint32_t *)(base + off), v.y = 0u;
+    else v = *(const dword2 *)(base + off);
+    return v;
+}
+__device__ __forceinline__ void put8(bf16_t *dst, const dword2 &v, bool one)
+{
+    if (one) *(uint32_t *)dst = v.x;
+    else *(dword2 *)dst = v;
+}
+
+// Streamed operand pair of a unit.  QDO: X = q (strided), Y = dO (dense), extras = LSE, delta.
+// Otherwise X = k, Y = v (both strided), extras = ones.
+struct Stream {
+    const char *xb, *yb, *fb;       // this image's and head's slices; this head's RIB table
+    const float *lse, *delta;       // this unit's rows (QDO)
+    uint32_t xs, ys, frow;          // token strides and RIB row in bytes
+};
+
+template <int DQK>
+struct Regs {
+    dword2 x[2], y[2], fa[2], fb[DQK == 64 ? 2 : 1];
+    float e0;
+};
+
+// Request tile `tile`: slots tid and tid + NT of the tile's T * 8 (8 lanes a token).
+template <int DQK, int T, bool QDO, bool ALN, bool TINY>
+__device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
+{
+    const int lane = opaque_tid() & 63, l = lane >> 3;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int slot = p * nt + wave * 64;                // the wave's first slot
+        if (T == 64 || slot < T * 8) {
+            const int n0 = tile * T + (slot >> 3);
+            const uint32_t t = win.token<ALN>(n0, l);
+            rg.x[p] = get8(s.xb, __umul24(t, s.xs) + 4u * pc.dc, pc.c1);
+            rg.y[p] = get8(s.yb, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+            if (!pc.fnone) {
+                const int n = n0 + l, nc = ALN ? n : (n < win.last ? n : win.last);
+                const uint32_t fr = __umul24((uint32_t)nc, s.frow);
+                rg.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
+                if (DQK == 64) rg.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+            }
+        }
+    }
+    if (QDO && wave < T / 32) {     // LSE by the lower, delta by the upper T of T / 32 waves' lanes
+        const int tid = wave * 64 + lane, n = tile * T + (tid & (T - 1));
+        rg.e0 = ((tid & T) ? s.delta : s.lse)[ALN ? n : (n < win.last ? n : win.last)];
+    }
+}
+
+template <int DQK, int T, bool QDO, bool XS, bool XD, bool TINY>
+__device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int nt, int wave)
+{
+    using L = Lay<DQK, T>;
+    const int lane = opaque_tid() & 63, l = lane >> 3;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+    bf16_t *xr = S + __mul24(l, L::XS) + 2 * pc.dc, *yr = S + L::YR + __mul24(l, L::YS) + 2 * pc.dc;
+    bf16_t *fr = S + __mul24(l, L::XS) + g.d + 2 * pc.f0, *fr1 = S + __mul24(l, L::XS) + g.d + 2 * pc.f1;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int slot = p * nt + wave * 64;
+        if (T == 64 || slot < T * 8) {
+            dword2 x = rg.x[p], fa = rg.fa[p], fb;
+            if (DQK == 64) fb = rg.fb[p];
+            if (QDO) {
+                x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
+                fa.x = scale_pair(fa.x, sp), fa.y = scale_pair(fa.y, sp);
+                if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
+            }
+            const int r0 = slot >> 3;                       // (uniform)
+            put8(xr + r0 * L::XS, x, pc.c1);
+            put8(yr + r0 * L::YS, rg.y[p], pc.c1);
+            if (!pc.fnone) {
+                put8(fr + r0 * L::XS, fa, pc.f1d);
+                if (DQK == 64) put8(fr1 + r0 * L::XS, fb, pc.f1d);
+            }
+        }
+    }
+    if (QDO && wave < T / 32) {
+        const int tid = wave * 64 + lane, row = tid & (T - 1);
+        const bool dl = (tid & T) != 0;
+        const float v = dl ? -rg.e0 : kTruncLog2 - rg.e0 * kLog2e;
+        const uint32_t pk = split_bf16(v);
+        if (dl) {
+            if (XD) ((float *)(S + L::EX))[T + row] = v;
+            else *(uint32_t *)(S + L::YR + row * L::YS + L::DVK - 2) = pk;
+        } else {
+            if (XS) ((float *)(S + L::EX))[row] = v;
+            else *(uint32_t *)(S + row * L::XS + DQK - 2) = pk;
+        }
+    }
+}
+
+// The columns no staging code writes, once for every row of every stage: zero padding (it meets
+// the zero padding of the stationary operands, so it only has to be finite), and for K / V tiles
+// the ones that LSE and delta meet.
+template <int DQK, int T, bool QDO, bool XS, bool XD>
+__device__ __forceinline__ void init_pads(const Geo &g, bf16_t *stages, int nt)
+{
+    using L = Lay<DQK, T>;
+    for (int e = threadIdx.x; e < L::NSTAGE * T; e += nt) {
+        bf16_t *xr = stages + (e / T) * L::STAGE + (e % T) * L::XS, *yr = stages + (e / T) * L::STAGE + L::YR + (e % T) * L::YS;
+        for (int c = g.d + g.r; c < DQK; c += 2)
+            if (c < DQK - 2 || XS) *(uint32_t *)(xr + c) = 0u;
+            else if (!QDO) *(uint32_t *)(xr + c) = 0x3f803f80u;
+        for (int c = g.d; c < L::DVK; c += 2)
+            if (c < L::DVK - 2 || XD) *(uint32_t *)(yr + c) = 0u;
+            else if (!QDO) *(uint32_t *)(yr + c) = 0x3f803f80u;
+    }
+}
+
+// Raw words of a wave's 64 stationary rows between their request and their staging: 8 lanes share
+// a row, 8 rows a pass.
+template <int DQK, bool WITH_O>
+struct StatRegs {
+    dword2 x[8], y[8], fa[8], fb[DQK == 64 ? 8 : 1], o[WITH_O ? 8 : 1];
+    float e0, e1;
+};
+template <int DQK, bool QDO, bool WITH_O, bool ALN, bool TINY>
+__device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo &g, const Win &win, const Stream &s, int n0,
+                                             const char *ob, bool from_o)
+{
+    const int lane = threadIdx.x & 63, l = lane >> 3;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        // (a wave past the window's end repeats its last rows)
+        const int nb = ALN && n0 + p * 8 > win.last - 7 ? win.last - 7 : n0 + p * 8, n = nb + l;
+        const uint32_t t = win.token<ALN>(nb, l);
+        r.x[p] = get8(s.xb, __umul24(t, s.xs) + 4u * pc.dc, pc.c1);
+        r.y[p] = get8(s.yb, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+        if (WITH_O && from_o) r.o[p] = get8(ob, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+        if (!pc.fnone) {
+            const uint32_t fr = __umul24((uint32_t)(n < win.last ? n : win.last), s.frow);
+            r.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
+            if (DQK == 64) r.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+        }
+    }
+    r.e0 = r.e1 = 0.f;
+    if (QDO) {
+        const int n = n0 + lane, nc = n < win.last ? n : win.last;
+        r.e0 = s.lse[nc];
+        if (!WITH_O || !from_o) r.e1 = s.delta[nc];
+    }
+}
+
+// delta_i = dO_i . O_i (paper Sec. 2.2 backward; the softmax Jacobian's row term) of the wave's 64
+// rows from the words the lanes hold: each lane multiplies its two channel pairs, three halving
+// steps over the 8 lanes of a row (lane ^ 7, ^ 2, ^ 1: DPP patterns) leave lane j of the group with
+// row j * 8 + sub, and a lane permute hands row `lane` its value.
+template <int DQK>
+__device__ __forceinline__ float make_delta(const StatRegs<DQK, true> &r, const Geo &g)
+{
+    const int lane = threadIdx.x & 63, j = lane & 7, hp = g.d >> 1;
+    const bool first = 2 * j + 1 < hp || (hp == 1 && j == 0), second = hp > 1 && 2 * j < hp;   // (a slid pair counts its new half only)
+    float part[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        const float a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r.y[p].x), __builtin_bit_cast(bf16x2, r.o[p].x), 0.f, false);
+        const float b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r.y[p].y), __builtin_bit_cast(bf16x2, r.o[p].y), 0.f, false);
+        part[p] = (first ? a : 0.f) + (second ? b : 0.f);
+    }
+#define RIB_DPP(x, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (x)), (ctrl), 0xF, 0xF, true))
+    const bool b2 = (j & 4) != 0, b1 = (j & 2) != 0, b0 = (j & 1) != 0;
+    float h4[4], h2[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float keep = b2 ? part[4 + i] : part[i], give = b2 ? part[i] : part[4 + i];
+        h4[i] = keep + RIB_DPP(give, 0x141);        // row_half_mirror: lane ^ 7
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float keep = b1 ? h4[2 + i] : h4[i], give = b1 ? h4[i] : h4[2 + i];
+        h2[i] = keep + RIB_DPP(give, 0x4E);         // quad_perm [2,3,0,1]: lane ^ 2
+    }
+    const float keep = b0 ? h2[1] : h2[0], give = b0 ? h2[0] : h2[1];
+    const float mine = keep + RIB_DPP(give, 0xB1);  // quad_perm [1,0,3,2]: lane ^ 1
+#undef RIB_DPP
+    return __shfl(mine, (lane & 7) * 8 + (lane >> 3));
+}
+
+// Stage the wave's 64 rows through its private LDS area and read them back as MFMA B operands.
+template <int DQK, bool QDO, bool XS, bool XD, bool WITH_O, bool TINY>
+__device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O> &r, const Geo &g, bf16_t *W, float sc, float sp, float nl,
+                                           float nd, bf16x8 (&Xb)[2][DQK / 16], bf16x8 (&Yb)[2][2])
+{
+    using L = Lay<DQK, 64>;
+    const int lane = threadIdx.x & 63, l = lane >> 3, col = lane & 31, hf = lane >> 5;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+    bf16_t *Xs = W, *Ys = W + 64 * L::XS;
+    {   // padding columns and extras of row `lane`
+        bf16_t *xr = Xs + lane * L::XS, *yr = Ys + lane * L::YS;
+        for (int c = g.d + g.r; c < DQK - (XS ? 0 : 2); c += 2) *(uint32_t *)(xr + c) = 0u;
+        for (int c = g.d; c < L::DVK - (XD ? 0 : 2); c += 2) *(uint32_t *)(yr + c) = 0u;
+        if (!XS) *(uint32_t *)(xr + DQK - 2) = QDO ? split_bf16(nl) : 0x3f803f80u;
+        if (!XD) *(uint32_t *)(yr + L::DVK - 2) = QDO ? split_bf16(nd) : 0x3f803f80u;
+    }
+    bf16_t *xr = Xs + l * L::XS + 2 * pc.dc, *yr = Ys + l * L::YS + 2 * pc.dc;
+    bf16_t *fr = Xs + l * L::XS + g.d + 2 * pc.f0, *fr1 = Xs + l * L::XS + g.d + 2 * pc.f1;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        dword2 x = r.x[p], fa = r.fa[p], fb;
+        if (DQK == 64) fb = r.fb[p];
+        if (QDO) {
+            x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
+            fa.x = scale_pair(fa.x, sp), fa.y = scale_pair(fa.y, sp);
+            if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
+        }
+        put8(xr + p * 8 * L::XS, x, pc.c1);
+        put8(yr + p * 8 * L::YS, r.y[p], pc.c1);
+        if (!pc.fnone) {
+            put8(fr + p * 8 * L::XS, fa, pc.f1d);
+            if (DQK == 64) put8(fr1 + p * 8 * L::XS, fb, pc.f1d);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        read_rows<L::KS>(Xb[b], Xs + (b * 32 + col) * L::XS + 8 * hf);
+        read_rows<L::VS>(Yb[b], Ys + (b * 32 + col) * L::YS + 8 * hf);
+    }
+}
+
+// One 32-row accumulator block of a gradient: this lane's token, rows 32*mb + 8*a + 4*hf + 0..3 in
+// registers 4a .. 4a+3.  Columns below d go to the grid tensor (bf16, times sc), the next r to this
+// unit's RIB partial (fp32, times sp).
+__device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, const Geo &g, float sc, float sp, char *grid_dst,
+                                            char *part_dst)
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const int c = 32 * mb + 8 * a + 4 * hf;
+        const float v0 = acc[4 * a], v1 = acc[4 * a + 1], v2 = acc[4 * a + 2], v3 = acc[4 * a + 3];
+        if (c + 2 <= g.d) {
+            dword2 w;
+            w.x = pack_bf16(v0 * sc, v1 * sc);
+            w.y = pack_bf16(v2 * sc, v3 * sc);
+            if (c + 4 <= g.d) {
+                *(dword2 *)(grid_dst + 2 * c) = w;
+            } else {            // the head's last pair, then the first two RIB columns
+                *(uint32_t *)(grid_dst + 2 * c) = w.x;
+                if (g.r > 0 && part_dst) *(float2u *)part_dst = float2u{v2 * sp, v3 * sp};
+            }
+        } else if (part_dst && c + 2 <= g.d + g.r) {
+            char *dst = part_dst + 4 * (c - g.d);
+            if (c + 4 <= g.d + g.r) *(float4u *)dst = float4u{v0 * sp, v1 * sp, v2 * sp, v3 * sp};
+            else *(float2u *)dst = float2u{v0 * sp, v1 * sp};
+        }
+    }
+}
+
+// Rows of a score block whose streamed token lies past the window: minus infinity, so that P and
+// dS vanish there (the staged rows repeat the last token, so everything else is finite).
+__device__ __forceinline__ void mask_rows(f32x16 &S, int first, int N, int hf)
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (first + 8 * (i >> 2) + 4 * hf + (i & 3) >= N) S[i] = -INFINITY;
+}
+
+// Common start of both kernels.
+#define RIB_BWD_SETUP                                                                                      \
+    using L = Lay<DQK, T>;                                                                                 \
+    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];                                          \
+    const int nt = T == 64 ? 256 : (int)blockDim.x, waves = nt >> 6;                                       \
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);                                     \
+    const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;                                    \
+    int64_t u;                                                                                             \
+    int blk, b;                                                                                            \
+    block_coords(nblk, u, blk);                                                                            \
+    const int w = (int)(u / g.heads), hd = (int)(u - (int64_t)w * g.heads);                                \
+    const Win win = window_of<ALN>(g, w, nt, (int *)((char *)smem + L::bytes(waves)), b);                  \
+    const int64_t img = (int64_t)b * g.H * g.W;                                                            \
+    Stream ks, qs;                                                                                         \
+    ks.xb = (const char *)(k + img * g.tstride + hd * g.d);                                                \
+    ks.yb = (const char *)(v + img * g.tstride + hd * g.d);                                                \
+    ks.fb = (const char *)(fk + (int64_t)hd * g.N * g.r);                                                  \
+    ks.xs = ks.ys = qs.xs = (uint32_t)g.tstride * 2u;                                                      \
+    ks.frow = qs.frow = (uint32_t)g.r * 2u;                                                                \
+    qs.xb = (const char *)(q + img * g.tstride + hd * g.d);                                                \
+    qs.yb = (const char *)(dout + img * g.C + hd * g.d);                                                   \
+    qs.fb = (const char *)(fq + (int64_t)hd * g.N * g.r);                                                  \
+    qs.ys = (uint32_t)g.C * 2u;                                                                            \
+    ks.lse = qs.lse = lse + u * g.N;                                                                       \
+    ks.delta = qs.delta = delta + u * g.N;                                                                 \
+    const float sc2 = g.scale_c * kLog2e, sp2 = g.scale_p * kLog2e;                                        \
+    const int n0 = (blk * waves + wave) * 64;                                                              \
+    const int ntiles = (g.N + T - 1) / T;                                                                  \
+    if (!ALN) __syncthreads();
+
+#define RIB_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// dQ (+ dF_q partial).  A lane stages at most two tokens a tile: T = 64 with 4 waves, T = 32 with 2 or 3.
+//
+// One step is one 32x32 block s = (key block, query block); its instructions are written in the
+// order they should issue and pinned with scheduling fences: the 5 score MFMAs of block s + 1 and
+// the 2 * RB gradient MFMAs of block s - 1 are spread between the exponentials, products and packs
+// of block s, so that the matrix pipe and the vector ALU always have independent work (left alone,
+// the compiler chains exp2 -> multiply -> pack element by element and waits for every LDS read
+// where it is issued).
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+__global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+                                                      const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
+                                                      const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
+                                                      const bf16_t *__restrict__ dout, const float *__restrict__ lse,
+                                                      float *__restrict__ delta, bf16_t *__restrict__ dq,
+                                                      float *__restrict__ dfq_part)
+{
+    RIB_BWD_SETUP
+    constexpr int NB = T / 32, NS = 2 * NB;
+
+    // one exposed memory latency: the wave's rows and the first two tiles are requested together
+    Regs<DQK> rg, rg1;
+    bf16x8 Qb[2][L::KS], Gb[2][L::VS];
+    float nl[2] = {0.f, 0.f}, nd[2] = {0.f, 0.f};
+    {
+        StatRegs<DQK, true> sr;
+        const bool from_o = g.gate == nullptr;          // a gated call's pass over dO', G and O has made delta already
+        stat_request<DQK, true, true, ALN, TINY>(sr, g, win, qs, n0, (const char *)(out + img * g.C + hd * g.d), from_o);
+        request<DQK, T, false, ALN, TINY>(rg, g, win, ks, 0, nt, wave);
+        request<DQK, T, false, ALN, TINY>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
+        float dl = sr.e1;
+        if (from_o) {
+            dl = make_delta<DQK>(sr, g);
+            if (n0 + lane < g.N) delta[u * g.N + n0 + lane] = dl;       // for the dkv kernel, which runs second
+        }
+        const float l2 = kTruncLog2 - sr.e0 * kLog2e;
+        stat_stage<DQK, true, XS, XD, true, TINY>(sr, g, smem + wave * L::WAVE_STAT, sc2, sp2, l2, -dl, Qb, Gb);
+        if (XS) nl[0] = __shfl(l2, col), nl[1] = __shfl(l2, 32 + col);
+        if (XD) nd[0] = -__shfl(dl, col), nd[1] = -__shfl(dl, 32 + col);
+    }
+    __syncthreads();
+    init_pads<DQK, T, false, XS, XD>(g, smem, nt);
+    commit<DQK, T, false, XS, XD, TINY>(rg, g, smem, 1.f, 1.f, nt, wave);
+    commit<DQK, T, false, XS, XD, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, nt, wave);
+    request<DQK, T, false, ALN, TINY>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
+    __syncthreads();
+
+    f32x16 acc[2][L::RB];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[qb][mb][i] = 0.f;
+
+    const int tro = tr_lane_offset<L::XS>(lane), ako = col * L::XS + 8 * hf, avo = L::YR + col * L::YS + 8 * hf;
+    bf16x8 Ak[L::KS], Av[L::VS], At[L::RB][2];
+    f32x16 S[2], D[2];
+    uint32_t P[2][8];
+    read_rows<L::KS>(Ak, smem + ako);
+    read_rows<L::VS>(Av, smem + avo);
+    {
+        const f32x16 z = {0};
+        S[0] = mfma(Ak[0], Qb[0][0], z);
+        D[0] = mfma(Av[0], Gb[0][0], z);
+#pragma unroll
+        for (int i = 1; i < L::KS; ++i) S[0] = mfma(Ak[i], Qb[0][i], S[0]);
+        D[0] = mfma(Av[1], Gb[0][1], D[0]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) P[1][i] = 0u;         // (the first step's gradient products add zero)
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) At[mb][i] = Ak[0];
+    }
+    int c0 = 0, c1 = L::STAGE, c2 = 2 * L::STAGE;        // this tile's, the next tile's and the free stage
+    for (int tile = 0; tile < ntiles; ++tile) {
+        const bf16_t *cur = smem + c0, *nxt = smem + c1;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int kb = s >> 1, qb = s & 1, cs = s & 1, ns = cs ^ 1, qn = qb ^ 1;
+            const f32x16 z = {0};
+            RIB_FENCE();
+            // scores of block s + 1
+            S[ns] = mfma(Ak[0], Qb[qn][0], z);
+            D[ns] = mfma(Av[0], Gb[qn][0], z);
+            if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + kb * 32, g.N, hf);
+            float p[16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
+            RIB_FENCE();
+            S[ns] = mfma(Ak[1], Qb[qn][1], S[ns]);
+            D[ns] = mfma(Av[1], Gb[qn][1], D[ns]);
+#pragma unroll
+            for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
+            if (s == 0) commit<DQK, T, false, XS, XD, TINY>(rg, g, smem + c2, 1.f, 1.f, nt, wave);
+            RIB_FENCE();
+#pragma unroll
+            for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
+#pragma unroll
+            for (int i = 8; i < 12; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
+            P[cs][0] = trunc_pack(p[0], p[1]);
+            P[cs][1] = trunc_pack(p[2], p[3]);
+#pragma unroll
+            for (int i = 4; i < 8; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
+            if (qb == 0) {      // operands of the next key block (behind this tile's last, of the next tile)
+                read_rows<L::KS>(Ak, (kb + 1 < NB ? cur + (kb + 1) * 32 * L::XS : nxt) + ako);
+                read_rows<L::VS>(Av, (kb + 1 < NB ? cur + (kb + 1) * 32 * L::YS : nxt) + avo);
+            }
+            RIB_FENCE();
+            // gradient of block s - 1
+            const bf16x8 B0 = as_bf16x8(P[ns][0], P[ns][1], P[ns][2], P[ns][3]), B1 = as_bf16x8(P[ns][4], P[ns][5], P[ns][6], P[ns][7]);
+#pragma unroll
+            for (int mb = 0; mb < L::RB; ++mb) acc[qn][mb] = mfma(At[mb][0], B0, acc[qn][mb]);
+#pragma unroll
+            for (int i = 12; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
+            P[cs][2] = trunc_pack(p[4], p[5]);
+            P[cs][3] = trunc_pack(p[6], p[7]);
+#pragma unroll
+            for (int i = 8; i < 12; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
+            RIB_FENCE();
+#pragma unroll
+            for (int mb = 0; mb < L::RB; ++mb) acc[qn][mb] = mfma(At[mb][1], B1, acc[qn][mb]);
+            P[cs][4] = trunc_pack(p[8], p[9]);
+            P[cs][5] = trunc_pack(p[10], p[11]);
+#pragma unroll
+            for (int i = 12; i < 16; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
+            P[cs][6] = trunc_pack(p[12], p[13]);
+            P[cs][7] = trunc_pack(p[14], p[15]);
+            RIB_FENCE();
+            if (qb == 0) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int mb = 0; mb < L::RB; ++mb) At[mb][i] = read_tr<L::XS>(cur + (kb * 32 + 16 * i) * L::XS, tro, 32 * mb);
+            }
+            if (s == NS - 1) request<DQK, T, false, ALN, TINY>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
+        }
+        RIB_FENCE();
+        __syncthreads();
+        const int r0 = c0;
+        c0 = c1, c1 = c2, c2 = r0;
+    }
+    {   // gradient of the last block
+        const bf16x8 B0 = as_bf16x8(P[1][0], P[1][1], P[1][2], P[1][3]), B1 = as_bf16x8(P[1][4], P[1][5], P[1][6], P[1][7]);
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb) {
+            acc[1][mb] = mfma(At[mb][0], B0, acc[1][mb]);
+            acc[1][mb] = mfma(At[mb][1], B1, acc[1][mb]);
+        }
+    }
+
+    // Outputs straight from the accumulator layout: a lane holds, for one token, groups of four
+    // consecutive columns (8-byte stores of the gradient, 16-byte stores of the partial).
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const int n = n0 + qb * 32 + col;
+        if (n < g.N) {
+            char *gd = (char *)(dq + (img + win.any(n)) * g.C + hd * g.d);
+            char *pd = (char *)(dfq_part + (u * g.N + n) * g.r);
+#pragma unroll
+            for (int mb = 0; mb < L::RB; ++mb) store_block(acc[qb][mb], mb, hf, g, g.scale_c, g.scale_p, gd, pd);
+        }
+    }
+}
+
+// dK, dV (+ dF_k partial).  Same walk with the roles exchanged.  There are no registers for a second
+// pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
+// other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+__global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+                                                       const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
+                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ dout,
+                                                       const float *__restrict__ lse, const float *__restrict__ delta,
+                                                       bf16_t *__restrict__ dk, bf16_t *__restrict__ dv,
+                                                       float *__restrict__ dfk_part)
+{
+    RIB_BWD_SETUP
+    constexpr int NB = T / 32;
+
+    Regs<DQK> rg, rg1;
+    bf16x8 Kb[2][L::KS], Vb[2][L::VS];
+    {
+        StatRegs<DQK, false> sr;
+        stat_request<DQK, false, false, ALN, TINY>(sr, g, win, ks, n0, nullptr, false);
+        request<DQK, T, true, ALN, TINY>(rg, g, win, qs, 0, nt, wave);
+        request<DQK, T, true, ALN, TINY>(rg1, g, win, qs, ntiles > 1 ? 1 : 0, nt, wave);
+        stat_stage<DQK, false, XS, XD, false, TINY>(sr, g, smem + wave * L::WAVE_STAT, 1.f, 1.f, 0.f, 0.f, Kb, Vb);
+    }
+    __syncthreads();
+    init_pads<DQK, T, true, XS, XD>(g, smem, nt);
+    commit<DQK, T, true, XS, XD, TINY>(rg, g, smem, sc2, sp2, nt, wave);
+    commit<DQK, T, true, XS, XD, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, nt, wave);
+    request<DQK, T, true, ALN, TINY>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
+    __syncthreads();
+
+    f32x16 accV[2], accK[2][L::RB];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) accV[kb][i] = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) accK[kb][mb][i] = 0.f;
+    }
+
+    const int trx = tr_lane_offset<L::XS>(lane), try_ = L::YR + tr_lane_offset<L::YS>(lane);
+    const int aqo = col * L::XS + 8 * hf, ago = L::YR + col * L::YS + 8 * hf;
+    bf16x8 Aq[L::KS], Ag[L::VS];
+    read_rows<L::KS>(Aq, smem + aqo);
+    read_rows<L::VS>(Ag, smem + ago);
+    int c0 = 0, c1 = L::STAGE, c2 = 2 * L::STAGE;
+    for (int tile = 0; tile < ntiles; ++tile) {
+        const bf16_t *cur = smem + c0, *nxt = smem + c1;
+#pragma unroll
+        for (int qb = 0; qb < NB; ++qb) {
+            bf16x8 Aqt[L::RB][2], Agt[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                f32x16 S = {0}, D = {0};
+                if (XS || XD) {
+                    // accumulator row 8j + 4*hf + e is query qb*32 + that: four consecutive floats per j
+                    const float *ex = (const float *)(cur + L::EX) + qb * 32 + 4 * hf;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (XS) {
+                            const float4 a = *(const float4 *)(ex + 8 * j);
+                            S[4 * j] = a.x, S[4 * j + 1] = a.y, S[4 * j + 2] = a.z, S[4 * j + 3] = a.w;
+                        }
+                        if (XD) {
+                            const float4 a = *(const float4 *)(ex + T + 8 * j);
+                            D[4 * j] = a.x, D[4 * j + 1] = a.y, D[4 * j + 2] = a.z, D[4 * j + 3] = a.w;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < L::KS; ++i) S = mfma(Aq[i], Kb[kb][i], S);
+#pragma unroll
+                for (int i = 0; i < L::VS; ++i) D = mfma(Ag[i], Vb[kb][i], D);
+                RIB_FENCE();
+                if (kb == 0) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        Agt[i] = read_tr<L::YS>(cur + (qb * 32 + 16 * i) * L::YS, try_, 0);
+#pragma unroll
+                        for (int mb = 0; mb < L::RB; ++mb)
+                            Aqt[mb][i] = read_tr<L::XS>(cur + (qb * 32 + 16 * i) * L::XS, trx, 32 * mb);
+                    }
+                    if (qb == 0) commit<DQK, T, true, XS, XD, TINY>(rg, g, smem + c2, sc2, sp2, nt, wave);
+                } else {
+                    read_rows<L::KS>(Aq, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::XS : nxt) + aqo);
+                    read_rows<L::VS>(Ag, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::YS : nxt) + ago);
+                    if (qb == NB - 1)
+                        request<DQK, T, true, ALN, TINY>(rg, g, win, qs, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
+                }
+                RIB_FENCE();
+                if (!ALN && tile == ntiles - 1) mask_rows(S, tile * T + qb * 32, g.N, hf);
+                uint32_t wp[8], wds[8];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int i = 8 * h; i < 8 * h + 8; ++i) S[i] = __builtin_amdgcn_exp2f(S[i]);
+                    RIB_FENCE();
+#pragma unroll
+                    for (int i = 8 * h; i < 8 * h + 8; ++i) D[i] *= S[i];
+#pragma unroll
+                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wp[i >> 1] = trunc_pack(S[i], S[i + 1]);
+#pragma unroll
+                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wds[i >> 1] = trunc_pack(D[i], D[i + 1]);
+                    RIB_FENCE();
+                    const bf16x8 B = as_bf16x8(wds[4 * h], wds[4 * h + 1], wds[4 * h + 2], wds[4 * h + 3]);
+                    accV[kb] = mfma(Agt[h], as_bf16x8(wp[4 * h], wp[4 * h + 1], wp[4 * h + 2], wp[4 * h + 3]), accV[kb]);
+#pragma unroll
+                    for (int mb = 0; mb < L::RB; ++mb) accK[kb][mb] = mfma(Aqt[mb][h], B, accK[kb][mb]);
+                }
+            }
+        }
+        RIB_FENCE();
+        __syncthreads();
+        const int r0 = c0;
+        c0 = c1, c1 = c2, c2 = r0;
+    }
+
+    // (the streamed Q_aug rows carry scale * log2 e: undo the log2 e here)
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        const int n = n0 + kb * 32 + col;
+        if (n < g.N) {
+            const int64_t base = (img + win.any(n)) * g.C + hd * g.d;
+            char *pd = (char *)(dfk_part + (u * g.N + n) * g.r);
+#pragma unroll
+            for (int mb = 0; mb < L::RB; ++mb) store_block(accK[kb][mb], mb, hf, g, kLn2, kLn2, (char *)(dk + base), pd);
+            store_block(accV[kb], 0, hf, g, 1.f, 1.f, (char *)(dv + base), nullptr);
+        }
+    }
+}
+
+struct Args {
+    const bf16_t *q, *k, *v, *fq, *fk, *out, *dout;
+    const float *lse;
+    float *delta;
+    bf16_t *dq, *dk, *dv;
+    float *pq, *pk;
+    hipStream_t st;
+};
+
+// Launch the pair with workgroups of `waves` waves, `nblk` of them per unit.
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
+{
+    using L = Lay<DQK, T>;
+    const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+    if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
+    auto kdq = dq_kernel<DQK, T, XS, XD, ALN, TINY>;
+    auto kdkv = dkv_kernel<DQK, T, XS, XD, ALN, TINY>;
+    hipError_t e = prepare_kernel((const void *)kdkv, nullptr);
+    if (e == hipSuccess) e = prepare_kernel((const void *)kdq, nullptr);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(g.units * nblk)), block(waves * 64);
+    // dq first: it writes the delta rows the dkv kernel streams
+    hipLaunchKernelGGL(kdq, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout, a.lse, a.delta, a.dq, a.pq);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kdkv, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.dout, a.lse, a.delta, a.dk, a.dv, a.pk);
+    return hipGetLastError();
+}
+
+// Workgroup shape: up to 4 waves of 64 stationary tokens, an equal number in every workgroup of a
+// unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).
+template <int DQK, bool XS, bool XD>
+hipError_t launch_width(const Geo &g, const Args &a)
+{
+    const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
+    int waves = (nb + nblk - 1) / nblk;
+    if (waves < 2) waves = 2;
+    if (g.d < 4 || g.r < 4)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, true>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, false, true>(g, waves, nblk, a);
+    if (g.M % 8 == 0)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, true, false>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, true, false>(g, waves, nblk, a);
+    return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, false>(g, waves, nblk, a)
+                      : launch_pair<DQK, 32, XS, XD, false, false>(g, waves, nblk, a);
+}
+
+// d + r within the padded width; columns carry LSE / delta wherever two are free.
+hipError_t launch32(const Geo &g, const Args &a);
+hipError_t launch48(const Geo &g, const Args &a);
+hipError_t launch64(const Geo &g, const Args &a);
+template <int DQK>
+hipError_t launch_flags(const Geo &g, const Args &a)
+{
+    const bool xs = g.d + g.r + 2 > DQK, xd = g.d + 2 > 32;
+    if constexpr (DQK == 32) {
+        return xs ? launch_width<DQK, true, false>(g, a) : launch_width<DQK, false, false>(g, a);
+    } else {
+        if (xd) return xs ? launch_width<DQK, true, true>(g, a) : launch_width<DQK, false, true>(g, a);
+        return xs ? launch_width<DQK, true, false>(g, a) : launch_width<DQK, false, false>(g, a);
+    }
+}
+
+}  // namespace bwd
+}  // namespace rib

@@ -1,0 +1,8 @@
+// The bf16 backward kernels for augmented rows of up to 32 columns (see rib_mfma_bwd.h).
+#include "rib_mfma_bwd.h"
+
+namespace rib {
+namespace bwd {
+hipError_t launch32(const Geo &g, const Args &a) { return launch_flags<32>(g, a); }
+}  // namespace bwd
+}  // namespace rib

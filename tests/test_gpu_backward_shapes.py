@@ -1,0 +1,55 @@
+"""The bf16 backward kernels where their dispatch changes hands, against the oracle, every element: padded
+widths 32 / 48 / 64 with LSE and delta in columns, in the C operand or mixed; window sides that are and are not
+multiples of 8; workgroups of 2, 3 and 4 waves, with waves wholly or half past the window's end; rows of a single
+dword and no RIB at all.
+
+Tolerance: bf16 operands round P, dS and the gradients to 2^-8 relative, and a gradient element of these shapes is a
+sum of about N terms of size P <= 1 whose roundings add at random; 2e-2 absolute is the bound the parity tests
+derive for logits of this size."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2603_06738_amd import binding as rb
+from paper_2603_06738_amd import workloads as wk
+from helpers import geometry
+
+SHAPES = [  # (d, r, M, shift, H / M, W / M)
+    (16, 14, 8, 3, 1, 2),       # one 64-token block: the second wave idles; width 32, extras in columns
+    (16, 16, 24, 12, 1, 1),     # 3 workgroups of 3 waves; width 32, LSE in the C operand
+    (30, 2, 40, 7, 1, 1),       # width 32, single-dword RIB rows, 25 blocks over 7 workgroups: idle waves
+    (30, 16, 24, 5, 2, 1),      # width 48, columns
+    (32, 8, 16, 0, 1, 2),       # width 48, delta in the C operand, LSE in columns
+    (30, 18, 40, 9, 1, 1),      # width 48, LSE in the C operand
+    (32, 16, 24, 0, 1, 1),      # width 48, both in the C operand
+    (30, 34, 8, 4, 2, 2),       # width 64, LSE in the C operand
+    (32, 32, 40, 0, 1, 1),      # width 64, both
+    (24, 20, 9, 4, 1, 2),       # 81 tokens: two waves, the second in its first block
+    (30, 16, 11, 10, 1, 1),     # 121 tokens
+    (30, 18, 13, 6, 1, 1),      # 169 tokens: three waves
+    (28, 36, 15, 1, 1, 1),      # 225 tokens: four waves, width 64
+    (32, 30, 17, 16, 1, 1),     # 289 tokens: two workgroups of three
+    (30, 34, 25, 3, 1, 1),      # 625 tokens: ten blocks over three workgroups of four
+    (2, 2, 9, 0, 1, 1),         # single-dword content and RIB rows
+    (4, 0, 10, 2, 1, 1),        # no RIB
+    (2, 44, 12, 5, 1, 1),       # RIB rows of more than 32 values
+]
+
+
+@pytest.mark.parametrize("d,r,M,s,ny,nx", SHAPES)
+@pytest.mark.parametrize("packed", [False, True], ids=["dense", "packed"])
+def test_backward_shapes(oracle, d, r, M, s, ny, nx, packed):
+    import gpu_helpers as gh
+    wl = wk.custom(f"bwd-d{d}r{r}m{M}", "bf16", 2, ny * M, nx * M, 2, d, r, M, s, 7000 + 64 * M + d + r, backward=True)
+    assert rb.kernel_name(rb.params_of(wl), True) == "mfma-bf16"
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x, packed=packed)
+    out, lse = gh.gpu_fwd(wl, t, packed=packed)
+    got = gh.gpu_bwd(wl, t, out, lse, packed=packed)
+    again = gh.gpu_bwd(wl, t, out, lse, packed=packed)
+    ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    names = ("dQ", "dK", "dV", "dF_q", "dF_k") if r > 0 else ("dQ", "dK", "dV")
+    for name, a, a2, b in zip(names, got, again, ref):
+        assert bool((a == a2).all()), name                  # fixed summation order
+        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"], name
