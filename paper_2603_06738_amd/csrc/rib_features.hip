@@ -1,15 +1,19 @@
 // RIB feature generator (paper Sec. 3.1 Eq. 1-3) and its backward.
 //
 // The work is tiny next to the attention it feeds (N <= 65536 tokens, 42 -> 32 -> heads*r
-// features) and runs once per weight update, so these are plain vector-ALU kernels laid out
-// for coalesced access and a fixed summation order, not for the matrix cores.
+// features) and runs once per weight update: plain vector-ALU kernels with a fixed summation
+// order.  What bounds them is latency -- a handful of workgroups, each a chain of fp64 sincos,
+// dot products and loads -- so a workgroup takes only 16 tokens, every sincos and every hidden
+// unit has a lane of its own, and operands are staged in bulk (48 x 48 window, 3 heads, r = 16:
+// forward 31 -> 12 us, backward 129 -> 30 us; 64 tokens a workgroup and strided global reads before).
 //
-//   forward:  one workgroup per 64 tokens: Fourier features (fp64 sines / cosines of the
-//             token's row and column coordinate, rounded to fp32) into LDS, the shared hidden
-//             layer into LDS, then every (head, token, column) output as a d_h-long dot product.
+//   forward:  Fourier features (fp64 sines / cosines of the token's row and column coordinate,
+//             rounded to fp32) into LDS, the shared hidden layer into LDS, then a lane per
+//             (table, head, column) runs over the 16 tokens.
 //   backward: (1) the same two stages, kept in the workspace (r_in, h) together with
 //             dpre = ReLU'(pre) * sum over heads of dF W_p^T;
-//             (2) per 256-token chunk, one thread per weight-gradient element sums its chunk;
+//             (2) per 64-token chunk and per (table, head), a workgroup sums its slice of the
+//             weight gradients from LDS tiles;
 //             (3) chunks are added in ascending order.
 #include <hip/hip_runtime.h>
 
@@ -18,33 +22,33 @@
 namespace rib {
 namespace {
 
-constexpr int kTok = 64;        // tokens per workgroup in the token-parallel kernels
-constexpr int kChunk = 256;     // tokens per partial sum in the weight-gradient kernel
+constexpr int kTok = 16;        // tokens per workgroup in the token-parallel kernels
+constexpr int kChunk = 64;      // tokens per partial sum in the weight-gradient kernel
 constexpr int kGenNT = 256;
+constexpr int kStageFloats = 12 * 1024;     // LDS for the staged dF and W_p tiles of a group of heads
 
 struct Gen {
     int M, N, heads, r, L, d_h, n_in;
 };
 
-// Fourier features of the workgroup's tokens -> rin[kTok][n_in] (LDS).  One thread per
-// (token, axis): coordinate in fp64, then 2L sines / cosines in fp64.
+// Fourier features of the workgroup's tokens -> rin[kTok][n_in] (LDS).  One lane per (token, axis,
+// band): coordinate and sine / cosine in fp64.
 __device__ __forceinline__ void stage_fourier(const Gen &g, int n0, float *rin)
 {
-    for (int e = threadIdx.x; e < kTok * 2; e += kGenNT) {
-        const int t = e >> 1, axis = e & 1, n = n0 + t;
+    for (int e = threadIdx.x; e < kTok * 2 * (g.L + 1); e += kGenNT) {
+        const int t = e & (kTok - 1), la = e / kTok, axis = la & 1, l = (la >> 1) - 1, n = n0 + t;
         if (n >= g.N) continue;
         const int iy = n / g.M, ix = n - iy * g.M;
         const int i = axis == 0 ? iy : ix;
         const double x = g.M > 1 ? -1.0 + 2.0 * (double)i / (double)(g.M - 1) : 0.0;
         float *row = rin + t * g.n_in;
-        row[axis] = (float)x;
-        double f = 1.0;
-        for (int l = 0; l < g.L; ++l) {
+        if (l < 0) {
+            row[axis] = (float)x;
+        } else {
             double s, c;
-            sincos(f * x, &s, &c);
+            sincos((double)(1 << l) * x, &s, &c);
             row[2 + 4 * l + axis] = (float)s;
             row[4 + 4 * l + axis] = (float)c;
-            f *= 2.0;
         }
     }
 }
@@ -54,6 +58,7 @@ __device__ __forceinline__ float hidden_pre(const Gen &g, const float *rin_row, 
                                             const float *__restrict__ b_h, int c)
 {
     float acc = b_h[c];
+#pragma unroll 6
     for (int a = 0; a < g.n_in; ++a) acc = fmaf(rin_row[a], W_h[a * g.d_h + c], acc);
     return acc;
 }
@@ -65,34 +70,47 @@ __global__ __launch_bounds__(kGenNT) void features_fwd_kernel(Gen g, const float
                                                               const float *__restrict__ W_pk, T *__restrict__ f_q,
                                                               T *__restrict__ f_k)
 {
-    extern __shared__ float lds[];
-    float *rin = lds, *hs = lds + kTok * g.n_in;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    float *hs = lds, *rin = lds + kTok * g.d_h;     // h transposed: [d_h][kTok]
     const int n0 = blockIdx.x * kTok;
     const int live = min(kTok, g.N - n0);
     stage_fourier(g, n0, rin);
     __syncthreads();
-    for (int e = threadIdx.x; e < live * g.d_h; e += kGenNT) {
+    for (int e = threadIdx.x; e < kTok * g.d_h; e += kGenNT) {
         const int t = e / g.d_h, c = e - t * g.d_h;
-        hs[t * g.d_h + c] = fmaxf(hidden_pre(g, rin + t * g.n_in, W_h, b_h, c), 0.f);
+        hs[c * kTok + t] = t < live ? fmaxf(hidden_pre(g, rin + t * g.n_in, W_h, b_h, c), 0.f) : 0.f;
     }
     __syncthreads();
-    // outputs: (which, head, token, column) with the column fastest
-    const int per_head = live * g.r;
-    for (int e = threadIdx.x; e < 2 * g.heads * per_head; e += kGenNT) {
-        const int wh = e / per_head, rem = e - wh * per_head;
-        const int which = wh / g.heads, hd = wh - which * g.heads;
-        const int t = rem / g.r, j = rem - t * g.r;
+    const int cols = g.heads * g.r;
+    for (int e = blockIdx.y * kGenNT + threadIdx.x; e < 2 * cols; e += gridDim.y * kGenNT) {
+        const int which = e >= cols, ee = e - which * cols, hd = ee / g.r, j = ee - hd * g.r;
         const float *W = (which ? W_pk : W_pq) + (size_t)hd * g.d_h * g.r + j;
-        const float *h = hs + t * g.d_h;
-        float acc = 0.f;
-        for (int c = 0; c < g.d_h; ++c) acc = fmaf(h[c], W[c * g.r], acc);
-        T *dst = (which ? f_k : f_q) + ((size_t)hd * g.N + n0 + t) * g.r + j;
-        store_as(dst, acc);
+        float acc[kTok];
+#pragma unroll
+        for (int t = 0; t < kTok; ++t) acc[t] = 0.f;
+#pragma unroll 4
+        for (int c = 0; c < g.d_h; ++c) {
+            const float w = W[c * g.r];
+            const float4 *h = (const float4 *)(hs + c * kTok);
+#pragma unroll
+            for (int i = 0; i < kTok / 4; ++i) {
+                const float4 v = h[i];
+                acc[4 * i] = fmaf(v.x, w, acc[4 * i]);
+                acc[4 * i + 1] = fmaf(v.y, w, acc[4 * i + 1]);
+                acc[4 * i + 2] = fmaf(v.z, w, acc[4 * i + 2]);
+                acc[4 * i + 3] = fmaf(v.w, w, acc[4 * i + 3]);
+            }
+        }
+        T *dst = (which ? f_k : f_q) + ((size_t)hd * g.N + n0) * g.r + j;
+#pragma unroll
+        for (int t = 0; t < kTok; ++t)
+            if (t < live) store_as(dst + t * g.r, acc[t]);
     }
 }
 
-// Backward stage 1: r_in, h and dpre of every token into the workspace.
-__global__ __launch_bounds__(kGenNT) void features_hidden_kernel(Gen g, const float *__restrict__ W_h,
+// Backward stage 1: r_in, h and dpre of every token into the workspace.  The dF rows and W_p slices
+// of as many heads as fit are staged in LDS at a time, with one round of loads in flight.
+__global__ __launch_bounds__(kGenNT) void features_hidden_kernel(Gen g, int group, const float *__restrict__ W_h,
                                                                  const float *__restrict__ b_h,
                                                                  const float *__restrict__ W_pq,
                                                                  const float *__restrict__ W_pk,
@@ -100,28 +118,55 @@ __global__ __launch_bounds__(kGenNT) void features_hidden_kernel(Gen g, const fl
                                                                  const float *__restrict__ df_k, float *__restrict__ ws_rin,
                                                                  float *__restrict__ ws_h, float *__restrict__ ws_dpre)
 {
-    extern __shared__ float lds[];
-    float *rin = lds;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int ws = g.r | 1;                             // odd row stride: the lanes of a read are consecutive units
+    float *rin = lds, *gs = lds + kTok * g.n_in, *wl = gs + 2 * group * kTok * g.r;
     const int n0 = blockIdx.x * kTok;
     const int live = min(kTok, g.N - n0);
     stage_fourier(g, n0, rin);
+    constexpr int kPer = kTok * 64 / kGenNT;            // (token, unit) pairs per lane, d_h <= 64
+    float dh[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) dh[i] = 0.f;
+    for (int h0 = 0; h0 < g.heads; h0 += group) {
+        const int nh = min(group, g.heads - h0);
+        __syncthreads();
+        // gs[(2*head + which)][t][j], wl[(2*head + which)][c][j]
+        const int grow = live * g.r;
+        for (int s = 0; s < 2 * nh; ++s) {
+            const float *src = ((s & 1) ? df_k : df_q) + ((size_t)(h0 + (s >> 1)) * g.N + n0) * g.r;
+            for (int e = threadIdx.x; e < grow; e += kGenNT) gs[s * kTok * g.r + e] = src[e];
+            const float *w = ((s & 1) ? W_pk : W_pq) + (size_t)(h0 + (s >> 1)) * g.d_h * g.r;
+            for (int e = threadIdx.x; e < g.d_h * g.r; e += kGenNT) {
+                const int c = e / g.r;
+                wl[(s * g.d_h + c) * ws + (e - c * g.r)] = w[e];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = i * kGenNT + threadIdx.x;
+            if (e >= live * g.d_h) break;
+            const int t = e / g.d_h, c = e - t * g.d_h;
+            float acc = dh[i];
+            for (int s = 0; s < 2 * nh; ++s) {
+                const float *gr = gs + (s * kTok + t) * g.r, *wr = wl + (s * g.d_h + c) * ws;
+#pragma unroll 8
+                for (int j = 0; j < g.r; ++j) acc = fmaf(gr[j], wr[j], acc);
+            }
+            dh[i] = acc;
+        }
+    }
     __syncthreads();
     for (int e = threadIdx.x; e < live * g.n_in; e += kGenNT) ws_rin[(size_t)n0 * g.n_in + e] = rin[e];
-    for (int e = threadIdx.x; e < live * g.d_h; e += kGenNT) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = i * kGenNT + threadIdx.x;
+        if (e >= live * g.d_h) break;
         const int t = e / g.d_h, c = e - t * g.d_h;
         const float pre = hidden_pre(g, rin + t * g.n_in, W_h, b_h, c);
-        // dh[t][c] = sum over heads and columns of dF_q W_pq + dF_k W_pk, heads ascending
-        float dh = 0.f;
-        for (int hd = 0; hd < g.heads; ++hd) {
-            const float *gq = df_q + ((size_t)hd * g.N + n0 + t) * g.r;
-            const float *gk = df_k + ((size_t)hd * g.N + n0 + t) * g.r;
-            const float *wq = W_pq + ((size_t)hd * g.d_h + c) * g.r;
-            const float *wk = W_pk + ((size_t)hd * g.d_h + c) * g.r;
-            for (int j = 0; j < g.r; ++j) dh = fmaf(gq[j], wq[j], dh);
-            for (int j = 0; j < g.r; ++j) dh = fmaf(gk[j], wk[j], dh);
-        }
         ws_h[(size_t)n0 * g.d_h + e] = fmaxf(pre, 0.f);
-        ws_dpre[(size_t)n0 * g.d_h + e] = pre > 0.f ? dh : 0.f;
+        ws_dpre[(size_t)n0 * g.d_h + e] = pre > 0.f ? dh[i] : 0.f;
     }
 }
 
@@ -132,41 +177,61 @@ __global__ __launch_bounds__(kGenNT) void features_hidden_kernel(Gen g, const fl
 //   [2P + I, .. + d_h) db_h[c]          = sum_n dpre[n][c]
 __device__ __forceinline__ int n_grad_elems(const Gen &g) { return 2 * g.heads * g.d_h * g.r + g.n_in * g.d_h + g.d_h; }
 
-// Backward stage 2: partial[chunk][e] = the sum over the chunk's tokens, ascending.
+// Backward stage 2: partial[chunk][e] = the sum over the chunk's tokens, ascending.  blockIdx.x names
+// the slice: (table, head) -> its [d_h][r] block of dW_p from h and dF; the last one -> dW_h from
+// r_in and dpre, with db_h.  The chunk's rows of both factors are staged in LDS with the tokens
+// contiguous (zeros past the end), so that an element is 16 pairs of 16-byte reads.
+constexpr int kCS = kChunk + 4; // row stride of a staged factor (an odd multiple of 16 bytes)
 __global__ __launch_bounds__(kGenNT) void features_wgrad_kernel(Gen g, const float *__restrict__ df_q,
                                                                 const float *__restrict__ df_k,
                                                                 const float *__restrict__ ws_rin,
                                                                 const float *__restrict__ ws_h,
                                                                 const float *__restrict__ ws_dpre, float *__restrict__ partial)
 {
-    const int e = blockIdx.x * kGenNT + threadIdx.x, total = n_grad_elems(g);
-    if (e >= total) return;
-    const int n0 = blockIdx.y * kChunk, n1 = min(g.N, n0 + kChunk);
-    const int P = g.heads * g.d_h * g.r, I = g.n_in * g.d_h;
-    const float *a, *b;          // the two factors, with their strides per token
-    int sa, sb;
-    if (e < 2 * P) {
-        const int which = e >= P, ee = e - which * P;
-        const int hd = ee / (g.d_h * g.r), rem = ee - hd * g.d_h * g.r, c = rem / g.r, j = rem - c * g.r;
-        a = ws_h + c, sa = g.d_h;
-        b = (which ? df_k : df_q) + (size_t)hd * g.N * g.r + j, sb = g.r;
-    } else if (e < 2 * P + I) {
-        const int ee = e - 2 * P, ai = ee / g.d_h, c = ee - ai * g.d_h;
-        a = ws_rin + ai, sa = g.n_in;
-        b = ws_dpre + c, sb = g.d_h;
-    } else {
-        a = nullptr, sa = 0;
-        b = ws_dpre + (e - 2 * P - I), sb = g.d_h;
+    __shared__ __attribute__((aligned(16))) float as[66 * kCS], bs[64 * kCS];
+    const int slice = blockIdx.x, total = n_grad_elems(g), P = g.heads * g.d_h * g.r, I = g.n_in * g.d_h;
+    const bool wh = slice == 2 * g.heads;
+    const int which = slice >= g.heads, hd = slice - which * g.heads;
+    const int ra = wh ? g.n_in : g.d_h, cb = wh ? g.d_h : g.r, count = ra * cb;
+    const float *a = wh ? ws_rin : ws_h, *b = wh ? ws_dpre : (which ? df_k : df_q) + (size_t)hd * g.N * g.r;
+    const int n0 = blockIdx.y * kChunk, nt = min(kChunk, g.N - n0);
+    for (int e = threadIdx.x; e < kChunk * ra; e += kGenNT) {
+        const int t = e / ra;
+        as[(e - t * ra) * kCS + t] = t < nt ? a[(size_t)n0 * ra + e] : 0.f;
     }
-    float acc = 0.f;
-    if (a) {
-#pragma unroll 8
-        for (int n = n0; n < n1; ++n) acc = fmaf(a[(size_t)n * sa], b[(size_t)n * sb], acc);
-    } else {
-#pragma unroll 8
-        for (int n = n0; n < n1; ++n) acc += b[(size_t)n * sb];
+    for (int e = threadIdx.x; e < kChunk * cb; e += kGenNT) {
+        const int t = e / cb;
+        bs[(e - t * cb) * kCS + t] = t < nt ? b[(size_t)n0 * cb + e] : 0.f;
     }
-    partial[(size_t)blockIdx.y * total + e] = acc;
+    __syncthreads();
+    float *dst = partial + (size_t)blockIdx.y * total + (wh ? 2 * P : which * P + hd * g.d_h * g.r);
+    for (int e = threadIdx.x; e < count; e += kGenNT) {
+        const int i = e / cb;
+        const float4 *x = (const float4 *)(as + i * kCS), *y = (const float4 *)(bs + (e - i * cb) * kCS);
+        float acc = 0.f;
+#pragma unroll 8
+        for (int t = 0; t < kChunk / 4; ++t) {
+            const float4 u = x[t], v = y[t];
+            acc = fmaf(u.x, v.x, acc);
+            acc = fmaf(u.y, v.y, acc);
+            acc = fmaf(u.z, v.z, acc);
+            acc = fmaf(u.w, v.w, acc);
+        }
+        dst[e] = acc;
+    }
+    if (wh && (int)threadIdx.x < g.d_h) {
+        const float4 *y = (const float4 *)(bs + threadIdx.x * kCS);
+        float acc = 0.f;
+#pragma unroll
+        for (int t = 0; t < kChunk / 4; ++t) {
+            const float4 v = y[t];
+            acc += v.x;
+            acc += v.y;
+            acc += v.z;
+            acc += v.w;
+        }
+        dst[I + threadIdx.x] = acc;
+    }
 }
 
 // Backward stage 3: chunks ascending, scattered to the four gradient tensors.
@@ -177,6 +242,7 @@ __global__ __launch_bounds__(kGenNT) void features_reduce_kernel(Gen g, int nchu
     const int e = blockIdx.x * kGenNT + threadIdx.x, total = n_grad_elems(g);
     if (e >= total) return;
     float acc = 0.f;
+#pragma unroll 8
     for (int ch = 0; ch < nchunks; ++ch) acc += partial[(size_t)ch * total + e];
     const int P = g.heads * g.d_h * g.r, I = g.n_in * g.d_h;
     if (e < P) dW_pq[e] = acc;
@@ -230,7 +296,8 @@ rib_status rib_features_fwd(const rib_gen_params *p, const float *W_h, const flo
     rib_status st;
     if (!make_gen(p, &g, &st)) return st;
     if (!W_h || !b_h || !W_pq || !W_pk || !f_q || !f_k) return RIB_ERR_NULL;
-    const dim3 grid((unsigned)((g.N + kTok - 1) / kTok)), block(kGenNT);
+    // a second grid dimension where a workgroup's columns would take several turns
+    const dim3 grid((unsigned)((g.N + kTok - 1) / kTok), (unsigned)((2 * g.heads * g.r + kGenNT - 1) / kGenNT)), block(kGenNT);
     const size_t lds = (size_t)kTok * (g.n_in + g.d_h) * sizeof(float);
     hipStream_t s = (hipStream_t)stream;
     if (p->dtype == RIB_BF16)
@@ -265,11 +332,15 @@ rib_status rib_features_bwd(const rib_gen_params *p, const float *W_h, const flo
           *partial = (float *)(ws + l.partial_off);
     hipStream_t s = (hipStream_t)stream;
     const int total = 2 * g.heads * g.d_h * g.r + g.n_in * g.d_h + g.d_h;
+    // heads staged at a time (at least one: 2 * (16 + 64) rows of up to 65 floats)
+    const int per_head = 2 * (kTok * g.r + g.d_h * (g.r | 1));
+    const int group = per_head * g.heads <= kStageFloats ? g.heads : per_head <= kStageFloats ? kStageFloats / per_head : 1;
     hipLaunchKernelGGL(features_hidden_kernel, dim3((unsigned)((g.N + kTok - 1) / kTok)), dim3(kGenNT),
-                       (size_t)kTok * g.n_in * sizeof(float), s, g, W_h, b_h, W_pq, W_pk, df_q, df_k, ws_rin, ws_h, ws_dpre);
+                       ((size_t)kTok * g.n_in + (size_t)group * per_head) * sizeof(float), s, g, group, W_h, b_h, W_pq, W_pk,
+                       df_q, df_k, ws_rin, ws_h, ws_dpre);
     if (hipGetLastError() != hipSuccess) return RIB_ERR_LAUNCH;
     const unsigned eb = (unsigned)((total + kGenNT - 1) / kGenNT);
-    hipLaunchKernelGGL(features_wgrad_kernel, dim3(eb, (unsigned)l.nchunks), dim3(kGenNT), 0, s, g, df_q, df_k, ws_rin, ws_h,
+    hipLaunchKernelGGL(features_wgrad_kernel, dim3((unsigned)(2 * g.heads + 1), (unsigned)l.nchunks), dim3(kGenNT), 0, s, g, df_q, df_k, ws_rin, ws_h,
                        ws_dpre, partial);
     if (hipGetLastError() != hipSuccess) return RIB_ERR_LAUNCH;
     hipLaunchKernelGGL(features_reduce_kernel, dim3(eb), dim3(kGenNT), 0, s, g, l.nchunks, partial, dW_h, db_h, dW_pq, dW_pk);

@@ -1,0 +1,21 @@
+"""The feature generator where its launches change shape: tokens that do not fill a workgroup's 16 or a chunk's 64,
+heads staged in several groups, more columns than two grid rows of lanes.  Same oracle and bounds as
+test_gpu_features.py (fp32 sums of at most 64 terms forward, of N terms relative to the largest gradient backward)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import test_gpu_features as base
+
+SHAPES = [  # (M, heads, r, L, d_h)
+    (11, 9, 33, 10, 32),        # 121 tokens: 7 full workgroups and 9 tokens, a chunk of 57; 594 columns; heads in groups of 4
+    (4, 1, 2, 16, 1),           # exactly one workgroup, a quarter of a chunk, a single hidden unit
+    (8, 13, 17, 0, 64),         # exactly one chunk, no Fourier bands, groups of 2
+]
+
+
+@pytest.mark.parametrize("M,heads,r,L,d_h", SHAPES)
+def test_generator_shapes(M, heads, r, L, d_h):
+    for dtype in ("f32", "bf16"):
+        base.test_generator_forward(M, heads, r, L, d_h, dtype)
+    base.test_generator_backward(M, heads, r, L, d_h)
