@@ -87,9 +87,9 @@ enum {
      * tracking only if a row fails.  Results are the same within rounding; this
      * exists so that both code paths can be tested and timed. */
     RIB_FLAG_FORCE_ROW_MAX = 1,
-    /* Use the wide workgroups (8 waves sharing each streamed tile) whenever the
-     * window has a multiple of 512 tokens, in the bf16 forward; the other kernels
-     * have one workgroup shape.  Same results within rounding (tile boundaries
+    /* Run the bf16 forward's streaming kernel (8 waves sharing each streamed tile)
+     * whenever the window has a multiple of 512 tokens and d < 32, however few
+     * there are; the other kernels pick their own shape.  Same results within rounding (tile boundaries
      * do not enter the arithmetic).  For tests and tuning. */
     RIB_FLAG_WIDE = 2,
     /* Run on the vector-ALU kernels even where a matrix-core kernel serves the

@@ -120,25 +120,33 @@ rib_status enqueue_bwd(const Geo &g, int dtype, const void *q, const void *k, co
 
 namespace rib {
 
-hipError_t prepare_kernel(const void *kern, int *cus)
+hipError_t compute_units(int *cus)
 {
-    static std::mutex mu;
-    static std::set<std::pair<const void *, int>> raised;      // (kernel, device) pairs whose limit is set
-    static int cu_count[kMaxDevices];                          // 0 = not looked up yet
+    static std::atomic<int> count[kMaxDevices];                // 0 = not looked up yet
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(mu);
-    if (cus != nullptr) {
-        if (cu_count[dev] == 0) {
-            int n = 0;
-            e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
-            if (e != hipSuccess) return e;
-            cu_count[dev] = n;
-        }
-        *cus = cu_count[dev];
+    int n = count[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        count[dev].store(n, std::memory_order_relaxed);        // (racing threads store the same number)
     }
+    *cus = n;
+    return hipSuccess;
+}
+
+hipError_t prepare_kernel(const void *kern, int *cus)
+{
+    static std::mutex mu;
+    static std::set<std::pair<const void *, int>> raised;      // (kernel, device) pairs whose limit is set
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (cus != nullptr && (e = compute_units(cus)) != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
     const auto key = std::make_pair(kern, dev);
     if (raised.find(key) == raised.end()) {
         e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds);

@@ -141,6 +141,8 @@ __device__ __forceinline__ TokMap fill_tok_map(const Geo &g, int w, int *lds)
 // remembered, so a later call tries again.  If `cus` is given it receives the number of compute
 // units of the current device (looked up once per device).  Thread-safe.
 hipError_t prepare_kernel(const void *kern, int *cus);
+// The number of compute units of the current device (looked up once per device).
+hipError_t compute_units(int *cus);
 
 // Launchers (each returns the hipError_t of its launches).
 hipError_t launch_valu_fwd(const Geo &g, int dtype, const void *q, const void *k, const void *v,
@@ -167,6 +169,13 @@ hipError_t launch_delta(const Geo &g, int dtype, const void *out, const void *do
 // dF[hd][e] = sum over windows (ascending) of part[(w*heads + hd)][e].
 hipError_t launch_reduce_df(const Geo &g, const float *part_q, const float *part_k, float *dfq, float *dfk,
                             hipStream_t st);
+
+// Whether offsets inside one image fit the 32 bits (and the 24-bit multiply) that the token-row kernels build them with.
+inline bool rows_supported(const Geo &g)
+{
+    const int64_t pixels = (int64_t)g.H * g.W, stride = g.tstride > g.C ? g.tstride : (int64_t)g.C;
+    return pixels < (1 << 24) && stride * 2 < (1 << 24) && pixels * stride * 2 < ((int64_t)1 << 32);
+}
 
 // Matrix-core forward (bf16): whether it serves this problem, and its launcher.
 bool mfma_fwd_supported(const Geo &g, int dtype);

@@ -6,11 +6,8 @@ namespace rib {
 
 bool mfma_bwd_supported(const Geo &g, int dtype)
 {
-    // offsets inside one image fit 32 bits and are built with a 24-bit multiply
-    const int64_t pixels = (int64_t)g.H * g.W, stride = g.tstride > g.C ? g.tstride : (int64_t)g.C;
     return dtype == RIB_BF16 && !(g.flags & RIB_FLAG_VECTOR_ONLY) && g.d <= 32 && (g.d & 1) == 0 && (g.r & 1) == 0 &&
-           g.d + g.r <= 64 && g.N >= 64 && g.N <= 9216 && (g.tstride & 1) == 0 && pixels < (1 << 24) &&
-           stride * 2 < (1 << 24) && pixels * stride * 2 < ((int64_t)1 << 32);
+           g.d + g.r <= 64 && g.N >= 64 && g.N <= 9216 && (g.tstride & 1) == 0 && rows_supported(g);
 }
 
 hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const void *v, const void *fq, const void *fk,

@@ -3,15 +3,17 @@
 //
 // Shape of the computation
 //   A wave owns 64 consecutive window-local queries of one (window, head) unit; a
-//   workgroup (4 or 8 waves) owns one (unit, query block) item at a time.  The unit's
+//   workgroup (8 waves, the general kernel 4) owns one (unit, query block) item at a time.  The unit's
 //   keys/values stream through LDS in tiles (double buffered), gathered from the
 //   channel-last grid through a per-window token map that encodes the window partition
 //   and the cyclic shift.  K_aug = [k || f_k] rows are assembled in LDS (Eq. 5), the
 //   matching Q_aug = [scale_c q || scale_p f_q] rows (pre-multiplied by log2 e) live in
-//   registers; neither ever reaches HBM.  Two kernels: the general one (one workgroup
-//   per item, 64-key tiles, any window size) and the streaming one (whole 128/256-key
-//   tiles; a grid of resident workgroups, each walking a list of items with one
-//   software pipeline running across them).
+//   registers; neither ever reaches HBM.  Three kernels, picked at the end of this file: the
+//   streaming one here (whole 256-key tiles; a grid of resident workgroups, each walking a list of
+//   items with one software pipeline running across them) for launches of enough 512-query items,
+//   the token-row one of rib_mfma_rows.h for every other window, and the general one here (64-key
+//   tiles, 64-bit offsets) for images whose offsets need more than 32 bits; its body is also the
+//   streaming kernel's second walk.
 //
 //   The scores are computed TRANSPOSED, S^T = K_aug Q_aug^T, with the 32x32x16
 //   bf16 MFMA: in its accumulator layout a lane owns ONE query column and 16 of
@@ -33,7 +35,7 @@
 //   redoes them after its last one.  Both paths compute the exact softmax up to
 //   rounding.
 
-#include "rib_common.h"
+#include "rib_mfma_rows.h"
 
 namespace rib {
 namespace {
@@ -279,19 +281,19 @@ __device__ __forceinline__ void attend(const Geo &g, int hd, const TK &tok, bf16
 
 
 // ---------------------------------------------------------------------------------------
-// Fast path: full tiles of 128 keys, no masking, no running maximum, and a hand-ordered
+// Fast path: full tiles of 256 keys, no masking, no running maximum, and a hand-ordered
 // software pipeline.  For the 32x32 block s of a tile the wave issues, interleaved,
 //   the 3 score MFMAs of block s+1, the 16 exp2 + 8 bf16 packs of block s, and the
 //   2 PV MFMAs of block s-1,
 // so the matrix pipe and the vector ALU work on independent data all the time; the
 // staging of the next tile (global loads early, LDS writes late) rides in the gaps.
 // Scheduling fences keep the compiler from regrouping the instruction stream.
-// The fast path runs with 4 or 8 waves per workgroup; a K/V tile holds 32 keys per wave (128 or
-// 256), so that one pass of the staging code (8 lanes per token, 4 tokens per thread) fills it.
+// A K/V tile holds 32 keys per wave, so that one pass of the staging code (8 lanes per token, 4 tokens
+// per thread) fills it.
 template <int WAVES>
 struct FastTile {
     static constexpr int FT = 32 * WAVES;       // keys per tile
-    static constexpr int FVS = FT + 8;          // bf16 per V^T row (272 / 528 B: conflict-free 16-byte reads)
+    static constexpr int FVS = FT + 8;          // bf16 per V^T row (528 B: conflict-free 16-byte reads)
 };
 
 // Two dwords at a 4-byte aligned address (global memory only needs dword alignment for
@@ -462,10 +464,10 @@ __device__ __forceinline__ void read_v_operand(Operands<DQK> &A, int buf, const 
 // the next tile (which lives in (Kn, Vn)) are read behind it: the tail of this tile's arithmetic
 // covers the barrier and the read latency.  On entry A holds the operands of key blocks 0 and 1
 // (V: block 0) of this tile; on exit those of the next tile.
-template <int DQK, bool ONES, int WAVES>
+template <int DQK, int WAVES>
 __device__ __forceinline__ void fast_tile(const Geo &g, const LoadCursor &lc, const char *kbase, const char *vbase,
                                           FastRegs<DQK> &rg, Operands<DQK> &A, const bf16_t *Kc, const bf16_t *Vc, bf16_t *Kn,
-                                          bf16_t *Vn, const bf16x8 (&Q)[2][DQK / 16], f32x16 (&O)[2], float (&lsum)[2])
+                                          bf16_t *Vn, const bf16x8 (&Q)[2][DQK / 16], f32x16 (&O)[2])
 {
     constexpr int KS = DQK / 16;
     constexpr int kFT = FastTile<WAVES>::FT;
@@ -512,10 +514,6 @@ __device__ __forceinline__ void fast_tile(const Geo &g, const LoadCursor &lc, co
             // rounding convert.  Numerator and denominator use the same truncated P.
             const uint32_t w0 = trunc_pack(pe[4 * grp], pe[4 * grp + 1]);
             const uint32_t w1 = trunc_pack(pe[4 * grp + 2], pe[4 * grp + 3]);
-            if (!ONES) {    // no spare V^T row for the ones: sum the packed pairs with the bf16 dot product
-                lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w0), kOnes2, lsum[qb], false);
-                lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w1), kOnes2, lsum[qb], false);
-            }
             if ((grp & 1) == 0) {
                 P[cs][grp >> 1].x = w0;
                 P[cs][grp >> 1].y = w1;
@@ -576,7 +574,7 @@ __device__ __forceinline__ void init_generic_tiles(const Geo &g, bf16_t *Ka, bf1
 }
 // `bias`: the first padding column of K_aug holds 1.0 (its partner in Q_aug is a constant that
 // the score MFMA then adds to every logit), the others 0.
-template <int DQK, int NT, bool ONES>
+template <int DQK, int NT>
 __device__ __forceinline__ void init_fast_tiles(const Geo &g, bf16_t *Kf, bf16_t *Vf, bool bias)
 {
     constexpr int KSTR = DQK + 8, kFT = FastTile<NT / 64>::FT, kFVS = FastTile<NT / 64>::FVS;
@@ -588,13 +586,13 @@ __device__ __forceinline__ void init_fast_tiles(const Geo &g, bf16_t *Kf, bf16_t
         const int per = vrows * (kFVS / 2);
         const int st = e / per, rem = e - st * per;
         const int row = g.d + rem / (kFVS / 2), cw = rem - (rem / (kFVS / 2)) * (kFVS / 2);
-        *(uint32_t *)(Vf + (st * 32 + row) * kFVS + 2 * cw) = (ONES && row == g.d) ? 0x3f803f80u : 0u;
+        *(uint32_t *)(Vf + (st * 32 + row) * kFVS + 2 * cw) = row == g.d ? 0x3f803f80u : 0u;
     }
 }
 
 constexpr int kMaxItemsPerWg = 512;    // items one workgroup of the streaming kernel may be given per launch
 
-template <int DQK, bool FAST, int WAVES = 4>
+template <int DQK, bool FAST, int WAVES = 8>
 struct FwdSmem {
     static constexpr int KSTR = DQK + 8;
     static constexpr int GEN_K = 2 * kTK * KSTR, GEN_V = 2 * 32 * kVStr;       // bf16 elements
@@ -751,7 +749,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void mfma_fwd_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Streaming forward kernel for the common case (whole 128-key tiles, 32-bit byte offsets,
+// Streaming forward kernel for many items (whole 256-key tiles, 32-bit byte offsets,
 // r > 0).  The grid is as many workgroups as the chip holds at once; each walks a list of
 // (unit, query block) items and keeps ONE software pipeline running across them: while the
 // last K/V tiles of an item are in the matrix cores, the first tiles of the next item are
@@ -791,10 +789,8 @@ __device__ __forceinline__ TokMap map_at(const Geo &g, const int *slot)
 
 
 
-// Raw q / f_q words of a wave's 64 query rows, between their request and their staging.  Two layouts
-// share the registers: the general one (16 lanes per token, 4 tokens per pass: w[p] content pair, w[16 + p]
-// and w[32 + p] RIB pairs of row p*4 + sub) and the direct one (the lane's own two query columns in operand
-// order: w[(qb * KS + t) * 4 + i] = dword i of k-step t).
+// Raw q / f_q words of a wave's 64 query rows, between their request and their staging: 16 lanes per
+// token, 4 tokens per pass; w[p] content pair, w[16 + p] and w[32 + p] RIB pairs of row p*4 + sub.
 template <int DQK>
 struct QRaw {
     uint32_t w[DQK == 64 ? 48 : 32];
@@ -851,82 +847,8 @@ __device__ __forceinline__ void q_stage(const QRaw<DQK> &r, const Geo &g, bf16_t
     }
 }
 
-// The direct form, for ranks that are multiples of 8: the row [f_q || q || padding] then falls into whole
-// 16-byte pieces of ONE source each, and a lane fetches the pieces of its own two query columns in
-// operand order -- piece 2t + hf of row q0 + 32 qb + col is k-step t of query block qb -- with no trip
-// through LDS: 3 or 4 loads per query block instead of 16 or 24, one token look-up instead of eight.
-// The last content piece may be short (d = 30: 12 bytes); nothing past the head's slice is read.
-struct __attribute__((packed, aligned(4))) dword4 {
-    uint32_t x, y, z, w;
-};
-template <int DQK>
-__device__ __forceinline__ void q_request_direct(QRaw<DQK> &r, const Geo &g, const TokMap &tok, int hd, int q0,
-                                                 uint32_t tsb, const bf16_t *__restrict__ q,
-                                                 const bf16_t *__restrict__ fq)
-{
-    constexpr int KS = DQK / 16;
-    const int lane = opaque_tid() & 63, col = lane & 31, hf = lane >> 5;
-    const int nf = g.r >> 3;                                    // RIB pieces
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int n = q0 + qb * 32 + col;
-        const char *qsrc = (const char *)q + (__umul24((uint32_t)tok[n], tsb) + (uint32_t)(hd * g.d) * 2u);
-        const char *fsrc = (const char *)fq + (uint32_t)(hd * g.N + n) * (uint32_t)(g.r * 2);
-#pragma unroll
-        for (int t = 0; t < KS; ++t) {
-            const int p = 2 * t + hf, base = (qb * KS + t) * 4;
-            r.w[base] = r.w[base + 1] = r.w[base + 2] = r.w[base + 3] = 0u;
-            if (p < nf) {
-                const dword4 x = *(const dword4 *)(fsrc + 16 * p);
-                r.w[base] = x.x, r.w[base + 1] = x.y, r.w[base + 2] = x.z, r.w[base + 3] = x.w;
-            } else {
-                const int e0 = 8 * (p - nf), nd = (g.d - e0) >> 1;      // first content element, dwords left
-                const char *src = qsrc + 2 * e0;
-                if (nd >= 4) {
-                    const dword4 x = *(const dword4 *)src;
-                    r.w[base] = x.x, r.w[base + 1] = x.y, r.w[base + 2] = x.z, r.w[base + 3] = x.w;
-                } else {
-                    if (nd >= 2) {
-                        const dword2 x = *(const dword2 *)src;
-                        r.w[base] = x.x, r.w[base + 1] = x.y;
-                    }
-                    if (nd == 1) r.w[base] = *(const uint32_t *)src;
-                    if (nd == 3) r.w[base + 2] = *(const uint32_t *)(src + 8);
-                }
-            }
-        }
-    }
-}
-template <int DQK>
-__device__ __forceinline__ void q_stage_direct(const QRaw<DQK> &r, const Geo &g, uint32_t padw, bool bias,
-                                               bf16x8 (&Q)[2][DQK / 16])
-{
-    constexpr int KS = DQK / 16;
-    const int hf = (opaque_tid() & 63) >> 5;
-    const int nf = g.r >> 3;
-    const float sc = g.scale_c * kLog2e, sp = g.scale_p * kLog2e;
-    const int eb = g.d + g.r;                                   // the column of the logit offset
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int t = 0; t < KS; ++t) {
-            const int p = 2 * t + hf, base = (qb * KS + t) * 4;
-            const float s = p < nf ? sp : sc;
-            uint4 o;
-            o.x = pack_bf16(lo_bf16(r.w[base]) * s, hi_bf16(r.w[base]) * s);
-            o.y = pack_bf16(lo_bf16(r.w[base + 1]) * s, hi_bf16(r.w[base + 1]) * s);
-            o.z = pack_bf16(lo_bf16(r.w[base + 2]) * s, hi_bf16(r.w[base + 2]) * s);
-            o.w = pack_bf16(lo_bf16(r.w[base + 3]) * s, hi_bf16(r.w[base + 3]) * s);
-            if (bias && p == (eb >> 3)) {       // (d and r even, r a multiple of 8: the column opens a dword)
-                const int dw = (eb & 7) >> 1;
-                o.x = dw == 0 ? padw : o.x, o.y = dw == 1 ? padw : o.y, o.z = dw == 2 ? padw : o.z, o.w = dw == 3 ? padw : o.w;
-            }
-            Q[qb][t] = __builtin_bit_cast(bf16x8, o);
-        }
-}
-
 // The pipelined walk of one workgroup over its items (see the kernel below).
-template <int DQK, bool ONES, int WAVES>
+template <int DQK, int WAVES>
 __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0, int nx, int my_n, char *smem,
                                              const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                              const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
@@ -956,16 +878,12 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
     const bool bias = g.d + g.r < DQK;
     const uint32_t padw = bias ? (uint32_t)narrow_bf16(kTruncLog2) : 0u;
     const uint32_t tsb = (uint32_t)g.tstride * 2u;
-    // Q rows straight into operand order (see q_request_direct) where that measured faster: the 64-column
-    // variants with d = 32 (r = 32: 6 % at N = 2304).  With 48 columns the scattered 16-byte loads take longer to
-    // land than the 16-lanes-per-token requests, and the time between items is waiting, not issuing: 2 % slower.
-    const bool direct = DQK == 64 && !ONES && (g.r & 7) == 0;
     const char *kbase = (const char *)k, *vbase = (const char *)v;
 
     Item ci = decode_item(g, item0, nqblk);
     fill_tok_map<NT>(g, ci.w, maps);
     if (my_n > 1) fill_tok_map<NT>(g, decode_item(g, item0 + nx, nqblk).w, maps + map_words);
-    init_fast_tiles<DQK, NT, ONES>(g, Kf, Vf, bias);
+    init_fast_tiles<DQK, NT>(g, Kf, Vf, bias);
     __syncthreads();
 
     LoadCursor lc;
@@ -1000,16 +918,14 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
         request(rg);
         advance();
         QRaw<DQK> qr;
-        if (direct) q_request_direct<DQK>(qr, g, lc.tok, ci.hd, ci.blk * NT + wave * 64, tsb, q, fq);   // (cursor still in item 0)
-        else q_request<DQK>(qr, g, lc.tok, ci.hd, ci.blk * NT + wave * 64, tsb, q, fq);
+        q_request<DQK>(qr, g, lc.tok, ci.hd, ci.blk * NT + wave * 64, tsb, q, fq);   // (cursor still in item 0)
         {
             const FastConst<DQK> c0 = fast_const<DQK, WAVES>(g, ci.hd, opaque_tid());
             fast_store<DQK, WAVES>(rg, c0, Kf, Vf);
         }
         request(rg);
         advance();
-        if (direct) q_stage_direct<DQK>(qr, g, padw, bias, Q);
-        else q_stage<DQK>(qr, g, Ws, padw, Q);
+        q_stage<DQK>(qr, g, Ws, padw, Q);
     }
     for (int e = tid; e < my_n; e += NT) redo_flag[e] = 0;
     __syncthreads();
@@ -1020,7 +936,6 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
     int cur = 0;
     for (int t = 0; t < my_n; ++t) {
         f32x16 O[2];
-        float lsum[2] = {0.f, 0.f};
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -1031,8 +946,8 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
             // barrier inside the last tile publishes it
             if (tile == ntiles - 1 && t + 2 < my_n)
                 fill_tok_map<NT>(g, decode_item(g, item0 + nx * (t + 2), nqblk).w, maps + ((t + 2) % 3) * map_words);
-            fast_tile<DQK, ONES, WAVES>(g, lc, kbase, vbase, rg, A, Kf + cur * KSZ, Vf + cur * VSZ, Kf + (cur ^ 1) * KSZ,
-                                        Vf + (cur ^ 1) * VSZ, Q, O, lsum);
+            fast_tile<DQK, WAVES>(g, lc, kbase, vbase, rg, A, Kf + cur * KSZ, Vf + cur * VSZ, Kf + (cur ^ 1) * KSZ,
+                                        Vf + (cur ^ 1) * VSZ, Q, O);
             advance();
             cur ^= 1;
         }
@@ -1041,7 +956,7 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
         bool bad = false;
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            const float l = ONES ? ones_row(O[qb], g.d) : lsum[qb] + __shfl_xor(lsum[qb], 32);
+            const float l = ones_row(O[qb], g.d);
             if (!((l >= 0x1p-60f) && (l <= 0x1p60f))) bad = true;
         }
         const bool redo = __any(bad);
@@ -1055,14 +970,13 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
         if (t + 1 < my_n) {     // the next item's Q rows are requested now and land during the epilogue
             ni = decode_item(g, item0 + nx * (t + 1), nqblk);
             const TokMap ntok = map_at(g, maps + ((t + 1) % 3) * map_words);
-            if (direct) q_request_direct<DQK>(qr, g, ntok, ni.hd, ni.blk * NT + wave * 64, tsb, q, fq);
-            else q_request<DQK>(qr, g, ntok, ni.hd, ni.blk * NT + wave * 64, tsb, q, fq);
+            q_request<DQK>(qr, g, ntok, ni.hd, ni.blk * NT + wave * 64, tsb, q, fq);
         }
 
-        // Two forms of the output stage; which one is faster was measured per variant: the narrow variants
-        // with the ones row (d < 32, d + r <= 48: the benchmark configs, r = 18) store directly (1 % at N = 1024,
-        // 5 % at N = 256), the 64-column and d = 32 variants are 1-4 % faster through the LDS transpose.
-        constexpr bool kDirectStores = ONES && DQK <= 48;
+        // Two forms of the output stage; which one is faster was measured per variant: the narrow one (d + r <= 48:
+        // the benchmark configs, r = 18) stores directly (1 % at N = 1024), the 64-column one is 1-4 % faster
+        // through the LDS transpose.
+        constexpr bool kDirectStores = DQK <= 48;
         if constexpr (kDirectStores) {
         if (!redo) {
             // Normalise and store straight from the accumulator layout: a lane holds, for ONE token, four
@@ -1085,7 +999,7 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
                         else if (8 * c4 + 4 * hf + 2 <= g.d) gw[c4].x = *(const uint32_t *)gp;
                     }
                 }
-                const float l = ONES ? ones_row(O[qb], g.d) : lsum[qb] + __shfl_xor(lsum[qb], 32);
+                const float l = ones_row(O[qb], g.d);
                 const float inv = 1.f / l;
                 if (lse != nullptr && hf == 0)
                     lse[(int64_t)ci.u * g.N + q0 + qb * 32 + col] = (__builtin_amdgcn_logf(l) + (bias ? 0.f : kTruncLog2)) * kLn2;
@@ -1129,7 +1043,7 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
                         gw[pp] = *(const uint32_t *)((const bf16_t *)g.gate +
                                                      (int64_t)ctok[q0 + qb * 32 + pp * 4 + sub] * g.C + ci.hd * g.d + 2 * jc);
                 }
-                const float l = ONES ? ones_row(O[qb], g.d) : lsum[qb] + __shfl_xor(lsum[qb], 32);
+                const float l = ones_row(O[qb], g.d);
                 const float inv = 1.f / l;
 #pragma unroll
                 for (int i = 0; i < 16; i += 2) {
@@ -1160,13 +1074,12 @@ __device__ __forceinline__ void stream_items(const Geo &g, int nqblk, int item0,
 
         if (t + 1 < my_n) {
             ci = ni;
-            if (direct) q_stage_direct<DQK>(qr, g, padw, bias, Q);
-            else q_stage<DQK>(qr, g, Ws, padw, Q);
+            q_stage<DQK>(qr, g, Ws, padw, Q);
         }
     }
 }
 
-template <int DQK, bool ONES, int WAVES>
+template <int DQK, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 2) void mfma_fwd_stream_kernel(
     Geo g, int nqblk, int item_base, int n_items, int force_max, const bf16_t *__restrict__ q,
     const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
@@ -1187,7 +1100,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void mfma_fwd_stream_kernel(
     if (my_n == 0) return;
     const int item0 = item_base + first + j;
 
-    if (!force_max) stream_items<DQK, ONES, WAVES>(g, nqblk, item0, nx, my_n, smem, q, k, v, fq, fk, out, lse);
+    if (!force_max) stream_items<DQK, WAVES>(g, nqblk, item0, nx, my_n, smem, q, k, v, fq, fk, out, lse);
 
     // Cold path: the noted items (every item under force_max) on the max-tracking general kernel body.
     __syncthreads();
@@ -1196,64 +1109,53 @@ __global__ __launch_bounds__(WAVES * 64, 2) void mfma_fwd_stream_kernel(
         __syncthreads();
         const Item it = decode_item(g, item0 + nx * t, nqblk);
         const TokMap tok = fill_tok_map<NT>(g, it.w, maps);
-        generic_item<DQK, WAVES, ONES, true>(g, it.u, it.blk, it.hd, tok, (bf16_t *)smem, 1, q, k, v, fq, fk, out, lse);
+        generic_item<DQK, WAVES, true, true>(g, it.u, it.blk, it.hd, tok, (bf16_t *)smem, 1, q, k, v, fq, fk, out, lse);
     }
 }
 
-// WAVES = 0: the general kernel (4 waves, 64-key tiles, one workgroup per item); 4 or 8: the
-// streaming kernel (as many workgroups as the chip holds at once).
-template <int DQK, bool ONES, int WAVES>
-hipError_t launch(const Geo &g, int force_max, const void *q, const void *k, const void *v, const void *fq,
-                  const void *fk, void *out, float *lse, hipStream_t st)
+// The streaming kernel: as many workgroups of 8 waves as the chip holds at once (one per CU).
+template <int DQK>
+hipError_t launch_stream(const Geo &g, int force_max, const void *q, const void *k, const void *v, const void *fq,
+                         const void *fk, void *out, float *lse, hipStream_t st)
 {
-    constexpr bool FAST = WAVES != 0;
-    constexpr int NW = FAST ? WAVES : 4;
-    using Sm = FwdSmem<DQK, FAST, NW>;
-    const int nqblk = (g.N + NW * 64 - 1) / (NW * 64);
-    const int ntiles = (g.N + kTK - 1) / kTK;
+    using Sm = FwdSmem<DQK, true, 8>;
+    const int nqblk = g.N / 512;
     const int64_t items = g.units * nqblk;
-    if constexpr (FAST) {
-        const size_t dyn = Sm::TILE_BYTES + (size_t)NW * Sm::WAVE_ELEMS * sizeof(bf16_t) +
-                           ((size_t)kMaxItemsPerWg + (size_t)3 * 2 * g.M) * sizeof(int);
-        if (dyn > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-        auto kern = mfma_fwd_stream_kernel<DQK, ONES, NW>;
-        int cus = 0;
-        hipError_t e = prepare_kernel((const void *)kern, &cus);
+    const size_t dyn = Sm::TILE_BYTES + (size_t)8 * Sm::WAVE_ELEMS * sizeof(bf16_t) +
+                       ((size_t)kMaxItemsPerWg + (size_t)3 * 2 * g.M) * sizeof(int);
+    if (dyn > (size_t)kMaxDynLds) return hipErrorInvalidValue;
+    auto kern = mfma_fwd_stream_kernel<DQK, 8>;
+    int cus = 0;
+    hipError_t e = prepare_kernel((const void *)kern, &cus);
+    if (e != hipSuccess) return e;
+    // (a launch hands a workgroup at most kMaxItemsPerWg items; larger problems take several launches)
+    for (int64_t done = 0; done < items;) {
+        const int64_t n = items - done < (int64_t)cus * kMaxItemsPerWg ? items - done : (int64_t)cus * kMaxItemsPerWg;
+        const unsigned grid = (unsigned)(n < cus ? n : cus);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), dyn, st, g, nqblk, (int)done, (int)n, force_max,
+                           (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)fq,
+                           (const bf16_t *)fk, (bf16_t *)out, lse);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
-        int per_cu = NW == 4 ? 2 : 1;               // what LDS and registers allow
-        const int64_t slots = (int64_t)cus * per_cu;
-        // (a launch hands a workgroup at most kMaxItemsPerWg items; larger problems take several launches)
-        for (int64_t done = 0; done < items;) {
-            const int64_t n = items - done < slots * kMaxItemsPerWg ? items - done : slots * kMaxItemsPerWg;
-            const unsigned grid = (unsigned)(n < slots ? n : slots);
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), dyn, st, g, nqblk, (int)done, (int)n, force_max,
-                               (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)fq,
-                               (const bf16_t *)fk, (bf16_t *)out, lse);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            done += n;
-        }
-        return hipSuccess;
-    } else {
-        const size_t dyn = Sm::TILE_BYTES + (size_t)ntiles * kTK * sizeof(int);
-        if (dyn > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-        auto kern = mfma_fwd_kernel<DQK, 4, ONES, false>;
-        hipError_t e = prepare_kernel((const void *)kern, nullptr);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)items), dim3(NW * 64), dyn, st, g, nqblk, force_max, (const bf16_t *)q,
-                           (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)fq, (const bf16_t *)fk, (bf16_t *)out,
-                           lse);
-        return hipGetLastError();
+        done += n;
     }
+    return hipSuccess;
 }
 
+// The general kernel: 4 waves, 64-key tiles, one workgroup per item, 64-bit offsets.
 template <int DQK, bool ONES>
-hipError_t launch_pick(const Geo &g, int waves, int force_max, const void *q, const void *k, const void *v,
-                       const void *fq, const void *fk, void *out, float *lse, hipStream_t st)
+hipError_t launch_general(const Geo &g, int force_max, const void *q, const void *k, const void *v, const void *fq,
+                          const void *fk, void *out, float *lse, hipStream_t st)
 {
-    if (waves == 8) return launch<DQK, ONES, 8>(g, force_max, q, k, v, fq, fk, out, lse, st);
-    if (waves == 4) return launch<DQK, ONES, 4>(g, force_max, q, k, v, fq, fk, out, lse, st);
-    return launch<DQK, ONES, 0>(g, force_max, q, k, v, fq, fk, out, lse, st);
+    const int nqblk = (g.N + 255) / 256, ntiles = (g.N + kTK - 1) / kTK;
+    const size_t dyn = FwdSmem<DQK, false>::TILE_BYTES + (size_t)ntiles * kTK * sizeof(int);
+    if (dyn > (size_t)kMaxDynLds) return hipErrorInvalidValue;
+    auto kern = mfma_fwd_kernel<DQK, 4, ONES, false>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nqblk)), dim3(256), dyn, st, g, nqblk, force_max, (const bf16_t *)q,
+                       (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)fq, (const bf16_t *)fk, (bf16_t *)out, lse);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1265,37 +1167,56 @@ bool mfma_fwd_supported(const Geo &g, int dtype)
            g.d + g.r <= 64 && g.N >= 64 && g.N <= 9216 && (g.tstride & 1) == 0;
 }
 
-// The streaming path needs whole tiles (128 keys with 4 waves, 256 with 8) and 32-bit byte
-// offsets built with a 24-bit multiply.  Returns the number of waves per workgroup to run it
-// with, 0 for the general kernel.  Eight waves (one workgroup per CU, each wave stages half as
-// much per key block) are the faster form wherever the kernel variant fits its registers: head
-// dims under 32 (the softmax denominator then comes out of the matrix cores) with 48 columns
-// from 512 tokens per window on, with 64 columns from 4096 on (measured; config 5: 182 against
-// 198 us).  The variants that sum the denominator on the vector ALU (d = 32) spill inside the
-// loop with eight waves and stay at four.
-static int fast_waves(const Geo &g)
+// Whether the streaming kernel serves the problem.  It needs whole 512-query items, the ones row
+// (d < 32), RIB rows its lanes can stage, and 32-bit byte offsets into the whole batch built with a
+// 24-bit multiply.  One 8-wave workgroup per CU takes 512 queries at a time, so its time goes in
+// whole rounds of items: it is taken where the last round is full enough.  Measured against the
+// token-row kernel (us, streaming / rows, 6 heads of 30 channels, r = 16): 32 x 32 windows, 96 x 96
+// images: 2.5 rounds 70 / 73, 3.4 rounds 94 / 90, 5.1 rounds 134 / 131, 6.75 rounds 164 / 174, 10.1
+// rounds 256 / 274; larger windows lose less at an item's ends: 64 x 64, 1.5 rounds 144 / 140, 3.0
+// rounds 239 / 265; 96 x 96, 1.7 rounds 315 / 370, 3.4 rounds 631 / 651.  Under 4096 tokens the
+// 64-column variant stays behind at every size (32 x 32, r = 34, 6.75 rounds: 230 / 194).
+static bool streams(const Geo &g, int cus)
 {
     const int64_t tokens = (int64_t)g.B * g.H * g.W;
-    const bool small_r = (g.d + g.r <= 48) ? (g.r <= 32) : true;
-    if (!(g.r >= 4 && g.d >= 4 && g.N % 128 == 0 && g.N >= 256 && tokens < (1 << 24) && g.tstride * 2 < (1 << 24) &&
-          tokens * g.tstride * 2 < ((int64_t)1 << 32) && small_r))
-        return 0;
-    if (g.N % 512 != 0) return 4;
-    if (g.flags & RIB_FLAG_WIDE) return 8;
-    const bool ones = g.d < 32, narrow = g.d + g.r <= 48;
-    return ones && (narrow || g.N >= 4096) ? 8 : 4;
+    const bool narrow = g.d + g.r <= 48;
+    if (!(g.d < 32 && g.r >= 4 && g.d >= 4 && g.N % 512 == 0 && tokens < (1 << 24) && g.tstride * 2 < (1 << 24) &&
+          tokens * g.tstride * 2 < ((int64_t)1 << 32) && (!narrow || g.r <= 32)))
+        return false;
+    if (g.flags & RIB_FLAG_WIDE) return true;
+    if (!narrow && g.N < 4096) return false;
+    const int64_t items = g.units * (g.N / 512), rounds = (items + cus - 1) / cus;
+    return items * 10 >= rounds * cus * (g.N < 4096 ? 9 : 8);
 }
 
 hipError_t launch_mfma_fwd(const Geo &g, int force_max, const void *q, const void *k, const void *v, const void *fq,
                            const void *fk, void *out, float *lse, hipStream_t st)
 {
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    if (streams(g, cus))
+        return g.d + g.r <= 48 ? launch_stream<48>(g, force_max, q, k, v, fq, fk, out, lse, st)
+                               : launch_stream<64>(g, force_max, q, k, v, fq, fk, out, lse, st);
+    if (rows_supported(g)) {
+        const fwd_rows::Args a = {(const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (const bf16_t *)fq, (const bf16_t *)fk,
+                                  (bf16_t *)out, lse, force_max, st};
+        // 32 queries a wave where 64 a wave would give fewer waves than the chip has SIMDs (us, 32 / 64 a wave:
+        // 6 windows of 24 x 24, 54 waves of 64: 11.9 / 15.0; 9 of 96 x 96, 432 waves: 98 / 113; 24 of 48 x 48,
+        // 576 waves: 30.8 / 33.4; 384 of 16 x 16, 1536 waves: 14.2 / 13.8)
+        const int64_t waves = g.units * ((g.N + 63) / 64);
+        const int qb = waves <= 4 * cus ? 1 : 2, aug = g.d + g.r;
+        // (RIB rows of more than 32 values are staged by the 64-column kernels only)
+        return aug <= 32 && g.d <= 30 ? fwd_rows::launch32(g, qb, a)
+               : aug <= 48 && g.r <= 32 ? fwd_rows::launch48(g, qb, a) : fwd_rows::launch64(g, qb, a);
+    }
+    // images of 2^32 bytes and more
     const bool ones = g.d < 32;
-    const int fast = fast_waves(g);
     if (g.d + g.r <= 48)
-        return ones ? launch_pick<48, true>(g, fast, force_max, q, k, v, fq, fk, out, lse, st)
-                    : launch_pick<48, false>(g, fast, force_max, q, k, v, fq, fk, out, lse, st);
-    return ones ? launch_pick<64, true>(g, fast, force_max, q, k, v, fq, fk, out, lse, st)
-                : launch_pick<64, false>(g, fast, force_max, q, k, v, fq, fk, out, lse, st);
+        return ones ? launch_general<48, true>(g, force_max, q, k, v, fq, fk, out, lse, st)
+                    : launch_general<48, false>(g, force_max, q, k, v, fq, fk, out, lse, st);
+    return ones ? launch_general<64, true>(g, force_max, q, k, v, fq, fk, out, lse, st)
+                : launch_general<64, false>(g, force_max, q, k, v, fq, fk, out, lse, st);
 }
 
 }  // namespace rib

@@ -1,0 +1,350 @@
+// What the bf16 matrix-core kernels that stream token rows share (both backward kernels and the
+// forward kernel for windows of any size): operand types, the LDS image of a streamed tile, the
+// window map, and the staging of a tile from the grid tensors into that image.
+//
+// A streamed tile lies in LDS as plain token rows, written as 8-byte pieces by 8 lanes a token; the
+// operands of products that contract over tokens are read TRANSPOSED from the same rows
+// (ds_read_b64_tr_b16).  A last partial tile repeats the window's last token and the kernels mask
+// its rows of the scores.
+#pragma once
+
+#include "rib_common.h"
+
+namespace rib {
+namespace rows {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+// P and dS go to bf16 by truncation (one byte-permute per pair), which loses half a unit in the
+// last place on average (relative 2^-8 * 0.7213 for log-uniform mantissas).  The loss is made up
+// BEFORE the truncation: this constant is added to the -LSE * log2(e) that rides with every
+// logit, so P (and with it dS = P (dP - delta)) is scaled up by the mean loss and then truncated.
+// Values that are exactly representable (P = 1 of a one-hot row, P = 2^-k of a uniform row) come
+// through unchanged, the others are right on average.
+constexpr float kTruncLog2 = 0.0040593f;   // log2(1 + 2^-8 * 0.7213)
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    bf16x2 v;
+    v[0] = (__bf16)a;
+    v[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ uint32_t scale_pair(uint32_t w, float s) { return pack_bf16(lo_bf16(w) * s, hi_bf16(w) * s); }
+// x as a bf16 pair (hi, lo) with hi + lo == x to ~2^-17 relative
+__device__ __forceinline__ uint32_t split_bf16(float x)
+{
+    bf16x2 v;
+    v[0] = (__bf16)x;
+    v[1] = (__bf16)(x - (float)v[0]);
+    return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ uint32_t trunc_pack(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    uint4 w = {a, b, c, d};
+    return __builtin_bit_cast(bf16x8, w);
+}
+__device__ __forceinline__ f32x16 mfma(const bf16x8 &a, const bf16x8 &b, const f32x16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// The thread id as a value the optimiser cannot trace back: lane constants derived from it are
+// recomputed where they are used instead of being held in registers across the MFMA blocks.
+__device__ __forceinline__ int opaque_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// Two dwords at a 4-byte aligned address.
+struct __attribute__((packed, aligned(4))) dword2 {
+    uint32_t x, y;
+};
+struct __attribute__((packed, aligned(4))) float2u {
+    float x, y;
+};
+struct __attribute__((packed, aligned(4))) float4u {
+    float x, y, z, w;
+};
+
+// A operand of a product that contracts over tokens: 32 columns starting at `c0` (a lane's row is
+// column c0 + lane % 32) of 16 tokens starting at row image `rows`, in the order the 32x32
+// accumulator layout hands its rows to the next MFMA (tokens 4*hf + 0..3, then 8 + 4*hf + 0..3).
+// ds_read_b64_tr_b16 transposes 4 rows x 16 columns per group of 16 lanes: lane a of the group
+// names row a / 4, columns 4 * (a % 4) .. + 3, and receives column a of the four rows.
+// `lane_off` = tr_lane_offset<STRIDE>().
+template <int STRIDE>
+__device__ __forceinline__ int tr_lane_offset(int lane)
+{
+    const int a = lane & 15, chalf = (lane >> 4) & 1, hf = lane >> 5;
+    return (4 * hf + (a >> 2)) * STRIDE + 16 * chalf + 4 * (a & 3);
+}
+typedef s16x4 __attribute__((address_space(3))) *lds_s16x4;
+template <int STRIDE>
+__device__ __forceinline__ bf16x8 read_tr(const bf16_t *rows, int lane_off, int c0)
+{
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(rows + lane_off + c0));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(rows + lane_off + c0 + 8 * STRIDE));
+    return u.v;
+}
+template <int N>
+__device__ __forceinline__ void read_rows(bf16x8 (&dst)[N], const bf16_t *base)
+{
+#pragma unroll
+    for (int t = 0; t < N; ++t) dst[t] = *(const bf16x8 *)(base + 16 * t);
+}
+
+// LDS image of one streamed tile of T tokens: X = augmented rows (content | RIB | zero pad | two
+// extra columns), Y = value-like rows (content | zero pad | two extra columns), then (XS / XD) the
+// tile's -LSE*log2(e) and -delta as floats.  Strides are odd multiples of 16 bytes (conflict-free
+// 16-byte reads).  Three stages rotate: while a tile is multiplied, the next one is complete (its
+// first operands are read ahead of the barrier) and the one after it is being written.
+template <int DQK, int T>
+struct Lay {
+    static constexpr int DVK = 32;
+    static constexpr int XS = DQK + 8, YS = DVK + 8;
+    static constexpr int YR = T * XS, EX = YR + T * YS;
+    static constexpr int STAGE = EX + 4 * T;                        // bf16 elements
+    static constexpr int KS = DQK / 16, VS = DVK / 16;
+    static constexpr int RB = (DQK + 31) / 32;                      // 32-row blocks of dQ_aug^T / dK_aug^T
+    static constexpr int NSTAGE = 3;
+    static constexpr int WAVE_STAT = 64 * (XS + YS);                // one wave's stationary rows (before the first tile)
+    static constexpr size_t bytes(int waves)
+    {
+        return (size_t)(NSTAGE * STAGE > waves * WAVE_STAT ? NSTAGE * STAGE : waves * WAVE_STAT) * sizeof(bf16_t);
+    }
+};
+
+// A window of one image: where its tokens lie, relative to the image's first token.  ALN (window
+// side a multiple of 8): eight consecutive tokens lie in one window row, so a wave's row is scalar
+// arithmetic and a lane adds its column (wrapped once at the image edge).  Otherwise the separable
+// map in LDS (row bases, then wrapped columns), with lookups clamped to the window's last token.
+struct Win {
+    const int *rowb, *colo;
+    uint32_t inv_m;
+    int M, last, y0, x0, H, W;
+    // `n0`: the wave's first token (uniform), this lane's token is n0 + l
+    template <bool ALN>
+    __device__ __forceinline__ uint32_t token(int n0, int l) const
+    {
+        if (ALN) {
+            const int iy = (int)__umulhi((uint32_t)n0, inv_m);
+            int y = y0 + iy;
+            if (y >= H) y -= H;
+            const uint32_t x = (uint32_t)(x0 + n0 - iy * M) + (uint32_t)l, xw = x - (uint32_t)W;
+            return (x < xw ? x : xw) + (uint32_t)(y * W);
+        }
+        const int n = n0 + l, nc = n < last ? n : last;
+        const int iy = (int)__umulhi((uint32_t)nc, inv_m);
+        return (uint32_t)(rowb[iy] + colo[nc - __mul24(iy, M)]);
+    }
+    // any token (per lane)
+    __device__ __forceinline__ uint32_t any(int n) const
+    {
+        const int iy = (int)__umulhi((uint32_t)n, inv_m);
+        int y = y0 + iy;
+        if (y >= H) y -= H;
+        int x = x0 + n - __mul24(iy, M);
+        if (x >= W) x -= W;
+        return (uint32_t)(y * W + x);
+    }
+};
+template <bool ALN>
+__device__ __forceinline__ Win window_of(const Geo &g, int w, int nt, int *lds, int &b)
+{
+    const int wx = w % g.nwx, t = w / g.nwx, wy = t % g.nwy;
+    b = t / g.nwy;
+    Win m;
+    m.y0 = wy * g.M + g.s, m.x0 = wx * g.M + g.s;
+    m.rowb = lds, m.colo = lds + g.M;
+    m.inv_m = g.inv_m, m.M = g.M, m.last = g.N - 1, m.H = g.H, m.W = g.W;
+    if (!ALN) {
+        for (int i = threadIdx.x; i < 2 * g.M; i += nt) {
+            if (i < g.M) {
+                const int y = m.y0 + i;
+                lds[i] = (y >= g.H ? y - g.H : y) * g.W;
+            } else {
+                const int x = m.x0 + i - g.M;
+                lds[i] = x >= g.W ? x - g.W : x;
+            }
+        }
+    }
+    return m;
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs; renumber them so that each XCD works on a
+// contiguous range of (unit, block) and its L2 sees all users of a window's lines.
+__device__ __forceinline__ void block_coords(int nblk, int64_t &u, int &blk)
+{
+    const int G = gridDim.x, per = G >> 3, rem = G & 7, xcd = blockIdx.x & 7;
+    const int logical = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
+    u = logical / nblk;
+    blk = logical - (int)(u * nblk);
+}
+
+// What a lane moves when 8 lanes share a token: the dword pair 2j, 2j+1 of the content row and of
+// the RIB row (a second pair for rows longer than 32 values).  Lanes past the end slide back onto
+// the last pair (they duplicate a neighbour); rows of a single dword (d = 2, r = 2) move alone.
+// TINY compiles those single-dword rows (and r = 0) in; without it d >= 4 and r >= 4.
+struct Piece {
+    int dc, f0, f1;                 // first dword of the content / RIB pieces
+    bool c1, f1d, fnone;            // single-dword content / RIB rows, no RIB at all (uniform)
+};
+template <bool TINY>
+__device__ __forceinline__ Piece piece_of(const Geo &g, int j)
+{
+    const int hp = g.d >> 1, rh = g.r >> 1;
+    Piece p;
+    p.c1 = TINY && hp < 2;
+    p.f1d = TINY && rh < 2;
+    p.fnone = TINY && rh == 0;
+    p.dc = p.c1 ? 0 : (2 * j < hp - 2 ? 2 * j : hp - 2);
+    p.f0 = p.f1d ? 0 : (2 * j < rh - 2 ? 2 * j : rh - 2);
+    p.f1 = p.f1d ? 0 : (16 + 2 * j < rh - 2 ? 16 + 2 * j : rh - 2);
+    return p;
+}
+__device__ __forceinline__ dword2 get8(const char *base, uint32_t off, bool one)
+{
+    dword2 v;
+    if (one) v.x = *(const uint32_t *)(base + off), v.y = 0u;
+    else v = *(const dword2 *)(base + off);
+    return v;
+}
+__device__ __forceinline__ void put8(bf16_t *dst, const dword2 &v, bool one)
+{
+    if (one) *(uint32_t *)dst = v.x;
+    else *(dword2 *)dst = v;
+}
+
+// Streamed operand pair of a unit.  QDO: X = q (strided), Y = dO (dense), extras = LSE, delta.
+// Otherwise X = k, Y = v (both strided), extras = ones.
+struct Stream {
+    const char *xb, *yb, *fb;       // this image's and head's slices; this head's RIB table
+    const float *lse, *delta;       // this unit's rows (QDO)
+    uint32_t xs, ys, frow;          // token strides and RIB row in bytes
+};
+
+template <int DQK>
+struct Regs {
+    dword2 x[2], y[2], fa[2], fb[DQK == 64 ? 2 : 1];
+    float e0;
+};
+
+// Request tile `tile`: slots tid and tid + NT of the tile's T * 8 (8 lanes a token).
+template <int DQK, int T, bool QDO, bool ALN, bool TINY>
+__device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
+{
+    const int lane = opaque_tid() & 63, l = lane >> 3;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int slot = p * nt + wave * 64;                // the wave's first slot
+        if ((T == 64 && nt == 256) || slot < T * 8) {
+            const int n0 = tile * T + (slot >> 3);
+            const uint32_t t = win.token<ALN>(n0, l);
+            rg.x[p] = get8(s.xb, __umul24(t, s.xs) + 4u * pc.dc, pc.c1);
+            rg.y[p] = get8(s.yb, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+            if (!pc.fnone) {
+                const int n = n0 + l, nc = ALN ? n : (n < win.last ? n : win.last);
+                const uint32_t fr = __umul24((uint32_t)nc, s.frow);
+                rg.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
+                if (DQK == 64) rg.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+            }
+        }
+    }
+    if (QDO && wave < T / 32) {     // LSE by the lower, delta by the upper T of T / 32 waves' lanes
+        const int tid = wave * 64 + lane, n = tile * T + (tid & (T - 1));
+        rg.e0 = ((tid & T) ? s.delta : s.lse)[ALN ? n : (n < win.last ? n : win.last)];
+    }
+}
+
+template <int DQK, int T, bool QDO, bool XS, bool XD, bool TINY>
+__device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int nt, int wave)
+{
+    using L = Lay<DQK, T>;
+    const int lane = opaque_tid() & 63, l = lane >> 3;
+    const Piece pc = piece_of<TINY>(g, lane & 7);
+    bf16_t *xr = S + __mul24(l, L::XS) + 2 * pc.dc, *yr = S + L::YR + __mul24(l, L::YS) + 2 * pc.dc;
+    bf16_t *fr = S + __mul24(l, L::XS) + g.d + 2 * pc.f0, *fr1 = S + __mul24(l, L::XS) + g.d + 2 * pc.f1;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int slot = p * nt + wave * 64;
+        if ((T == 64 && nt == 256) || slot < T * 8) {
+            dword2 x = rg.x[p], fa = rg.fa[p], fb;
+            if (DQK == 64) fb = rg.fb[p];
+            if (QDO) {
+                x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
+                fa.x = scale_pair(fa.x, sp), fa.y = scale_pair(fa.y, sp);
+                if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
+            }
+            const int r0 = slot >> 3;                       // (uniform)
+            put8(xr + r0 * L::XS, x, pc.c1);
+            put8(yr + r0 * L::YS, rg.y[p], pc.c1);
+            if (!pc.fnone) {
+                put8(fr + r0 * L::XS, fa, pc.f1d);
+                if (DQK == 64) put8(fr1 + r0 * L::XS, fb, pc.f1d);
+            }
+        }
+    }
+    if (QDO && wave < T / 32) {
+        const int tid = wave * 64 + lane, row = tid & (T - 1);
+        const bool dl = (tid & T) != 0;
+        const float v = dl ? -rg.e0 : kTruncLog2 - rg.e0 * kLog2e;
+        const uint32_t pk = split_bf16(v);
+        if (dl) {
+            if (XD) ((float *)(S + L::EX))[T + row] = v;
+            else *(uint32_t *)(S + L::YR + row * L::YS + L::DVK - 2) = pk;
+        } else {
+            if (XS) ((float *)(S + L::EX))[row] = v;
+            else *(uint32_t *)(S + row * L::XS + DQK - 2) = pk;
+        }
+    }
+}
+
+// The columns no staging code writes, once for every row of every stage: zero padding (it meets
+// the zero padding of the stationary operands, so it only has to be finite), and for K / V tiles
+// the ones that LSE and delta meet.
+template <int DQK, int T, bool QDO, bool XS, bool XD>
+__device__ __forceinline__ void init_pads(const Geo &g, bf16_t *stages, int nt)
+{
+    using L = Lay<DQK, T>;
+    for (int e = threadIdx.x; e < L::NSTAGE * T; e += nt) {
+        bf16_t *xr = stages + (e / T) * L::STAGE + (e % T) * L::XS, *yr = stages + (e / T) * L::STAGE + L::YR + (e % T) * L::YS;
+        for (int c = g.d + g.r; c < DQK; c += 2)
+            if (c < DQK - 2 || XS) *(uint32_t *)(xr + c) = 0u;
+            else if (!QDO) *(uint32_t *)(xr + c) = 0x3f803f80u;
+        for (int c = g.d; c < L::DVK; c += 2)
+            if (c < L::DVK - 2 || XD) *(uint32_t *)(yr + c) = 0u;
+            else if (!QDO) *(uint32_t *)(yr + c) = 0x3f803f80u;
+    }
+}
+
+// Rows of a score block whose streamed token lies past the window: minus infinity, so that P and
+// dS vanish there (the staged rows repeat the last token, so everything else is finite).
+__device__ __forceinline__ void mask_rows(f32x16 &S, int first, int N, int hf)
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (first + 8 * (i >> 2) + 4 * hf + (i & 3) >= N) S[i] = -INFINITY;
+}
+
+#define RIB_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+}  // namespace rows
+}  // namespace rib

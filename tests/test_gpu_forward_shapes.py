@@ -1,0 +1,61 @@
+"""The bf16 token-row forward kernels where their dispatch changes hands, against the oracle, every element: padded
+widths 32 / 48 / 64 with the truncation offset in a column or on the denominator; denominators from the ones columns
+and from the packed sums (d = 32); window sides that are and are not multiples of 8; workgroups of 2, 3, 4 waves of 64
+queries (grids that fill the chip) and 4 to 8 waves of 32 (grids that do not), with waves wholly or half past the
+window's end; single-dword rows and no RIB; the walk with the running maximum.
+
+Tolerance: the parity tests' 2e-2 absolute for logits of this size; bf16 rounds the scaled Q row and P to 2^-8
+relative each, and O is an average of values of size one."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2603_06738_amd import binding as rb
+from paper_2603_06738_amd import workloads as wk
+from helpers import geometry
+
+SHAPES = [  # (d, r, M, shift, H / M, W / M); `many` repeats the image until 64-query waves outnumber 1024 SIMDs
+    (16, 14, 8, 3, 1, 2),       # one 64-token block; width 32, offset in the columns
+    (16, 16, 24, 12, 1, 1),     # 3 waves of 64, 6 of 32; width 32, offset on the denominator
+    (30, 2, 40, 7, 1, 1),       # width 32, single-dword RIB rows
+    (30, 16, 24, 5, 2, 1),      # width 48, columns
+    (32, 8, 16, 0, 1, 2),       # packed sums, columns
+    (30, 18, 40, 9, 1, 1),      # width 48, denominator
+    (32, 16, 24, 0, 1, 1),      # packed sums, denominator
+    (30, 34, 8, 4, 2, 2),       # width 64, two RIB pieces a lane
+    (24, 20, 9, 4, 1, 2),       # 81 tokens: a 64-token tile and 17
+    (30, 16, 11, 10, 1, 1),     # 121 tokens
+    (30, 18, 13, 6, 1, 1),      # 169 tokens: three waves of 64, six of 32
+    (28, 36, 15, 1, 1, 1),      # 225 tokens
+    (32, 30, 17, 16, 1, 1),     # 289 tokens: two workgroups of three waves, or of five
+    (30, 34, 25, 3, 1, 1),      # 625 tokens
+    (30, 16, 32, 16, 1, 1),     # whole 512-query items that do not fill the chip
+    (2, 2, 9, 0, 1, 1),         # single-dword content and RIB rows
+    (4, 0, 10, 2, 1, 1),        # no RIB
+    (2, 44, 12, 5, 1, 1),       # RIB rows of more than 32 values
+]
+
+
+@pytest.mark.parametrize("many", [False, True], ids=["few", "many"])
+@pytest.mark.parametrize("d,r,M,s,ny,nx", SHAPES)
+def test_forward_shapes(oracle, d, r, M, s, ny, nx, many):
+    import torch
+    import gpu_helpers as gh
+    per_image = 2 * ny * nx * ((M * M + 63) // 64)
+    B = 1 + 1024 // per_image if many else 2
+    wl = wk.custom(f"fwd-d{d}r{r}m{M}", "bf16", B, ny * M, nx * M, 2, d, r, M, s, 8000 + 64 * M + d + r)
+    assert rb.kernel_name(rb.params_of(wl), False) == "mfma-bf16"
+    x = wk.make_inputs(wl)
+    O_ref, lse_ref = oracle.fwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"])
+    for packed in (False, True):
+        t = gh.device_inputs(wl, x, packed=packed)
+        for flags in (0, rb.RIB_FLAG_FORCE_ROW_MAX):
+            out, lse = gh.gpu_fwd(wl, t, flags=flags, packed=packed)
+            assert gh.max_abs(gh.host(out), O_ref) <= gh.TOL["bf16"], flags
+            assert gh.max_abs(gh.host(lse), lse_ref) <= gh.TOL["bf16"], flags
+    # logits far outside the optimistic walk's range: the second walk, element by element the forced one's
+    t = gh.device_inputs(wl, x)
+    hot = dict(t, q=t["q"] * 64)
+    (a, la), (b, lb) = (gh.gpu_fwd(wl, hot, flags=f, packed=False) for f in (0, rb.RIB_FLAG_FORCE_ROW_MAX))
+    assert bool(torch.isfinite(a).all()) and bool(torch.isfinite(la).all())
+    assert gh.max_abs(gh.host(a), gh.host(b)) <= gh.TOL["bf16"] and gh.max_abs(gh.host(la), gh.host(lb)) <= gh.TOL["bf16"]
