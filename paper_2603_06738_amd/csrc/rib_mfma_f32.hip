@@ -1,4 +1,7 @@
-// RIB window attention for fp32 problems on the matrix cores (v_mfma_f32_32x32x2_f32).
+// RIB window attention for fp32 problems on the matrix cores: the host side, and the kernels on
+// v_mfma_f32_32x32x2_f32.  Most problems run on the faster kernels of rib_f32_split.h (three bf16
+// parts a value); the bodies here serve what those do not take, and the workgroups of theirs that
+// meet values the parts cannot carry.
 //
 // Same operator as include/rib_attn.h describes (paper Sec. 2.2; Sec. 3.1 Eq. 5-6), in fp32
 // throughout: operands, products, accumulators and the softmax state are fp32, so the result
@@ -18,8 +21,8 @@
 // (register, lane half) pairs in whatever order, as long as the A operand is read in the
 // same order.  No value ever moves between lanes except the row max / row sum halves.
 //
-// One workgroup = 4 waves = 128 consecutive window-local tokens of one (window, head) unit
-// kept in registers; the other side is streamed through LDS in tiles of 64 tokens, fetched
+// One workgroup = 4 waves (a split kernel's: up to 8) of 32 consecutive window-local tokens of one
+// (window, head) unit kept in registers; the other side is streamed through LDS in tiles of 64 tokens, fetched
 // one tile ahead into registers, two LDS stages, one workgroup barrier per tile.  Any window of
 // 32 or more tokens, any d <= 32, d + r <= 64.
 #include "rib_common.h"
@@ -113,7 +116,7 @@ __device__ __forceinline__ void tile_request(TileRegs<DA> &rg, const Geo &g, int
                                              const ImgBase &ib, uint32_t xs4, uint32_t ys4, const float *__restrict__ f,
                                              const float *__restrict__ lse, const float *__restrict__ delta)
 {
-    const int tid = threadIdx.x, jj = tid >> 5, c = tid & 31;
+    const int tid = threadIdx.x & (kNT - 1), jj = tid >> 5, c = tid & 31;
     const int valid = g.N - j0 < kTS ? g.N - j0 : kTS;
     const uint32_t ch4 = (uint32_t)(hd * g.d + (c < g.d ? c : g.d - 1)) * 4u;
 #pragma unroll
@@ -145,7 +148,7 @@ template <int DA, int XS, bool EXTRA>
 __device__ __forceinline__ void tile_commit(const TileRegs<DA> &rg, const Geo &g, int j0, uint32_t inv_r, float sc, float sp,
                                             float *Xs, float *Ys, float *Es)
 {
-    const int tid = threadIdx.x, jj = tid >> 5, c = tid & 31;
+    const int tid = threadIdx.x & (kNT - 1), jj = tid >> 5, c = tid & 31;
     const int valid = g.N - j0 < kTS ? g.N - j0 : kTS;
     const bool cv = c < g.d;
 #pragma unroll
@@ -194,20 +197,16 @@ __device__ __forceinline__ void zero_x_tiles(float *Xs)
 }
 
 // Forward: Q_aug rows stationary (pre-multiplied by the scales and log2 e), K_aug / V streamed;
-// online softmax with the running row max per lane.  Three workgroups per CU.
+// online softmax with the running row max per lane.
 template <int DA>
-__global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void fwd_body(const Geo &g, Smem<DA + 1> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
                                                                const float *__restrict__ k, const float *__restrict__ v,
                                                                const float *__restrict__ fq, const float *__restrict__ fk,
                                                                float *__restrict__ out, float *__restrict__ lse)
 {
     constexpr int XS = DA + 1;
-    __shared__ Smem<XS> sm;
-    int64_t u;
-    int blk;
-    unit_of_block(nblk, u, blk);
     const int w = (int)(u / g.heads), hd = (int)(u - (int64_t)w * g.heads);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
 
     const TokMap tok = fill_tok_map<kNT>(g, w, sm.tokl);
     zero_x_tiles<XS>(sm.X[0]);
@@ -220,9 +219,9 @@ __global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, u
     TileRegs<DA> rg;
     tile_request<DA, false>(rg, g, hd, u, 0, tok, ib, ts4, ts4, fk, nullptr, nullptr);
 
-    const int qi = blk * kRowsWg + wave * 32 + col;
+    const int qi = row0 + wave * 32 + col;
     const bool live = qi < g.N;
-    const int qc = live ? qi : g.N - 1;
+    const int qc = qi < g.N ? qi : g.N - 1;
     const int tq = tok[qc];
     float Qr[DA / 2];
 #pragma unroll
@@ -311,7 +310,7 @@ __global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, u
 // dQ and this unit's dF_q contribution: Q_aug, dO rows stationary, K_aug / V streamed.
 //   S^T = K_aug Q_aug^T, dP^T = V dO^T, dS = P (dP - delta), dQ_aug^T += K_aug^T dS^T.
 template <int DA>
-__global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
                                                               const float *__restrict__ k, const float *__restrict__ v,
                                                               const float *__restrict__ fq, const float *__restrict__ fk,
                                                               const float *__restrict__ dout, const float *__restrict__ lse,
@@ -320,12 +319,8 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, ui
 {
     constexpr int RB = DA > 32 ? 2 : 1;     // 32-row blocks of dQ_aug^T
     constexpr int XS = kXS;                 // all 64 columns: the second row block reads columns 32..63
-    __shared__ Smem<XS> sm;
-    int64_t u;
-    int blk;
-    unit_of_block(nblk, u, blk);
     const int w = (int)(u / g.heads), hd = (int)(u - (int64_t)w * g.heads);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
 
     const TokMap tok = fill_tok_map<kNT>(g, w, sm.tokl);
     zero_x_tiles<XS>(sm.X[0]);      // zero operands beyond d + r, and finite (unused) rows of dQ_aug^T there
@@ -338,9 +333,9 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, ui
     TileRegs<DA> rg;
     tile_request<DA, false>(rg, g, hd, u, 0, tok, ib, ts4, ts4, fk, nullptr, nullptr);
 
-    const int qi = blk * kRowsWg + wave * 32 + col;
+    const int qi = row0 + wave * 32 + col;
     const bool live = qi < g.N;
-    const int qc = live ? qi : g.N - 1;
+    const int qc = qi < g.N ? qi : g.N - 1;
     const int tq = tok[qc];
     float Qr[DA / 2], Gr[16];
 #pragma unroll
@@ -428,7 +423,7 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, ui
 //   S = Q_aug K_aug^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta),
 //   dV^T += dO^T P, dK_aug^T += Q_aug^T dS.
 template <int DA>
-__global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void dkv_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
                                                                const float *__restrict__ k, const float *__restrict__ v,
                                                                const float *__restrict__ fq, const float *__restrict__ fk,
                                                                const float *__restrict__ dout, const float *__restrict__ lse,
@@ -437,12 +432,8 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, u
 {
     constexpr int RB = DA > 32 ? 2 : 1;
     constexpr int XS = kXS;
-    __shared__ Smem<XS> sm;
-    int64_t u;
-    int blk;
-    unit_of_block(nblk, u, blk);
     const int w = (int)(u / g.heads), hd = (int)(u - (int64_t)w * g.heads);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
 
     const TokMap tok = fill_tok_map<kNT>(g, w, sm.tokl);
     zero_x_tiles<XS>(sm.X[0]);
@@ -455,9 +446,9 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, u
     TileRegs<DA> rg;
     tile_request<DA, true>(rg, g, hd, u, 0, tok, ib, ts4, (uint32_t)g.C * 4u, fq, lse, delta);
 
-    const int ki = blk * kRowsWg + wave * 32 + col;
+    const int ki = row0 + wave * 32 + col;
     const bool live = ki < g.N;
-    const int kc = live ? ki : g.N - 1;
+    const int kc = ki < g.N ? ki : g.N - 1;
     const int tk = tok[kc];
     float Kr[DA / 2], Vr[16];
 #pragma unroll
@@ -558,36 +549,154 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, u
 }
 
 inline uint32_t inv_r_of(const Geo &g) { return g.r > 1 ? (uint32_t)((((uint64_t)1 << 32) + g.r - 1) / g.r) : 0u; }
-inline int padded_da(const Geo &g) { return (g.d + g.r + 15) / 16 * 16; }
+// The fp32-MFMA bodies as kernels of their own, for what the split kernels do not take (images of 2^32
+// bytes, windows under 64 tokens, odd d and odd r with d + r > 62).
+template <int DA>
+__global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                               const float *__restrict__ k, const float *__restrict__ v,
+                                                               const float *__restrict__ fq, const float *__restrict__ fk,
+                                                               float *__restrict__ out, float *__restrict__ lse)
+{
+    __shared__ Smem<DA + 1> sm;
+    int64_t u;
+    int blk;
+    unit_of_block(nblk, u, blk);
+    fwd_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, out, lse);
+}
+template <int DA>
+__global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                              const float *__restrict__ k, const float *__restrict__ v,
+                                                              const float *__restrict__ fq, const float *__restrict__ fk,
+                                                              const float *__restrict__ dout, const float *__restrict__ lse,
+                                                              const float *__restrict__ delta, float *__restrict__ dq,
+                                                              float *__restrict__ dfq_part)
+{
+    __shared__ Smem<kXS> sm;
+    int64_t u;
+    int blk;
+    unit_of_block(nblk, u, blk);
+    dq_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
+}
+template <int DA>
+__global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                               const float *__restrict__ k, const float *__restrict__ v,
+                                                               const float *__restrict__ fq, const float *__restrict__ fk,
+                                                               const float *__restrict__ dout, const float *__restrict__ lse,
+                                                               const float *__restrict__ delta, float *__restrict__ dk,
+                                                               float *__restrict__ dv, float *__restrict__ dfk_part)
+{
+    __shared__ Smem<kXS> sm;
+    int64_t u;
+    int blk;
+    unit_of_block(nblk, u, blk);
+    dkv_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
+}
+
+}  // namespace
+}  // namespace rib
+
+#include "rib_f32_split.h"
+
+namespace rib {
+namespace {
+
+// Workgroup shape of the split kernels: up to eight waves of 32 stationary tokens, an equal number in
+// every workgroup of a unit, four at the least (they share the staging).  Eight (one workgroup a CU)
+// split a streamed value half as often as four (two a CU); four where eight would leave CUs without a
+// workgroup, or where four fill fewer rounds of the chip (144 units of 324 tokens, forward: eight 62.9 us
+// in two rounds, against 55.2 with the fp32 products).
+inline int split_waves(const Geo &g, int cus, int *nblk)
+{
+    const int nb = (g.N + 31) / 32;
+    const int64_t wg8 = g.units * ((nb + 7) / 8), wg4 = g.units * ((nb + 3) / 4);
+    const bool four = wg8 < cus || (wg4 + 2 * cus - 1) / (2 * cus) < (wg8 + cus - 1) / cus;
+    const int most = four ? 4 : 8;
+    *nblk = (nb + most - 1) / most;
+    const int waves = (nb + *nblk - 1) / *nblk;
+    return waves < 4 ? 4 : waves;
+}
+
+// (tiles of 64 tokens for six waves and up, one workgroup a CU; of 32 for four and five, two a CU)
+template <int DA, int T>
+hipError_t split_fwd(const Geo &g, int waves, int nblk, const float *q, const float *k, const float *v, const float *fq,
+                     const float *fk, float *out, float *lse, hipStream_t st)
+{
+    const size_t lds = split::lds_tiles<DA, T, DA + 1>() + (size_t)2 * g.M * sizeof(int);
+    auto kern = split::fwd_kernel<DA, T>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), lds, st, g, nblk, inv_r_of(g), q, k, v, fq, fk,
+                       out, lse);
+    return hipGetLastError();
+}
+template <int DA, int T>
+hipError_t split_bwd(const Geo &g, int waves, int nblk, const float *q, const float *k, const float *v, const float *fq,
+                     const float *fk, const float *dout, const float *lse, const float *delta, float *dq, float *dk, float *dv,
+                     float *pq, float *pk, hipStream_t st)
+{
+    const size_t lds = split::lds_tiles<DA, T, kXS>() + (size_t)2 * g.M * sizeof(int);
+    auto kdkv = split::dkv_kernel<DA, T>;
+    auto kdq = split::dq_kernel<DA, T>;
+    hipError_t e = prepare_kernel((const void *)kdkv, nullptr);
+    if (e == hipSuccess) e = prepare_kernel((const void *)kdq, nullptr);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(g.units * nblk)), block(waves * 64);
+    hipLaunchKernelGGL(kdkv, grid, block, lds, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, dout, lse, delta, dk, dv, pk);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kdq, grid, block, lds, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, dout, lse, delta, dq, pq);
+    return hipGetLastError();
+}
 
 template <int DA>
-hipError_t fwd_t(const Geo &g, const void *q, const void *k, const void *v, const void *fq, const void *fk, void *out,
+hipError_t fwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, const void *fq_, const void *fk_, void *out_,
                  float *lse, hipStream_t st)
 {
+    const float *q = (const float *)q_, *k = (const float *)k_, *v = (const float *)v_, *fq = (const float *)fq_,
+                *fk = (const float *)fk_;
+    float *out = (float *)out_;
+    if (split::supported(g)) {
+        int cus = 0, nblk = 0;
+        const hipError_t e = compute_units(&cus);
+        if (e != hipSuccess) return e;
+        const int waves = split_waves(g, cus, &nblk);
+        return waves < 6 ? split_fwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, out, lse, st)
+                         : split_fwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, out, lse, st);
+    }
     const int nblk = (g.N + kRowsWg - 1) / kRowsWg;
-    hipLaunchKernelGGL((mfma_f32_fwd_kernel<DA>), dim3((unsigned)(g.units * nblk)), dim3(kNT), 0, st, g, nblk, inv_r_of(g),
-                       (const float *)q, (const float *)k, (const float *)v, (const float *)fq, (const float *)fk,
-                       (float *)out, lse);
+    hipLaunchKernelGGL((mfma_f32_fwd_kernel<DA>), dim3((unsigned)(g.units * nblk)), dim3(kNT), 0, st, g, nblk, inv_r_of(g), q, k,
+                       v, fq, fk, out, lse);
     return hipGetLastError();
 }
 
 template <int DA>
-hipError_t bwd_t(const Geo &g, const void *q, const void *k, const void *v, const void *fq, const void *fk,
-                 const void *dout, const float *lse, const float *delta, void *dq, void *dk, void *dv, float *pq,
+hipError_t bwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, const void *fq_, const void *fk_,
+                 const void *dout_, const float *lse, const float *delta, void *dq_, void *dk_, void *dv_, float *pq,
                  float *pk, hipStream_t st)
 {
+    const float *q = (const float *)q_, *k = (const float *)k_, *v = (const float *)v_, *fq = (const float *)fq_,
+                *fk = (const float *)fk_, *dout = (const float *)dout_;
+    float *dq = (float *)dq_, *dk = (float *)dk_, *dv = (float *)dv_;
+    if (split::supported(g)) {
+        int cus = 0, nblk = 0;
+        const hipError_t e = compute_units(&cus);
+        if (e != hipSuccess) return e;
+        const int waves = split_waves(g, cus, &nblk);
+        return waves < 6 ? split_bwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st)
+                         : split_bwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);
+    }
     const int nblk = (g.N + kRowsWg - 1) / kRowsWg;
     const dim3 grid((unsigned)(g.units * nblk));
-    hipLaunchKernelGGL((mfma_f32_dkv_kernel<DA>), grid, dim3(kNT), 0, st, g, nblk, inv_r_of(g), (const float *)q, (const float *)k,
-                       (const float *)v, (const float *)fq, (const float *)fk, (const float *)dout, lse, delta,
-                       (float *)dk, (float *)dv, pk);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL((mfma_f32_dkv_kernel<DA>), grid, dim3(kNT), 0, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, dout, lse,
+                       delta, dk, dv, pk);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((mfma_f32_dq_kernel<DA>), grid, dim3(kNT), 0, st, g, nblk, inv_r_of(g), (const float *)q, (const float *)k,
-                       (const float *)v, (const float *)fq, (const float *)fk, (const float *)dout, lse, delta,
-                       (float *)dq, pq);
+    hipLaunchKernelGGL((mfma_f32_dq_kernel<DA>), grid, dim3(kNT), 0, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, dout, lse, delta,
+                       dq, pq);
     return hipGetLastError();
 }
+
+inline int padded_da(const Geo &g) { return split::supported(g) ? split::width(g) : (g.d + g.r + 15) / 16 * 16; }
 
 }  // namespace
 

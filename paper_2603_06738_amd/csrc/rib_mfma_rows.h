@@ -109,7 +109,7 @@ constexpr int max_threads(int T, int QB) { return QB == 1 ? 512 : T == 64 ? 256 
 // PV products of block s - 1 ride between the exponentials and packs of block s, in an order pinned
 // with scheduling fences (as in the streaming kernel).
 template <int DQK, int T, int QB, bool XS, bool SUM, bool ALN, bool TINY>
-__global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) void rows_kernel(
+__global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) void rows_fwd_kernel(
     Geo g, int nblk, int force_max, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ fq, const bf16_t *__restrict__ fk, bf16_t *__restrict__ out, float *__restrict__ lse)
 {
@@ -357,7 +357,7 @@ hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 {
     const size_t smem = lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kern = rows_kernel<DQK, T, QB, XS, SUM, ALN, TINY>;
+    auto kern = rows_fwd_kernel<DQK, T, QB, XS, SUM, ALN, TINY>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.force_max, a.q, a.k, a.v,

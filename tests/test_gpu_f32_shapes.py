@@ -1,0 +1,80 @@
+"""The fp32 kernels on three bf16 parts a value, where their staging and dispatch change hands, against the oracle, every
+element: padded widths 16 to 64, odd head dims and ranks (rows padded to even lengths), a second RIB slot a lane, no
+RIB, windows with a partial last block, packed projections; and the rows that go back to fp32 products because a value
+leaves the range of the parts.
+
+Tolerance: products keep 24 bits and sums are fp32.  A logit is a sum of up to 64 products of size one, good to
+about 64 * 2^-24 = 4e-6; O, LSE and the gradients (sums of size one over softmax weights) follow it linearly, with a
+factor of a few: 3e-5 absolute, relative above one."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2603_06738_amd import binding as rb
+from paper_2603_06738_amd import workloads as wk
+from helpers import geometry
+
+SHAPES = [  # (d, r, M, shift, H / M, W / M)
+    (8, 6, 8, 3, 1, 2),         # width 16, one 64-token tile
+    (7, 9, 9, 4, 1, 1),         # both odd: 8 + 10 columns of 32; 81 tokens
+    (30, 2, 12, 7, 1, 1),       # width 32, a single RIB pair; two tiles and a quarter
+    (31, 1, 10, 0, 1, 1),       # odd single-value RIB rows; the last block has 4 keys
+    (16, 0, 8, 5, 2, 1),        # no RIB
+    (30, 18, 16, 5, 1, 1),      # width 48, full
+    (15, 20, 11, 3, 1, 1),      # odd d: RIB starts on the next even column
+    (32, 32, 13, 6, 1, 1),      # width 64, full
+    (30, 33, 14, 1, 1, 1),      # width 64, odd rank in the second slot
+    (5, 47, 9, 2, 1, 1),        # long RIB rows
+    (31, 33, 9, 0, 1, 1),       # both odd and 64 together: the fp32-product kernels
+    (30, 16, 24, 12, 1, 1),     # 576 tokens, five workgroups
+]
+NAMES = ("dQ", "dK", "dV", "dF_q", "dF_k")
+
+
+def _close(gh, a, b, name):
+    scale = max(1.0, float(np.abs(b).max())) if b.size else 1.0
+    assert gh.max_abs(a, b) <= 3e-5 * scale, name
+
+
+@pytest.mark.parametrize("packed", [False, True], ids=["dense", "packed"])
+@pytest.mark.parametrize("d,r,M,s,ny,nx", SHAPES)
+def test_f32_shapes(oracle, d, r, M, s, ny, nx, packed):
+    import gpu_helpers as gh
+    wl = wk.custom(f"f32-d{d}r{r}m{M}", "f32", 2, ny * M, nx * M, 2, d, r, M, s, 9000 + 64 * M + d + r, backward=True)
+    assert rb.kernel_name(rb.params_of(wl), True) == "mfma-f32"
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x, packed=packed)
+    out, lse = gh.gpu_fwd(wl, t, packed=packed)
+    got = gh.gpu_bwd(wl, t, out, lse, packed=packed)
+    g = geometry(oracle, wl)
+    O_ref, lse_ref = oracle.fwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"])
+    ref = oracle.bwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    _close(gh, gh.host(out), O_ref, "O")
+    _close(gh, gh.host(lse), lse_ref, "LSE")
+    for name, a, b in zip(NAMES if r else NAMES[:3], got, ref):
+        _close(gh, gh.host(a), b, name)
+
+
+@pytest.mark.parametrize("tensor,value", [("v", float("inf")), ("v", float("nan")), ("v", 2.0 ** 40), ("d_out", 2.0 ** 40),
+                                          ("d_out", float("-inf")), ("k", float("nan")), ("q", float("inf"))])
+def test_f32_values_outside_the_parts(tensor, value):
+    """One element that three bf16 parts cannot carry: where the vector kernels are finite, infinite or NaN, so are
+    these, and the finite values agree to fp32 rounding (relative to the element's tensor)."""
+    import torch
+    import gpu_helpers as gh
+    wl = wk.custom("f32-range", "f32", 1, 12, 24, 2, 30, 17, 12, 5, 9900, backward=True)
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x)
+    t[tensor][0, 3, 5, 7] = value
+    res = []
+    for flags in (0, rb.RIB_FLAG_VECTOR_ONLY):
+        out, lse = gh.gpu_fwd(wl, t, flags=flags)
+        res.append((out, lse, *gh.gpu_bwd(wl, t, out, lse, flags=flags)))
+    for name, a, b in zip(("O", "LSE") + NAMES, *res):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)), name
+        inf = torch.isinf(b)
+        assert torch.equal(torch.isinf(a), inf) and torch.equal(a[inf], b[inf]), name
+        fin = torch.isfinite(b)
+        if bool(fin.any()):
+            assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
