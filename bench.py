@@ -31,10 +31,10 @@ PEAK_HBM_GBS = 8000.0
 # scaled by a plain copy of known size).  Where such a run of this very workload is committed under profiles/,
 # `traffic` carries its figure and `traffic_from_profile` says which file it comes from; otherwise `traffic` is null.
 PROFILED_TRAFFIC = {
-    "c5": {"forward": {"bytes": 250.5e6, "source": "profiles/c5_step_hbm_traffic.md"},
-           "backward": {"bytes": 1041.0e6, "source": "profiles/c5_step_hbm_traffic.md"},
-           "kernels": {"mfma_fwd_stream_kernel": 250.5e6, "mfma_bwd_dq_fast_kernel": 451.5e6,
-                       "mfma_bwd_dkv_fast_kernel": 475.4e6, "reduce_df_kernel": 114.1e6}},
+    "c5": {"forward": {"bytes": 249.9e6, "source": "profiles/c5_step_hbm_traffic.md"},
+           "backward": {"bytes": 1004.5e6, "source": "profiles/c5_step_hbm_traffic.md"},
+           "kernels": {"mfma_fwd_stream_kernel": 249.9e6, "dq_kernel": 441.8e6,
+                       "dkv_kernel": 448.6e6, "reduce_df_kernel": 114.1e6}},
 }
 
 
@@ -45,7 +45,7 @@ def parse():
     ap.add_argument("--warmup", type=int, default=50)
     ap.add_argument("--workload", default="c5")
     ap.add_argument("--dtype", choices=["bf16", "f32"], default=None,
-                    help="run the workload in this storage type instead of its own (fp32: the fp32 MFMA kernels)")
+                    help="run the workload in this storage type instead of its own (fp32: the fp32 matrix-core kernels)")
     ap.add_argument("--all", action="store_true", help="also time the forward of every named workload")
     ap.add_argument("--rotate", type=int, default=1,
                     help="cycle the steps through this many distinct sets of buffers, so that a workload smaller than "
