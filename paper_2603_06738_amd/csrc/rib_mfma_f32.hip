@@ -604,7 +604,7 @@ namespace {
 // every workgroup of a unit, four at the least (they share the staging).  Eight (one workgroup a CU)
 // split a streamed value half as often as four (two a CU); four where eight would leave CUs without a
 // workgroup, or where four fill fewer rounds of the chip (144 units of 324 tokens, forward: eight 62.9 us
-// in two rounds, against 55.2 with the fp32 products).
+// in two rounds, four 34.6 in one; the fp32 products took 55.2).
 inline int split_waves(const Geo &g, int cus, int *nblk)
 {
     const int nb = (g.N + 31) / 32;
