@@ -249,7 +249,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
             dl = make_delta<DQK>(sr, g);
             if (n0 + lane < g.N) delta[u * g.N + n0 + lane] = dl;       // for the dkv kernel, which runs second
         }
-        const float l2 = kTruncLog2 - sr.e0 * kLog2e;
+        const float l2 = -sr.e0 * kLog2e;
         stat_stage<DQK, true, XS, XD, true, TINY>(sr, g, smem + wave * L::WAVE_STAT, sc2, sp2, l2, -dl, Qb, Gb);
         if (XS) nl[0] = __shfl(l2, col), nl[1] = __shfl(l2, 32 + col);
         if (XD) nd[0] = -__shfl(dl, col), nd[1] = -__shfl(dl, 32 + col);
@@ -317,8 +317,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
             for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
 #pragma unroll
             for (int i = 8; i < 12; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
-            P[cs][0] = trunc_pack(p[0], p[1]);
-            P[cs][1] = trunc_pack(p[2], p[3]);
+            P[cs][0] = pack_bf16(p[0], p[1]);
+            P[cs][1] = pack_bf16(p[2], p[3]);
 #pragma unroll
             for (int i = 4; i < 8; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
             if (qb == 0) {      // operands of the next key block (behind this tile's last, of the next tile)
@@ -332,19 +332,19 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
             for (int mb = 0; mb < L::RB; ++mb) acc[qn][mb] = mfma(At[mb][0], B0, acc[qn][mb]);
 #pragma unroll
             for (int i = 12; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
-            P[cs][2] = trunc_pack(p[4], p[5]);
-            P[cs][3] = trunc_pack(p[6], p[7]);
+            P[cs][2] = pack_bf16(p[4], p[5]);
+            P[cs][3] = pack_bf16(p[6], p[7]);
 #pragma unroll
             for (int i = 8; i < 12; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
             RIB_FENCE();
 #pragma unroll
             for (int mb = 0; mb < L::RB; ++mb) acc[qn][mb] = mfma(At[mb][1], B1, acc[qn][mb]);
-            P[cs][4] = trunc_pack(p[8], p[9]);
-            P[cs][5] = trunc_pack(p[10], p[11]);
+            P[cs][4] = pack_bf16(p[8], p[9]);
+            P[cs][5] = pack_bf16(p[10], p[11]);
 #pragma unroll
             for (int i = 12; i < 16; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
-            P[cs][6] = trunc_pack(p[12], p[13]);
-            P[cs][7] = trunc_pack(p[14], p[15]);
+            P[cs][6] = pack_bf16(p[12], p[13]);
+            P[cs][7] = pack_bf16(p[14], p[15]);
             RIB_FENCE();
             if (qb == 0) {
 #pragma unroll
@@ -483,9 +483,9 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
 #pragma unroll
                     for (int i = 8 * h; i < 8 * h + 8; ++i) D[i] *= S[i];
 #pragma unroll
-                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wp[i >> 1] = trunc_pack(S[i], S[i + 1]);
+                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wp[i >> 1] = pack_bf16(S[i], S[i + 1]);
 #pragma unroll
-                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wds[i >> 1] = trunc_pack(D[i], D[i + 1]);
+                    for (int i = 8 * h; i < 8 * h + 8; i += 2) wds[i >> 1] = pack_bf16(D[i], D[i + 1]);
                     RIB_FENCE();
                     const bf16x8 B = as_bf16x8(wds[4 * h], wds[4 * h + 1], wds[4 * h + 2], wds[4 * h + 3]);
                     accV[kb] = mfma(Agt[h], as_bf16x8(wp[4 * h], wp[4 * h + 1], wp[4 * h + 2], wp[4 * h + 3]), accV[kb]);

@@ -7,11 +7,8 @@
 // scores S^T = K_aug Q_aug^T (a lane owns a query column), packed probabilities as B operand of
 // O^T += V^T P^T, V^T read transposed from the V rows.  Where the head dimension leaves two free
 // columns of V (d <= 30) they hold ones and rows 30 and 31 of O^T are the softmax denominator;
-// d = 32 (SUM) adds the packed probabilities up with the bf16 dot product.  Probabilities go to
-// bf16 by truncation with the mean loss made up beforehand: a constant in the last two columns of
-// Q_aug against ones in K_aug or, where those are taken (XS), on the denominator's log2 (numerator
-// and denominator share the truncated P either way).  (As C operand of the first score MFMA it cost
-// 16 moves a block: 24 x 24 windows, r = 18, 84 us instead of 65.)
+// d = 32 (SUM) adds the probabilities up in fp32.  Probabilities are rounded to bf16
+// (v_cvt_pk_bf16_f32, which issues like the byte-permute a truncation takes).
 //
 // What bounds it: like the other kernels the vector issue of exp2 and packs beside the MFMAs (881 TFLOP/s
 // at 2304 tokens, d = r = 32), under 600 tokens the start and end of a workgroup.  Three waves a SIMD
@@ -62,7 +59,7 @@ __device__ __forceinline__ void q_request(QRows<DQK, QB> &r, const Geo &g, const
     }
 }
 // Scale (Eq. 5, times log2 e), round to bf16 and read back as B operands through the wave's own LDS area.
-template <int DQK, int QB, bool XS, bool TINY>
+template <int DQK, int QB, bool TINY>
 __device__ __forceinline__ void q_stage(const QRows<DQK, QB> &r, const Geo &g, bf16_t *W, bf16x8 (&Q)[QB][DQK / 16])
 {
     constexpr int STR = Lay<DQK, 64>::XS;
@@ -71,8 +68,7 @@ __device__ __forceinline__ void q_stage(const QRows<DQK, QB> &r, const Geo &g, b
     const Piece pc = piece_of<TINY>(g, lane & 7);
     if (lane < 32 * QB) {       // padding columns of row `lane`
         bf16_t *xr = W + lane * STR;
-        for (int c = g.d + g.r; c < DQK - (XS ? 0 : 2); c += 2) *(uint32_t *)(xr + c) = 0u;
-        if (!XS) *(uint32_t *)(xr + DQK - 2) = split_bf16(kTruncLog2);
+        for (int c = g.d + g.r; c < DQK; c += 2) *(uint32_t *)(xr + c) = 0u;
     }
     bf16_t *xr = W + l * STR + 2 * pc.dc, *fr = W + l * STR + g.d + 2 * pc.f0, *fr1 = W + l * STR + g.d + 2 * pc.f1;
 #pragma unroll
@@ -103,12 +99,20 @@ constexpr size_t lds_bytes(int waves)
     const size_t tiles = (size_t)L::NSTAGE * L::STAGE, stat = (size_t)waves * QB * 32 * L::XS;
     return (tiles > stat ? tiles : stat) * sizeof(bf16_t);
 }
+// The sum of a lane's 16 probabilities of a block, in fp32.
+template <class V>
+__device__ __forceinline__ float sum16(const V &p)
+{
+    const float a = (p[0] + p[1]) + (p[2] + p[3]), b = (p[4] + p[5]) + (p[6] + p[7]);
+    const float c = (p[8] + p[9]) + (p[10] + p[11]), d = (p[12] + p[13]) + (p[14] + p[15]);
+    return (a + b) + (c + d);
+}
 constexpr int max_threads(int T, int QB) { return QB == 1 ? 512 : T == 64 ? 256 : 192; }
 
 // One step is one 32x32 block s = (key block, query block): the score MFMAs of block s + 1 and the two
 // PV products of block s - 1 ride between the exponentials and packs of block s, in an order pinned
 // with scheduling fences (as in the streaming kernel).
-template <int DQK, int T, int QB, bool XS, bool SUM, bool ALN, bool TINY>
+template <int DQK, int T, int QB, bool SUM, bool ALN, bool TINY>
 __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) void rows_fwd_kernel(
     Geo g, int nblk, int force_max, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ fq, const bf16_t *__restrict__ fk, bf16_t *__restrict__ out, float *__restrict__ lse)
@@ -150,12 +154,12 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
         q_request<DQK, QB, ALN, TINY>(qr, g, win, qs, n0);
         request<DQK, T, false, ALN, TINY>(rg, g, win, ks, 0, nt, wave);
         request<DQK, T, false, ALN, TINY>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
-        q_stage<DQK, QB, XS, TINY>(qr, g, smem + wave * (QB * 32 * L::XS), Qb);
+        q_stage<DQK, QB, TINY>(qr, g, smem + wave * (QB * 32 * L::XS), Qb);
     }
     __syncthreads();
-    init_pads<DQK, T, false, XS, SUM>(g, smem, nt);
-    commit<DQK, T, false, XS, SUM, TINY>(rg, g, smem, 1.f, 1.f, nt, wave);
-    commit<DQK, T, false, XS, SUM, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, nt, wave);
+    init_pads<DQK, T, false, true, SUM>(g, smem, nt);
+    commit<DQK, T, false, true, SUM, TINY>(rg, g, smem, 1.f, 1.f, nt, wave);
+    commit<DQK, T, false, true, SUM, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, nt, wave);
     request<DQK, T, false, ALN, TINY>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -166,9 +170,8 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
 #pragma unroll
         for (int i = 0; i < 16; ++i) O[qb][i] = 0.f;
         lsum[qb] = 0.f;
-        mrun[qb] = XS ? kTruncLog2 : 0.f;       // what LSE adds to the denominator's log2
+        mrun[qb] = 0.f;         // what LSE adds to the denominator's log2
     }
-    const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3f803f80u);
     const int tro = L::YR + tr_lane_offset<L::YS>(lane), ako = col * L::XS + 8 * hf;
     const f32x16 z = {0};
     // denominators: row 30 of O^T is register 14 of the upper lane half
@@ -205,22 +208,22 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
                 if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + kb * 32, g.N, hf);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
-                P[cs][0] = trunc_pack(p[0], p[1]);
-                P[cs][1] = trunc_pack(p[2], p[3]);
+                P[cs][0] = pack_bf16(p[0], p[1]);
+                P[cs][1] = pack_bf16(p[2], p[3]);
                 RIB_FENCE();
                 S[ns] = mfma(Ak[1], Qb[qn][1], S[ns]);
 #pragma unroll
                 for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
-                P[cs][2] = trunc_pack(p[4], p[5]);
-                P[cs][3] = trunc_pack(p[6], p[7]);
-                if (s == 0) commit<DQK, T, false, XS, SUM, TINY>(rg, g, smem + c2, 1.f, 1.f, nt, wave);
+                P[cs][2] = pack_bf16(p[4], p[5]);
+                P[cs][3] = pack_bf16(p[6], p[7]);
+                if (s == 0) commit<DQK, T, false, true, SUM, TINY>(rg, g, smem + c2, 1.f, 1.f, nt, wave);
                 RIB_FENCE();
 #pragma unroll
                 for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
 #pragma unroll
                 for (int i = 8; i < 12; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
-                P[cs][4] = trunc_pack(p[8], p[9]);
-                P[cs][5] = trunc_pack(p[10], p[11]);
+                P[cs][4] = pack_bf16(p[8], p[9]);
+                P[cs][5] = pack_bf16(p[10], p[11]);
                 if (turn) {     // K of the next key block (QB = 1: of the one after it)
                     const int kn = kb + (QB == 1 ? 2 : 1);
                     read_rows<L::KS>(Ak, (kn < NB ? cur + kn * 32 * L::XS : nxt + (kn - NB) * 32 * L::XS) + ako);
@@ -229,15 +232,11 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
                 O[qn] = mfma(At[0], as_bf16x8(P[ns][0], P[ns][1], P[ns][2], P[ns][3]), O[qn]);
 #pragma unroll
                 for (int i = 12; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
-                P[cs][6] = trunc_pack(p[12], p[13]);
-                P[cs][7] = trunc_pack(p[14], p[15]);
+                P[cs][6] = pack_bf16(p[12], p[13]);
+                P[cs][7] = pack_bf16(p[14], p[15]);
                 RIB_FENCE();
                 O[qn] = mfma(At[1], as_bf16x8(P[ns][4], P[ns][5], P[ns][6], P[ns][7]), O[qn]);
-                if (SUM) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, P[cs][i]), ones2, lsum[qb], false);
-                }
+                if (SUM) lsum[qb] += sum16(p);
                 RIB_FENCE();
                 if (turn) {
 #pragma unroll
@@ -272,7 +271,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
 #pragma unroll 1
         for (int tile = 0; tile < ntiles; ++tile) {     // two stages in turn, one barrier a tile
             bf16_t *cur = smem + (tile & 1) * L::STAGE;
-            commit<DQK, T, false, XS, SUM, TINY>(rg, g, cur, 1.f, 1.f, nt, wave);
+            commit<DQK, T, false, true, SUM, TINY>(rg, g, cur, 1.f, 1.f, nt, wave);
             request<DQK, T, false, ALN, TINY>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
             __syncthreads();
 #pragma unroll 1
@@ -292,24 +291,20 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
                     float m = S[0];
 #pragma unroll
                     for (int i = 1; i < 16; ++i) m = fmaxf(m, S[i]);
-                    // (the maximum of the logits proper, so that P <= 2^kTruncLog2 with the offset)
-                    m = fmaxf(mrun[qb], fmaxf(m, __shfl_xor(m, 32)) - (XS ? 0.f : kTruncLog2));
+                    m = fmaxf(mrun[qb], fmaxf(m, __shfl_xor(m, 32)));
                     // (a row of minus infinities so far: any finite stabiliser does)
                     const float ms = m == -INFINITY ? 0.f : m, alpha = __builtin_amdgcn_exp2f(mrun[qb] - ms);
-                    const float sub = XS ? ms - kTruncLog2 : ms;
                     mrun[qb] = m;
                     uint32_t P[8];
                     lsum[qb] *= alpha;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        S[i] = __builtin_amdgcn_exp2f(S[i] - sub);
+                        S[i] = __builtin_amdgcn_exp2f(S[i] - ms);
                         O[qb][i] *= alpha;
                     }
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        P[i] = trunc_pack(S[2 * i], S[2 * i + 1]);
-                        if (SUM) lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, P[i]), ones2, lsum[qb], false);
-                    }
+                    for (int i = 0; i < 8; ++i) P[i] = pack_bf16(S[2 * i], S[2 * i + 1]);
+                    if (SUM) lsum[qb] += sum16(S);
                     O[qb] = mfma(At[0], as_bf16x8(P[0], P[1], P[2], P[3]), O[qb]);
                     O[qb] = mfma(At[1], as_bf16x8(P[4], P[5], P[6], P[7]), O[qb]);
                 }
@@ -352,12 +347,12 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
     }
 }
 
-template <int DQK, int T, int QB, bool XS, bool SUM, bool ALN, bool TINY>
+template <int DQK, int T, int QB, bool SUM, bool ALN, bool TINY>
 hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 {
     const size_t smem = lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kern = rows_fwd_kernel<DQK, T, QB, XS, SUM, ALN, TINY>;
+    auto kern = rows_fwd_kernel<DQK, T, QB, SUM, ALN, TINY>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.force_max, a.q, a.k, a.v,
@@ -369,7 +364,7 @@ hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 // number in every workgroup of a unit; workgroups under 4 waves stream tiles of 32 tokens (a lane
 // stages at most two).  32 queries a wave, up to 8 waves, are for grids that leave SIMDs idle: half
 // the work per wave and a second wave on each SIMD.
-template <int DQK, bool XS, bool SUM>
+template <int DQK, bool SUM>
 hipError_t launch_width(const Geo &g, int qb, const Args &a)
 {
     const bool tiny = g.d < 4 || g.r < 4, aln = g.M % 8 == 0;
@@ -377,20 +372,20 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
         const int nb = (g.N + 31) / 32, nblk = (nb + 7) / 8;
         int waves = (nb + nblk - 1) / nblk;
         if (waves < 4) waves = 4;
-        return aln ? launch_one<DQK, 64, 1, XS, SUM, true, false>(g, waves, nblk, a)
-                   : launch_one<DQK, 64, 1, XS, SUM, false, false>(g, waves, nblk, a);
+        return aln ? launch_one<DQK, 64, 1, SUM, true, false>(g, waves, nblk, a)
+                   : launch_one<DQK, 64, 1, SUM, false, false>(g, waves, nblk, a);
     }
     const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
     int waves = (nb + nblk - 1) / nblk;
     if (waves < 2) waves = 2;
     if (tiny)
-        return waves == 4 ? launch_one<DQK, 64, 2, XS, SUM, false, true>(g, waves, nblk, a)
-                          : launch_one<DQK, 32, 2, XS, SUM, false, true>(g, waves, nblk, a);
+        return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, true>(g, waves, nblk, a)
+                          : launch_one<DQK, 32, 2, SUM, false, true>(g, waves, nblk, a);
     if (aln)
-        return waves == 4 ? launch_one<DQK, 64, 2, XS, SUM, true, false>(g, waves, nblk, a)
-                          : launch_one<DQK, 32, 2, XS, SUM, true, false>(g, waves, nblk, a);
-    return waves == 4 ? launch_one<DQK, 64, 2, XS, SUM, false, false>(g, waves, nblk, a)
-                      : launch_one<DQK, 32, 2, XS, SUM, false, false>(g, waves, nblk, a);
+        return waves == 4 ? launch_one<DQK, 64, 2, SUM, true, false>(g, waves, nblk, a)
+                          : launch_one<DQK, 32, 2, SUM, true, false>(g, waves, nblk, a);
+    return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, false>(g, waves, nblk, a)
+                      : launch_one<DQK, 32, 2, SUM, false, false>(g, waves, nblk, a);
 }
 
 hipError_t launch32(const Geo &g, int qb, const Args &a);
@@ -399,13 +394,10 @@ hipError_t launch64(const Geo &g, int qb, const Args &a);
 template <int DQK>
 hipError_t launch_flags(const Geo &g, int qb, const Args &a)
 {
-    const bool xs = g.d + g.r + 2 > DQK, sum = g.d + 2 > 32;
-    if constexpr (DQK == 32) {
-        return xs ? launch_width<DQK, true, false>(g, qb, a) : launch_width<DQK, false, false>(g, qb, a);
-    } else {
-        if (sum) return xs ? launch_width<DQK, true, true>(g, qb, a) : launch_width<DQK, false, true>(g, qb, a);
-        return xs ? launch_width<DQK, true, false>(g, qb, a) : launch_width<DQK, false, false>(g, qb, a);
+    if constexpr (DQK > 32) {
+        if (g.d + 2 > 32) return launch_width<DQK, true>(g, qb, a);
     }
+    return launch_width<DQK, false>(g, qb, a);
 }
 
 }  // namespace fwd_rows

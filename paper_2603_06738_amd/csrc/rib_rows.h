@@ -20,14 +20,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-// P and dS go to bf16 by truncation (one byte-permute per pair), which loses half a unit in the
-// last place on average (relative 2^-8 * 0.7213 for log-uniform mantissas).  The loss is made up
-// BEFORE the truncation: this constant is added to the -LSE * log2(e) that rides with every
-// logit, so P (and with it dS = P (dP - delta)) is scaled up by the mean loss and then truncated.
-// Values that are exactly representable (P = 1 of a one-hot row, P = 2^-k of a uniform row) come
-// through unchanged, the others are right on average.
-constexpr float kTruncLog2 = 0.0040593f;   // log2(1 + 2^-8 * 0.7213)
-
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
     bf16x2 v;
@@ -305,7 +297,7 @@ __device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t
     if (QDO && wave < T / 32) {
         const int tid = wave * 64 + lane, row = tid & (T - 1);
         const bool dl = (tid & T) != 0;
-        const float v = dl ? -rg.e0 : kTruncLog2 - rg.e0 * kLog2e;
+        const float v = dl ? -rg.e0 : -rg.e0 * kLog2e;
         const uint32_t pk = split_bf16(v);
         if (dl) {
             if (XD) ((float *)(S + L::EX))[T + row] = v;
