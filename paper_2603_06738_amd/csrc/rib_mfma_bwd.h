@@ -256,8 +256,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
     }
     __syncthreads();
     init_pads<DQK, T, false, XS, XD>(g, smem, nt);
-    commit<DQK, T, false, XS, XD, TINY>(rg, g, smem, 1.f, 1.f, nt, wave);
-    commit<DQK, T, false, XS, XD, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, false, ALN, TINY>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
             for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
-            if (s == 0) commit<DQK, T, false, XS, XD, TINY>(rg, g, smem + c2, 1.f, 1.f, nt, wave);
+            if (s == 0) commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem + c2, 1.f, 1.f, rows_left<T>(g, tile + 2), nt, wave);
             RIB_FENCE();
 #pragma unroll
             for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
@@ -407,8 +407,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
     }
     __syncthreads();
     init_pads<DQK, T, true, XS, XD>(g, smem, nt);
-    commit<DQK, T, true, XS, XD, TINY>(rg, g, smem, sc2, sp2, nt, wave);
-    commit<DQK, T, true, XS, XD, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, sp2, g.N, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, true, ALN, TINY>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
                         for (int mb = 0; mb < L::RB; ++mb)
                             Aqt[mb][i] = read_tr<L::XS>(cur + (qb * 32 + 16 * i) * L::XS, trx, 32 * mb);
                     }
-                    if (qb == 0) commit<DQK, T, true, XS, XD, TINY>(rg, g, smem + c2, sc2, sp2, nt, wave);
+                    if (qb == 0) commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem + c2, sc2, sp2, rows_left<T>(g, tile + 2), nt, wave);
                 } else {
                     read_rows<L::KS>(Aq, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::XS : nxt) + aqo);
                     read_rows<L::VS>(Ag, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::YS : nxt) + ago);

@@ -4,8 +4,8 @@
 //
 // A streamed tile lies in LDS as plain token rows, written as 8-byte pieces by 8 lanes a token; the
 // operands of products that contract over tokens are read TRANSPOSED from the same rows
-// (ds_read_b64_tr_b16).  A last partial tile repeats the window's last token and the kernels mask
-// its rows of the scores.
+// (ds_read_b64_tr_b16).  A last partial tile repeats the window's last token, with zeros in place of its
+// V / dO, and the kernels mask its rows of the scores.
 #pragma once
 
 #include "rib_common.h"
@@ -266,8 +266,17 @@ __device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &
     }
 }
 
-template <int DQK, int T, bool QDO, bool XS, bool XD, bool TINY>
-__device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int nt, int wave)
+// Rows of tile `tile` (past the last one: of the last, which is staged in its place) inside the window.
+template <int T>
+__device__ __forceinline__ int rows_left(const Geo &g, int tile)
+{
+    const int left = g.N - tile * T;
+    return left > 0 ? left : (g.N - 1) % T + 1;
+}
+// `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
+// infinity in the repeated last token does not meet the zero P of a masked row.
+template <int DQK, int T, bool QDO, bool XS, bool XD, bool ALN, bool TINY>
+__device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int left, int nt, int wave)
 {
     using L = Lay<DQK, T>;
     const int lane = opaque_tid() & 63, l = lane >> 3;
@@ -286,8 +295,10 @@ __device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t
                 if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
             }
             const int r0 = slot >> 3;                       // (uniform)
+            dword2 y = rg.y[p];
+            if (!ALN && r0 + l >= left) y.x = y.y = 0u;
             put8(xr + r0 * L::XS, x, pc.c1);
-            put8(yr + r0 * L::YS, rg.y[p], pc.c1);
+            put8(yr + r0 * L::YS, y, pc.c1);
             if (!pc.fnone) {
                 put8(fr + r0 * L::XS, fa, pc.f1d);
                 if (DQK == 64) put8(fr1 + r0 * L::XS, fb, pc.f1d);
@@ -328,7 +339,8 @@ __device__ __forceinline__ void init_pads(const Geo &g, bf16_t *stages, int nt)
 }
 
 // Rows of a score block whose streamed token lies past the window: minus infinity, so that P and
-// dS vanish there (the staged rows repeat the last token, so everything else is finite).
+// dS vanish there.  (The staged rows repeat the last token's: what is not finite in one of them is
+// not in the last token's own products either.)
 __device__ __forceinline__ void mask_rows(f32x16 &S, int first, int N, int hf)
 {
 #pragma unroll
