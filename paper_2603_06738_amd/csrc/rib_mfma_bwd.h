@@ -287,7 +287,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
 #pragma unroll
         for (int mb = 0; mb < L::RB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) At[mb][i] = Ak[0];
+            for (int i = 0; i < 2; ++i) At[mb][i] = as_bf16x8(0u, 0u, 0u, 0u);
     }
     int c0 = 0, c1 = L::STAGE, c2 = 2 * L::STAGE;        // this tile's, the next tile's and the free stage
     for (int tile = 0; tile < ntiles; ++tile) {

@@ -191,10 +191,10 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
         S[0] = mfma(Ak[0], Qb[0][0], z);
 #pragma unroll
         for (int i = 1; i < L::KS; ++i) S[0] = mfma(Ak[i], Qb[0][i], S[0]);
-        At[0] = At[1] = Ak[0];
+        At[0] = At[1] = as_bf16x8(0u, 0u, 0u, 0u);      // (the first step's PV products add zero)
         if (QB == 1) read_rows<L::KS>(Ak, smem + 32 * L::XS + ako);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) P[1][i] = 0u;         // (the first step's PV products add zero)
+        for (int i = 0; i < 8; ++i) P[1][i] = 0u;
         int c0 = 0, c1 = L::STAGE, c2 = 2 * L::STAGE;    // this tile's, the next tile's and the free stage
         for (int tile = 0; tile < ntiles; ++tile) {
             const bf16_t *cur = smem + c0, *nxt = smem + c1;

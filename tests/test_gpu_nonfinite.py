@@ -44,3 +44,19 @@ def test_last_token(d, r, M, flags):
     wl, t = problem(d, r, M, 600 + M)
     t["d_out"][0, M - 1, M - 1, 1] = -INF
     both(wl, t, ("dV",), flags)
+
+
+@pytest.mark.parametrize("flags", [0, rb.RIB_FLAG_FORCE_ROW_MAX], ids=["optimistic", "row-max"])
+@pytest.mark.parametrize("d,r,M", SHAPES + [(30, 16, 32)])
+def test_keys_masked_by_an_infinity(d, r, M, flags):
+    """Keys taken out by minus infinity in a channel where every q is positive: P is 0 at them, O, LSE and every
+    gradient but that channel of dQ (0 times infinity) finite.  Masked keys in the first block and, in the larger
+    windows, whole later ones."""
+    wl, t = problem(d, r, M, 700 + M)
+    C = wl.C
+    for hd in range(wl.heads):
+        t["q"][..., hd * d] = t["q"][..., hd * d].abs() + 0.5
+    keys = t["k"].view(wl.H * wl.W, C)
+    for n in [3, 7, 20, 30] + list(range(40, M * M - 1 if M < 16 else 130)):
+        keys[(n // M) * wl.W + n % M, ::d] = -INF           # the first window's token n, channel 0 of every head
+    both(wl, t, ("O", "LSE", "dQ", "dK", "dV"), flags)
