@@ -52,7 +52,7 @@ struct StatRegs {
     dword2 x[8], y[8], fa[8], fb[DQK == 64 ? 8 : 1], o[WITH_O ? 8 : 1];
     float e0, e1;
 };
-template <int DQK, bool QDO, bool WITH_O, bool ALN, bool TINY>
+template <int DQK, bool QDO, bool WITH_O, bool ALN, bool TINY, bool BIG>
 __device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo &g, const Win &win, const Stream &s, int n0,
                                              const char *ob, bool from_o)
 {
@@ -63,9 +63,9 @@ __device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo
         // (a wave past the window's end repeats its last rows)
         const int nb = ALN && n0 + p * 8 > win.last - 7 ? win.last - 7 : n0 + p * 8, n = nb + l;
         const uint32_t t = win.token<ALN>(nb, l);
-        r.x[p] = get8(s.xb, __umul24(t, s.xs) + 4u * pc.dc, pc.c1);
-        r.y[p] = get8(s.yb, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
-        if (WITH_O && from_o) r.o[p] = get8(ob, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+        r.x[p] = get8(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
+        r.y[p] = get8(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
+        if (WITH_O && from_o) r.o[p] = get8(ob, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
         if (!pc.fnone) {
             const uint32_t fr = __umul24((uint32_t)(n < win.last ? n : win.last), s.frow);
             r.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
@@ -202,12 +202,12 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
     ks.xb = (const char *)(k + img * g.tstride + hd * g.d);                                                \
     ks.yb = (const char *)(v + img * g.tstride + hd * g.d);                                                \
     ks.fb = (const char *)(fk + (int64_t)hd * g.N * g.r);                                                  \
-    ks.xs = ks.ys = qs.xs = (uint32_t)g.tstride * 2u;                                                      \
+    ks.xs = ks.ys = qs.xs = g.tstride * 2;                                                                 \
     ks.frow = qs.frow = (uint32_t)g.r * 2u;                                                                \
     qs.xb = (const char *)(q + img * g.tstride + hd * g.d);                                                \
     qs.yb = (const char *)(dout + img * g.C + hd * g.d);                                                   \
     qs.fb = (const char *)(fq + (int64_t)hd * g.N * g.r);                                                  \
-    qs.ys = (uint32_t)g.C * 2u;                                                                            \
+    qs.ys = (int64_t)g.C * 2;                                                                              \
     ks.lse = qs.lse = lse + u * g.N;                                                                       \
     ks.delta = qs.delta = delta + u * g.N;                                                                 \
     const float sc2 = g.scale_c * kLog2e, sp2 = g.scale_p * kLog2e;                                        \
@@ -223,7 +223,7 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
 // of block s, so that the matrix pipe and the vector ALU always have independent work (left alone,
 // the compiler chains exp2 -> multiply -> pack element by element and waits for every LDS read
 // where it is issued).
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
 __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                       const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
@@ -241,9 +241,9 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
     {
         StatRegs<DQK, true> sr;
         const bool from_o = g.gate == nullptr;          // a gated call's pass over dO', G and O has made delta already
-        stat_request<DQK, true, true, ALN, TINY>(sr, g, win, qs, n0, (const char *)(out + img * g.C + hd * g.d), from_o);
-        request<DQK, T, false, ALN, TINY>(rg, g, win, ks, 0, nt, wave);
-        request<DQK, T, false, ALN, TINY>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
+        stat_request<DQK, true, true, ALN, TINY, BIG>(sr, g, win, qs, n0, (const char *)(out + img * g.C + hd * g.d), from_o);
+        request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, 0, nt, wave);
+        request<DQK, T, false, ALN, TINY, BIG>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
         float dl = sr.e1;
         if (from_o) {
             dl = make_delta<DQK>(sr, g);
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
     init_pads<DQK, T, false, XS, XD>(g, smem, nt);
     commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
     commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
-    request<DQK, T, false, ALN, TINY>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
+    request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
     f32x16 acc[2][L::RB];
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
 #pragma unroll
                     for (int mb = 0; mb < L::RB; ++mb) At[mb][i] = read_tr<L::XS>(cur + (kb * 32 + 16 * i) * L::XS, tro, 32 * mb);
             }
-            if (s == NS - 1) request<DQK, T, false, ALN, TINY>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
+            if (s == NS - 1) request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
         }
         RIB_FENCE();
         __syncthreads();
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
 // dK, dV (+ dF_k partial).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
 __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                        const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                        const bf16_t *__restrict__ fk, const bf16_t *__restrict__ dout,
@@ -400,16 +400,16 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
     bf16x8 Kb[2][L::KS], Vb[2][L::VS];
     {
         StatRegs<DQK, false> sr;
-        stat_request<DQK, false, false, ALN, TINY>(sr, g, win, ks, n0, nullptr, false);
-        request<DQK, T, true, ALN, TINY>(rg, g, win, qs, 0, nt, wave);
-        request<DQK, T, true, ALN, TINY>(rg1, g, win, qs, ntiles > 1 ? 1 : 0, nt, wave);
+        stat_request<DQK, false, false, ALN, TINY, BIG>(sr, g, win, ks, n0, nullptr, false);
+        request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, 0, nt, wave);
+        request<DQK, T, true, ALN, TINY, BIG>(rg1, g, win, qs, ntiles > 1 ? 1 : 0, nt, wave);
         stat_stage<DQK, false, XS, XD, false, TINY>(sr, g, smem + wave * L::WAVE_STAT, 1.f, 1.f, 0.f, 0.f, Kb, Vb);
     }
     __syncthreads();
     init_pads<DQK, T, true, XS, XD>(g, smem, nt);
     commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, sp2, g.N, nt, wave);
     commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, ntiles > 1 ? g.N - T : g.N, nt, wave);
-    request<DQK, T, true, ALN, TINY>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
+    request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
     f32x16 accV[2], accK[2][L::RB];
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
                     read_rows<L::KS>(Aq, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::XS : nxt) + aqo);
                     read_rows<L::VS>(Ag, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::YS : nxt) + ago);
                     if (qb == NB - 1)
-                        request<DQK, T, true, ALN, TINY>(rg, g, win, qs, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
+                        request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
                 }
                 RIB_FENCE();
                 if (!ALN && tile == ntiles - 1) mask_rows(S, tile * T + qb * 32, g.N, hf);
@@ -524,14 +524,14 @@ struct Args {
 };
 
 // Launch the pair with workgroups of `waves` waves, `nblk` of them per unit.
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY>
+template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
 hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
 {
     using L = Lay<DQK, T>;
     const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kdq = dq_kernel<DQK, T, XS, XD, ALN, TINY>;
-    auto kdkv = dkv_kernel<DQK, T, XS, XD, ALN, TINY>;
+    auto kdq = dq_kernel<DQK, T, XS, XD, ALN, TINY, BIG>;
+    auto kdkv = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG>;
     hipError_t e = prepare_kernel((const void *)kdkv, nullptr);
     if (e == hipSuccess) e = prepare_kernel((const void *)kdq, nullptr);
     if (e != hipSuccess) return e;
@@ -545,21 +545,27 @@ hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
 }
 
 // Workgroup shape: up to 4 waves of 64 stationary tokens, an equal number in every workgroup of a
-// unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).
+// unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).  Images whose
+// offsets need more than 32 bits run the four-wave form with 64-bit offsets at every size.
 template <int DQK, bool XS, bool XD>
 hipError_t launch_width(const Geo &g, const Args &a)
 {
     const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
     int waves = (nb + nblk - 1) / nblk;
     if (waves < 2) waves = 2;
-    if (g.d < 4 || g.r < 4)
-        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, true>(g, waves, nblk, a)
-                          : launch_pair<DQK, 32, XS, XD, false, true>(g, waves, nblk, a);
-    if (g.M % 8 == 0)
-        return waves == 4 ? launch_pair<DQK, 64, XS, XD, true, false>(g, waves, nblk, a)
-                          : launch_pair<DQK, 32, XS, XD, true, false>(g, waves, nblk, a);
-    return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, false>(g, waves, nblk, a)
-                      : launch_pair<DQK, 32, XS, XD, false, false>(g, waves, nblk, a);
+    const bool tiny = g.d < 4 || g.r < 4, aln = g.M % 8 == 0;
+    if (!rows_supported(g))
+        return tiny ? launch_pair<DQK, 64, XS, XD, false, true, true>(g, 4, nblk, a)
+               : aln ? launch_pair<DQK, 64, XS, XD, true, false, true>(g, 4, nblk, a)
+                     : launch_pair<DQK, 64, XS, XD, false, false, true>(g, 4, nblk, a);
+    if (tiny)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, true, false>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, false, true, false>(g, waves, nblk, a);
+    if (aln)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, true, false, false>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, true, false, false>(g, waves, nblk, a);
+    return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, false, false>(g, waves, nblk, a)
+                      : launch_pair<DQK, 32, XS, XD, false, false, false>(g, waves, nblk, a);
 }
 
 // d + r within the padded width; columns carry LSE / delta wherever two are free.

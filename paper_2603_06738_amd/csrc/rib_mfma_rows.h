@@ -50,7 +50,7 @@ __device__ __forceinline__ void q_request(QRows<DQK, QB> &r, const Geo &g, const
     for (int p = 0; p < 4 * QB; ++p) {
         // (a wave past the window's end repeats its last rows)
         const int nb = ALN && n0 + p * 8 > win.last - 7 ? win.last - 7 : n0 + p * 8, n = nb + l;
-        r.x[p] = get8(s.xb, __umul24(win.token<ALN>(nb, l), s.xs) + 4u * pc.dc, pc.c1);
+        r.x[p] = get8(s.xb, token_offset<false>(win.token<ALN>(nb, l), s.xs) + 4u * pc.dc, pc.c1);
         if (!pc.fnone) {
             const uint32_t fr = __umul24((uint32_t)(n < win.last ? n : win.last), s.frow);
             r.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
     ks.xb = (const char *)(k + img * g.tstride + hd * g.d);
     ks.yb = (const char *)(v + img * g.tstride + hd * g.d);
     ks.fb = (const char *)(fk + (int64_t)hd * g.N * g.r);
-    ks.xs = ks.ys = qs.xs = qs.ys = (uint32_t)g.tstride * 2u;
+    ks.xs = ks.ys = qs.xs = qs.ys = g.tstride * 2;
     ks.frow = qs.frow = (uint32_t)g.r * 2u;
     qs.xb = qs.yb = (const char *)(q + img * g.tstride + hd * g.d);
     qs.fb = (const char *)(fq + (int64_t)hd * g.N * g.r);
@@ -152,15 +152,15 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
     {
         QRows<DQK, QB> qr;
         q_request<DQK, QB, ALN, TINY>(qr, g, win, qs, n0);
-        request<DQK, T, false, ALN, TINY>(rg, g, win, ks, 0, nt, wave);
-        request<DQK, T, false, ALN, TINY>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
+        request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, 0, nt, wave);
+        request<DQK, T, false, ALN, TINY, false>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
         q_stage<DQK, QB, TINY>(qr, g, smem + wave * (QB * 32 * L::XS), Qb);
     }
     __syncthreads();
     init_pads<DQK, T, false, true, SUM>(g, smem, nt);
     commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
     commit<DQK, T, false, true, SUM, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
-    request<DQK, T, false, ALN, TINY>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
+    request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
     f32x16 O[QB];
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
 #pragma unroll
                     for (int i = 0; i < 2; ++i) At[i] = read_tr<L::YS>(cur + (kb * 32 + 16 * i) * L::YS, tro, 0);
                 }
-                if (s == NS - 1) request<DQK, T, false, ALN, TINY>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
+                if (s == NS - 1) request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
             }
             RIB_FENCE();
             __syncthreads();
@@ -267,12 +267,12 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
             lsum[qb] = 0.f;
             mrun[qb] = -INFINITY;
         }
-        request<DQK, T, false, ALN, TINY>(rg, g, win, ks, 0, nt, wave);
+        request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, 0, nt, wave);
 #pragma unroll 1
         for (int tile = 0; tile < ntiles; ++tile) {     // two stages in turn, one barrier a tile
             bf16_t *cur = smem + (tile & 1) * L::STAGE;
             commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, cur, 1.f, 1.f, g.N - tile * T, nt, wave);
-            request<DQK, T, false, ALN, TINY>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
+            request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
             __syncthreads();
 #pragma unroll 1
             for (int kb = 0; kb < NB; ++kb) {

@@ -211,7 +211,8 @@ __device__ __forceinline__ Piece piece_of(const Geo &g, int j)
     p.f1 = p.f1d ? 0 : (16 + 2 * j < rh - 2 ? 16 + 2 * j : rh - 2);
     return p;
 }
-__device__ __forceinline__ dword2 get8(const char *base, uint32_t off, bool one)
+template <class Off>
+__device__ __forceinline__ dword2 get8(const char *base, Off off, bool one)
 {
     dword2 v;
     if (one) v.x = *(const uint32_t *)(base + off), v.y = 0u;
@@ -229,8 +230,16 @@ __device__ __forceinline__ void put8(bf16_t *dst, const dword2 &v, bool one)
 struct Stream {
     const char *xb, *yb, *fb;       // this image's and head's slices; this head's RIB table
     const float *lse, *delta;       // this unit's rows (QDO)
-    uint32_t xs, ys, frow;          // token strides and RIB row in bytes
+    int64_t xs, ys;                 // token strides in bytes
+    uint32_t frow;                  // RIB row in bytes
 };
+// Byte offset of an image's token `t`: 32 bits and a 24-bit multiply (rows_supported), BIG in 64 bits.
+template <bool BIG>
+__device__ __forceinline__ auto token_offset(uint32_t t, int64_t stride)
+{
+    if constexpr (BIG) return (uint64_t)t * (uint64_t)stride;
+    else return (uint32_t)__umul24(t, (uint32_t)stride);
+}
 
 template <int DQK>
 struct Regs {
@@ -239,7 +248,7 @@ struct Regs {
 };
 
 // Request tile `tile`: slots tid and tid + NT of the tile's T * 8 (8 lanes a token).
-template <int DQK, int T, bool QDO, bool ALN, bool TINY>
+template <int DQK, int T, bool QDO, bool ALN, bool TINY, bool BIG>
 __device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
 {
     const int lane = opaque_tid() & 63, l = lane >> 3;
@@ -250,8 +259,8 @@ __device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &
         if ((T == 64 && nt == 256) || slot < T * 8) {
             const int n0 = tile * T + (slot >> 3);
             const uint32_t t = win.token<ALN>(n0, l);
-            rg.x[p] = get8(s.xb, __umul24(t, s.xs) + 4u * pc.dc, pc.c1);
-            rg.y[p] = get8(s.yb, __umul24(t, s.ys) + 4u * pc.dc, pc.c1);
+            rg.x[p] = get8(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
+            rg.y[p] = get8(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
             if (!pc.fnone) {
                 const int n = n0 + l, nc = ALN ? n : (n < win.last ? n : win.last);
                 const uint32_t fr = __umul24((uint32_t)nc, s.frow);
