@@ -12,8 +12,8 @@
 //             (table, head, column) runs over the 16 tokens.
 //   backward: (1) the same two stages, kept in the workspace (r_in, h) together with
 //             dpre = ReLU'(pre) * sum over heads of dF W_p^T;
-//             (2) per 64-token chunk and per (table, head), a workgroup sums its slice of the
-//             weight gradients from LDS tiles;
+//             (2) per 256-token chunk, (table, head) and 8 to 32 hidden units, a workgroup sums its slice
+//             of the weight gradients from LDS tiles, four lanes an element;
 //             (3) chunks are added in ascending order.
 #include <hip/hip_runtime.h>
 
@@ -23,7 +23,7 @@ namespace rib {
 namespace {
 
 constexpr int kTok = 16;        // tokens per workgroup in the token-parallel kernels
-constexpr int kChunk = 64;      // tokens per partial sum in the weight-gradient kernel
+constexpr int kChunk = 256;     // tokens per partial sum in the weight-gradient kernel
 constexpr int kGenNT = 256;
 constexpr int kStageFloats = 12 * 1024;     // LDS for the staged dF and W_p tiles of a group of heads
 
@@ -177,60 +177,95 @@ __global__ __launch_bounds__(kGenNT) void features_hidden_kernel(Gen g, int grou
 //   [2P + I, .. + d_h) db_h[c]          = sum_n dpre[n][c]
 __device__ __forceinline__ int n_grad_elems(const Gen &g) { return 2 * g.heads * g.d_h * g.r + g.n_in * g.d_h + g.d_h; }
 
-// Backward stage 2: partial[chunk][e] = the sum over the chunk's tokens, ascending.  blockIdx.x names
-// the slice: (table, head) -> its [d_h][r] block of dW_p from h and dF; the last one -> dW_h from
-// r_in and dpre, with db_h.  The chunk's rows of both factors are staged in LDS with the tokens
-// contiguous (zeros past the end), so that an element is 16 pairs of 16-byte reads.
-constexpr int kCS = kChunk + 4; // row stride of a staged factor (an odd multiple of 16 bytes)
-__global__ __launch_bounds__(kGenNT) void features_wgrad_kernel(Gen g, const float *__restrict__ df_q,
-                                                                const float *__restrict__ df_k,
-                                                                const float *__restrict__ ws_rin,
-                                                                const float *__restrict__ ws_h,
-                                                                const float *__restrict__ ws_dpre, float *__restrict__ partial)
+// Backward stage 2: partial[chunk][e] = the sum over the chunk's tokens.  blockIdx.x names the slice:
+// (table, head) and 8 * RPL hidden units -> those rows of its [d_h][r] block of dW_p, from h and dF;
+// behind those, 8 * RPL input features -> rows of dW_h from r_in and dpre (the first one also db_h).
+// The chunk's rows of both factors are staged in LDS with the tokens contiguous (zeros past the end).
+// Four lanes share an element, 64 tokens each in ascending order, and their sums are added in ascending
+// order, so that the scratch holds one partial per 256 tokens and the critical path is that of 64.
+// What bounds it is the LDS bandwidth of a CU: small slices for few tokens, several rows a lane for many.
+constexpr int kQuarter = kChunk / 4;
+// Floats ahead of row `c` of a staged factor, and of its token `t`: the 16 lanes of a 16-byte read (four
+// quarters of four rows) fall on different banks, and so do the writes of 16 rows.
+__host__ __device__ inline int factor_row(int c) { return c * 4 * (kQuarter + 4) + (c >> 2) * 4; }
+__device__ __forceinline__ int factor_token(int t) { return t + (t / kQuarter) * 4; }
+__device__ __forceinline__ float add_quarters(float x)
 {
-    __shared__ __attribute__((aligned(16))) float as[66 * kCS], bs[64 * kCS];
-    const int slice = blockIdx.x, total = n_grad_elems(g), P = g.heads * g.d_h * g.r, I = g.n_in * g.d_h;
-    const bool wh = slice == 2 * g.heads;
-    const int which = slice >= g.heads, hd = slice - which * g.heads;
-    const int ra = wh ? g.n_in : g.d_h, cb = wh ? g.d_h : g.r, count = ra * cb;
+    const int base = (int)(threadIdx.x & 63) & ~3;      // every lane of the four: ((s0 + s1) + s2) + s3
+    return ((__shfl(x, base) + __shfl(x, base + 1)) + __shfl(x, base + 2)) + __shfl(x, base + 3);
+}
+// RPL: rows a lane sums at once, 8 * RPL rows a slice.
+template <int RPL>
+constexpr int grad_threads() { return RPL == 4 ? 1024 : 512; }
+template <int RPL>
+__global__ __launch_bounds__(grad_threads<RPL>()) void features_wgrad_kernel(Gen g, const float *__restrict__ df_q,
+                                                                 const float *__restrict__ df_k,
+                                                                 const float *__restrict__ ws_rin,
+                                                                 const float *__restrict__ ws_h,
+                                                                 const float *__restrict__ ws_dpre, float *__restrict__ partial)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    constexpr int rows = 8 * RPL, kGradNT = grad_threads<RPL>();
+    const int total = n_grad_elems(g), P = g.heads * g.d_h * g.r, I = g.n_in * g.d_h;
+    const int per = (g.d_h + rows - 1) / rows, np = 2 * g.heads * per;
+    const bool wh = (int)blockIdx.x >= np;
+    const int slice = blockIdx.x / per, which = slice >= g.heads, hd = slice - which * g.heads;
+    const int row0 = (wh ? blockIdx.x - np : blockIdx.x - slice * per) * rows;
+    const int wa = wh ? g.n_in : g.d_h, ra = min(rows, wa - row0), cb = wh ? g.d_h : g.r, count = min(ra, 8) * cb;
     const float *a = wh ? ws_rin : ws_h, *b = wh ? ws_dpre : (which ? df_k : df_q) + (size_t)hd * g.N * g.r;
+    float *as = lds, *bs = lds + factor_row(rows);
     const int n0 = blockIdx.y * kChunk, nt = min(kChunk, g.N - n0);
-    for (int e = threadIdx.x; e < kChunk * ra; e += kGenNT) {
-        const int t = e / ra;
-        as[(e - t * ra) * kCS + t] = t < nt ? a[(size_t)n0 * ra + e] : 0.f;
+    for (int e = threadIdx.x; e < kChunk * rows; e += kGradNT) {
+        const int t = e / rows, c = e % rows;
+        as[factor_row(c) + factor_token(t)] = t < nt && c < ra ? a[(size_t)(n0 + t) * wa + row0 + c] : 0.f;
     }
-    for (int e = threadIdx.x; e < kChunk * cb; e += kGenNT) {
+    for (int e = threadIdx.x; e < kChunk * cb; e += kGradNT) {
         const int t = e / cb;
-        bs[(e - t * cb) * kCS + t] = t < nt ? b[(size_t)n0 * cb + e] : 0.f;
+        bs[factor_row(e - t * cb) + factor_token(t)] = t < nt ? b[(size_t)n0 * cb + e] : 0.f;
     }
     __syncthreads();
-    float *dst = partial + (size_t)blockIdx.y * total + (wh ? 2 * P : which * P + hd * g.d_h * g.r);
-    for (int e = threadIdx.x; e < count; e += kGenNT) {
-        const int i = e / cb;
-        const float4 *x = (const float4 *)(as + i * kCS), *y = (const float4 *)(bs + (e - i * cb) * kCS);
-        float acc = 0.f;
-#pragma unroll 8
-        for (int t = 0; t < kChunk / 4; ++t) {
-            const float4 u = x[t], v = y[t];
-            acc = fmaf(u.x, v.x, acc);
-            acc = fmaf(u.y, v.y, acc);
-            acc = fmaf(u.z, v.z, acc);
-            acc = fmaf(u.w, v.w, acc);
+    float *dst = partial + (size_t)blockIdx.y * total + (wh ? 2 * P : which * P + hd * g.d_h * g.r) + row0 * cb;
+    const int part = threadIdx.x & 3, first = threadIdx.x >> 2;
+    // (a lane past the end sums the last element again: all lanes meet in add_quarters)
+    for (int e0 = 0; e0 < count; e0 += kGradNT / 4) {
+        const int e = min(e0 + first, count - 1), i = e / cb;
+        const float *x = as + factor_row(i) + factor_token(part * kQuarter);
+        const float4 *y = (const float4 *)(bs + factor_row(e - i * cb) + factor_token(part * kQuarter));
+        float acc[RPL];
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) acc[k] = 0.f;
+#pragma unroll 8 / RPL
+        for (int t = 0; t < kQuarter / 4; ++t) {
+            const float4 v = y[t];
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                const float4 u = ((const float4 *)(x + factor_row(8 * k)))[t];
+                acc[k] = fmaf(u.x, v.x, acc[k]);
+                acc[k] = fmaf(u.y, v.y, acc[k]);
+                acc[k] = fmaf(u.z, v.z, acc[k]);
+                acc[k] = fmaf(u.w, v.w, acc[k]);
+            }
         }
-        dst[e] = acc;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            const float sum = add_quarters(acc[k]);
+            if (part == 0 && e0 + first < count && i + 8 * k < ra) dst[e + 8 * k * cb] = sum;
+        }
     }
-    if (wh && (int)threadIdx.x < g.d_h) {
-        const float4 *y = (const float4 *)(bs + threadIdx.x * kCS);
+    if (wh && row0 == 0) {
+        const int c = min(first, g.d_h - 1);
+        const float4 *y = (const float4 *)(bs + factor_row(c) + factor_token(part * kQuarter));
         float acc = 0.f;
 #pragma unroll
-        for (int t = 0; t < kChunk / 4; ++t) {
+        for (int t = 0; t < kQuarter / 4; ++t) {
             const float4 v = y[t];
             acc += v.x;
             acc += v.y;
             acc += v.z;
             acc += v.w;
         }
-        dst[I + threadIdx.x] = acc;
+        acc = add_quarters(acc);
+        if (part == 0 && first < g.d_h) dst[I + first] = acc;
     }
 }
 
@@ -280,6 +315,21 @@ GenWs gen_ws_layout(const Gen &g)
     l.partial_off = l.dpre_off + up((size_t)g.N * g.d_h * 4);
     l.total = l.partial_off + up((size_t)l.nchunks * elems * 4);
     return l;
+}
+
+int grad_slices(const Gen &g, int rows) { return 2 * g.heads * ((g.d_h + rows - 1) / rows) + (g.n_in + rows - 1) / rows; }
+template <int RPL>
+hipError_t launch_wgrad(const Gen &g, int nchunks, const float *df_q, const float *df_k, const float *ws_rin, const float *ws_h,
+                        const float *ws_dpre, float *partial, hipStream_t s)
+{
+    auto kern = features_wgrad_kernel<RPL>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
+    if (e != hipSuccess) return e;
+    const int cols = g.d_h > g.r ? g.d_h : g.r;
+    const size_t lds = (size_t)(factor_row(8 * RPL) + factor_row((cols + 3) & ~3)) * sizeof(float);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grad_slices(g, 8 * RPL), (unsigned)nchunks), dim3(grad_threads<RPL>()), lds, s, g, df_q,
+                       df_k, ws_rin, ws_h, ws_dpre, partial);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -340,9 +390,14 @@ rib_status rib_features_bwd(const rib_gen_params *p, const float *W_h, const flo
                        df_q, df_k, ws_rin, ws_h, ws_dpre);
     if (hipGetLastError() != hipSuccess) return RIB_ERR_LAUNCH;
     const unsigned eb = (unsigned)((total + kGenNT - 1) / kGenNT);
-    hipLaunchKernelGGL(features_wgrad_kernel, dim3((unsigned)(2 * g.heads + 1), (unsigned)l.nchunks), dim3(kGenNT), 0, s, g, df_q, df_k, ws_rin, ws_h,
-                       ws_dpre, partial);
-    if (hipGetLastError() != hipSuccess) return RIB_ERR_LAUNCH;
+    // Rows a lane: more of them read less LDS a product, but make fewer workgroups.  (Whole backward, us, with
+    // 1 / 2 / 4, 6 heads, r = 16: 48 x 48 window, 3 heads, 270 slices of 8 rows 24.9 / 26.4 / 29.6; 64 x 64, 864
+    // slices 34.4 / 32.6 / 34.9; 96 x 96, 1944 slices 54.7 / 50.5 / 45.5.)
+    const int64_t slices = (int64_t)grad_slices(g, 8) * l.nchunks;
+    const hipError_t e = slices <= 512    ? launch_wgrad<1>(g, l.nchunks, df_q, df_k, ws_rin, ws_h, ws_dpre, partial, s)
+                         : slices <= 1024 ? launch_wgrad<2>(g, l.nchunks, df_q, df_k, ws_rin, ws_h, ws_dpre, partial, s)
+                                          : launch_wgrad<4>(g, l.nchunks, df_q, df_k, ws_rin, ws_h, ws_dpre, partial, s);
+    if (e != hipSuccess) return RIB_ERR_LAUNCH;
     hipLaunchKernelGGL(features_reduce_kernel, dim3(eb), dim3(kGenNT), 0, s, g, l.nchunks, partial, dW_h, db_h, dW_pq, dW_pk);
     return hipGetLastError() == hipSuccess ? RIB_OK : RIB_ERR_LAUNCH;
 }
