@@ -3,8 +3,12 @@
 // x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = the rest: 8 + 8 + 8 bits and the signs
 // hold all 24 of an fp32 significand.  A product of two such values is six bf16 products,
 //   x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0),
-// exact in fp32 each; what is left out is below 2^-24 of the product, less than the rounding of one
-// fp32 multiplication.  The small ones are accumulated first.  v_mfma_f32_32x32x16_bf16 does 16 times
+// exact in fp32 each.  What is left out (x1 y2 + x2 y1 + x2 y2) depends on how the parts are made.  Inputs
+// have theirs rounded to nearest, so that the scores and dP lose at most 0.9 * 2^-24 of a product, as much
+// as one fp32 multiplication.  P and dS are split by truncation: their products with V, dO, Q and K lose up
+// to 2.5 * 2^-24, to either side.  (Truncated on both sides it would be 6.8 * 2^-24 and mostly to one;
+// rounding P and dS too costs 3 %: 4 images of 32 x 32 windows, forward and backward, 1191 us / 1233.)
+// The small ones are accumulated first.  v_mfma_f32_32x32x16_bf16 does 16 times
 // the work of v_mfma_f32_32x32x2_f32 in half its time (32 clk against 64), so the six are 2.7 times
 // faster than fp32 MFMAs, and unlike these they leave the vector ALU free.
 //
@@ -37,7 +41,6 @@ namespace split {
 
 using rows::bf16x8;
 using rows::as_bf16x8;
-using rows::trunc_pack;
 using rows::pack_bf16;
 using rows::lo_bf16;
 using rows::hi_bf16;
@@ -95,18 +98,6 @@ __device__ __forceinline__ Parts split_pair(float a, float b)
     const float a1 = a - lo_bf16(r.p[0]), b1 = b - hi_bf16(r.p[0]);
     r.p[1] = pack_bf16(a1, b1);
     r.p[2] = pack_bf16(a1 - lo_bf16(r.p[1]), b1 - hi_bf16(r.p[1]));
-    return r;
-}
-// The same by truncation: cheaper, and the parts are exact all the same.  What the six products leave
-// out is one-sided then, so one side of a product of two inputs is rounded (the stationary one).
-__device__ __forceinline__ float high_part(float a) { return __uint_as_float(__float_as_uint(a) & 0xffff0000u); }
-__device__ __forceinline__ Parts split_pair_trunc(float a, float b)
-{
-    Parts r;
-    r.p[0] = trunc_pack(a, b);
-    const float a1 = a - high_part(a), b1 = b - high_part(b);
-    r.p[1] = trunc_pack(a1, b1);
-    r.p[2] = trunc_pack(a1 - high_part(a1), b1 - high_part(b1));
     return r;
 }
 // Largest magnitude so far.  (A NaN is passed over: its first part is a NaN, which reaches what fp32
@@ -180,13 +171,12 @@ __device__ __forceinline__ void request(Regs<DA, T> &rg, const Geo &g, const row
 struct __attribute__((packed, aligned(4))) dwords2 {
     uint32_t x, y;
 };
-template <bool ROUND>
 __device__ __forceinline__ void put4(bf16_t *dst, int part, const float4u &v, float s, float &mx)
 {
     const float a = v.x * s, b = v.y * s, c = v.z * s, d = v.w * s;
     note(mx, a, b);
     note(mx, c, d);
-    const Parts lo = ROUND ? split_pair(a, b) : split_pair_trunc(a, b), hi = ROUND ? split_pair(c, d) : split_pair_trunc(c, d);
+    const Parts lo = split_pair(a, b), hi = split_pair(c, d);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *(dwords2 *)(dst + i * part) = dwords2{lo.p[i], hi.p[i]};
 }
@@ -201,11 +191,11 @@ __device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16
         const int slot = p * nt + wave * 64;
         if (slot < T * 8) {
             bf16_t *xr = S + __mul24((slot >> 3) + l, L::XS), *yr = S + L::YR + __mul24((slot >> 3) + l, L::YS);
-            put4<false>(xr + pc.c, L::XP, rg.x[p], sc, mx);
-            put4<false>(yr + pc.c, L::YP, rg.y[p], 1.f, mx);
+            put4(xr + pc.c, L::XP, rg.x[p], sc, mx);
+            put4(yr + pc.c, L::YP, rg.y[p], 1.f, mx);
             if (!pc.fnone) {
-                put4<false>(xr + pd + pc.f0, L::XP, rg.fa[p], sp, mx);
-                if (DA == 64) put4<false>(xr + pd + pc.f1, L::XP, rg.fb[p], sp, mx);
+                put4(xr + pd + pc.f0, L::XP, rg.fa[p], sp, mx);
+                if (DA == 64) put4(xr + pd + pc.f1, L::XP, rg.fb[p], sp, mx);
             }
         }
     }
@@ -268,10 +258,10 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const 
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         bf16_t *xr = W + (p * 8 + l) * XS;
-        put4<true>(xr + pc.c, 32 * XS, r.x[p], sc, mx);
+        put4(xr + pc.c, 32 * XS, r.x[p], sc, mx);
         if (!pc.fnone) {
-            put4<true>(xr + pd + pc.f0, 32 * XS, r.fa[p], sp, mx);
-            if (DA == 64) put4<true>(xr + pd + pc.f1, 32 * XS, r.fb[p], sp, mx);
+            put4(xr + pd + pc.f0, 32 * XS, r.fa[p], sp, mx);
+            if (DA == 64) put4(xr + pd + pc.f1, 32 * XS, r.fb[p], sp, mx);
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -282,7 +272,7 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const 
         for (int e = lane; e < 96; e += 64)
             for (int c = pd; c < 32; c += 2) *(uint32_t *)(W + e * YS + c) = 0u;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) put4<true>(W + (p * 8 + l) * YS + pc.c, 32 * YS, r.y[p], 1.f, mx);
+        for (int p = 0; p < 4; ++p) put4(W + (p * 8 + l) * YS + pc.c, 32 * YS, r.y[p], 1.f, mx);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int p = 0; p < 3; ++p) read_rows<2>(Y[p], W + p * 32 * YS + col * YS + 8 * hf);
@@ -346,6 +336,17 @@ __device__ __forceinline__ void interleave()
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x002, PER, 0);
     }
+}
+// The same by truncation: cheaper, and the parts are exact all the same.
+__device__ __forceinline__ float high_part(float a) { return __uint_as_float(__float_as_uint(a) & 0xffff0000u); }
+__device__ __forceinline__ Parts split_pair_trunc(float a, float b)
+{
+    Parts r;
+    r.p[0] = rows::trunc_pack(a, b);
+    const float a1 = a - high_part(a), b1 = b - high_part(b);
+    r.p[1] = rows::trunc_pack(a1, b1);
+    r.p[2] = rows::trunc_pack(a1 - high_part(a1), b1 - high_part(b1));
+    return r;
 }
 // A finished block of P or dS as B operands of the products over its rows.
 __device__ __forceinline__ void split_block(bf16x8 (&B)[3][2], const f32x16 &S)
