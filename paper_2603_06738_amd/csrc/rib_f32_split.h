@@ -12,10 +12,11 @@
 // the work of v_mfma_f32_32x32x2_f32 in half its time (32 clk against 64), so the six are 2.7 times
 // faster than fp32 MFMAs, and unlike these they leave the vector ALU free.
 //
-// Everything else stays fp32: softmax state, P, dS, accumulators.  Values whose parts would leave
-// the exponent range (2^32 and beyond, infinities, NaN) are noticed while they are staged, and the
-// workgroup then does its rows again with fp32 MFMAs (the *_body functions), whose arithmetic is
-// defined for them.
+// Everything else stays fp32: softmax state, P, dS, accumulators.  Inputs whose parts would leave
+// the exponent range (2^32 and beyond, infinities; below 2^-100 the last part has fewer bits than it
+// needs) are noticed while they are staged, and the workgroup then does its rows again with fp32 MFMAs
+// (the *_body functions), whose arithmetic is defined for them.  P and dS are not checked: elements of
+// theirs below 2^-110 go into their products with fewer than 24 bits.
 //
 // Layout: a wave owns 32 stationary tokens as B operands in registers, a workgroup of four to eight
 // waves streams the other side through three LDS stages of 64 or 32 tokens: for each part the augmented rows
@@ -50,7 +51,8 @@ using rows::tr_lane_offset;
 using rows::float2u;
 using rows::float4u;
 
-constexpr float kLimit = 0x1p32f;
+constexpr float kLimit = 0x1p32f;     // magnitudes the parts carry: below this,
+constexpr int kSmallExp = 100;        // and 2^-kSmallExp or more (or zero)
 
 // Offsets inside one image fit 32 bits and are built with a 24-bit multiply; both parts of an augmented row,
 // padded to even lengths, fit its 64 columns and hold whole four-value pieces.
@@ -100,9 +102,27 @@ __device__ __forceinline__ Parts split_pair(float a, float b)
     r.p[2] = pack_bf16(a1 - lo_bf16(r.p[1]), b1 - hi_bf16(r.p[1]));
     return r;
 }
-// Largest magnitude so far.  (A NaN is passed over: its first part is a NaN, which reaches what fp32
-// products would have reached.)
-__device__ __forceinline__ void note(float &mx, float a, float b) { mx = fmaxf(fmaxf(mx, fabsf(a)), fabsf(b)); }
+// What a lane has staged so far: the largest magnitude, and the smallest first part that is not zero (of the
+// low and the high halves of the dwords apart; twice the bits, minus one: without the sign, and zero the
+// largest).  (A NaN is passed over: its first part is a NaN, which reaches what fp32 products would have
+// reached.)
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+struct Range {
+    float mx;
+    u16x2 mn;
+    __device__ __forceinline__ bool outside() const
+    {
+        constexpr unsigned short small = (unsigned short)((127 - kSmallExp) << 8) - 1;
+        return mx >= kLimit || mn.x < small || mn.y < small;
+    }
+};
+__device__ __forceinline__ void note_high(Range &rn, float a, float b) { rn.mx = fmaxf(fmaxf(rn.mx, fabsf(a)), fabsf(b)); }
+__device__ __forceinline__ void note_low(Range &rn, const Parts &r)
+{
+    uint32_t key;       // (the compiler takes two instructions for 2 x - 1)
+    asm("v_pk_mad_u16 %0, %1, 2, -1 op_sel_hi:[1,0,0]" : "=v"(key) : "v"(r.p[0]));
+    rn.mn = __builtin_elementwise_min(rn.mn, __builtin_bit_cast(u16x2, key));
+}
 
 // The streamed pair of tensors of one (image, head), in bytes.
 struct Stream {
@@ -171,17 +191,24 @@ __device__ __forceinline__ void request(Regs<DA, T> &rg, const Geo &g, const row
 struct __attribute__((packed, aligned(4))) dwords2 {
     uint32_t x, y;
 };
-__device__ __forceinline__ void put4(bf16_t *dst, int part, const float4u &v, float s, float &mx)
+// LOW: whether a small value matters.  It does not in the operands of the scores (an error of 2^-100 in a logit).
+template <bool LOW>
+__device__ __forceinline__ void put4(bf16_t *dst, int part, const float4u &v, float s, Range &rn)
 {
     const float a = v.x * s, b = v.y * s, c = v.z * s, d = v.w * s;
-    note(mx, a, b);
-    note(mx, c, d);
+    note_high(rn, a, b);
+    note_high(rn, c, d);
     const Parts lo = split_pair(a, b), hi = split_pair(c, d);
+    if (LOW) {
+        note_low(rn, lo);
+        note_low(rn, hi);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i) *(dwords2 *)(dst + i * part) = dwords2{lo.p[i], hi.p[i]};
 }
-template <int DA, int T, bool EXTRA>
-__device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16_t *S, float sc, float sp, int wave, float &mx)
+// GRAD: the X rows are operands of gradients too.
+template <int DA, int T, bool GRAD, bool EXTRA>
+__device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16_t *S, float sc, float sp, int wave, Range &rn)
 {
     using L = Lay<DA, T>;
     const int nt = blockDim.x, lane = rows::opaque_tid() & 63, l = lane >> 3, pd = (g.d + 1) & ~1;
@@ -191,18 +218,18 @@ __device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16
         const int slot = p * nt + wave * 64;
         if (slot < T * 8) {
             bf16_t *xr = S + __mul24((slot >> 3) + l, L::XS), *yr = S + L::YR + __mul24((slot >> 3) + l, L::YS);
-            put4(xr + pc.c, L::XP, rg.x[p], sc, mx);
-            put4(yr + pc.c, L::YP, rg.y[p], 1.f, mx);
+            put4<GRAD>(xr + pc.c, L::XP, rg.x[p], sc, rn);
+            put4<true>(yr + pc.c, L::YP, rg.y[p], 1.f, rn);
             if (!pc.fnone) {
-                put4(xr + pd + pc.f0, L::XP, rg.fa[p], sp, mx);
-                if (DA == 64) put4(xr + pd + pc.f1, L::XP, rg.fb[p], sp, mx);
+                put4<GRAD>(xr + pd + pc.f0, L::XP, rg.fa[p], sp, rn);
+                if (DA == 64) put4<GRAD>(xr + pd + pc.f1, L::XP, rg.fb[p], sp, rn);
             }
         }
     }
     if (EXTRA && wave < T / 32) {
         const int e = wave * 64 + lane;
         const float v = e < T ? rg.e0 * kLog2e : rg.e0;
-        note(mx, v, v);
+        note_high(rn, v, v);
         ((float *)(S + L::EX))[e] = v;
     }
 }
@@ -246,7 +273,7 @@ __device__ __forceinline__ void stat_request(StatRegs<DA, WITH_Y> &r, const Geo 
 // ... scaled, split and read back as B operands through the wave's own LDS area (three parts of 32 rows;
 // the value-like rows follow in the same place).
 template <int DA, bool WITH_Y>
-__device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const Geo &g, bf16_t *W, float sc, float sp, float &mx,
+__device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const Geo &g, bf16_t *W, float sc, float sp, Range &rn,
                                            bf16x8 (&X)[3][DA / 16], bf16x8 (&Y)[3][2])
 {
     constexpr int XS = DA + 8, YS = 40;
@@ -258,10 +285,10 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const 
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         bf16_t *xr = W + (p * 8 + l) * XS;
-        put4(xr + pc.c, 32 * XS, r.x[p], sc, mx);
+        put4<false>(xr + pc.c, 32 * XS, r.x[p], sc, rn);
         if (!pc.fnone) {
-            put4(xr + pd + pc.f0, 32 * XS, r.fa[p], sp, mx);
-            if (DA == 64) put4(xr + pd + pc.f1, 32 * XS, r.fb[p], sp, mx);
+            put4<false>(xr + pd + pc.f0, 32 * XS, r.fa[p], sp, rn);
+            if (DA == 64) put4<false>(xr + pd + pc.f1, 32 * XS, r.fb[p], sp, rn);
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -272,7 +299,7 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DA, WITH_Y> &r, const 
         for (int e = lane; e < 96; e += 64)
             for (int c = pd; c < 32; c += 2) *(uint32_t *)(W + e * YS + c) = 0u;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) put4(W + (p * 8 + l) * YS + pc.c, 32 * YS, r.y[p], 1.f, mx);
+        for (int p = 0; p < 4; ++p) put4<true>(W + (p * 8 + l) * YS + pc.c, 32 * YS, r.y[p], 1.f, rn);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int p = 0; p < 3; ++p) read_rows<2>(Y[p], W + p * 32 * YS + col * YS + 8 * hf);
@@ -398,7 +425,7 @@ __device__ __forceinline__ void store_cols(const f32x16 &acc, int mb, int hf, co
     /* this lane's stationary token (past the window's end: its last, whose results are not stored) */         \
     const int row0 = blk * (int)(blockDim.x >> 1), n = row0 + wave * 32 + col, nc = n < win.last ? n : win.last;\
     const int64_t tn = img + win.any(nc);                                                                      \
-    float mx = 0.f;         /* largest magnitude staged */                                                     \
+    Range rn = {0.f, {0xffff, 0xffff}};                                                                                  \
     __syncthreads();
 
 // ln(2^m l) with one rounding of the sum: the integer part of log2 l joins m's product with ln 2, whose
@@ -435,12 +462,12 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(Geo g, int nblk, uint32_t i
         stat_request<DA, false>(sr, g, win, qs, row0 + wave * 32);
         request<DA, T, false>(rg, g, win, ks, 0, wave, nullptr, nullptr);
         request<DA, T, false>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, wave, nullptr, nullptr);
-        stat_stage<DA, false>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, mx, Q, none);
+        stat_stage<DA, false>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, rn, Q, none);
     }
     __syncthreads();
     zero_pads<DA, T>(g, smem);
-    commit<DA, T, false>(rg, g, smem, 1.f, 1.f, wave, mx);
-    commit<DA, T, false>(rg1, g, smem + L::STAGE, 1.f, 1.f, wave, mx);
+    commit<DA, T, false, false>(rg, g, smem, 1.f, 1.f, wave, rn);
+    commit<DA, T, false, false>(rg1, g, smem + L::STAGE, 1.f, 1.f, wave, rn);
     request<DA, T, false>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, wave, nullptr, nullptr);
     __syncthreads();
 
@@ -488,7 +515,7 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(Geo g, int nblk, uint32_t i
             interleave<6 * L::KS, 150 / (6 * L::KS)>();
             RIB_FENCE();
             if (kb == 0) {
-                commit<DA, T, false>(rg, g, smem + c2, 1.f, 1.f, wave, mx);
+                commit<DA, T, false, false>(rg, g, smem + c2, 1.f, 1.f, wave, rn);
                 request<DA, T, false>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, wave, nullptr, nullptr);
             }
             load_tr<L::YS>(V, cur + L::YR + kb * 32 * L::YS, L::YP, tro_y, 0);
@@ -499,7 +526,7 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(Geo g, int nblk, uint32_t i
         const int r0 = c0;
         c0 = c1, c1 = c2, c2 = r0;
     }
-    if (__syncthreads_or(mx >= kLimit)) {
+    if (__syncthreads_or(rn.outside())) {
         fwd_body<DA>(g, *(Smem<DA + 1> *)smem, u, row0, inv_r, q, k, v, fq, fk, out, lse);
         return;
     }
@@ -541,7 +568,7 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
                        (const char *)(fq + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.C * 4u,
                        (uint32_t)g.r * 4u};
     const float lse2 = lse[u * g.N + nc] * kLog2e, dl = delta[u * g.N + nc];
-    note(mx, lse2, dl);
+    note_high(rn, lse2, dl);
     Regs<DA, T> rg, rg1;
     bf16x8 Q[3][L::KS], G[3][2];
     {
@@ -550,12 +577,12 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
         stat_request<DA, true>(sr, g, win, qs, row0 + wave * 32);
         request<DA, T, false>(rg, g, win, ks, 0, wave, nullptr, nullptr);
         request<DA, T, false>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, wave, nullptr, nullptr);
-        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, mx, Q, G);
+        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, rn, Q, G);
     }
     __syncthreads();
     zero_pads<DA, T>(g, smem);
-    commit<DA, T, false>(rg, g, smem, 1.f, 1.f, wave, mx);
-    commit<DA, T, false>(rg1, g, smem + L::STAGE, 1.f, 1.f, wave, mx);
+    commit<DA, T, true, false>(rg, g, smem, 1.f, 1.f, wave, rn);
+    commit<DA, T, true, false>(rg1, g, smem + L::STAGE, 1.f, 1.f, wave, rn);
     request<DA, T, false>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, wave, nullptr, nullptr);
     __syncthreads();
 
@@ -592,7 +619,7 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
             interleave<6 * L::KS + 12, 160 / (6 * L::KS + 12)>();
             RIB_FENCE();
             if (kb == 0) {
-                commit<DA, T, false>(rg, g, smem + c2, 1.f, 1.f, wave, mx);
+                commit<DA, T, true, false>(rg, g, smem + c2, 1.f, 1.f, wave, rn);
                 request<DA, T, false>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, wave, nullptr, nullptr);
             }
 #pragma unroll
@@ -607,7 +634,7 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
         const int r0 = c0;
         c0 = c1, c1 = c2, c2 = r0;
     }
-    if (__syncthreads_or(mx >= kLimit)) {
+    if (__syncthreads_or(rn.outside())) {
         dq_body<DA>(g, *(Smem<kXS> *)smem, u, row0, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
         return;
     }
@@ -643,12 +670,12 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
         stat_request<DA, true>(sr, g, win, ks, row0 + wave * 32);
         request<DA, T, true>(rg, g, win, qs, 0, wave, lu, du);
         request<DA, T, true>(rg1, g, win, qs, ntiles > 1 ? 1 : 0, wave, lu, du);
-        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), 1.f, 1.f, mx, K, V);
+        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), 1.f, 1.f, rn, K, V);
     }
     __syncthreads();
     zero_pads<DA, T>(g, smem);
-    commit<DA, T, true>(rg, g, smem, g.scale_c, g.scale_p, wave, mx);
-    commit<DA, T, true>(rg1, g, smem + L::STAGE, g.scale_c, g.scale_p, wave, mx);
+    commit<DA, T, true, true>(rg, g, smem, g.scale_c, g.scale_p, wave, rn);
+    commit<DA, T, true, true>(rg1, g, smem + L::STAGE, g.scale_c, g.scale_p, wave, rn);
     request<DA, T, true>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, wave, lu, du);
     __syncthreads();
 
@@ -691,7 +718,7 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
             split_block(B, S);
             RIB_FENCE();
             if (qb == 0) {
-                commit<DA, T, true>(rg, g, smem + c2, g.scale_c, g.scale_p, wave, mx);
+                commit<DA, T, true, true>(rg, g, smem + c2, g.scale_c, g.scale_p, wave, rn);
                 request<DA, T, true>(rg, g, win, qs, tile + 3 < ntiles ? tile + 3 : ntiles - 1, wave, lu, du);
             }
             load_tr<L::YS>(A, cur + L::YR + qb * 32 * L::YS, L::YP, tro_y, 0);
@@ -708,7 +735,7 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
         const int r0 = c0;
         c0 = c1, c1 = c2, c2 = r0;
     }
-    if (__syncthreads_or(mx >= kLimit)) {
+    if (__syncthreads_or(rn.outside())) {
         dkv_body<DA>(g, *(Smem<kXS> *)smem, u, row0, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
         return;
     }

@@ -78,3 +78,29 @@ def test_f32_values_outside_the_parts(tensor, value):
         fin = torch.isfinite(b)
         if bool(fin.any()):
             assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
+
+
+@pytest.mark.parametrize("tensor,power", [("v", 118), ("d_out", 118), ("k", 120), ("q", 120), ("f_k", 120), ("f_q", 120)])
+@pytest.mark.parametrize("part", ["all", "channel"])
+def test_f32_values_too_small_for_the_parts(oracle, tensor, power, part):
+    """A tensor, or one channel of it, so small that its third bf16 part would leave the exponent range: the outputs it
+    scales keep fp32's relative accuracy, here 3e-6 of the largest element (of the channel)."""
+    import gpu_helpers as gh
+    wl = wk.custom("f32-small", "f32", 1, 12, 24, 2, 30, 17, 12, 5, 9910, backward=True)
+    x = wk.make_inputs(wl)
+    pick = slice(None) if part == "all" else slice(4, 5)
+    x[tensor] = x[tensor].copy()
+    x[tensor][..., pick] *= np.float32(2.0) ** -power
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t)
+    got = [out, *gh.gpu_bwd(wl, t, out, lse)]
+    g = geometry(oracle, wl)
+    args = [x[n].astype(np.float64) for n in ("q", "k", "v", "f_q", "f_k")]
+    ref = [oracle.fwd(g, *args)[0], *oracle.bwd(g, *args, x["d_out"].astype(np.float64))]
+    scaled = {"v": ("O",), "d_out": ("dV",), "k": ("dQ",), "q": ("dK",), "f_k": ("dF_q",), "f_q": ("dF_k",)}[tensor]
+    if part == "all" and tensor in ("v", "d_out"):
+        scaled += ("dQ", "dK")
+    for name, a, b in zip(("O",) + NAMES, got, ref):
+        if name in scaled:
+            a, b = gh.host(a)[..., pick], b[..., pick]
+            assert np.abs(a - b).max() <= 3e-6 * np.abs(b).max(), name
