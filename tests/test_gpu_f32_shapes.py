@@ -104,3 +104,58 @@ def test_f32_values_too_small_for_the_parts(oracle, tensor, power, part):
         if name in scaled:
             a, b = gh.host(a)[..., pick], b[..., pick]
             assert np.abs(a - b).max() <= 3e-6 * np.abs(b).max(), name
+
+
+MANY = [  # (d, r, M, shift, units): grids that fill the chip take workgroups of up to eight waves and tiles of 64 tokens
+    (30, 16, 12, 6, 256),       # five waves, tiles of 32 still; width 48
+    (7, 9, 13, 4, 256),         # six waves, 169 tokens, both odd; width 32
+    (16, 0, 14, 3, 256),        # seven waves, no RIB; width 16
+    (31, 1, 15, 0, 256),        # eight waves, 225 tokens, odd, a single-value RIB row; width 48
+    (30, 2, 16, 5, 256),        # eight waves, whole tiles; width 32
+    (30, 33, 13, 6, 256),       # six waves, a second RIB slot, odd; width 64
+    (32, 32, 15, 1, 256),       # eight waves; width 64, full
+    (8, 6, 20, 9, 256),         # two workgroups of seven; width 16
+    (15, 20, 18, 2, 128),       # two workgroups of six, odd d; width 48
+    (30, 18, 25, 24, 256),      # three workgroups of seven, the last partly past the window's end
+]
+
+
+@pytest.mark.parametrize("d,r,M,s,units", MANY)
+def test_f32_shapes_of_large_batches(oracle, d, r, M, s, units):
+    import gpu_helpers as gh
+    wl = wk.custom(f"f32-many-d{d}r{r}m{M}", "f32", units // 4, M, 2 * M, 2, d, r, M, s, 9300 + 64 * M + d + r, backward=True)
+    assert rb.kernel_name(rb.params_of(wl), True) == "mfma-f32"
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x, packed=True)
+    out, lse = gh.gpu_fwd(wl, t, packed=True)
+    got = gh.gpu_bwd(wl, t, out, lse, packed=True)
+    g = geometry(oracle, wl)
+    O_ref, lse_ref = oracle.fwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"])
+    ref = oracle.bwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    _close(gh, gh.host(out), O_ref, "O")
+    _close(gh, gh.host(lse), lse_ref, "LSE")
+    for name, a, b in zip(NAMES if r else NAMES[:3], got, ref):
+        _close(gh, gh.host(a), b, name)
+
+
+@pytest.mark.parametrize("tensor,value", [("v", float("inf")), ("v", 2.0 ** -118), ("d_out", 2.0 ** 40), ("k", 2.0 ** -118), ("q", 2.0 ** 40)])
+@pytest.mark.parametrize("d,r,M", [(30, 17, 12), (30, 16, 14), (30, 33, 15)], ids=["five-waves", "seven-waves", "eight-waves"])
+def test_f32_fallback_in_large_workgroups(d, r, M, tensor, value):
+    """The rows that go back to fp32 products, where a workgroup has more waves than those were written for: one value in
+    one window; every output of every window as the vector kernels have it."""
+    import torch
+    import gpu_helpers as gh
+    wl = wk.custom(f"f32-wide-m{M}", "f32", 64, M, 2 * M, 2, d, r, M, 5, 9400 + M, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    t[tensor][3, 3, 5, 7] = value
+    res = []
+    for flags in (0, rb.RIB_FLAG_VECTOR_ONLY):
+        out, lse = gh.gpu_fwd(wl, t, flags=flags)
+        res.append((out, lse, *gh.gpu_bwd(wl, t, out, lse, flags=flags)))
+    for name, a, b in zip(("O", "LSE") + NAMES, *res):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)), name
+        inf = torch.isinf(b)
+        assert torch.equal(torch.isinf(a), inf) and torch.equal(a[inf], b[inf]), name
+        fin = torch.isfinite(b)
+        if bool(fin.any()):
+            assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
