@@ -367,7 +367,6 @@ __device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, 
 #pragma unroll 1
         for (int kb = 0; kb < kTS / 32; ++kb) {
             if (j0 + kb * 32 >= g.N) break;
-            // keys >= N are zero rows: their dS is finite and meets a zero K_aug row
             const float *Xb = Xc + (kb * 32 + col) * XS + hf;
             const float *Yb = Yc + (kb * 32 + col) * kYS + hf;
             const float *Xt = Xc + (kb * 32 + 4 * hf) * XS + col;
@@ -382,6 +381,11 @@ __device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, 
 #pragma unroll
                              for (int i = 0; i < 8; ++i) nx.v[i] = Xt[acc_row(i) * XS];
                          });
+            if (j0 + kb * 32 + 32 > g.N) {      // keys >= N are zero rows, whose exp2(0 - LSE) need not be finite
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (j0 + kb * 32 + acc_row(i) + 4 * hf >= g.N) S[i] = -INFINITY;
+            }
 #pragma unroll
             for (int i = 0; i < 16; ++i) S[i] = __builtin_amdgcn_exp2f(S[i] - lse2) * (D[i] - dl);
 #pragma unroll

@@ -159,3 +159,23 @@ def test_f32_fallback_in_large_workgroups(d, r, M, tensor, value):
         fin = torch.isfinite(b)
         if bool(fin.any()):
             assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
+
+
+@pytest.mark.parametrize("d,r,M", [(30, 16, 6), (31, 33, 9), (30, 16, 9)], ids=["36-tokens", "fp32-products", "parts"])
+def test_f32_logits_far_below_zero(oracle, d, r, M):
+    """Every logit near -160, so that LSE is too: the rows past a partial block's end (logit 0) must not come in as
+    exp(0 - LSE), which is infinite."""
+    import gpu_helpers as gh
+    wl = wk.custom("f32-low", "f32", 1, M, 2 * M, 2, d, r, M, 0, 9500 + M, backward=True)
+    x = wk.make_inputs(wl)
+    x["f_q"], x["f_k"] = x["f_q"].copy(), x["f_k"].copy()
+    x["f_q"][..., 0], x["f_k"][..., 0] = 20.0, -8.0 / wl.scale_p
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t)
+    got = gh.gpu_bwd(wl, t, out, lse)
+    g = geometry(oracle, wl)
+    O_ref, lse_ref = oracle.fwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"])
+    ref = oracle.bwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    # (a logit of 160 in base 2 is good to 2^-16: ten times the bound of logits of size one)
+    for name, a, b in zip(("O", "LSE") + NAMES, (out, lse, *got), (O_ref, lse_ref, *ref)):
+        assert gh.max_abs(gh.host(a), b) <= 3e-4 * max(1.0, float(np.abs(b).max())), name
