@@ -52,7 +52,7 @@ struct StatRegs {
     dword2 x[8], y[8], fa[8], fb[DQK == 64 ? 8 : 1], o[WITH_O ? 8 : 1];
     float e0, e1;
 };
-template <int DQK, bool QDO, bool WITH_O, bool ALN, bool TINY, bool BIG>
+template <int DQK, bool QDO, bool WITH_O, bool ALN, int TINY, bool BIG>
 __device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo &g, const Win &win, const Stream &s, int n0,
                                              const char *ob, bool from_o)
 {
@@ -116,7 +116,7 @@ __device__ __forceinline__ float make_delta(const StatRegs<DQK, true> &r, const 
 }
 
 // Stage the wave's 64 rows through its private LDS area and read them back as MFMA B operands.
-template <int DQK, bool QDO, bool XS, bool XD, bool WITH_O, bool TINY>
+template <int DQK, bool QDO, bool XS, bool XD, bool WITH_O, int TINY>
 __device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O> &r, const Geo &g, bf16_t *W, float sc, float sp, float nl,
                                            float nd, bf16x8 (&Xb)[2][DQK / 16], bf16x8 (&Yb)[2][2])
 {
@@ -223,7 +223,7 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
 // of block s, so that the matrix pipe and the vector ALU always have independent work (left alone,
 // the compiler chains exp2 -> multiply -> pack element by element and waits for every LDS read
 // where it is issued).
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
 __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                       const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
 // dK, dV (+ dF_k partial).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
 __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                        const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                        const bf16_t *__restrict__ fk, const bf16_t *__restrict__ dout,
@@ -524,7 +524,7 @@ struct Args {
 };
 
 // Launch the pair with workgroups of `waves` waves, `nblk` of them per unit.
-template <int DQK, int T, bool XS, bool XD, bool ALN, bool TINY, bool BIG>
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
 hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
 {
     using L = Lay<DQK, T>;
@@ -544,6 +544,16 @@ hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
     return hipGetLastError();
 }
 
+template <int DQK, bool XS, bool XD, int TINY>
+hipError_t launch_rows(const Geo &g, bool aln, int waves, int nblk, const Args &a)
+{
+    if (aln)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, true, TINY, false>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, true, TINY, false>(g, waves, nblk, a);
+    return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, TINY, false>(g, waves, nblk, a)
+                      : launch_pair<DQK, 32, XS, XD, false, TINY, false>(g, waves, nblk, a);
+}
+
 // Workgroup shape: up to 4 waves of 64 stationary tokens, an equal number in every workgroup of a
 // unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).  Images whose
 // offsets need more than 32 bits run the four-wave form with 64-bit offsets at every size.
@@ -553,19 +563,22 @@ hipError_t launch_width(const Geo &g, const Args &a)
     const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
     int waves = (nb + nblk - 1) / nblk;
     if (waves < 2) waves = 2;
-    const bool tiny = g.d < 4 || g.r < 4, aln = g.M % 8 == 0;
+    const Short kind = short_rows(g);
+    const bool aln = g.M % 8 == 0;
     if (!rows_supported(g))
-        return tiny ? launch_pair<DQK, 64, XS, XD, false, true, true>(g, 4, nblk, a)
-               : aln ? launch_pair<DQK, 64, XS, XD, true, false, true>(g, 4, nblk, a)
-                     : launch_pair<DQK, 64, XS, XD, false, false, true>(g, 4, nblk, a);
-    if (tiny)
-        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, true, false>(g, waves, nblk, a)
-                          : launch_pair<DQK, 32, XS, XD, false, true, false>(g, waves, nblk, a);
-    if (aln)
-        return waves == 4 ? launch_pair<DQK, 64, XS, XD, true, false, false>(g, waves, nblk, a)
-                          : launch_pair<DQK, 32, XS, XD, true, false, false>(g, waves, nblk, a);
-    return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, false, false>(g, waves, nblk, a)
-                      : launch_pair<DQK, 32, XS, XD, false, false, false>(g, waves, nblk, a);
+        return kind != kLong ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, true>(g, 4, nblk, a)
+               : aln         ? launch_pair<DQK, 64, XS, XD, true, kLong, true>(g, 4, nblk, a)
+                             : launch_pair<DQK, 64, XS, XD, false, kLong, true>(g, 4, nblk, a);
+    if (kind == kAnyShort)
+        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, false>(g, waves, nblk, a)
+                          : launch_pair<DQK, 32, XS, XD, false, kAnyShort, false>(g, waves, nblk, a);
+    // (short RIB rows beside d >= 4: d + r <= 32, or d = 32)
+    if constexpr (DQK == 32 || (DQK == 48 && !XS && XD)) {
+        if (kind == kPairRib) return launch_rows<DQK, XS, XD, kPairRib>(g, aln, waves, nblk, a);
+        if (kind == kNoRib) return launch_rows<DQK, XS, XD, kNoRib>(g, aln, waves, nblk, a);
+    }
+    if (kind != kLong) return hipErrorInvalidValue;
+    return launch_rows<DQK, XS, XD, kLong>(g, aln, waves, nblk, a);
 }
 
 // d + r within the padded width; columns carry LSE / delta wherever two are free.

@@ -41,7 +41,7 @@ template <int DQK, int QB>
 struct QRows {
     dword2 x[4 * QB], fa[4 * QB], fb[DQK == 64 ? 4 * QB : 1];
 };
-template <int DQK, int QB, bool ALN, bool TINY>
+template <int DQK, int QB, bool ALN, int TINY>
 __device__ __forceinline__ void q_request(QRows<DQK, QB> &r, const Geo &g, const Win &win, const Stream &s, int n0)
 {
     const int lane = threadIdx.x & 63, l = lane >> 3;
@@ -59,7 +59,7 @@ __device__ __forceinline__ void q_request(QRows<DQK, QB> &r, const Geo &g, const
     }
 }
 // Scale (Eq. 5, times log2 e), round to bf16 and read back as B operands through the wave's own LDS area.
-template <int DQK, int QB, bool TINY>
+template <int DQK, int QB, int TINY>
 __device__ __forceinline__ void q_stage(const QRows<DQK, QB> &r, const Geo &g, bf16_t *W, bf16x8 (&Q)[QB][DQK / 16])
 {
     constexpr int STR = Lay<DQK, 64>::XS;
@@ -112,8 +112,8 @@ constexpr int max_threads(int T, int QB) { return QB == 1 ? 512 : T == 64 ? 256 
 // One step is one 32x32 block s = (key block, query block): the score MFMAs of block s + 1 and the two
 // PV products of block s - 1 ride between the exponentials and packs of block s, in an order pinned
 // with scheduling fences (as in the streaming kernel).
-template <int DQK, int T, int QB, bool SUM, bool ALN, bool TINY>
-__global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) void rows_fwd_kernel(
+template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY>
+__global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort ? 3 : 2) void rows_fwd_kernel(
     Geo g, int nblk, int force_max, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ fq, const bf16_t *__restrict__ fk, bf16_t *__restrict__ out, float *__restrict__ lse)
 {
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && !TINY ? 3 : 2) voi
     }
 }
 
-template <int DQK, int T, int QB, bool SUM, bool ALN, bool TINY>
+template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY>
 hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 {
     const size_t smem = lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
@@ -360,6 +360,16 @@ hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
     return hipGetLastError();
 }
 
+template <int DQK, bool SUM, int TINY>
+hipError_t launch_queries64(const Geo &g, bool aln, int waves, int nblk, const Args &a)
+{
+    if (aln)
+        return waves == 4 ? launch_one<DQK, 64, 2, SUM, true, TINY>(g, waves, nblk, a)
+                          : launch_one<DQK, 32, 2, SUM, true, TINY>(g, waves, nblk, a);
+    return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, TINY>(g, waves, nblk, a)
+                      : launch_one<DQK, 32, 2, SUM, false, TINY>(g, waves, nblk, a);
+}
+
 // Workgroup shape.  64 queries a wave (half the operand reads per product): up to 4 waves, an equal
 // number in every workgroup of a unit; workgroups under 4 waves stream tiles of 32 tokens (a lane
 // stages at most two).  32 queries a wave, up to 8 waves, are for grids that leave SIMDs idle: half
@@ -367,25 +377,28 @@ hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 template <int DQK, bool SUM>
 hipError_t launch_width(const Geo &g, int qb, const Args &a)
 {
-    const bool tiny = g.d < 4 || g.r < 4, aln = g.M % 8 == 0;
-    if (qb == 1 && !tiny) {
+    const Short kind = short_rows(g);
+    const bool aln = g.M % 8 == 0;
+    if (qb == 1 && kind == kLong) {
         const int nb = (g.N + 31) / 32, nblk = (nb + 7) / 8;
         int waves = (nb + nblk - 1) / nblk;
         if (waves < 4) waves = 4;
-        return aln ? launch_one<DQK, 64, 1, SUM, true, false>(g, waves, nblk, a)
-                   : launch_one<DQK, 64, 1, SUM, false, false>(g, waves, nblk, a);
+        return aln ? launch_one<DQK, 64, 1, SUM, true, kLong>(g, waves, nblk, a)
+                   : launch_one<DQK, 64, 1, SUM, false, kLong>(g, waves, nblk, a);
     }
     const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
     int waves = (nb + nblk - 1) / nblk;
     if (waves < 2) waves = 2;
-    if (tiny)
-        return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, true>(g, waves, nblk, a)
-                          : launch_one<DQK, 32, 2, SUM, false, true>(g, waves, nblk, a);
-    if (aln)
-        return waves == 4 ? launch_one<DQK, 64, 2, SUM, true, false>(g, waves, nblk, a)
-                          : launch_one<DQK, 32, 2, SUM, true, false>(g, waves, nblk, a);
-    return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, false>(g, waves, nblk, a)
-                      : launch_one<DQK, 32, 2, SUM, false, false>(g, waves, nblk, a);
+    if (kind == kAnyShort)
+        return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, kAnyShort>(g, waves, nblk, a)
+                          : launch_one<DQK, 32, 2, SUM, false, kAnyShort>(g, waves, nblk, a);
+    // (short RIB rows beside d >= 4: d + r <= 32, or d = 32)
+    if constexpr (DQK == 32 || (DQK == 48 && SUM)) {
+        if (kind == kPairRib) return launch_queries64<DQK, SUM, kPairRib>(g, aln, waves, nblk, a);
+        if (kind == kNoRib) return launch_queries64<DQK, SUM, kNoRib>(g, aln, waves, nblk, a);
+    }
+    if (kind != kLong) return hipErrorInvalidValue;
+    return launch_queries64<DQK, SUM, kLong>(g, aln, waves, nblk, a);
 }
 
 hipError_t launch32(const Geo &g, int qb, const Args &a);

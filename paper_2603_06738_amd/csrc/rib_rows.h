@@ -193,19 +193,23 @@ __device__ __forceinline__ void block_coords(int nblk, int64_t &u, int &blk)
 // What a lane moves when 8 lanes share a token: the dword pair 2j, 2j+1 of the content row and of
 // the RIB row (a second pair for rows longer than 32 values).  Lanes past the end slide back onto
 // the last pair (they duplicate a neighbour); rows of a single dword (d = 2, r = 2) move alone.
-// TINY compiles those single-dword rows (and r = 0) in; without it d >= 4 and r >= 4.
+// Which rows are that short is compiled in: a branch in the staging code splits the pinned order of the
+// blocks it rides in (forward and backward of 8 images of 96 x 96, 6 heads, d = 30, r = 2, us with branches /
+// without: 32 x 32 windows 601 / 369, 16 x 16 299 / 186, 24 x 24 594 / 337; r = 0, 32 x 32: 464 / 343).
+enum Short { kLong = 0, kPairRib = 1, kNoRib = 2, kAnyShort = 3 };      // d, r >= 4 | r = 2 | r = 0 | d = 2, any r (branches)
+inline Short short_rows(const Geo &g) { return g.d < 4 ? kAnyShort : g.r == 0 ? kNoRib : g.r < 4 ? kPairRib : kLong; }
 struct Piece {
     int dc, f0, f1;                 // first dword of the content / RIB pieces
     bool c1, f1d, fnone;            // single-dword content / RIB rows, no RIB at all (uniform)
 };
-template <bool TINY>
+template <int TINY>
 __device__ __forceinline__ Piece piece_of(const Geo &g, int j)
 {
     const int hp = g.d >> 1, rh = g.r >> 1;
     Piece p;
-    p.c1 = TINY && hp < 2;
-    p.f1d = TINY && rh < 2;
-    p.fnone = TINY && rh == 0;
+    p.c1 = TINY == kAnyShort && hp < 2;
+    p.f1d = TINY == kPairRib || (TINY == kAnyShort && rh < 2);
+    p.fnone = TINY == kNoRib || (TINY == kAnyShort && rh == 0);
     p.dc = p.c1 ? 0 : (2 * j < hp - 2 ? 2 * j : hp - 2);
     p.f0 = p.f1d ? 0 : (2 * j < rh - 2 ? 2 * j : rh - 2);
     p.f1 = p.f1d ? 0 : (16 + 2 * j < rh - 2 ? 16 + 2 * j : rh - 2);
@@ -248,7 +252,7 @@ struct Regs {
 };
 
 // Request tile `tile`: slots tid and tid + NT of the tile's T * 8 (8 lanes a token).
-template <int DQK, int T, bool QDO, bool ALN, bool TINY, bool BIG>
+template <int DQK, int T, bool QDO, bool ALN, int TINY, bool BIG>
 __device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
 {
     const int lane = opaque_tid() & 63, l = lane >> 3;
@@ -284,7 +288,7 @@ __device__ __forceinline__ int rows_left(const Geo &g, int tile)
 }
 // `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
 // infinity in the repeated last token does not meet the zero P of a masked row.
-template <int DQK, int T, bool QDO, bool XS, bool XD, bool ALN, bool TINY>
+template <int DQK, int T, bool QDO, bool XS, bool XD, bool ALN, int TINY>
 __device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int left, int nt, int wave)
 {
     using L = Lay<DQK, T>;
