@@ -75,7 +75,7 @@ typedef enum {
 } rib_status;
 
 typedef enum {
-    RIB_F32 = 0,             /* fp32 storage, fp32 arithmetic */
+    RIB_F32 = 0,             /* fp32 storage, fp32 precision: products keep 24 bits, sums and softmax state are fp32 */
     RIB_BF16 = 1             /* bf16 storage, bf16 matrix-core operands, fp32 accumulation and softmax state */
 } rib_dtype;
 
@@ -110,9 +110,12 @@ typedef struct {
 } rib_params;
 
 /* Built for: 1 <= d <= 64, 0 <= r <= 64, any window side M with M*M <= 65536.
- * Problems with d <= 32 and d + r <= 64 run on the matrix-core kernels (bf16
- * storage: bf16 MFMA with fp32 accumulation; fp32 storage: fp32 MFMA);
- * everything else runs on a slower fp32 vector-ALU kernel with the same results. */
+ * Problems with d <= 32 and d + r <= 64 run on the matrix-core kernels: bf16
+ * storage (even d and r, windows of 64 to 9216 tokens, images of any size) on
+ * bf16 MFMA with fp32 accumulation; fp32 storage (windows of 32 tokens and more,
+ * images under 2^32 bytes) with every value as three bf16 parts on the same
+ * instruction, or on the fp32 MFMA.  Everything else runs on a slower fp32
+ * vector-ALU kernel with the same results. */
 
 /* Forward:  out[B][H][W][C]  (dtype of q),  lse[B*nW][heads][N] fp32 or NULL.
  *   q, k, v : [B][H][W] tokens of C channels, token stride p->token_stride
@@ -253,7 +256,7 @@ const char *rib_status_string(rib_status st);
 
 /* Name of the kernel family that would serve this problem: "mfma-bf16" (bf16
  * storage on the bf16 matrix instructions), "mfma-f32" (fp32 storage on the
- * fp32 matrix instruction) or "valu-f32" (vector ALU, any storage); NULL if the
+ * matrix cores) or "valu-f32" (vector ALU, any storage); NULL if the
  * parameters are invalid.  For logs and tests. */
 const char *rib_window_attn_kernel_name(const rib_params *p, int backward);
 

@@ -171,6 +171,7 @@ hipError_t launch_reduce_df(const Geo &g, const float *part_q, const float *part
                             hipStream_t st);
 
 // Whether offsets inside one image fit the 32 bits (and the 24-bit multiply) that the token-row kernels build them with.
+// (Elsewhere the backward pair has a form with 64-bit offsets, the forward its general kernel.)
 inline bool rows_supported(const Geo &g)
 {
     const int64_t pixels = (int64_t)g.H * g.W, stride = g.tstride > g.C ? g.tstride : (int64_t)g.C;
@@ -187,7 +188,7 @@ hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const voi
                            const void *fk, const void *out, const void *dout, const float *lse, void *dq,
                            void *dk, void *dv, float *dfq, float *dfk, void *ws, hipStream_t st,
                            void *gated_dout = nullptr, void *dgate = nullptr);
-// Matrix-core kernels for fp32 storage (fp32 MFMA, fp32 throughout), forward and backward.
+// Matrix-core kernels for fp32 storage (three bf16 parts a value, or the fp32 MFMA), forward and backward.
 bool mfma_f32_supported(const Geo &g, int dtype);
 hipError_t launch_mfma_f32_fwd(const Geo &g, const void *q, const void *k, const void *v, const void *fq,
                                const void *fk, void *out, float *lse, hipStream_t st);

@@ -23,15 +23,17 @@
 // [content, padded to even | RIB | zeros] and the value-like rows, which are also read transposed
 // (rib_rows.h).  Splitting the streamed values is vector work that all waves of a workgroup share.
 //
-// What bounds them: the matrix pipe (30 / 54 / 66 MFMAs of 32 clk a 32x32 block in fwd / dq / dkv at 48
-// columns: 40-53 % of the cycles by counters) and the vector ALU (exponentials and splits: 44-48 %), which
-// hardly overlap; under 300 tokens the start of a workgroup.  Against the fp32-MFMA kernels (us, 96 x 96
-// images, 6 heads, d = 30, r = 16; before / after): 4 images of 32 x 32 windows forward 366 / 257, backward
-// 1335 / 907; 8 images of 12 x 12 windows 266 / 165 and 1076 / 646.  Error against fp64 (2-norm, the 32 x 32
-// case): O 6.7e-7 / 2.9e-7, LSE 4.7e-8 / 2.4e-8, dQ 7.5e-7 / 4.1e-7, dK 7.7e-7 / 4.0e-7, dV 7.5e-7 / 3.9e-7.
+// What bounds them: the matrix pipe (31 / 55 / 67 MFMAs of 32 clk a 32x32 block in fwd / dq / dkv at 48
+// columns: 37 / 43 / 40 % of the SIMD-cycles at 2.4 GHz by counters) and the vector ALU (301 / 371 / 499
+// instructions a block, exponentials, splits and staging: 48 / 38 / 38 %), which hardly overlap; under 300
+// tokens the start of a workgroup.  dkv spills (56 registers at 48 columns, 175 at 64).  Against the
+// fp32-MFMA kernels (us, 96 x 96 images, 6 heads, d = 30, r = 16; before / after): 4 images of 32 x 32 windows
+// forward 366 / 259, backward 1330 / 943; 8 images of 12 x 12 windows 266 / 169 and 1076 / 650.  Error against
+// fp64 (2-norm, the 32 x 32 case): O 6.7e-7 / 2.8e-7, LSE 4.9e-8 / 2.5e-8, dQ 7.5e-7 / 4.0e-7, dK 7.6e-7 / 4.1e-7,
+// dV 7.4e-7 / 4.0e-7.
 // Measured and left out: the two waves of a SIMD half a block apart (no change), two LDS stages with two
-// workgroups of four waves a CU (295 / 870 us), operands of the stationary side fetched element by
-// element (ten microseconds more at a workgroup's start).
+// workgroups of four waves a CU (295 / 870 us when the three stages took 257 / 907), operands of the stationary
+// side fetched element by element (ten microseconds more at a workgroup's start).
 #pragma once
 
 #include "rib_rows.h"

@@ -553,8 +553,9 @@ __device__ __forceinline__ void dkv_body(const Geo &g, Smem<kXS> &sm, int64_t u,
 }
 
 inline uint32_t inv_r_of(const Geo &g) { return g.r > 1 ? (uint32_t)((((uint64_t)1 << 32) + g.r - 1) / g.r) : 0u; }
-// The fp32-MFMA bodies as kernels of their own, for what the split kernels do not take (images of 2^32
-// bytes, windows under 64 tokens, odd d and odd r with d + r > 62).
+// The fp32-MFMA bodies as kernels of their own, for what the split kernels do not take: windows under 64
+// tokens, d or r of 1 and 2, odd d and odd r with d + r > 62, images of 2^24 pixels or token strides of 2^24
+// bytes (under 2^32 bytes an image: larger ones run on the vector ALU).
 template <int DA>
 __global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
                                                                const float *__restrict__ k, const float *__restrict__ v,

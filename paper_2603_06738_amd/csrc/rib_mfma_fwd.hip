@@ -510,8 +510,8 @@ __device__ __forceinline__ void fast_tile(const Geo &g, const LoadCursor &lc, co
             // 4 exp2 and 2 packs of this block
 #pragma unroll
             for (int i = 4 * grp; i < 4 * grp + 4; ++i) pe[i] = __builtin_amdgcn_exp2f(S[cs][i]);
-            // fp32 -> bf16 by truncation: one byte-permute per pair instead of the (slow)
-            // rounding convert.  Numerator and denominator use the same truncated P.
+            // fp32 -> bf16 by truncation, one byte-permute per pair.  Numerator and denominator use the
+            // same truncated P.
             const uint32_t w0 = trunc_pack(pe[4 * grp], pe[4 * grp + 1]);
             const uint32_t w1 = trunc_pack(pe[4 * grp + 2], pe[4 * grp + 3]);
             if ((grp & 1) == 0) {
@@ -1173,8 +1173,9 @@ bool mfma_fwd_supported(const Geo &g, int dtype)
 // whole rounds of items: it is taken where the last round is full enough.  Measured against the
 // token-row kernel (us, streaming / rows, 6 heads of 30 channels, r = 16): 32 x 32 windows, 96 x 96
 // images: 2.5 rounds 70 / 73, 3.4 rounds 94 / 90, 5.1 rounds 134 / 131, 6.75 rounds 164 / 174, 10.1
-// rounds 256 / 274; larger windows lose less at an item's ends: 64 x 64, 1.5 rounds 144 / 140, 3.0
-// rounds 239 / 265; 96 x 96, 1.7 rounds 315 / 370, 3.4 rounds 631 / 651.  Under 4096 tokens the
+// rounds 256 / 274 (the line gives up the 3 us of the first, which fills its rounds as well as the second
+// and third); larger windows lose less at an item's ends: 64 x 64, 1.5 rounds 144 / 140, 3.0 rounds
+// 239 / 265; 96 x 96, 1.7 rounds 315 / 370, 3.4 rounds 631 / 651.  Under 4096 tokens the
 // 64-column variant stays behind at every size (32 x 32, r = 34, 6.75 rounds: 230 / 194).
 static bool streams(const Geo &g, int cus)
 {

@@ -1,8 +1,8 @@
 """The bf16 token-row forward kernels where their dispatch changes hands, against the oracle, every element: padded
-widths 32 / 48 / 64 with the truncation offset in a column or on the denominator; denominators from the ones columns
-and from the packed sums (d = 32); window sides that are and are not multiples of 8; workgroups of 2, 3, 4 waves of 64
-queries (grids that fill the chip) and 4 to 8 waves of 32 (grids that do not), with waves wholly or half past the
-window's end; single-dword rows and no RIB; the walk with the running maximum.
+widths 32 / 48 / 64, full and with columns to spare; denominators from the ones columns and from fp32 sums (d = 32);
+window sides that are and are not multiples of 8; workgroups of 2, 3, 4 waves of 64 queries (grids that fill the chip)
+and 4 to 8 waves of 32 (grids that do not), with waves wholly or half past the window's end; single-dword rows and no
+RIB; the walk with the running maximum.
 
 Tolerance: the parity tests' 2e-2 absolute for logits of this size; bf16 rounds the scaled Q row and P to 2^-8
 relative each, and O is an average of values of size one."""
@@ -15,13 +15,13 @@ from paper_2603_06738_amd import workloads as wk
 from helpers import geometry
 
 SHAPES = [  # (d, r, M, shift, H / M, W / M); `many` repeats the image until 64-query waves outnumber 1024 SIMDs
-    (16, 14, 8, 3, 1, 2),       # one 64-token block; width 32, offset in the columns
-    (16, 16, 24, 12, 1, 1),     # 3 waves of 64, 6 of 32; width 32, offset on the denominator
+    (16, 14, 8, 3, 1, 2),       # one 64-token block; width 32, two columns to spare
+    (16, 16, 24, 12, 1, 1),     # 3 waves of 64, 6 of 32; width 32, full
     (30, 2, 40, 7, 1, 1),       # width 32, single-dword RIB rows
-    (30, 16, 24, 5, 2, 1),      # width 48, columns
-    (32, 8, 16, 0, 1, 2),       # packed sums, columns
-    (30, 18, 40, 9, 1, 1),      # width 48, denominator
-    (32, 16, 24, 0, 1, 1),      # packed sums, denominator
+    (30, 16, 24, 5, 2, 1),      # width 48, two columns to spare
+    (32, 8, 16, 0, 1, 2),       # fp32 sums, eight columns to spare
+    (30, 18, 40, 9, 1, 1),      # width 48, full
+    (32, 16, 24, 0, 1, 1),      # fp32 sums, full
     (30, 34, 8, 4, 2, 2),       # width 64, two RIB pieces a lane
     (24, 20, 9, 4, 1, 2),       # 81 tokens: a 64-token tile and 17
     (30, 16, 11, 10, 1, 1),     # 121 tokens

@@ -421,9 +421,9 @@ WIDE = [
 
 @pytest.mark.parametrize("wl", WIDE, ids=lambda w: w.name)
 def test_wide_workgroups(oracle, gh, wl):
-    """The 8-wave forward and backward kernels (default only for large windows) forced onto small
-    problems so that every variant is checked element by element, the forward in both softmax
-    paths."""
+    """The streaming forward (8 waves; by default only where its items fill rounds of the chip) forced onto
+    small problems with d < 32, in both softmax paths, and the forms the flag does not reach (d = 32,
+    every backward) on the same problems, element by element."""
     x = wk.make_inputs(wl)
     _check_fwd(oracle, gh, wl, x, flags=rb.RIB_FLAG_WIDE | FORCE_MAX)
     t, out, lse = _check_fwd(oracle, gh, wl, x, flags=rb.RIB_FLAG_WIDE)
@@ -511,7 +511,7 @@ F32_MATRIX = [
 
 @pytest.mark.parametrize("wl", F32_MATRIX, ids=lambda w: w.name)
 def test_f32_matrix_core_kernels(oracle, gh, wl):
-    """fp32 problems on the fp32 MFMA kernels: forward (O, LSE) and backward, every element, 1e-4."""
+    """fp32 problems on the matrix cores: forward (O, LSE) and backward, every element, 1e-4."""
     assert rb.kernel_name(rb.params_of(wl)) == "mfma-f32" and rb.kernel_name(rb.params_of(wl), True) == "mfma-f32"
     x = wk.make_inputs(wl)
     t, out, lse = _check_fwd(oracle, gh, wl, x)
