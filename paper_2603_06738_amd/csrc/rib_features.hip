@@ -5,7 +5,7 @@
 // order.  What bounds them is latency -- a handful of workgroups, each a chain of fp64 sincos,
 // dot products and loads -- so a workgroup takes only 16 tokens, every sincos and every hidden
 // unit has a lane of its own, and operands are staged in bulk (48 x 48 window, 3 heads, r = 16:
-// forward 31 -> 12 us, backward 129 -> 30 us; 64 tokens a workgroup and strided global reads before).
+// forward 31 -> 12 us, backward 120 -> 25 us; 64 tokens a workgroup and strided global reads before).
 //
 //   forward:  Fourier features (fp64 sines / cosines of the token's row and column coordinate,
 //             rounded to fp32) into LDS, the shared hidden layer into LDS, then a lane per

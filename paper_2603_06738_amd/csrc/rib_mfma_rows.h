@@ -7,8 +7,9 @@
 // scores S^T = K_aug Q_aug^T (a lane owns a query column), packed probabilities as B operand of
 // O^T += V^T P^T, V^T read transposed from the V rows.  Where the head dimension leaves two free
 // columns of V (d <= 30) they hold ones and rows 30 and 31 of O^T are the softmax denominator;
-// d = 32 (SUM) adds the probabilities up in fp32.  Probabilities are rounded to bf16
-// (v_cvt_pk_bf16_f32, which issues like the byte-permute a truncation takes).
+// d = 32 (SUM) adds the probabilities up in fp32 (16 additions a block, 7 to 14 % of the forward; bf16
+// dot products of the packed pairs cost half of that, but sum rounded values).  Probabilities are
+// rounded to bf16 (v_cvt_pk_bf16_f32, which issues like the byte-permute a truncation takes).
 //
 // What bounds it: the vector issue beside the MFMAs (32 x 32 windows: 52 vector instructions a 32x32 block, of
 // which exp2 and packs are 24, the vector ALU busy half of the cycles, the matrix pipe 30 %, and 42 % of a wave's
