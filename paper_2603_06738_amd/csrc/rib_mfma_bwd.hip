@@ -1,6 +1,7 @@
-// Host side of the bf16 matrix-core backward: which problems it serves and which padded width
-// (rib_mfma_bwd.h holds the kernels; one translation unit per width keeps the build parallel).
+// Host side of the bf16 matrix-core backward: which problems it serves, by which kernels and in which padded width
+// (rib_mfma_unit.h, rib_mfma_bwd.h; one translation unit per width keeps the build parallel).
 #include "rib_mfma_bwd.h"
+#include "rib_mfma_unit.h"
 
 namespace rib {
 
@@ -29,10 +30,13 @@ hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const voi
     a.out = (const bf16_t *)out, a.dout = (const bf16_t *)dout, a.lse = lse;
     a.dq = (bf16_t *)dq, a.dk = (bf16_t *)dk, a.dv = (bf16_t *)dv;
     a.st = st;
-    // (RIB rows of more than 32 values are staged by the 64-column kernels only)
+    // RIB rows of more than 32 values are staged by the 64-column kernels only.  Units that one workgroup holds are done
+    // in one kernel (the figures stand in rib_mfma_unit.h); rows of a pair or less and 64-bit offsets have forms in the pair only.
     const int aug = g.d + g.r;
-    const hipError_t e = aug <= 32 && g.d <= 30 ? bwd::launch32(g, a)
-                         : aug <= 48 && g.r <= 32 ? bwd::launch48(g, a) : bwd::launch64(g, a);
+    const int width = aug <= 32 && g.d <= 30 ? 32 : aug <= 48 && g.r <= 32 ? 48 : 64;
+    const bool one = g.N <= 512 && rows::short_rows(g) == rows::kLong && rows_supported(g);
+    const hipError_t e = one ? (width == 32 ? unit::launch32(g, a) : width == 48 ? unit::launch48(g, a) : unit::launch64(g, a))
+                             : (width == 32 ? bwd::launch32(g, a) : width == 48 ? bwd::launch48(g, a) : bwd::launch64(g, a));
     if (e != hipSuccess) return e;
     return launch_reduce_df(g, a.pq, a.pk, dfq, dfk, st);
 }

@@ -336,11 +336,11 @@ __device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t
 // The columns no staging code writes, once for every row of every stage: zero padding (it meets
 // the zero padding of the stationary operands, so it only has to be finite), and for K / V tiles
 // the ones that LSE and delta meet.
-template <int DQK, int T, bool QDO, bool XS, bool XD>
+template <int DQK, int T, bool QDO, bool XS, bool XD, int STAGES = Lay<DQK, T>::NSTAGE>
 __device__ __forceinline__ void init_pads(const Geo &g, bf16_t *stages, int nt)
 {
     using L = Lay<DQK, T>;
-    for (int e = threadIdx.x; e < L::NSTAGE * T; e += nt) {
+    for (int e = threadIdx.x; e < STAGES * T; e += nt) {
         bf16_t *xr = stages + (e / T) * L::STAGE + (e % T) * L::XS, *yr = stages + (e / T) * L::STAGE + L::YR + (e % T) * L::YS;
         for (int c = g.d + g.r; c < DQK; c += 2)
             if (c < DQK - 2 || XS) *(uint32_t *)(xr + c) = 0u;
