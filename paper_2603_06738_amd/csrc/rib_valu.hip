@@ -404,33 +404,42 @@ __global__ __launch_bounds__(kThreads) void valu_bwd_dkv_kernel(Geo g, int nblk,
         if (t % kSplit == part && t < g.d) store_as(vdst + t, dva[t]);
 }
 
-// dF[hd][e] = sum over windows w (ascending) of part[(w*heads + hd)][e]; e over N*r.
-__global__ __launch_bounds__(kThreads) void reduce_df_kernel(Geo g, const float *__restrict__ part_q,
+// dF[hd][e] = sum over windows w of part[(w*heads + hd)][e]; e over N*r, VEC of them a lane.  A workgroup's lanes are
+// `slices` groups that each sum a run of windows (eight loads in flight), added through LDS in ascending order: the
+// order is fixed by the sizes.
+template <int VEC>
+__global__ __launch_bounds__(kThreads) void reduce_df_kernel(int64_t per_head, int heads, int blocks, int nwin, int slices, const float *__restrict__ part_q,
                                                              const float *__restrict__ part_k,
                                                              float *__restrict__ dfq, float *__restrict__ dfk)
 {
-    const int64_t per_head = (int64_t)g.N * g.r;
-    int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= per_head * g.heads) return;
-    int hd = (int)(idx / per_head);
-    int64_t e = idx - hd * per_head;
-    const float *src = blockIdx.y == 0 ? part_q : part_k;
-    float *dst = blockIdx.y == 0 ? dfq : dfk;
-    const int64_t nwin = g.units / g.heads;
-    const int64_t step = (int64_t)g.heads * per_head;
-    const float *p = src + (int64_t)hd * per_head + e;
-    // fixed order (ascending windows); eight loads in flight per lane
-    float acc = 0.f;
-    int64_t w = 0;
-    for (; w + 8 <= nwin; w += 8) {
-        float t[8];
+    typedef float vec __attribute__((ext_vector_type(VEC)));
+    __shared__ vec sums[kThreads];
+    const int lanes = kThreads / slices, slice = threadIdx.x / lanes, lane = threadIdx.x - slice * lanes;
+    const int hd = blockIdx.x / blocks, block = blockIdx.x - hd * blocks;
+    const int64_t e = ((int64_t)block * lanes + lane) * VEC;
+    const bool in = e < per_head;
+    const int64_t step = (int64_t)heads * per_head;
+    const float *p = (blockIdx.y == 0 ? part_q : part_k) + hd * per_head + (in ? e : 0);
+    float *dst = (blockIdx.y == 0 ? dfq : dfk) + hd * per_head + e;
+    const int run = (nwin + slices - 1) / slices;
+    int w = slice * run;
+    const int end = w + run < nwin ? w + run : nwin;
+    vec acc = 0.f;
+    for (; w + 8 <= end; w += 8) {
+        vec t[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = p[(w + i) * step];
+        for (int i = 0; i < 8; ++i) t[i] = *(const vec *)(p + (w + i) * step);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc += t[i];
     }
-    for (; w < nwin; ++w) acc += p[w * step];
-    dst[idx] = acc;
+    for (; w < end; ++w) acc += *(const vec *)(p + w * step);
+    if (slices > 1) {
+        sums[threadIdx.x] = acc;
+        __syncthreads();
+        if (slice != 0) return;
+        for (int i = 1; i < slices; ++i) acc += sums[i * lanes + lane];
+    }
+    if (in) *(vec *)dst = acc;
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -539,9 +548,21 @@ hipError_t launch_reduce_df(const Geo &g, const float *part_q, const float *part
                             hipStream_t st)
 {
     if (g.r == 0) return hipSuccess;
-    const int64_t n = (int64_t)g.heads * g.N * g.r;
-    hipLaunchKernelGGL(reduce_df_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads), 2), dim3(kThreads), 0, st, g,
-                       part_q, part_k, dfq, dfk);
+    const int64_t per_head = (int64_t)g.N * g.r;
+    const int nwin = (int)(g.units / g.heads);
+    // 16 bytes a lane where the rows of every window (and the caller's dF) keep that alignment
+    const uintptr_t at = (uintptr_t)dfq | (uintptr_t)dfk;
+    const int vec = per_head % 4 == 0 && at % 16 == 0 ? 4 : per_head % 2 == 0 && at % 8 == 0 ? 2 : 1;
+    // Slices until the chip has two waves a SIMD: one slice / this rule / up to 16 until it has eight, us: 576 windows of 256
+    // tokens, 6 heads, r = 18 50 / 25 / 25, 144 of 1024, r = 16 21 / 21 / 23, 128 of 576, r = 18 12.6 / 11.0 / 11.7 (the
+    // partials of the first pass at 5 TB/s).  A slice of under eight windows has too few loads in flight.
+    int slices = 1;
+    while (slices < 16 && per_head * g.heads * 2 / vec * slices < 128 * 1024 && nwin / (2 * slices) >= 8) slices *= 2;
+    const int64_t lanes = kThreads / slices * vec;
+    const int blocks = (int)((per_head + lanes - 1) / lanes);
+    const dim3 grid((unsigned)((int64_t)blocks * g.heads), 2);
+    auto kern = vec == 4 ? reduce_df_kernel<4> : vec == 2 ? reduce_df_kernel<2> : reduce_df_kernel<1>;
+    hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, st, per_head, g.heads, blocks, nwin, slices, part_q, part_k, dfq, dfk);
     return hipGetLastError();
 }
 

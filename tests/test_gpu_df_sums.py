@@ -1,0 +1,36 @@
+"""The sums of the RIB gradients over windows where their dispatch changes: rows of 16, 8 and 4 bytes a lane, one slice
+of windows and several with a short last one, a last workgroup that is partly idle, many heads.  fp32 storage: the
+partials are those of the fp32 kernels, so the bound of 1e-4 of the parity tests holds for sums of unit-size terms too."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2603_06738_amd import workloads as wk
+from helpers import geometry
+
+SHAPES = [  # (dtype, B, windows down, across, heads, d, r, M)
+    ("f32", 1, 3, 5, 1, 6, 4, 6),           # 15 windows: one slice; 144 values a head, 16 bytes a lane
+    ("f32", 3, 5, 9, 2, 6, 4, 6),           # 135 windows: 16 slices, the last ones short
+    ("f32", 1, 17, 1, 3, 5, 3, 3),          # 27 values a head: 4 bytes a lane, 2 slices of 9 and 8
+    ("f32", 2, 4, 9, 2, 4, 2, 3),           # 18: 8 bytes a lane
+    ("f32", 1, 8, 5, 37, 2, 6, 2),          # 37 heads
+    ("bf16", 2, 3, 6, 2, 30, 18, 9),        # 1458: 8 bytes a lane, several workgroups a head
+    ("bf16", 4, 4, 4, 1, 16, 16, 8),        # 64 windows of 64 tokens
+]
+
+
+@pytest.mark.parametrize("dtype,B,ny,nx,heads,d,r,M", SHAPES)
+def test_rib_gradient_sums(oracle, dtype, B, ny, nx, heads, d, r, M):
+    import gpu_helpers as gh
+    wl = wk.custom(f"df-{dtype}m{M}r{r}", dtype, B, ny * M, nx * M, heads, d, r, M, 1, 3300 + ny * nx + M, backward=True)
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t)
+    got = gh.gpu_bwd(wl, t, out, lse)
+    again = gh.gpu_bwd(wl, t, out, lse)
+    ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    # bf16: the bound of one window's gradient, times the square root of the number of windows whose roundings add at random
+    tol = gh.TOL["f32"] if dtype == "f32" else gh.TOL["bf16"] * (B * ny * nx) ** 0.5
+    for name, a, a2, b in zip(("dF_q", "dF_k"), got[3:], again[3:], ref[3:]):
+        assert bool((a == a2).all()), name
+        assert gh.max_abs(gh.host(a), b) <= tol, name
