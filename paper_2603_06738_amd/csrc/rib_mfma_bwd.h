@@ -48,31 +48,32 @@ namespace bwd {
 
 using namespace rows;
 
-// Raw words of a wave's 64 stationary rows between their request and their staging: 8 lanes share
-// a row, 8 rows a pass.
-template <int DQK, bool WITH_O>
+// Raw words of a wave's 64 stationary rows between their request and their staging, 64 / LANES rows a pass.
+template <int DQK, bool WITH_O, int TINY>
 struct StatRegs {
-    dword2 x[8], y[8], fa[8], fb[DQK == 64 ? 8 : 1], o[WITH_O ? 8 : 1];
+    static constexpr int P = Moved<TINY>::LANES;        // passes
+    Words<TINY> x[P], y[P], fa[P], fb[DQK == 64 ? P : 1], o[WITH_O ? P : 1];
     float e0, e1;
 };
 template <int DQK, bool QDO, bool WITH_O, bool ALN, int TINY, bool BIG>
-__device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo &g, const Win &win, const Stream &s, int n0,
+__device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O, TINY> &r, const Geo &g, const Win &win, const Stream &s, int n0,
                                              const char *ob, bool from_o)
 {
-    const int lane = threadIdx.x & 63, l = lane >> 3;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    using M = Moved<TINY>;
+    const int lane = threadIdx.x & 63, l = lane / M::LANES;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
+    for (int p = 0; p < M::LANES; ++p) {
         // (a wave past the window's end repeats its last rows)
-        const int nb = ALN && n0 + p * 8 > win.last - 7 ? win.last - 7 : n0 + p * 8, n = nb + l;
-        const uint32_t t = win.token<ALN>(nb, l);
-        r.x[p] = get8(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
-        r.y[p] = get8(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
-        if (WITH_O && from_o) r.o[p] = get8(ob, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
+        const int nf = n0 + p * M::ROWS, nb = ALN && nf > win.last - (M::ROWS - 1) ? win.last - (M::ROWS - 1) : nf, n = nb + l;
+        const uint32_t t = win.token<ALN, M::ROWS>(nb, l);
+        r.x[p] = get<TINY>(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
+        r.y[p] = get<TINY>(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
+        if (WITH_O && from_o) r.o[p] = get<TINY>(ob, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
         if (!pc.fnone) {
             const uint32_t fr = __umul24((uint32_t)(n < win.last ? n : win.last), s.frow);
-            r.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
-            if (DQK == 64) r.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+            r.fa[p] = get<TINY>(s.fb, fr + 4u * pc.f0, pc.f1d);
+            if (DQK == 64) r.fb[p] = get<TINY>(s.fb, fr + 4u * pc.f1, pc.f1d);
         }
     }
     r.e0 = r.e1 = 0.f;
@@ -84,28 +85,38 @@ __device__ __forceinline__ void stat_request(StatRegs<DQK, WITH_O> &r, const Geo
 }
 
 // delta_i = dO_i . O_i (paper Sec. 2.2 backward; the softmax Jacobian's row term) of the wave's 64
-// rows from the words the lanes hold: each lane multiplies its two channel pairs, three halving
-// steps over the 8 lanes of a row (lane ^ 7, ^ 2, ^ 1: DPP patterns) leave lane j of the group with
-// row j * 8 + sub, and a lane permute hands row `lane` its value.
-template <int DQK>
-__device__ __forceinline__ float make_delta(const StatRegs<DQK, true> &r, const Geo &g)
+// rows from the words the lanes hold: each lane multiplies its channel pairs, halving
+// steps over the lanes of a row (lane ^ 7, ^ 2, ^ 1: DPP patterns; four lanes: the last two) leave lane j of a row's lanes
+// with the row of pass j, and a lane permute hands row `lane` its value.
+template <int DQK, int TINY>
+__device__ __forceinline__ float make_delta(const StatRegs<DQK, true, TINY> &r, const Geo &g)
 {
-    const int lane = threadIdx.x & 63, j = lane & 7, hp = g.d >> 1;
-    const bool first = 2 * j + 1 < hp || (hp == 1 && j == 0), second = hp > 1 && 2 * j < hp;   // (a slid pair counts its new half only)
-    float part[8];
+    using M = Moved<TINY>;
+    const int lane = threadIdx.x & 63, j = lane % M::LANES;
+    const Piece pc = piece_of<TINY>(g, j);
+    float part[M::LANES];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        const float a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r.y[p].x), __builtin_bit_cast(bf16x2, r.o[p].x), 0.f, false);
-        const float b = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r.y[p].y), __builtin_bit_cast(bf16x2, r.o[p].y), 0.f, false);
-        part[p] = (first ? a : 0.f) + (second ? b : 0.f);
+    for (int p = 0; p < M::LANES; ++p) {
+        part[p] = 0.f;
+#pragma unroll
+        for (int i = 0; i < M::WORDS; ++i) {
+            // (a slid piece counts its new words only)
+            const bool own = pc.c1 ? i == 0 && j == 0 : pc.dc + i >= M::WORDS * j;
+            const float a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r.y[p].w[i]), __builtin_bit_cast(bf16x2, r.o[p].w[i]), 0.f, false);
+            part[p] += own ? a : 0.f;
+        }
     }
 #define RIB_DPP(x, ctrl) __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (x)), (ctrl), 0xF, 0xF, true))
     const bool b2 = (j & 4) != 0, b1 = (j & 2) != 0, b0 = (j & 1) != 0;
     float h4[4], h2[2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float keep = b2 ? part[4 + i] : part[i], give = b2 ? part[i] : part[4 + i];
-        h4[i] = keep + RIB_DPP(give, 0x141);        // row_half_mirror: lane ^ 7
+        if constexpr (M::LANES == 8) {
+            const float keep = b2 ? part[4 + i] : part[i], give = b2 ? part[i] : part[4 + i];
+            h4[i] = keep + RIB_DPP(give, 0x141);        // row_half_mirror: lane ^ 7
+        } else {
+            h4[i] = part[i];
+        }
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -115,17 +126,20 @@ __device__ __forceinline__ float make_delta(const StatRegs<DQK, true> &r, const 
     const float keep = b0 ? h2[1] : h2[0], give = b0 ? h2[0] : h2[1];
     const float mine = keep + RIB_DPP(give, 0xB1);  // quad_perm [1,0,3,2]: lane ^ 1
 #undef RIB_DPP
-    return __shfl(mine, (lane & 7) * 8 + (lane >> 3));
+    return __shfl(mine, (lane % M::ROWS) * M::LANES + lane / M::ROWS);
 }
 
-// Stage the wave's 64 rows through its private LDS area and read them back as MFMA B operands.
+// Stage the wave's 64 rows through its private LDS area and read them back as MFMA B operands.  `ftab` (QDO, may be
+// null): where this head's scaled RIB rows go for the dkv kernel.
 template <int DQK, bool QDO, bool XS, bool XD, bool WITH_O, int TINY>
-__device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O> &r, const Geo &g, bf16_t *W, float sc, float sp, float nl,
-                                           float nd, bf16x8 (&Xb)[2][DQK / 16], bf16x8 (&Yb)[2][2])
+__device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O, TINY> &r, const Geo &g, bf16_t *W, float sc, float sp, float nl,
+                                           float nd, bf16x8 (&Xb)[2][DQK / 16], bf16x8 (&Yb)[2][2], char *ftab = nullptr,
+                                           int n0 = 0, bool aln = false)
 {
     using L = Lay<DQK, 64>;
-    const int lane = threadIdx.x & 63, l = lane >> 3, col = lane & 31, hf = lane >> 5;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    using M = Moved<TINY>;
+    const int lane = threadIdx.x & 63, l = lane / M::LANES, col = lane & 31, hf = lane >> 5;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
     bf16_t *Xs = W, *Ys = W + 64 * L::XS;
     {   // padding columns and extras of row `lane`
         bf16_t *xr = Xs + lane * L::XS, *yr = Ys + lane * L::YS;
@@ -137,19 +151,21 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O> &r, const
     bf16_t *xr = Xs + l * L::XS + 2 * pc.dc, *yr = Ys + l * L::YS + 2 * pc.dc;
     bf16_t *fr = Xs + l * L::XS + g.d + 2 * pc.f0, *fr1 = Xs + l * L::XS + g.d + 2 * pc.f1;
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        dword2 x = r.x[p], fa = r.fa[p], fb;
-        if (DQK == 64) fb = r.fb[p];
-        if (QDO) {
-            x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
-            fa.x = scale_pair(fa.x, sp), fa.y = scale_pair(fa.y, sp);
-            if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
-        }
-        put8(xr + p * 8 * L::XS, x, pc.c1);
-        put8(yr + p * 8 * L::YS, r.y[p], pc.c1);
+    for (int p = 0; p < M::LANES; ++p) {
+        put<TINY>(xr + p * M::ROWS * L::XS, QDO ? scaled<TINY>(r.x[p], sc) : r.x[p], pc.c1);
+        put<TINY>(yr + p * M::ROWS * L::YS, r.y[p], pc.c1);
         if (!pc.fnone) {
-            put8(fr + p * 8 * L::XS, fa, pc.f1d);
-            if (DQK == 64) put8(fr1 + p * 8 * L::XS, fb, pc.f1d);
+            const Words<TINY> fa = QDO ? scaled<TINY>(r.fa[p], sp) : r.fa[p];
+            Words<TINY> fb;
+            if (DQK == 64) fb = QDO ? scaled<TINY>(r.fb[p], sp) : r.fb[p];
+            put<TINY>(fr + p * M::ROWS * L::XS, fa, pc.f1d);
+            if (DQK == 64) put<TINY>(fr1 + p * M::ROWS * L::XS, fb, pc.f1d);
+            if (QDO && ftab) {
+                const int n = n0 + p * M::ROWS + l, last = g.N - 1, nb = aln && n0 + p * M::ROWS > last - (M::ROWS - 1) ? last - (M::ROWS - 1) + l : n;
+                char *row = ftab + __umul24((uint32_t)(nb < last ? nb : last), (uint32_t)g.r * 2u);
+                put<TINY>((bf16_t *)(row + 4u * pc.f0), fa, pc.f1d);
+                if (DQK == 64) put<TINY>((bf16_t *)(row + 4u * pc.f1), fb, pc.f1d);
+            }
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -213,7 +229,7 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
     qs.ys = (int64_t)g.C * 2;                                                                              \
     ks.lse = qs.lse = lse + u * g.N;                                                                       \
     ks.delta = qs.delta = delta + u * g.N;                                                                 \
-    const float sc2 = g.scale_c * kLog2e, sp2 = g.scale_p * kLog2e;                                        \
+    const float sc2 = g.scale_c * kLog2e;                                                                  \
     const int n0 = (blk * waves + wave) * 64;                                                              \
     const int ntiles = (g.N + T - 1) / T;                                                                  \
     if (!ALN) __syncthreads();
@@ -232,35 +248,37 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
                                                       const bf16_t *__restrict__ dout, const float *__restrict__ lse,
                                                       float *__restrict__ delta, bf16_t *__restrict__ dq,
-                                                      float *__restrict__ dfq_part)
+                                                      float *__restrict__ dfq_part, bf16_t *__restrict__ ftab)
 {
     RIB_BWD_SETUP
     constexpr int NB = T / 32, NS = 2 * NB;
+    const float sp2 = g.scale_p * kLog2e;
 
     // one exposed memory latency: the wave's rows and the first two tiles are requested together
-    Regs<DQK> rg, rg1;
+    Regs<DQK, TINY> rg, rg1;
     bf16x8 Qb[2][L::KS], Gb[2][L::VS];
     float nl[2] = {0.f, 0.f}, nd[2] = {0.f, 0.f};
     {
-        StatRegs<DQK, true> sr;
+        StatRegs<DQK, true, TINY> sr;
         const bool from_o = g.gate == nullptr;          // a gated call's pass over dO', G and O has made delta already
         stat_request<DQK, true, true, ALN, TINY, BIG>(sr, g, win, qs, n0, (const char *)(out + img * g.C + hd * g.d), from_o);
         request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, 0, nt, wave);
         request<DQK, T, false, ALN, TINY, BIG>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
         float dl = sr.e1;
         if (from_o) {
-            dl = make_delta<DQK>(sr, g);
+            dl = make_delta<DQK, TINY>(sr, g);
             if (n0 + lane < g.N) delta[u * g.N + n0 + lane] = dl;       // for the dkv kernel, which runs second
         }
         const float l2 = -sr.e0 * kLog2e;
-        stat_stage<DQK, true, XS, XD, true, TINY>(sr, g, smem + wave * L::WAVE_STAT, sc2, sp2, l2, -dl, Qb, Gb);
+        stat_stage<DQK, true, XS, XD, true, TINY>(sr, g, smem + wave * L::WAVE_STAT, sc2, sp2, l2, -dl, Qb, Gb,
+                                                      w == 0 ? (char *)(ftab + (int64_t)hd * g.N * g.r) : nullptr, n0, ALN);
         if (XS) nl[0] = __shfl(l2, col), nl[1] = __shfl(l2, 32 + col);
         if (XD) nd[0] = -__shfl(dl, col), nd[1] = -__shfl(dl, 32 + col);
     }
     __syncthreads();
     init_pads<DQK, T, false, XS, XD>(g, smem, nt);
-    commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
-    commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, g.N, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -314,7 +332,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
             for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
-            if (s == 0) commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem + c2, 1.f, 1.f, rows_left<T>(g, tile + 2), nt, wave);
+            if (s == 0) commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem + c2, 1.f, rows_left<T>(g, tile + 2), nt, wave);
             RIB_FENCE();
 #pragma unroll
             for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
@@ -385,7 +403,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
     }
 }
 
-// dK, dV (+ dF_k partial).  Same walk with the roles exchanged.  There are no registers for a second
+// dK, dV (+ dF_k partial).  `fq` is the dq kernel's table of scaled RIB rows (they are the same for every window, and
+// scaling them while they are staged cost a tenth of the loop's vector instructions).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
 template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
@@ -399,10 +418,10 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
     RIB_BWD_SETUP
     constexpr int NB = T / 32;
 
-    Regs<DQK> rg, rg1;
+    Regs<DQK, TINY> rg, rg1;
     bf16x8 Kb[2][L::KS], Vb[2][L::VS];
     {
-        StatRegs<DQK, false> sr;
+        StatRegs<DQK, false, TINY> sr;
         stat_request<DQK, false, false, ALN, TINY, BIG>(sr, g, win, ks, n0, nullptr, false);
         request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, 0, nt, wave);
         request<DQK, T, true, ALN, TINY, BIG>(rg1, g, win, qs, ntiles > 1 ? 1 : 0, nt, wave);
@@ -410,8 +429,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
     }
     __syncthreads();
     init_pads<DQK, T, true, XS, XD>(g, smem, nt);
-    commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, sp2, g.N, nt, wave);
-    commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, g.N, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -468,7 +487,7 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int 
                         for (int mb = 0; mb < L::RB; ++mb)
                             Aqt[mb][i] = read_tr<L::XS>(cur + (qb * 32 + 16 * i) * L::XS, trx, 32 * mb);
                     }
-                    if (qb == 0) commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem + c2, sc2, sp2, rows_left<T>(g, tile + 2), nt, wave);
+                    if (qb == 0) commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem + c2, sc2, rows_left<T>(g, tile + 2), nt, wave);
                 } else {
                     read_rows<L::KS>(Aq, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::XS : nxt) + aqo);
                     read_rows<L::VS>(Ag, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::YS : nxt) + ago);
@@ -523,6 +542,7 @@ struct Args {
     float *delta;
     bf16_t *dq, *dk, *dv;
     float *pq, *pk;
+    bf16_t *ftab;           // [heads][N][r]: scaled f_q rows, from the dq kernel (first window) to the dkv kernel
     hipStream_t st;
 };
 
@@ -540,10 +560,10 @@ hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(g.units * nblk)), block(waves * 64);
     // dq first: it writes the delta rows the dkv kernel streams
-    hipLaunchKernelGGL(kdq, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout, a.lse, a.delta, a.dq, a.pq);
+    hipLaunchKernelGGL(kdq, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout, a.lse, a.delta, a.dq, a.pq, a.ftab);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kdkv, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.dout, a.lse, a.delta, a.dk, a.dv, a.pk);
+    hipLaunchKernelGGL(kdkv, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.ftab, a.fk, a.dout, a.lse, a.delta, a.dk, a.dv, a.pk);
     return hipGetLastError();
 }
 
@@ -569,9 +589,9 @@ hipError_t launch_width(const Geo &g, const Args &a)
     const Short kind = short_rows(g);
     const bool aln = g.M % 8 == 0;
     if (!rows_supported(g))
-        return kind != kLong ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, true>(g, 4, nblk, a)
-               : aln         ? launch_pair<DQK, 64, XS, XD, true, kLong, true>(g, 4, nblk, a)
-                             : launch_pair<DQK, 64, XS, XD, false, kLong, true>(g, 4, nblk, a);
+        return kind != kLong && kind != kLong8 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, true>(g, 4, nblk, a)
+               : aln                           ? launch_pair<DQK, 64, XS, XD, true, kLong8, true>(g, 4, nblk, a)
+                                               : launch_pair<DQK, 64, XS, XD, false, kLong8, true>(g, 4, nblk, a);
     if (kind == kAnyShort)
         return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, false>(g, waves, nblk, a)
                           : launch_pair<DQK, 32, XS, XD, false, kAnyShort, false>(g, waves, nblk, a);
@@ -580,6 +600,7 @@ hipError_t launch_width(const Geo &g, const Args &a)
         if (kind == kPairRib) return launch_rows<DQK, XS, XD, kPairRib>(g, aln, waves, nblk, a);
         if (kind == kNoRib) return launch_rows<DQK, XS, XD, kNoRib>(g, aln, waves, nblk, a);
     }
+    if (kind == kLong8) return launch_rows<DQK, XS, XD, kLong8>(g, aln, waves, nblk, a);
     if (kind != kLong) return hipErrorInvalidValue;
     return launch_rows<DQK, XS, XD, kLong>(g, aln, waves, nblk, a);
 }

@@ -29,12 +29,14 @@ hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const voi
     a.fq = (const bf16_t *)fq, a.fk = (const bf16_t *)fk;
     a.out = (const bf16_t *)out, a.dout = (const bf16_t *)dout, a.lse = lse;
     a.dq = (bf16_t *)dq, a.dk = (bf16_t *)dk, a.dv = (bf16_t *)dv;
+    // the call's own dF_q output, which is written last, holds the scaled rows of f_q until then (2 of its 4 bytes a value)
+    a.ftab = (bf16_t *)dfq;
     a.st = st;
     // RIB rows of more than 32 values are staged by the 64-column kernels only.  Units that one workgroup holds are done
     // in one kernel (the figures stand in rib_mfma_unit.h); rows of a pair or less and 64-bit offsets have forms in the pair only.
     const int aug = g.d + g.r;
     const int width = aug <= 32 && g.d <= 30 ? 32 : aug <= 48 && g.r <= 32 ? 48 : 64;
-    const bool one = g.N <= 512 && rows::short_rows(g) == rows::kLong && rows_supported(g);
+    const bool one = g.N <= 512 && (rows::short_rows(g) == rows::kLong || rows::short_rows(g) == rows::kLong8) && rows_supported(g);
     const hipError_t e = one ? (width == 32 ? unit::launch32(g, a) : width == 48 ? unit::launch48(g, a) : unit::launch64(g, a))
                              : (width == 32 ? bwd::launch32(g, a) : width == 48 ? bwd::launch48(g, a) : bwd::launch64(g, a));
     if (e != hipSuccess) return e;

@@ -38,55 +38,50 @@ struct Args {
     hipStream_t st;
 };
 
-// Raw words of a wave's QB * 32 query rows: 8 lanes share a row, 8 rows a pass.
-template <int DQK, int QB>
+// Raw words of a wave's QB * 32 query rows, 64 / LANES rows a pass.
+template <int DQK, int QB, int TINY>
 struct QRows {
-    dword2 x[4 * QB], fa[4 * QB], fb[DQK == 64 ? 4 * QB : 1];
+    static constexpr int P = QB * 32 / Moved<TINY>::ROWS;
+    Words<TINY> x[P], fa[P], fb[DQK == 64 ? P : 1];
 };
 template <int DQK, int QB, bool ALN, int TINY>
-__device__ __forceinline__ void q_request(QRows<DQK, QB> &r, const Geo &g, const Win &win, const Stream &s, int n0)
+__device__ __forceinline__ void q_request(QRows<DQK, QB, TINY> &r, const Geo &g, const Win &win, const Stream &s, int n0)
 {
-    const int lane = threadIdx.x & 63, l = lane >> 3;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    using M = Moved<TINY>;
+    const int lane = threadIdx.x & 63, l = lane / M::LANES;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
 #pragma unroll
-    for (int p = 0; p < 4 * QB; ++p) {
+    for (int p = 0; p < QRows<DQK, QB, TINY>::P; ++p) {
         // (a wave past the window's end repeats its last rows)
-        const int nb = ALN && n0 + p * 8 > win.last - 7 ? win.last - 7 : n0 + p * 8, n = nb + l;
-        r.x[p] = get8(s.xb, token_offset<false>(win.token<ALN>(nb, l), s.xs) + 4u * pc.dc, pc.c1);
+        const int nf = n0 + p * M::ROWS, nb = ALN && nf > win.last - (M::ROWS - 1) ? win.last - (M::ROWS - 1) : nf, n = nb + l;
+        r.x[p] = get<TINY>(s.xb, token_offset<false>(win.token<ALN, M::ROWS>(nb, l), s.xs) + 4u * pc.dc, pc.c1);
         if (!pc.fnone) {
             const uint32_t fr = __umul24((uint32_t)(n < win.last ? n : win.last), s.frow);
-            r.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
-            if (DQK == 64) r.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+            r.fa[p] = get<TINY>(s.fb, fr + 4u * pc.f0, pc.f1d);
+            if (DQK == 64) r.fb[p] = get<TINY>(s.fb, fr + 4u * pc.f1, pc.f1d);
         }
     }
 }
 // Scale (Eq. 5, times log2 e), round to bf16 and read back as B operands through the wave's own LDS area.
 template <int DQK, int QB, int TINY>
-__device__ __forceinline__ void q_stage(const QRows<DQK, QB> &r, const Geo &g, bf16_t *W, bf16x8 (&Q)[QB][DQK / 16])
+__device__ __forceinline__ void q_stage(const QRows<DQK, QB, TINY> &r, const Geo &g, bf16_t *W, bf16x8 (&Q)[QB][DQK / 16])
 {
     constexpr int STR = Lay<DQK, 64>::XS;
+    using M = Moved<TINY>;
     const float sc = g.scale_c * kLog2e, sp = g.scale_p * kLog2e;
-    const int lane = threadIdx.x & 63, l = lane >> 3, col = lane & 31, hf = lane >> 5;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    const int lane = threadIdx.x & 63, l = lane / M::LANES, col = lane & 31, hf = lane >> 5;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
     if (lane < 32 * QB) {       // padding columns of row `lane`
         bf16_t *xr = W + lane * STR;
         for (int c = g.d + g.r; c < DQK; c += 2) *(uint32_t *)(xr + c) = 0u;
     }
     bf16_t *xr = W + l * STR + 2 * pc.dc, *fr = W + l * STR + g.d + 2 * pc.f0, *fr1 = W + l * STR + g.d + 2 * pc.f1;
 #pragma unroll
-    for (int p = 0; p < 4 * QB; ++p) {
-        dword2 x = r.x[p];
-        x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
-        put8(xr + p * 8 * STR, x, pc.c1);
+    for (int p = 0; p < QRows<DQK, QB, TINY>::P; ++p) {
+        put<TINY>(xr + p * M::ROWS * STR, scaled<TINY>(r.x[p], sc), pc.c1);
         if (!pc.fnone) {
-            dword2 f = r.fa[p];
-            f.x = scale_pair(f.x, sp), f.y = scale_pair(f.y, sp);
-            put8(fr + p * 8 * STR, f, pc.f1d);
-            if (DQK == 64) {
-                f = r.fb[p];
-                f.x = scale_pair(f.x, sp), f.y = scale_pair(f.y, sp);
-                put8(fr1 + p * 8 * STR, f, pc.f1d);
-            }
+            put<TINY>(fr + p * M::ROWS * STR, scaled<TINY>(r.fa[p], sp), pc.f1d);
+            if (DQK == 64) put<TINY>(fr1 + p * M::ROWS * STR, scaled<TINY>(r.fb[p], sp), pc.f1d);
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -149,10 +144,10 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
     if (!ALN) __syncthreads();
 
     // one exposed memory latency: the wave's rows and the first two tiles are requested together
-    Regs<DQK> rg, rg1;
+    Regs<DQK, TINY> rg, rg1;
     bf16x8 Qb[QB][L::KS];
     {
-        QRows<DQK, QB> qr;
+        QRows<DQK, QB, TINY> qr;
         q_request<DQK, QB, ALN, TINY>(qr, g, win, qs, n0);
         request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, 0, nt, wave);
         request<DQK, T, false, ALN, TINY, false>(rg1, g, win, ks, ntiles > 1 ? 1 : 0, nt, wave);
@@ -160,8 +155,8 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
     }
     __syncthreads();
     init_pads<DQK, T, false, true, SUM>(g, smem, nt);
-    commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
-    commit<DQK, T, false, true, SUM, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem, 1.f, g.N, nt, wave);
+    commit<DQK, T, false, true, SUM, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -218,7 +213,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
                 for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
                 P[cs][2] = pack_bf16(p[4], p[5]);
                 P[cs][3] = pack_bf16(p[6], p[7]);
-                if (s == 0) commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem + c2, 1.f, 1.f, rows_left<T>(g, tile + 2), nt, wave);
+                if (s == 0) commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem + c2, 1.f, rows_left<T>(g, tile + 2), nt, wave);
                 RIB_FENCE();
 #pragma unroll
                 for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
@@ -273,7 +268,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
 #pragma unroll 1
         for (int tile = 0; tile < ntiles; ++tile) {     // two stages in turn, one barrier a tile
             bf16_t *cur = smem + (tile & 1) * L::STAGE;
-            commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, cur, 1.f, 1.f, g.N - tile * T, nt, wave);
+            commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, cur, 1.f, g.N - tile * T, nt, wave);
             request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
             __syncthreads();
 #pragma unroll 1
@@ -381,10 +376,13 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
 {
     const Short kind = short_rows(g);
     const bool aln = g.M % 8 == 0;
-    if (qb == 1 && kind == kLong) {
+    if (qb == 1 && (kind == kLong || kind == kLong8)) {
         const int nb = (g.N + 31) / 32, nblk = (nb + 7) / 8;
         int waves = (nb + nblk - 1) / nblk;
         if (waves < 4) waves = 4;
+        if (kind == kLong8)
+            return aln ? launch_one<DQK, 64, 1, SUM, true, kLong8>(g, waves, nblk, a)
+                       : launch_one<DQK, 64, 1, SUM, false, kLong8>(g, waves, nblk, a);
         return aln ? launch_one<DQK, 64, 1, SUM, true, kLong>(g, waves, nblk, a)
                    : launch_one<DQK, 64, 1, SUM, false, kLong>(g, waves, nblk, a);
     }
@@ -399,6 +397,7 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
         if (kind == kPairRib) return launch_queries64<DQK, SUM, kPairRib>(g, aln, waves, nblk, a);
         if (kind == kNoRib) return launch_queries64<DQK, SUM, kNoRib>(g, aln, waves, nblk, a);
     }
+    if (kind == kLong8) return launch_queries64<DQK, SUM, kLong8>(g, aln, waves, nblk, a);
     if (kind != kLong) return hipErrorInvalidValue;
     return launch_queries64<DQK, SUM, kLong>(g, aln, waves, nblk, a);
 }

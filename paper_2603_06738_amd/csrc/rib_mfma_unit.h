@@ -69,7 +69,7 @@ __device__ __forceinline__ void q_request(QRegs<DQK, NP> &rg, const Geo &g, cons
                                           int nt, int wave)
 {
     const int lane = opaque_tid() & 63, l = lane >> 3;
-    const Piece pc = piece_of<kLong>(g, lane & 7);
+    const Piece pc = piece_of<kLong8>(g, lane & 7);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int slot = p * nt + wave * 64;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void q_commit(const QRegs<DQK, NP> &rg, const Geo &g,
 {
     using L = Lay<DQK, 32>;
     const int lane = opaque_tid() & 63, l = lane >> 3, j = lane & 7;
-    const Piece pc = piece_of<kLong>(g, j);
+    const Piece pc = piece_of<kLong8>(g, j);
     bf16_t *xr = S + __mul24(l, L::XS) + 2 * pc.dc, *yr = S + L::YR + __mul24(l, L::YS) + 2 * pc.dc;
     bf16_t *fr = S + __mul24(l, L::XS) + g.d + 2 * pc.f0, *fr1 = S + __mul24(l, L::XS) + g.d + 2 * pc.f1;
     const int hp = g.d >> 1;
@@ -138,13 +138,13 @@ __device__ __forceinline__ void q_commit(const QRegs<DQK, NP> &rg, const Geo &g,
 // The wave's 64 K / V rows: K_aug into its rows of the K image (`K`, rows row0 ..), V through `W`; both read back as
 // MFMA B operands.  Rows past the window's end are zero in the image.
 template <int DQK, bool XS, bool XD, bool ALN>
-__device__ __forceinline__ void kv_stage(const StatRegs<DQK, false> &r, const Geo &g, char *K, bf16_t *W, int row0, int left,
+__device__ __forceinline__ void kv_stage(const StatRegs<DQK, false, kLong8> &r, const Geo &g, char *K, bf16_t *W, int row0, int left,
                                          bf16x8 (&Kb)[2][DQK / 16], bf16x8 (&Vb)[2][2])
 {
     using U = ULay<DQK>;
     constexpr int YS = Lay<DQK, 32>::YS;
     const int lane = threadIdx.x & 63, l = lane >> 3, col = lane & 31, hf = lane >> 5;
-    const Piece pc = piece_of<kLong>(g, lane & 7);
+    const Piece pc = piece_of<kLong8>(g, lane & 7);
     const int hp = g.d >> 1;
     {
         const int row = row0 + lane;
@@ -157,17 +157,17 @@ __device__ __forceinline__ void kv_stage(const StatRegs<DQK, false> &r, const Ge
     for (int p = 0; p < 8; ++p) {
         const int rr = p * 8 + l, row = row0 + rr;
         const bool in = ALN ? left > 0 : rr < left;
-        const dword2 x = r.x[p], f = r.fa[p];
-        *(uint32_t *)(K + U::dword(row, pc.dc)) = in ? x.x : 0u;
-        *(uint32_t *)(K + U::dword(row, pc.dc + 1)) = in ? x.y : 0u;
-        *(uint32_t *)(K + U::dword(row, hp + pc.f0)) = in ? f.x : 0u;
-        *(uint32_t *)(K + U::dword(row, hp + pc.f0 + 1)) = in ? f.y : 0u;
+        const Words<kLong8> x = r.x[p], f = r.fa[p];
+        *(uint32_t *)(K + U::dword(row, pc.dc)) = in ? x.w[0] : 0u;
+        *(uint32_t *)(K + U::dword(row, pc.dc + 1)) = in ? x.w[1] : 0u;
+        *(uint32_t *)(K + U::dword(row, hp + pc.f0)) = in ? f.w[0] : 0u;
+        *(uint32_t *)(K + U::dword(row, hp + pc.f0 + 1)) = in ? f.w[1] : 0u;
         if (DQK == 64) {
-            const dword2 f1 = r.fb[p];
-            *(uint32_t *)(K + U::dword(row, hp + pc.f1)) = in ? f1.x : 0u;
-            *(uint32_t *)(K + U::dword(row, hp + pc.f1 + 1)) = in ? f1.y : 0u;
+            const Words<kLong8> f1 = r.fb[p];
+            *(uint32_t *)(K + U::dword(row, hp + pc.f1)) = in ? f1.w[0] : 0u;
+            *(uint32_t *)(K + U::dword(row, hp + pc.f1 + 1)) = in ? f1.w[1] : 0u;
         }
-        put8(W + rr * YS + 2 * pc.dc, r.y[p], false);
+        put<kLong8>(W + rr * YS + 2 * pc.dc, r.y[p], false);
     }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -229,8 +229,8 @@ __global__ __launch_bounds__(W * 64, 2) void unit_kernel(Geo g, const bf16_t *__
     QRegs<DQK, NP> rg;
     bf16x8 Kb[2][L::KS], Vb[2][L::VS];
     {
-        StatRegs<DQK, false> sr;
-        stat_request<DQK, false, false, ALN, kLong, false>(sr, g, win, ks, n0, nullptr, false);
+        StatRegs<DQK, false, kLong8> sr;
+        stat_request<DQK, false, false, ALN, kLong8, false>(sr, g, win, ks, n0, nullptr, false);
         q_request<DQK, NP, ALN>(rg, g, win, qs, ob, 0, nt, wave);
         init_pads<DQK, 32, true, XS, XD, 2>(g, stages, nt);
         kv_stage<DQK, XS, XD, ALN>(sr, g, kimg, (bf16_t *)dsb + wave * 64 * L::YS, n0, active ? g.N - n0 : 0, Kb, Vb);

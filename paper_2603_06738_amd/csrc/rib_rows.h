@@ -131,10 +131,17 @@ struct Win {
     const int *rowb, *colo;
     uint32_t inv_m;
     int M, last, y0, x0, H, W;
-    // `n0`: the wave's first token (uniform), this lane's token is n0 + l
-    template <bool ALN>
+    // `n0`: the wave's first token (uniform), this lane's token is n0 + l; l < 8, or l < 16 (ROWS): two runs of eight
+    template <bool ALN, int ROWS = 8>
     __device__ __forceinline__ uint32_t token(int n0, int l) const
     {
+        if (ALN && ROWS == 16) {
+            const int iy0 = (int)__umulhi((uint32_t)n0, inv_m), iy1 = (int)__umulhi((uint32_t)(n0 + 8), inv_m);
+            const int ya = y0 + iy0 >= H ? y0 + iy0 - H : y0 + iy0, yb = y0 + iy1 >= H ? y0 + iy1 - H : y0 + iy1;
+            const bool second = l >= 8;
+            const uint32_t x = (uint32_t)(x0 + n0) - (uint32_t)(second ? iy1 * M : iy0 * M) + (uint32_t)l, xw = x - (uint32_t)W;
+            return (x < xw ? x : xw) + (uint32_t)(second ? yb * W : ya * W);
+        }
         if (ALN) {
             const int iy = (int)__umulhi((uint32_t)n0, inv_m);
             int y = y0 + iy;
@@ -190,14 +197,33 @@ __device__ __forceinline__ void block_coords(int nblk, int64_t &u, int &blk)
     blk = logical - (int)(u * nblk);
 }
 
-// What a lane moves when 8 lanes share a token: the dword pair 2j, 2j+1 of the content row and of
-// the RIB row (a second pair for rows longer than 32 values).  Lanes past the end slide back onto
-// the last pair (they duplicate a neighbour); rows of a single dword (d = 2, r = 2) move alone.
+// What a lane moves: 4 lanes share a token, 16 bytes each: dwords 4j .. 4j+3 of the content row and of the RIB row (a second
+// piece for RIB rows longer than 32 values).  Lanes past the end slide back onto the last four (they duplicate a
+// neighbour).  Rows of less than 8 values are moved by 8 lanes, 8 bytes each; rows of a single dword (d = 2, r = 2)
+// move alone.  Both widths fill L1 at the same rate (64 rows of 60 bytes: 114 and 118 ns a CU), but 16 bytes a lane halve the
+// address arithmetic and the memory instructions, which ride on the vector issue beside the MFMAs (8 / 4 lanes, us: forward
+// + backward of 8 images of 96 x 96, 24 x 24 windows, r = 18 361 / 335, 16 images, 32 x 32, r = 16 836 / 815; forward of 4 images of 96 x
+// 144, 12 x 12 37 / 35).
 // Which rows are that short is compiled in: a branch in the staging code splits the pinned order of the
 // blocks it rides in (forward and backward of 8 images of 96 x 96, 6 heads, d = 30, r = 2, us with branches /
 // without: 32 x 32 windows 601 / 369, 16 x 16 299 / 186, 24 x 24 594 / 337; r = 0, 32 x 32: 464 / 343).
-enum Short { kLong = 0, kPairRib = 1, kNoRib = 2, kAnyShort = 3 };      // d, r >= 4 | r = 2 | r = 0 | d = 2, any r (branches)
-inline Short short_rows(const Geo &g) { return g.d < 4 ? kAnyShort : g.r == 0 ? kNoRib : g.r < 4 ? kPairRib : kLong; }
+enum Short { kLong = 0, kPairRib = 1, kNoRib = 2, kAnyShort = 3, kLong8 = 4 };  // d, r >= 8 | d >= 4: r = 2 | r = 0 | d = 2, any r (branches) | d, r >= 4
+inline Short short_rows(const Geo &g)
+{
+    return g.d < 4 ? kAnyShort : g.r == 0 ? kNoRib : g.r < 4 ? kPairRib : g.d < 8 || g.r < 8 ? kLong8 : kLong;
+}
+template <int TINY>
+struct Moved {
+    static constexpr int LANES = TINY == kLong ? 4 : 8;         // lanes a token
+    static constexpr int ROWS = 64 / LANES;                     // tokens an instruction
+    static constexpr int WORDS = 16 / LANES;                    // dwords a lane
+    static constexpr int SLOTS = LANES == 4 ? 1 : 2;            // tokens a lane moves of a streamed tile
+    struct __attribute__((packed, aligned(4))) Words {
+        uint32_t w[WORDS];
+    };
+};
+template <int TINY>
+using Words = typename Moved<TINY>::Words;
 struct Piece {
     int dc, f0, f1;                 // first dword of the content / RIB pieces
     bool c1, f1d, fnone;            // single-dword content / RIB rows, no RIB at all (uniform)
@@ -205,14 +231,15 @@ struct Piece {
 template <int TINY>
 __device__ __forceinline__ Piece piece_of(const Geo &g, int j)
 {
+    constexpr int WN = Moved<TINY>::WORDS;
     const int hp = g.d >> 1, rh = g.r >> 1;
     Piece p;
     p.c1 = TINY == kAnyShort && hp < 2;
     p.f1d = TINY == kPairRib || (TINY == kAnyShort && rh < 2);
     p.fnone = TINY == kNoRib || (TINY == kAnyShort && rh == 0);
-    p.dc = p.c1 ? 0 : (2 * j < hp - 2 ? 2 * j : hp - 2);
-    p.f0 = p.f1d ? 0 : (2 * j < rh - 2 ? 2 * j : rh - 2);
-    p.f1 = p.f1d ? 0 : (16 + 2 * j < rh - 2 ? 16 + 2 * j : rh - 2);
+    p.dc = p.c1 ? 0 : (WN * j < hp - WN ? WN * j : hp - WN);
+    p.f0 = p.f1d ? 0 : (WN * j < rh - WN ? WN * j : rh - WN);
+    p.f1 = p.f1d ? 0 : (16 + WN * j < rh - WN ? 16 + WN * j : rh - WN);
     return p;
 }
 template <class Off>
@@ -228,8 +255,34 @@ __device__ __forceinline__ void put8(bf16_t *dst, const dword2 &v, bool one)
     if (one) *(uint32_t *)dst = v.x;
     else *(dword2 *)dst = v;
 }
+template <int TINY, class Off>
+__device__ __forceinline__ Words<TINY> get(const char *base, Off off, bool one)
+{
+    Words<TINY> v;
+    if (one) {
+        v.w[0] = *(const uint32_t *)(base + off);
+#pragma unroll
+        for (int i = 1; i < Moved<TINY>::WORDS; ++i) v.w[i] = 0u;
+    } else {
+        v = *(const Words<TINY> *)(base + off);
+    }
+    return v;
+}
+template <int TINY>
+__device__ __forceinline__ void put(bf16_t *dst, const Words<TINY> &v, bool one)
+{
+    if (one) *(uint32_t *)dst = v.w[0];
+    else *(Words<TINY> *)dst = v;
+}
+template <int TINY>
+__device__ __forceinline__ Words<TINY> scaled(Words<TINY> v, float s)
+{
+#pragma unroll
+    for (int i = 0; i < Moved<TINY>::WORDS; ++i) v.w[i] = scale_pair(v.w[i], s);
+    return v;
+}
 
-// Streamed operand pair of a unit.  QDO: X = q (strided), Y = dO (dense), extras = LSE, delta.
+// Streamed operand pair of a unit.  QDO: X = q (strided; its RIB rows scaled already), Y = dO (dense), extras = LSE, delta.
 // Otherwise X = k, Y = v (both strided), extras = ones.
 struct Stream {
     const char *xb, *yb, *fb;       // this image's and head's slices; this head's RIB table
@@ -245,31 +298,33 @@ __device__ __forceinline__ auto token_offset(uint32_t t, int64_t stride)
     else return (uint32_t)__umul24(t, (uint32_t)stride);
 }
 
-template <int DQK>
+template <int DQK, int TINY>
 struct Regs {
-    dword2 x[2], y[2], fa[2], fb[DQK == 64 ? 2 : 1];
+    static constexpr int S = Moved<TINY>::SLOTS;
+    Words<TINY> x[S], y[S], fa[S], fb[DQK == 64 ? S : 1];
     float e0;
 };
 
-// Request tile `tile`: slots tid and tid + NT of the tile's T * 8 (8 lanes a token).
+// Request tile `tile`: slots tid (and tid + NT) of the tile's T * LANES.
 template <int DQK, int T, bool QDO, bool ALN, int TINY, bool BIG>
-__device__ __forceinline__ void request(Regs<DQK> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
+__device__ __forceinline__ void request(Regs<DQK, TINY> &rg, const Geo &g, const Win &win, const Stream &s, int tile, int nt, int wave)
 {
-    const int lane = opaque_tid() & 63, l = lane >> 3;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    using M = Moved<TINY>;
+    const int lane = opaque_tid() & 63, l = lane / M::LANES;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;                // the wave's first slot
-        if ((T == 64 && nt == 256) || slot < T * 8) {
-            const int n0 = tile * T + (slot >> 3);
-            const uint32_t t = win.token<ALN>(n0, l);
-            rg.x[p] = get8(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
-            rg.y[p] = get8(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
+        if ((T == 64 && nt == 256) || slot < T * M::LANES) {
+            const int n0 = tile * T + slot / M::LANES;
+            const uint32_t t = win.token<ALN, M::ROWS>(n0, l);
+            rg.x[p] = get<TINY>(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
+            rg.y[p] = get<TINY>(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
             if (!pc.fnone) {
                 const int n = n0 + l, nc = ALN ? n : (n < win.last ? n : win.last);
                 const uint32_t fr = __umul24((uint32_t)nc, s.frow);
-                rg.fa[p] = get8(s.fb, fr + 4u * pc.f0, pc.f1d);
-                if (DQK == 64) rg.fb[p] = get8(s.fb, fr + 4u * pc.f1, pc.f1d);
+                rg.fa[p] = get<TINY>(s.fb, fr + 4u * pc.f0, pc.f1d);
+                if (DQK == 64) rg.fb[p] = get<TINY>(s.fb, fr + 4u * pc.f1, pc.f1d);
             }
         }
     }
@@ -286,35 +341,31 @@ __device__ __forceinline__ int rows_left(const Geo &g, int tile)
     const int left = g.N - tile * T;
     return left > 0 ? left : (g.N - 1) % T + 1;
 }
-// `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
+// `sc`: what Q content is multiplied by (QDO).  `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
 // infinity in the repeated last token does not meet the zero P of a masked row.
 template <int DQK, int T, bool QDO, bool XS, bool XD, bool ALN, int TINY>
-__device__ __forceinline__ void commit(const Regs<DQK> &rg, const Geo &g, bf16_t *S, float sc, float sp, int left, int nt, int wave)
+__device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, bf16_t *S, float sc, int left, int nt, int wave)
 {
     using L = Lay<DQK, T>;
-    const int lane = opaque_tid() & 63, l = lane >> 3;
-    const Piece pc = piece_of<TINY>(g, lane & 7);
+    using M = Moved<TINY>;
+    const int lane = opaque_tid() & 63, l = lane / M::LANES;
+    const Piece pc = piece_of<TINY>(g, lane % M::LANES);
     bf16_t *xr = S + __mul24(l, L::XS) + 2 * pc.dc, *yr = S + L::YR + __mul24(l, L::YS) + 2 * pc.dc;
     bf16_t *fr = S + __mul24(l, L::XS) + g.d + 2 * pc.f0, *fr1 = S + __mul24(l, L::XS) + g.d + 2 * pc.f1;
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
-        if ((T == 64 && nt == 256) || slot < T * 8) {
-            dword2 x = rg.x[p], fa = rg.fa[p], fb;
-            if (DQK == 64) fb = rg.fb[p];
-            if (QDO) {
-                x.x = scale_pair(x.x, sc), x.y = scale_pair(x.y, sc);
-                fa.x = scale_pair(fa.x, sp), fa.y = scale_pair(fa.y, sp);
-                if (DQK == 64) fb.x = scale_pair(fb.x, sp), fb.y = scale_pair(fb.y, sp);
-            }
-            const int r0 = slot >> 3;                       // (uniform)
-            dword2 y = rg.y[p];
-            if (!ALN && r0 + l >= left) y.x = y.y = 0u;
-            put8(xr + r0 * L::XS, x, pc.c1);
-            put8(yr + r0 * L::YS, y, pc.c1);
+        if ((T == 64 && nt == 256) || slot < T * M::LANES) {
+            const int r0 = slot / M::LANES;                 // (uniform)
+            Words<TINY> y = rg.y[p];
+            if (!ALN && r0 + l >= left)
+#pragma unroll
+                for (int i = 0; i < M::WORDS; ++i) y.w[i] = 0u;
+            put<TINY>(xr + r0 * L::XS, QDO ? scaled<TINY>(rg.x[p], sc) : rg.x[p], pc.c1);
+            put<TINY>(yr + r0 * L::YS, y, pc.c1);
             if (!pc.fnone) {
-                put8(fr + r0 * L::XS, fa, pc.f1d);
-                if (DQK == 64) put8(fr1 + r0 * L::XS, fb, pc.f1d);
+                put<TINY>(fr + r0 * L::XS, rg.fa[p], pc.f1d);
+                if (DQK == 64) put<TINY>(fr1 + r0 * L::XS, rg.fb[p], pc.f1d);
             }
         }
     }
