@@ -32,8 +32,8 @@
 //   (ds_read_b64_tr_b16): no transposed image, no byte permutes to build one.  One pair of kernels
 //   serves every window of 64 or more tokens: a last partial tile repeats the window's last token
 //   and masks its rows of S (the separate kernels for windows that were not whole 256-token blocks,
-//   with their predicated staging, took 656 us where these take 302 us: 24 x 24 windows, 8 x 96 x 96
-//   tokens, 6 heads, d = 30, r = 18).  Registers: with 64 columns dkv spills 7 to 21 of them, dq 33 to 99 where
+//   with their predicated staging, took 656 us where these take 265 us: 24 x 24 windows, 8 x 96 x 96
+//   tokens, 6 heads, d = 30, r = 18).  Registers: with 64 columns the four-wave dkv spills 10 to 14 of them, dq 33 to 99 where
 //   the window side is no multiple of 8 (21 to 49 with 48 columns).
 //
 //   The last r columns of dQ_aug / dK_aug are this unit's contribution to dF_q /
@@ -208,7 +208,7 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
 #define RIB_BWD_SETUP                                                                                      \
     using L = Lay<DQK, T>;                                                                                 \
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];                                          \
-    const int nt = T == 64 ? 256 : (int)blockDim.x, waves = nt >> 6;                                       \
+    const int nt = T == 64 ? NT : (int)blockDim.x, waves = nt >> 6;                                        \
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);                                     \
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;                                    \
     int64_t u;                                                                                             \
@@ -234,7 +234,7 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
     const int ntiles = (g.N + T - 1) / T;                                                                  \
     if (!ALN) __syncthreads();
 
-// dQ (+ dF_q partial).  A lane stages at most two tokens a tile: T = 64 with 4 waves, T = 32 with 2 or 3.
+// dQ (+ dF_q partial).  A lane stages at most two tokens a tile: T = 64 with 4 waves (NT = 256 lanes; dkv also 8), T = 32 with 2 or 3.
 //
 // One step is one 32x32 block s = (key block, query block); its instructions are written in the
 // order they should issue and pinned with scheduling fences: the 5 score MFMAs of block s + 1 and
@@ -242,8 +242,8 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
 // of block s, so that the matrix pipe and the vector ALU always have independent work (left alone,
 // the compiler chains exp2 -> multiply -> pack element by element and waits for every LDS read
 // where it is issued).
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
-__global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT>
+__global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                       const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
                                                       const bf16_t *__restrict__ dout, const float *__restrict__ lse,
@@ -407,8 +407,8 @@ __global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dq_kernel(Geo g, int n
 // scaling them while they are staged cost a tenth of the loop's vector instructions).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
-__global__ __launch_bounds__(T == 64 ? 256 : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT>
+__global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                        const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                        const bf16_t *__restrict__ fk, const bf16_t *__restrict__ dout,
                                                        const float *__restrict__ lse, const float *__restrict__ delta,
@@ -546,25 +546,62 @@ struct Args {
     hipStream_t st;
 };
 
-// Launch the pair with workgroups of `waves` waves, `nblk` of them per unit.
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
-hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
+// Workgroups of `waves` waves, `nblk` of them per unit.
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT = 256>
+hipError_t launch_dkv(const Geo &g, int waves, int nblk, const Args &a)
 {
     using L = Lay<DQK, T>;
     const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kdq = dq_kernel<DQK, T, XS, XD, ALN, TINY, BIG>;
-    auto kdkv = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG>;
-    hipError_t e = prepare_kernel((const void *)kdkv, nullptr);
-    if (e == hipSuccess) e = prepare_kernel((const void *)kdq, nullptr);
+    auto kern = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG, NT>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)(g.units * nblk)), block(waves * 64);
-    // dq first: it writes the delta rows the dkv kernel streams
-    hipLaunchKernelGGL(kdq, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout, a.lse, a.delta, a.dq, a.pq, a.ftab);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kdkv, grid, block, smem, a.st, g, nblk, a.q, a.k, a.v, a.ftab, a.fk, a.dout, a.lse, a.delta, a.dk, a.dv, a.pk);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v, a.ftab, a.fk, a.dout, a.lse,
+                       a.delta, a.dk, a.dv, a.pk);
     return hipGetLastError();
+}
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
+hipError_t launch_dq(const Geo &g, int waves, int nblk, const Args &a)
+{
+    using L = Lay<DQK, T>;
+    const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+    if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
+    auto kern = dq_kernel<DQK, T, XS, XD, ALN, TINY, BIG, 256>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout,
+                       a.lse, a.delta, a.dq, a.pq, a.ftab);
+    return hipGetLastError();
+}
+
+// Whether the dkv kernel runs in workgroups of eight waves.  A lane then holds one 8-byte piece of each row instead of 16
+// bytes, and it is the registers that count: with 64 columns the four-wave form spills 10 to 14 of them (us, four waves / eight,
+// traced: 96 x 96 windows, r = 34 3089 / 2803, 64 x 64 2527 / 2282, 48 x 48, d = r = 32 537 / 512), with 48 and 32 none (64 x 64
+// windows, r = 16 1067 / 1089, 32 x 32 410 / 435), and no second workgroup runs beside one's start and end.  So: 64 columns;
+// windows that fill the larger workgroups to nine tenths (41 x 41, 27 blocks in 32: forward + backward 1638 / 1661); and grids of
+// two rounds and more that do not take more of them in the larger workgroups (fewer: a CU with four waves is faster
+// than half the CUs with eight).
+inline hipError_t eight_waves(const Geo &g, bool *yes)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    const int64_t nb = (g.N + 63) / 64, n8 = g.units * ((nb + 7) / 8), n4 = g.units * ((nb + 3) / 4);
+    *yes = e == hipSuccess && (nb + 7) / 8 * 72 <= nb * 80 && n8 >= 2 * cus && (n8 + cus - 1) / cus <= (n4 + 2 * cus - 1) / (2 * cus);
+    return e;
+}
+
+// The pair: dq first, it writes the delta rows and the scaled RIB rows the dkv kernel streams.
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
+hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
+{
+    hipError_t e = launch_dq<DQK, T, XS, XD, ALN, TINY, BIG>(g, waves, nblk, a);
+    if (e != hipSuccess) return e;
+    if constexpr (DQK == 64 && T == 64 && (TINY == kLong || TINY == kLong8) && !BIG) {
+        bool eight = false;
+        if ((e = eight_waves(g, &eight)) != hipSuccess) return e;
+        if (eight) return launch_dkv<DQK, 64, XS, XD, ALN, kLong8, false, 512>(g, 8, ((g.N + 63) / 64 + 7) / 8, a);
+    }
+    return launch_dkv<DQK, T, XS, XD, ALN, TINY, BIG>(g, waves, nblk, a);
 }
 
 template <int DQK, bool XS, bool XD, int TINY>

@@ -53,3 +53,22 @@ def test_backward_shapes(oracle, d, r, M, s, ny, nx, packed):
     for name, a, a2, b in zip(names, got, again, ref):
         assert bool((a == a2).all()), name                  # fixed summation order
         assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"], name
+
+
+@pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
+    (30, 34, 32, 16, 8, 2, 2, 8),       # 64 columns, LSE in the C operand; two whole workgroups a unit
+    (32, 32, 45, 3, 4, 2, 4, 4),        # both in the C operand; 2025 tokens: a partial last block and tile
+    (4, 56, 32, 0, 16, 2, 2, 4),        # a long RIB row beside 4-value content rows
+], ids=["whole", "partial", "short-content"])
+def test_eight_wave_workgroups(oracle, d, r, M, s, B, ny, nx, heads):
+    """Grids large enough for the 64-column dkv kernel's workgroups of 512 keys."""
+    import gpu_helpers as gh
+    wl = wk.custom(f"bwd8-d{d}r{r}m{M}", "bf16", B, ny * M, nx * M, heads, d, r, M, s, 7900 + M, backward=True)
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t)
+    got = gh.gpu_bwd(wl, t, out, lse)
+    ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    # dF sums windows, whose roundings add at random
+    for name, a, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, ref):
+        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"] * (1.0 if name[1] != "F" else (B * ny * nx) ** 0.5), name
