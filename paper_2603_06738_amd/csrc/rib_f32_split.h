@@ -158,20 +158,22 @@ __device__ __forceinline__ float4u get4(const char *base, uint32_t off, int c, i
     v.w = c + 3 < n ? p[c + 3 < n ? 3 : 2] : 0.f;
     return v;
 }
-template <int DA, int T>
+// (NT: the workgroup's lanes where they are a constant, 0: at least 256)
+template <int DA, int T, int NT = 0>
 struct Regs {
-    float4u x[T / 32], y[T / 32], fa[T / 32], fb[DA == 64 ? T / 32 : 1];
+    static constexpr int SLOTS = NT ? T * 8 / NT : T / 32;
+    float4u x[SLOTS], y[SLOTS], fa[SLOTS], fb[DA == 64 ? SLOTS : 1];
     float e0;
 };
-// Slots tid and tid + nt of a tile's T * 8.
-template <int DA, int T, bool EXTRA>
-__device__ __forceinline__ void request(Regs<DA, T> &rg, const Geo &g, const rows::Win &win, const Stream &s, int tile, int wave,
+// Slots tid, tid + nt, ... of a tile's T * 8.
+template <int DA, int T, bool EXTRA, int NT = 0>
+__device__ __forceinline__ void request(Regs<DA, T, NT> &rg, const Geo &g, const rows::Win &win, const Stream &s, int tile, int wave,
                                         const float *lse, const float *delta)
 {
-    const int nt = blockDim.x, lane = rows::opaque_tid() & 63, l = lane >> 3;
+    const int nt = NT ? NT : blockDim.x, lane = rows::opaque_tid() & 63, l = lane >> 3;
     const Piece pc = piece_of(g, lane & 7);
 #pragma unroll
-    for (int p = 0; p < T / 32; ++p) {
+    for (int p = 0; p < Regs<DA, T, NT>::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
         if (slot < T * 8) {
             const int n = tile * T + (slot >> 3) + l, nc = n < win.last ? n : win.last;
@@ -209,14 +211,14 @@ __device__ __forceinline__ void put4(bf16_t *dst, int part, const float4u &v, fl
     for (int i = 0; i < 3; ++i) *(dwords2 *)(dst + i * part) = dwords2{lo.p[i], hi.p[i]};
 }
 // GRAD: the X rows are operands of gradients too.
-template <int DA, int T, bool GRAD, bool EXTRA>
-__device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16_t *S, float sc, float sp, int wave, Range &rn)
+template <int DA, int T, bool GRAD, bool EXTRA, int NT = 0>
+__device__ __forceinline__ void commit(const Regs<DA, T, NT> &rg, const Geo &g, bf16_t *S, float sc, float sp, int wave, Range &rn)
 {
     using L = Lay<DA, T>;
-    const int nt = blockDim.x, lane = rows::opaque_tid() & 63, l = lane >> 3, pd = (g.d + 1) & ~1;
+    const int nt = NT ? NT : blockDim.x, lane = rows::opaque_tid() & 63, l = lane >> 3, pd = (g.d + 1) & ~1;
     const Piece pc = piece_of(g, lane & 7);
 #pragma unroll
-    for (int p = 0; p < T / 32; ++p) {
+    for (int p = 0; p < Regs<DA, T, NT>::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
         if (slot < T * 8) {
             bf16_t *xr = S + __mul24((slot >> 3) + l, L::XS), *yr = S + L::YR + __mul24((slot >> 3) + l, L::YS);
@@ -236,12 +238,12 @@ __device__ __forceinline__ void commit(const Regs<DA, T> &rg, const Geo &g, bf16
     }
 }
 // The columns no staging code writes (they meet zeros, so they only have to be finite).
-template <int DA, int T>
+template <int DA, int T, int STAGES = 3>
 __device__ __forceinline__ void zero_pads(const Geo &g, bf16_t *stages)
 {
     using L = Lay<DA, T>;
     const int pd = (g.d + 1) & ~1, pa = pd + ((g.r + 1) & ~1);
-    for (int e = threadIdx.x; e < 3 * 3 * T; e += (int)blockDim.x) {
+    for (int e = threadIdx.x; e < STAGES * 3 * T; e += (int)blockDim.x) {
         const int st = e / (3 * T), row = e - st * 3 * T;          // (the rows of the three parts follow one another)
         bf16_t *xr = stages + st * L::STAGE + row * L::XS, *yr = stages + st * L::STAGE + L::YR + row * L::YS;
         for (int c = pa; c < DA; c += 2) *(uint32_t *)(xr + c) = 0u;
@@ -412,7 +414,7 @@ __device__ __forceinline__ void store_cols(const f32x16 &acc, int mb, int hf, co
     }
 }
 
-#define RIB_SPLIT_SETUP(MAP)                                                                                   \
+#define RIB_SPLIT_SETUP(MAP, ROW0, WAVE)                                                                         \
     using L = Lay<DA, T>;                                                                                         \
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];                                              \
     int64_t u;                                                                                                 \
@@ -425,7 +427,7 @@ __device__ __forceinline__ void store_cols(const f32x16 &acc, int mb, int hf, co
     const int64_t img = (int64_t)b * g.H * g.W;                                                                \
     const int ntiles = (g.N + T - 1) / T;                                                                      \
     /* this lane's stationary token (past the window's end: its last, whose results are not stored) */         \
-    const int row0 = blk * (int)(blockDim.x >> 1), n = row0 + wave * 32 + col, nc = n < win.last ? n : win.last;\
+    const int row0 = ROW0, n = row0 + WAVE * 32 + col, nc = n < win.last ? n : win.last;                         \
     const int64_t tn = img + win.any(nc);                                                                      \
     Range rn = {0.f, {0xffff, 0xffff}};                                                                                  \
     __syncthreads();
@@ -442,13 +444,36 @@ __device__ __forceinline__ float log_sum(float m, float l)
     return s + (f + err);
 }
 
+// Normalised O of a lane's token, gated where asked for, and LSE.
+__device__ __forceinline__ void store_out(const f32x16 &O, float l, float m, const Geo &g, int hf, int64_t tn, int hd, int64_t u, int n,
+                                          float *out, float *lse)
+{
+    const float inv = 1.f / l;
+    const int64_t base = tn * g.C + hd * g.d;
+    if (g.gate) {           // CLA gate (Eq. 9) on the way out, the raw O beside it if asked for
+        const float *gt = (const float *)g.gate + base;
+        float *raw = g.out_raw ? (float *)g.out_raw + base : nullptr;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int c = acc_row(i) + 4 * hf;
+            if (c >= g.d) continue;
+            const float o = O[i] * inv;
+            out[base + c] = o * gt[c];
+            if (raw) raw[c] = o;
+        }
+    } else {
+        store_cols(O, 0, hf, g, inv, 0.f, out + base, nullptr);
+    }
+    if (lse != nullptr && hf == 0) lse[u * g.N + n] = log_sum(m, l);
+}
+
 template <int DA, int T>
 __global__ __launch_bounds__(512, 2) void fwd_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
                                                      const float *__restrict__ k, const float *__restrict__ v,
                                                      const float *__restrict__ fq, const float *__restrict__ fk,
                                                      float *__restrict__ out, float *__restrict__ lse)
 {
-    RIB_SPLIT_SETUP((lds_tiles<DA, T, DA + 1>()))
+    RIB_SPLIT_SETUP((lds_tiles<DA, T, DA + 1>()), blk * (int)(blockDim.x >> 1), wave)
     const int ax = col * L::XS + 8 * hf, tro_y = tr_lane_offset<L::YS>(lane);
     const Stream ks = {(const char *)(k + img * g.tstride + hd * g.d), (const char *)(v + img * g.tstride + hd * g.d),
                        (const char *)(fk + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.tstride * 4u,
@@ -529,28 +554,133 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(Geo g, int nblk, uint32_t i
         c0 = c1, c1 = c2, c2 = r0;
     }
     if (__syncthreads_or(rn.outside())) {
-        fwd_body<DA>(g, *(Smem<DA + 1> *)smem, u, row0, inv_r, q, k, v, fq, fk, out, lse);
+        fwd_body<DA>(g, *(Smem<DA + 1> *)smem, u, row0, g.N, inv_r, q, k, v, fq, fk, out, lse);
         return;
     }
     l += __shfl_xor(l, 32);
     if (n >= g.N) return;
-    const float inv = 1.f / l;
-    const int64_t base = tn * g.C + hd * g.d;
-    if (g.gate) {           // CLA gate (Eq. 9) on the way out, the raw O beside it if asked for
-        const float *gt = (const float *)g.gate + base;
-        float *raw = g.out_raw ? (float *)g.out_raw + base : nullptr;
+    store_out(O, l, m, g, hf, tn, hd, u, n, out, lse);
+}
+
+// Small grids: a wave that walks the whole window takes all of the call's time while most of the chip is idle (one 48 x 48 image
+// of 16 x 16 windows, 2 heads: 36 workgroups of four waves, 14 of the forward's 18 us in eight steps one after the other).
+// So the streamed side is dealt out as well: workgroups of eight waves, QW = 8 / G of them with 32 stationary
+// tokens each, in G groups; tiles of 32 G tokens, of which group `grp` takes the grp-th block; two stages, one barrier a
+// tile.  The groups' sums are added through LDS in ascending order (the forward's with their own stabilisers).
+// Us, before / with these kernels: that image's forward 18.5 / 14.0; forward + backward of one 32 x 32 window of 2 heads 204 /
+// 123, one 64 x 64 window 722 / 378, 4 x 4 windows of 16 x 16, 2 heads 78 / 61.  Taken where they fit one round of the chip: in two
+// they are slower (48 units of 256 tokens 18.7 / 25.7, 2 of 9216 402 / 441).
+template <int DA>
+struct Keys {
+    static constexpr int G = DA == 64 ? 2 : 4, QW = 8 / G, T = 32 * G;        // (two stages of 128 tokens of 64 columns exceed a CU's LDS)
+    using L = Lay<DA, T>;
+    static constexpr size_t sums = (size_t)8 * (L::RB + 1) * 16 * 64 * sizeof(float);     // (dK_aug and dV of every wave)
+    static constexpr size_t tiles = (size_t)2 * L::STAGE * sizeof(bf16_t), stat = (size_t)8 * stat_elems<DA>() * sizeof(bf16_t);
+    template <int XS>
+    static constexpr size_t lds()
+    {
+        constexpr size_t a = tiles > stat ? tiles : stat, b = sums > sizeof(Smem<XS>) ? sums : sizeof(Smem<XS>);
+        return a > b ? a : b;
+    }
+};
+template <int DA>
+__global__ __launch_bounds__(512, 2) void fwd_keys_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                          const float *__restrict__ k, const float *__restrict__ v,
+                                                          const float *__restrict__ fq, const float *__restrict__ fk,
+                                                          float *__restrict__ out, float *__restrict__ lse)
+{
+    using Z = Keys<DA>;
+    constexpr int T = Z::T, NT = 512;
+    RIB_SPLIT_SETUP((Z::template lds<DA + 1>()), blk * (32 * Z::QW), (wave % Z::QW))
+    const int grp = wave / Z::QW;
+    const int ax = col * L::XS + 8 * hf, tro_y = tr_lane_offset<L::YS>(lane);
+    const Stream ks = {(const char *)(k + img * g.tstride + hd * g.d), (const char *)(v + img * g.tstride + hd * g.d),
+                       (const char *)(fk + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.tstride * 4u,
+                       (uint32_t)g.r * 4u};
+    const Stream qs = {(const char *)(q + img * g.tstride + hd * g.d), nullptr,
+                       (const char *)(fq + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.C * 4u,
+                       (uint32_t)g.r * 4u};
+    Regs<DA, T, NT> rg;
+    bf16x8 Q[3][L::KS], none[3][2];
+    {
+        StatRegs<DA, false> sr;
+        stat_request<DA, false>(sr, g, win, qs, row0 + (wave % Z::QW) * 32);
+        request<DA, T, false, NT>(rg, g, win, ks, 0, wave, nullptr, nullptr);
+        stat_stage<DA, false>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, rn, Q, none);
+    }
+    __syncthreads();
+    zero_pads<DA, T, 2>(g, smem);
+    commit<DA, T, false, false, NT>(rg, g, smem, 1.f, 1.f, wave, rn);
+    request<DA, T, false, NT>(rg, g, win, ks, ntiles > 1 ? 1 : 0, wave, nullptr, nullptr);
+
+    f32x16 O = {0};
+    float m = -INFINITY, l = 0.f;
+#pragma unroll 1
+    for (int tile = 0; tile < ntiles; ++tile) {
+        const bf16_t *cur = smem + (tile & 1) * L::STAGE;
+        const int key0 = tile * T + grp * 32;
+        __syncthreads();
+        if (tile + 1 < ntiles) {
+            commit<DA, T, false, false, NT>(rg, g, smem + ((tile + 1) & 1) * L::STAGE, 1.f, 1.f, wave, rn);
+            request<DA, T, false, NT>(rg, g, win, ks, tile + 2 < ntiles ? tile + 2 : ntiles - 1, wave, nullptr, nullptr);
+        }
+        if (key0 >= g.N) continue;
+        f32x16 S = {0};
+        {
+            bf16x8 A[3][L::KS];
+            load_rows<L::KS>(A, cur + grp * 32 * L::XS + ax, L::XP);
+            mul6<L::KS>(S, A, Q);
+        }
+        if (key0 + 32 > g.N) rows::mask_rows(S, key0, g.N, hf);
+        float t = S[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) t = fmaxf(t, S[i]);
+        t = fmaxf(t, __shfl_xor(t, 32));
+        if (__any(t > m + 8.f)) {
+            const float mn = fmaxf(m, t), alpha = __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= alpha;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) O[i] *= alpha;
+        }
+        float ps = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int c = acc_row(i) + 4 * hf;
-            if (c >= g.d) continue;
-            const float o = O[i] * inv;
-            out[base + c] = o * gt[c];
-            if (raw) raw[c] = o;
+            S[i] = __builtin_amdgcn_exp2f(S[i] - m);
+            ps += S[i];
         }
-    } else {
-        store_cols(O, 0, hf, g, inv, 0.f, out + base, nullptr);
+        l += ps;
+        bf16x8 P[3][2], V[3][2];
+        split_block(P, S);
+        load_tr<L::YS>(V, cur + L::YR + grp * 32 * L::YS, L::YP, tro_y, 0);
+        mul6_apart<2>(O, V, P);
     }
-    if (lse != nullptr && hf == 0) lse[u * g.N + n] = log_sum(m, l);
+    if (__syncthreads_or(rn.outside())) {
+        fwd_body<DA>(g, *(Smem<DA + 1> *)smem, u, row0, row0 + 32 * Z::QW, inv_r, q, k, v, fq, fk, out, lse);
+        return;
+    }
+    float *const part = (float *)smem;          // [wave][18][64]
+    if (grp > 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[(wave * 18 + i) * 64 + lane] = O[i];
+        part[(wave * 18 + 16) * 64 + lane] = m;
+        part[(wave * 18 + 17) * 64 + lane] = l;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int j = 1; j < Z::G; ++j) {
+        const float *pw = part + (wave + j * Z::QW) * 18 * 64 + lane;
+        const float mj = pw[16 * 64], mn = fmaxf(m, mj);        // (no key of group j: minus infinity, and zeros)
+        const float a = __builtin_amdgcn_exp2f(m - mn), b = __builtin_amdgcn_exp2f(mj - mn);
+        m = mn;
+        l = l * a + pw[17 * 64] * b;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) O[i] = O[i] * a + pw[i * 64] * b;
+    }
+    l += __shfl_xor(l, 32);
+    if (n >= g.N) return;
+    store_out(O, l, m, g, hf, tn, hd, u, n, out, lse);
 }
 
 template <int DA, int T>
@@ -561,7 +691,7 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
                                                     const float *__restrict__ delta, float *__restrict__ dq,
                                                     float *__restrict__ dfq_part)
 {
-    RIB_SPLIT_SETUP((lds_tiles<DA, T, kXS>()))
+    RIB_SPLIT_SETUP((lds_tiles<DA, T, kXS>()), blk * (int)(blockDim.x >> 1), wave)
     const int ax = col * L::XS + 8 * hf, ay = L::YR + col * L::YS + 8 * hf, tro_x = tr_lane_offset<L::XS>(lane);
     const Stream ks = {(const char *)(k + img * g.tstride + hd * g.d), (const char *)(v + img * g.tstride + hd * g.d),
                        (const char *)(fk + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.tstride * 4u,
@@ -637,7 +767,7 @@ __global__ __launch_bounds__(512, 2) void dq_kernel(Geo g, int nblk, uint32_t in
         c0 = c1, c1 = c2, c2 = r0;
     }
     if (__syncthreads_or(rn.outside())) {
-        dq_body<DA>(g, *(Smem<kXS> *)smem, u, row0, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
+        dq_body<DA>(g, *(Smem<kXS> *)smem, u, row0, g.N, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
         return;
     }
     if (n >= g.N) return;
@@ -654,7 +784,7 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
                                                      const float *__restrict__ delta, float *__restrict__ dk,
                                                      float *__restrict__ dv, float *__restrict__ dfk_part)
 {
-    RIB_SPLIT_SETUP((lds_tiles<DA, T, kXS>()))
+    RIB_SPLIT_SETUP((lds_tiles<DA, T, kXS>()), blk * (int)(blockDim.x >> 1), wave)
     const int ax = col * L::XS + 8 * hf, ay = L::YR + col * L::YS + 8 * hf, tro_x = tr_lane_offset<L::XS>(lane),
               tro_y = tr_lane_offset<L::YS>(lane);
     const Stream qs = {(const char *)(q + img * g.tstride + hd * g.d), (const char *)(dout + img * g.C + hd * g.d),
@@ -738,7 +868,7 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
         c0 = c1, c1 = c2, c2 = r0;
     }
     if (__syncthreads_or(rn.outside())) {
-        dkv_body<DA>(g, *(Smem<kXS> *)smem, u, row0, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
+        dkv_body<DA>(g, *(Smem<kXS> *)smem, u, row0, g.N, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
         return;
     }
     if (n >= g.N) return;
@@ -746,6 +876,199 @@ __global__ __launch_bounds__(512, 2) void dkv_kernel(Geo g, int nblk, uint32_t i
     for (int mb = 0; mb < L::RB; ++mb)
         store_cols(accK[mb], mb, hf, g, 1.f, 1.f, dk + tn * g.C + hd * g.d, dfk_part + (u * g.N + n) * g.r);
     store_cols(accV, 0, hf, g, 1.f, 0.f, dv + tn * g.C + hd * g.d, nullptr);
+}
+
+// The backward of small grids (see Keys).
+template <int NB, int QW, int G>
+__device__ __forceinline__ bool add_groups(f32x16 (&acc)[NB], float *part, int wave, int lane)
+{
+    const int grp = wave / QW;
+    if (grp > 0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[((wave * NB + b) * 16 + i) * 64 + lane] = acc[b][i];
+    }
+    __syncthreads();
+    if (grp > 0) return false;
+#pragma unroll
+    for (int j = 1; j < G; ++j)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][i] += part[(((wave + j * QW) * NB + b) * 16 + i) * 64 + lane];
+    return true;
+}
+
+template <int DA>
+__global__ __launch_bounds__(512, 2) void dq_keys_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                         const float *__restrict__ k, const float *__restrict__ v,
+                                                         const float *__restrict__ fq, const float *__restrict__ fk,
+                                                         const float *__restrict__ dout, const float *__restrict__ lse,
+                                                         const float *__restrict__ delta, float *__restrict__ dq,
+                                                         float *__restrict__ dfq_part)
+{
+    using Z = Keys<DA>;
+    constexpr int T = Z::T, NT = 512;
+    RIB_SPLIT_SETUP((Z::template lds<kXS>()), blk * (32 * Z::QW), (wave % Z::QW))
+    const int grp = wave / Z::QW;
+    const int ax = col * L::XS + 8 * hf, ay = L::YR + col * L::YS + 8 * hf, tro_x = tr_lane_offset<L::XS>(lane);
+    const Stream ks = {(const char *)(k + img * g.tstride + hd * g.d), (const char *)(v + img * g.tstride + hd * g.d),
+                       (const char *)(fk + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.tstride * 4u,
+                       (uint32_t)g.r * 4u};
+    const Stream qs = {(const char *)(q + img * g.tstride + hd * g.d), (const char *)(dout + img * g.C + hd * g.d),
+                       (const char *)(fq + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.C * 4u,
+                       (uint32_t)g.r * 4u};
+    const float lse2 = lse[u * g.N + nc] * kLog2e, dl = delta[u * g.N + nc];
+    note_high(rn, lse2, dl);
+    Regs<DA, T, NT> rg;
+    bf16x8 Q[3][L::KS], G[3][2];
+    {
+        StatRegs<DA, true> sr;
+        stat_request<DA, true>(sr, g, win, qs, row0 + (wave % Z::QW) * 32);
+        request<DA, T, false, NT>(rg, g, win, ks, 0, wave, nullptr, nullptr);
+        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), g.scale_c * kLog2e, g.scale_p * kLog2e, rn, Q, G);
+    }
+    __syncthreads();
+    zero_pads<DA, T, 2>(g, smem);
+    commit<DA, T, true, false, NT>(rg, g, smem, 1.f, 1.f, wave, rn);
+    request<DA, T, false, NT>(rg, g, win, ks, ntiles > 1 ? 1 : 0, wave, nullptr, nullptr);
+
+    f32x16 acc[L::RB];
+#pragma unroll
+    for (int mb = 0; mb < L::RB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[mb][i] = 0.f;
+#pragma unroll 1
+    for (int tile = 0; tile < ntiles; ++tile) {
+        const bf16_t *cur = smem + (tile & 1) * L::STAGE;
+        const int key0 = tile * T + grp * 32;
+        __syncthreads();
+        if (tile + 1 < ntiles) {
+            commit<DA, T, true, false, NT>(rg, g, smem + ((tile + 1) & 1) * L::STAGE, 1.f, 1.f, wave, rn);
+            request<DA, T, false, NT>(rg, g, win, ks, tile + 2 < ntiles ? tile + 2 : ntiles - 1, wave, nullptr, nullptr);
+        }
+        if (key0 >= g.N) continue;
+        f32x16 S = {0}, D = {0};
+        {
+            bf16x8 A[3][L::KS], V[3][2];
+            load_rows<L::KS>(A, cur + grp * 32 * L::XS + ax, L::XP);
+            load_rows<2>(V, cur + grp * 32 * L::YS + ay, L::YP);
+            mul6<L::KS>(S, A, Q);
+            mul6_apart<2>(D, V, G);
+        }
+        if (key0 + 32 > g.N) rows::mask_rows(S, key0, g.N, hf);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) S[i] = __builtin_amdgcn_exp2f(S[i] - lse2) * (D[i] - dl);
+        bf16x8 B[3][2];
+        split_block(B, S);
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb) {
+            bf16x8 A[3][2];
+            load_tr<L::XS>(A, cur + grp * 32 * L::XS, L::XP, tro_x, 32 * mb);
+            mul6_apart<2>(acc[mb], A, B);
+        }
+    }
+    if (__syncthreads_or(rn.outside())) {
+        dq_body<DA>(g, *(Smem<kXS> *)smem, u, row0, row0 + 32 * Z::QW, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
+        return;
+    }
+    if (!add_groups<L::RB, Z::QW, Z::G>(acc, (float *)smem, wave, lane) || n >= g.N) return;
+#pragma unroll
+    for (int mb = 0; mb < L::RB; ++mb)
+        store_cols(acc[mb], mb, hf, g, g.scale_c, g.scale_p, dq + tn * g.C + hd * g.d, dfq_part + (u * g.N + n) * g.r);
+}
+
+template <int DA>
+__global__ __launch_bounds__(512, 2) void dkv_keys_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
+                                                          const float *__restrict__ k, const float *__restrict__ v,
+                                                          const float *__restrict__ fq, const float *__restrict__ fk,
+                                                          const float *__restrict__ dout, const float *__restrict__ lse,
+                                                          const float *__restrict__ delta, float *__restrict__ dk,
+                                                          float *__restrict__ dv, float *__restrict__ dfk_part)
+{
+    using Z = Keys<DA>;
+    constexpr int T = Z::T, NT = 512;
+    RIB_SPLIT_SETUP((Z::template lds<kXS>()), blk * (32 * Z::QW), (wave % Z::QW))
+    const int grp = wave / Z::QW;
+    const int ax = col * L::XS + 8 * hf, ay = L::YR + col * L::YS + 8 * hf, tro_x = tr_lane_offset<L::XS>(lane),
+              tro_y = tr_lane_offset<L::YS>(lane);
+    const Stream qs = {(const char *)(q + img * g.tstride + hd * g.d), (const char *)(dout + img * g.C + hd * g.d),
+                       (const char *)(fq + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.C * 4u,
+                       (uint32_t)g.r * 4u};
+    const float *lu = lse + u * g.N, *du = delta + u * g.N;
+    const Stream ks = {(const char *)(k + img * g.tstride + hd * g.d), (const char *)(v + img * g.tstride + hd * g.d),
+                       (const char *)(fk + (int64_t)hd * g.N * g.r), (uint32_t)g.tstride * 4u, (uint32_t)g.tstride * 4u,
+                       (uint32_t)g.r * 4u};
+    Regs<DA, T, NT> rg;
+    bf16x8 K[3][L::KS], V[3][2];
+    {
+        StatRegs<DA, true> sr;
+        stat_request<DA, true>(sr, g, win, ks, row0 + (wave % Z::QW) * 32);
+        request<DA, T, true, NT>(rg, g, win, qs, 0, wave, lu, du);
+        stat_stage<DA, true>(sr, g, smem + wave * stat_elems<DA>(), 1.f, 1.f, rn, K, V);
+    }
+    __syncthreads();
+    zero_pads<DA, T, 2>(g, smem);
+    commit<DA, T, true, true, NT>(rg, g, smem, g.scale_c, g.scale_p, wave, rn);
+    request<DA, T, true, NT>(rg, g, win, qs, ntiles > 1 ? 1 : 0, wave, lu, du);
+
+    f32x16 acc[L::RB + 1];          // dK_aug^T, then dV^T
+#pragma unroll
+    for (int mb = 0; mb <= L::RB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[mb][i] = 0.f;
+#pragma unroll 1
+    for (int tile = 0; tile < ntiles; ++tile) {
+        const bf16_t *cur = smem + (tile & 1) * L::STAGE;
+        const int q0 = tile * T + grp * 32;
+        __syncthreads();
+        if (tile + 1 < ntiles) {
+            commit<DA, T, true, true, NT>(rg, g, smem + ((tile + 1) & 1) * L::STAGE, g.scale_c, g.scale_p, wave, rn);
+            request<DA, T, true, NT>(rg, g, win, qs, tile + 2 < ntiles ? tile + 2 : ntiles - 1, wave, lu, du);
+        }
+        if (q0 >= g.N) continue;
+        f32x16 S = {0}, D = {0};
+        {
+            bf16x8 A[3][L::KS], G[3][2];
+            load_rows<L::KS>(A, cur + grp * 32 * L::XS + ax, L::XP);
+            load_rows<2>(G, cur + grp * 32 * L::YS + ay, L::YP);
+            mul6<L::KS>(S, A, K);
+            mul6_apart<2>(D, G, V);
+        }
+        if (q0 + 32 > g.N) rows::mask_rows(S, q0, g.N, hf);
+        // rows of S are queries: register 4j + i belongs to query 8j + 4hf + i of the block
+        const float *ex = (const float *)(cur + L::EX) + grp * 32 + 4 * hf;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 le = *(const float4 *)(ex + 8 * j), de = *(const float4 *)(ex + T + 8 * j);
+            const float ls[4] = {le.x, le.y, le.z, le.w}, ds[4] = {de.x, de.y, de.z, de.w};
+#pragma unroll
+            for (int i = 4 * j; i < 4 * j + 4; ++i) {
+                S[i] = __builtin_amdgcn_exp2f(fmaf(S[i], kLog2e, -ls[i & 3]));
+                D[i] = S[i] * (D[i] - ds[i & 3]);
+            }
+        }
+        bf16x8 B[3][2], A[3][2];
+        split_block(B, S);
+        load_tr<L::YS>(A, cur + L::YR + grp * 32 * L::YS, L::YP, tro_y, 0);
+        mul6_apart<2>(acc[L::RB], A, B);
+        split_block(B, D);
+#pragma unroll
+        for (int mb = 0; mb < L::RB; ++mb) {
+            load_tr<L::XS>(A, cur + grp * 32 * L::XS, L::XP, tro_x, 32 * mb);
+            mul6_apart<2>(acc[mb], A, B);
+        }
+    }
+    if (__syncthreads_or(rn.outside())) {
+        dkv_body<DA>(g, *(Smem<kXS> *)smem, u, row0, row0 + 32 * Z::QW, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
+        return;
+    }
+    if (!add_groups<L::RB + 1, Z::QW, Z::G>(acc, (float *)smem, wave, lane) || n >= g.N) return;
+#pragma unroll
+    for (int mb = 0; mb < L::RB; ++mb)
+        store_cols(acc[mb], mb, hf, g, 1.f, 1.f, dk + tn * g.C + hd * g.d, dfk_part + (u * g.N + n) * g.r);
+    store_cols(acc[L::RB], 0, hf, g, 1.f, 0.f, dv + tn * g.C + hd * g.d, nullptr);
 }
 
 }  // namespace split

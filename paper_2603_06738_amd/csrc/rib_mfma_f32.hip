@@ -199,7 +199,7 @@ __device__ __forceinline__ void zero_x_tiles(float *Xs)
 // Forward: Q_aug rows stationary (pre-multiplied by the scales and log2 e), K_aug / V streamed;
 // online softmax with the running row max per lane.
 template <int DA>
-__device__ __forceinline__ void fwd_body(const Geo &g, Smem<DA + 1> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void fwd_body(const Geo &g, Smem<DA + 1> &sm, int64_t u, int row0, int end, uint32_t inv_r, const float *__restrict__ q,
                                                                const float *__restrict__ k, const float *__restrict__ v,
                                                                const float *__restrict__ fq, const float *__restrict__ fk,
                                                                float *__restrict__ out, float *__restrict__ lse)
@@ -220,7 +220,7 @@ __device__ __forceinline__ void fwd_body(const Geo &g, Smem<DA + 1> &sm, int64_t
     tile_request<DA, false>(rg, g, hd, u, 0, tok, ib, ts4, ts4, fk, nullptr, nullptr);
 
     const int qi = row0 + wave * 32 + col;
-    const bool live = qi < g.N;
+    const bool live = qi < g.N && qi < end;
     const int qc = qi < g.N ? qi : g.N - 1;
     const int tq = tok[qc];
     float Qr[DA / 2];
@@ -310,7 +310,7 @@ __device__ __forceinline__ void fwd_body(const Geo &g, Smem<DA + 1> &sm, int64_t
 // dQ and this unit's dF_q contribution: Q_aug, dO rows stationary, K_aug / V streamed.
 //   S^T = K_aug Q_aug^T, dP^T = V dO^T, dS = P (dP - delta), dQ_aug^T += K_aug^T dS^T.
 template <int DA>
-__device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, int end, uint32_t inv_r, const float *__restrict__ q,
                                                               const float *__restrict__ k, const float *__restrict__ v,
                                                               const float *__restrict__ fq, const float *__restrict__ fk,
                                                               const float *__restrict__ dout, const float *__restrict__ lse,
@@ -334,7 +334,7 @@ __device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, 
     tile_request<DA, false>(rg, g, hd, u, 0, tok, ib, ts4, ts4, fk, nullptr, nullptr);
 
     const int qi = row0 + wave * 32 + col;
-    const bool live = qi < g.N;
+    const bool live = qi < g.N && qi < end;
     const int qc = qi < g.N ? qi : g.N - 1;
     const int tq = tok[qc];
     float Qr[DA / 2], Gr[16];
@@ -427,7 +427,7 @@ __device__ __forceinline__ void dq_body(const Geo &g, Smem<kXS> &sm, int64_t u, 
 //   S = Q_aug K_aug^T, dP = dO V^T, P = exp(S - LSE), dS = P (dP - delta),
 //   dV^T += dO^T P, dK_aug^T += Q_aug^T dS.
 template <int DA>
-__device__ __forceinline__ void dkv_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, uint32_t inv_r, const float *__restrict__ q,
+__device__ __forceinline__ void dkv_body(const Geo &g, Smem<kXS> &sm, int64_t u, int row0, int end, uint32_t inv_r, const float *__restrict__ q,
                                                                const float *__restrict__ k, const float *__restrict__ v,
                                                                const float *__restrict__ fq, const float *__restrict__ fk,
                                                                const float *__restrict__ dout, const float *__restrict__ lse,
@@ -451,7 +451,7 @@ __device__ __forceinline__ void dkv_body(const Geo &g, Smem<kXS> &sm, int64_t u,
     tile_request<DA, true>(rg, g, hd, u, 0, tok, ib, ts4, (uint32_t)g.C * 4u, fq, lse, delta);
 
     const int ki = row0 + wave * 32 + col;
-    const bool live = ki < g.N;
+    const bool live = ki < g.N && ki < end;
     const int kc = ki < g.N ? ki : g.N - 1;
     const int tk = tok[kc];
     float Kr[DA / 2], Vr[16];
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kNT, 3) void mfma_f32_fwd_kernel(Geo g, int nblk, u
     int64_t u;
     int blk;
     unit_of_block(nblk, u, blk);
-    fwd_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, out, lse);
+    fwd_body<DA>(g, sm, u, blk * kRowsWg, g.N, inv_r, q, k, v, fq, fk, out, lse);
 }
 template <int DA>
 __global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dq_kernel(Geo g, int nblk, ui
     int64_t u;
     int blk;
     unit_of_block(nblk, u, blk);
-    dq_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
+    dq_body<DA>(g, sm, u, blk * kRowsWg, g.N, inv_r, q, k, v, fq, fk, dout, lse, delta, dq, dfq_part);
 }
 template <int DA>
 __global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, uint32_t inv_r, const float *__restrict__ q,
@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kNT, 2) void mfma_f32_dkv_kernel(Geo g, int nblk, u
     int64_t u;
     int blk;
     unit_of_block(nblk, u, blk);
-    dkv_body<DA>(g, sm, u, blk * kRowsWg, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
+    dkv_body<DA>(g, sm, u, blk * kRowsWg, g.N, inv_r, q, k, v, fq, fk, dout, lse, delta, dk, dv, dfk_part);
 }
 
 }  // namespace
@@ -634,14 +634,27 @@ hipError_t split_fwd(const Geo &g, int waves, int nblk, const float *q, const fl
                        out, lse);
     return hipGetLastError();
 }
-template <int DA, int T>
-hipError_t split_bwd(const Geo &g, int waves, int nblk, const float *q, const float *k, const float *v, const float *fq,
-                     const float *fk, const float *dout, const float *lse, const float *delta, float *dq, float *dk, float *dv,
-                     float *pq, float *pk, hipStream_t st)
+template <int DA>
+int keys_blocks(const Geo &g) { return (g.N + 32 * split::Keys<DA>::QW - 1) / (32 * split::Keys<DA>::QW); }
+template <int DA>
+hipError_t split_fwd_keys(const Geo &g, int nblk, const float *q, const float *k, const float *v, const float *fq, const float *fk,
+                          float *out, float *lse, hipStream_t st)
 {
-    const size_t lds = split::lds_tiles<DA, T, kXS>() + (size_t)2 * g.M * sizeof(int);
-    auto kdkv = split::dkv_kernel<DA, T>;
-    auto kdq = split::dq_kernel<DA, T>;
+    const size_t lds = split::Keys<DA>::template lds<DA + 1>() + (size_t)2 * g.M * sizeof(int);
+    if (lds > (size_t)kMaxDynLds) return hipErrorInvalidValue;
+    auto kern = split::fwd_keys_kernel<DA>;
+    const hipError_t e = prepare_kernel((const void *)kern, nullptr);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(512), lds, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, out, lse);
+    return hipGetLastError();
+}
+template <class Dkv, class Dq>
+hipError_t launch_split_bwd(Dkv kdkv, Dq kdq, size_t lds, const Geo &g, int waves, int nblk, const float *q, const float *k, const float *v,
+                            const float *fq, const float *fk, const float *dout, const float *lse, const float *delta, float *dq,
+                            float *dk, float *dv, float *pq, float *pk, hipStream_t st)
+{
+    lds += (size_t)2 * g.M * sizeof(int);
+    if (lds > (size_t)kMaxDynLds) return hipErrorInvalidValue;
     hipError_t e = prepare_kernel((const void *)kdkv, nullptr);
     if (e == hipSuccess) e = prepare_kernel((const void *)kdq, nullptr);
     if (e != hipSuccess) return e;
@@ -651,6 +664,14 @@ hipError_t split_bwd(const Geo &g, int waves, int nblk, const float *q, const fl
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kdq, grid, block, lds, st, g, nblk, inv_r_of(g), q, k, v, fq, fk, dout, lse, delta, dq, pq);
     return hipGetLastError();
+}
+template <int DA, int T>
+hipError_t split_bwd(const Geo &g, int waves, int nblk, const float *q, const float *k, const float *v, const float *fq,
+                     const float *fk, const float *dout, const float *lse, const float *delta, float *dq, float *dk, float *dv,
+                     float *pq, float *pk, hipStream_t st)
+{
+    return launch_split_bwd(split::dkv_kernel<DA, T>, split::dq_kernel<DA, T>, split::lds_tiles<DA, T, kXS>(), g, waves, nblk, q, k, v, fq, fk,
+                            dout, lse, delta, dq, dk, dv, pq, pk, st);
 }
 
 template <int DA>
@@ -664,6 +685,8 @@ hipError_t fwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, c
         int cus = 0, nblk = 0;
         const hipError_t e = compute_units(&cus);
         if (e != hipSuccess) return e;
+        nblk = keys_blocks<DA>(g);
+        if (g.units * nblk <= cus) return split_fwd_keys<DA>(g, nblk, q, k, v, fq, fk, out, lse, st);
         const int waves = split_waves(g, cus, &nblk);
         return waves < 6 ? split_fwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, out, lse, st)
                          : split_fwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, out, lse, st);
@@ -686,6 +709,10 @@ hipError_t bwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, c
         int cus = 0, nblk = 0;
         const hipError_t e = compute_units(&cus);
         if (e != hipSuccess) return e;
+        nblk = keys_blocks<DA>(g);
+        if (g.units * nblk <= cus)
+            return launch_split_bwd(split::dkv_keys_kernel<DA>, split::dq_keys_kernel<DA>, split::Keys<DA>::template lds<kXS>(), g, 8, nblk, q, k, v,
+                                    fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);
         const int waves = split_waves(g, cus, &nblk);
         return waves < 6 ? split_bwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st)
                          : split_bwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);

@@ -179,3 +179,54 @@ def test_f32_logits_far_below_zero(oracle, d, r, M):
     # (a logit of 160 in base 2 is good to 2^-16: ten times the bound of logits of size one)
     for name, a, b in zip(("O", "LSE") + NAMES, (out, lse, *got), (O_ref, lse_ref, *ref)):
         assert gh.max_abs(gh.host(a), b) <= 3e-4 * max(1.0, float(np.abs(b).max())), name
+
+
+@pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
+    (5, 3, 8, 1, 1, 1, 1, 1),           # 16 columns, 64 tokens: half of the four streamed groups have none
+    (14, 4, 9, 8, 1, 1, 1, 1),          # 32 columns, 81: the third group a partial block, the second workgroup a partial wave
+    (30, 17, 11, 0, 1, 1, 2, 1),        # 48 columns, 121: just under a tile
+    (30, 8, 12, 5, 1, 2, 1, 2),         # 144: a second tile with one partial block
+    (32, 32, 13, 2, 1, 1, 1, 3),        # 64 columns: two groups, tiles of 64
+    (31, 33, 20, 0, 1, 1, 1, 1),
+    (16, 16, 32, 9, 1, 1, 1, 1),        # eight whole tiles
+    (30, 16, 16, 0, 4, 4, 2, 2),        # 64 units of 256: the last grid of one round
+    (30, 16, 16, 0, 1, 5, 13, 1),       # 65: four waves, no groups
+    (32, 30, 12, 3, 2, 4, 4, 3),        # 96 units of 144, 64 columns: two workgroups of 128 each, one round
+    (30, 8, 12, 3, 2, 4, 4, 3),         # 48 columns: three of 64, past one round
+])
+def test_streamed_side_shared_by_groups(oracle, d, r, M, s, B, ny, nx, heads):
+    """Small grids, whose waves share the streamed side, around the rule's edge, against the oracle; run to run the same."""
+    import gpu_helpers as gh
+    wl = wk.custom(f"f32-groups-m{M}d{d}", "f32", B, ny * M, nx * M, heads, d, r, M, s, 9500 + 64 * M + d, backward=True)
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x)
+    runs = []
+    for _ in range(2):
+        out, lse = gh.gpu_fwd(wl, t)
+        runs.append((out, lse, *gh.gpu_bwd(wl, t, out, lse)))
+    g = geometry(oracle, wl)
+    ref = oracle.fwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"]) + oracle.bwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    for name, a, a2, b in zip(("O", "LSE") + NAMES, *runs, ref):
+        assert bool((a == a2).all()), name
+        assert gh.max_abs(gh.host(a), b) <= gh.TOL["f32"], name
+
+
+@pytest.mark.parametrize("tensor", ["q", "v", "d_out"])
+@pytest.mark.parametrize("B,heads", [(1, 2), (16, 3)], ids=["groups", "four-waves"])
+def test_rows_done_again_stay_in_their_workgroup(tensor, B, heads):
+    """One value the parts cannot carry in the window's second block of rows: every row is written by its own workgroup."""
+    import torch
+    import gpu_helpers as gh
+    wl = wk.custom("f32-redo", "f32", B, 12, 24, heads, 30, 16, 12, 5, 9930, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    t[tensor][0, 11, 10, 3] = 2.0 ** 33
+    res = []
+    for flags in (0, 0, rb.RIB_FLAG_VECTOR_ONLY):
+        out, lse = gh.gpu_fwd(wl, t, flags=flags)
+        res.append((out, lse, *gh.gpu_bwd(wl, t, out, lse, flags=flags)))
+    for name, a, a2, b in zip(("O", "LSE") + NAMES, *res):
+        assert torch.equal(a, a2) or bool(torch.isnan(a).any()), name
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b)), name
+        fin = torch.isfinite(b)
+        # fp32 sums of up to 144 terms in another order: 144 * 2^-24 of the largest
+        assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
