@@ -204,11 +204,43 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
     }
 }
 
+// Sums of groups of waves that share stationary rows: accumulators through LDS, a row of 64 lanes a register.
+template <int DQK, bool DQ>
+constexpr int sums_of() { return (2 * Lay<DQK, 64>::RB + (DQ ? 0 : 2)) * 16 * 64; }    // floats a wave
+template <int N>
+__device__ __forceinline__ void give_sums(const f32x16 (&acc)[N], float *part)
+{
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[(b * 16 + i) * 64] = acc[b][i];
+}
+template <int N>
+__device__ __forceinline__ void take_sums(f32x16 (&acc)[N], const float *part)
+{
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][i] += part[(b * 16 + i) * 64];
+}
+template <int N, int M>
+__device__ __forceinline__ void give_sums(const f32x16 (&acc)[N][M], float *part)
+{
+#pragma unroll
+    for (int b = 0; b < N; ++b) give_sums(acc[b], part + b * M * 1024);
+}
+template <int N, int M>
+__device__ __forceinline__ void take_sums(f32x16 (&acc)[N][M], const float *part)
+{
+#pragma unroll
+    for (int b = 0; b < N; ++b) take_sums(acc[b], part + b * M * 1024);
+}
+
 // Common start of both kernels.
 #define RIB_BWD_SETUP                                                                                      \
     using L = Lay<DQK, T>;                                                                                 \
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];                                          \
-    const int nt = T == 64 ? NT : (int)blockDim.x, waves = nt >> 6;                                        \
+    const int nt = T >= 64 ? NT : (int)blockDim.x, waves = nt >> 6;                                        \
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);                                     \
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;                                    \
     int64_t u;                                                                                             \
@@ -230,7 +262,8 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
     ks.lse = qs.lse = lse + u * g.N;                                                                       \
     ks.delta = qs.delta = delta + u * g.N;                                                                 \
     const float sc2 = g.scale_c * kLog2e;                                                                  \
-    const int n0 = (blk * waves + wave) * 64;                                                              \
+    /* G groups share the stationary rows of waves / G waves */                                             \
+    const int own = waves / G, grp = G == 1 ? 0 : wave / own, n0 = (blk * own + (G == 1 ? wave : wave % own)) * 64;   \
     const int ntiles = (g.N + T - 1) / T;                                                                  \
     if (!ALN) __syncthreads();
 
@@ -242,8 +275,8 @@ __device__ __forceinline__ void store_block(const f32x16 &acc, int mb, int hf, c
 // of block s, so that the matrix pipe and the vector ALU always have independent work (left alone,
 // the compiler chains exp2 -> multiply -> pack element by element and waits for every LDS read
 // where it is issued).
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT>
-__global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT, int G>
+__global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dq_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                       const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                       const bf16_t *__restrict__ fk, const bf16_t *__restrict__ out,
                                                       const bf16_t *__restrict__ dout, const float *__restrict__ lse,
@@ -251,7 +284,7 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
                                                       float *__restrict__ dfq_part, bf16_t *__restrict__ ftab)
 {
     RIB_BWD_SETUP
-    constexpr int NB = T / 32, NS = 2 * NB;
+    constexpr int NB = T / 32 / G, NS = 2 * NB;             // key blocks of a tile: of this wave's group
     const float sp2 = g.scale_p * kLog2e;
 
     // one exposed memory latency: the wave's rows and the first two tiles are requested together
@@ -267,11 +300,11 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
         float dl = sr.e1;
         if (from_o) {
             dl = make_delta<DQK, TINY>(sr, g);
-            if (n0 + lane < g.N) delta[u * g.N + n0 + lane] = dl;       // for the dkv kernel, which runs second
+            if (n0 + lane < g.N && grp == 0) delta[u * g.N + n0 + lane] = dl;   // for the dkv kernel, which runs second
         }
         const float l2 = -sr.e0 * kLog2e;
         stat_stage<DQK, true, XS, XD, true, TINY>(sr, g, smem + wave * L::WAVE_STAT, sc2, sp2, l2, -dl, Qb, Gb,
-                                                      w == 0 ? (char *)(ftab + (int64_t)hd * g.N * g.r) : nullptr, n0, ALN);
+                                                      w == 0 && grp == 0 ? (char *)(ftab + (int64_t)hd * g.N * g.r) : nullptr, n0, ALN);
         if (XS) nl[0] = __shfl(l2, col), nl[1] = __shfl(l2, 32 + col);
         if (XD) nd[0] = -__shfl(dl, col), nd[1] = -__shfl(dl, 32 + col);
     }
@@ -290,7 +323,9 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[qb][mb][i] = 0.f;
 
-    const int tro = tr_lane_offset<L::XS>(lane), ako = col * L::XS + 8 * hf, avo = L::YR + col * L::YS + 8 * hf;
+    // (a group's first block of a tile: its rows are `g0` past the tile's)
+    const int g0 = G == 1 ? 0 : grp * 32 * NB;
+    const int tro = tr_lane_offset<L::XS>(lane) + g0 * L::XS, ako = (g0 + col) * L::XS + 8 * hf, avo = L::YR + (g0 + col) * L::YS + 8 * hf;
     bf16x8 Ak[L::KS], Av[L::VS], At[L::RB][2];
     f32x16 S[2], D[2];
     uint32_t P[2][8];
@@ -321,7 +356,7 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
             // scores of block s + 1
             S[ns] = mfma(Ak[0], Qb[qn][0], z);
             D[ns] = mfma(Av[0], Gb[qn][0], z);
-            if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + kb * 32, g.N, hf);
+            if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + g0 + kb * 32, g.N, hf);
             float p[16];
 #pragma unroll
             for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
@@ -389,6 +424,13 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
         }
     }
 
+    if (G > 1) {
+        float *const part = (float *)smem + lane;
+        if (grp > 0) give_sums(acc, part + (wave - own) * sums_of<DQK, true>());
+        __syncthreads();
+        if (grp > 0) return;
+        for (int j = 0; j < G - 1; ++j) take_sums(acc, part + (wave + j * own) * sums_of<DQK, true>());
+    }
     // Outputs straight from the accumulator layout: a lane holds, for one token, groups of four
     // consecutive columns (8-byte stores of the gradient, 16-byte stores of the partial).
 #pragma unroll
@@ -407,8 +449,8 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
 // scaling them while they are staged cost a tenth of the loop's vector instructions).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT>
-__global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT, int G>
+__global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dkv_kernel(Geo g, int nblk, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                        const bf16_t *__restrict__ v, const bf16_t *__restrict__ fq,
                                                        const bf16_t *__restrict__ fk, const bf16_t *__restrict__ dout,
                                                        const float *__restrict__ lse, const float *__restrict__ delta,
@@ -416,7 +458,7 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
                                                        float *__restrict__ dfk_part)
 {
     RIB_BWD_SETUP
-    constexpr int NB = T / 32;
+    constexpr int NB = T / 32 / G;          // query blocks of a tile: of this wave's group
 
     Regs<DQK, TINY> rg, rg1;
     bf16x8 Kb[2][L::KS], Vb[2][L::VS];
@@ -444,9 +486,10 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
 #pragma unroll
             for (int i = 0; i < 16; ++i) accK[kb][mb][i] = 0.f;
     }
+    const int g0 = G == 1 ? 0 : grp * 32 * NB;
 
-    const int trx = tr_lane_offset<L::XS>(lane), try_ = L::YR + tr_lane_offset<L::YS>(lane);
-    const int aqo = col * L::XS + 8 * hf, ago = L::YR + col * L::YS + 8 * hf;
+    const int trx = tr_lane_offset<L::XS>(lane) + g0 * L::XS, try_ = L::YR + tr_lane_offset<L::YS>(lane) + g0 * L::YS;
+    const int aqo = (g0 + col) * L::XS + 8 * hf, ago = L::YR + (g0 + col) * L::YS + 8 * hf;
     bf16x8 Aq[L::KS], Ag[L::VS];
     read_rows<L::KS>(Aq, smem + aqo);
     read_rows<L::VS>(Ag, smem + ago);
@@ -461,7 +504,7 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
                 f32x16 S = {0}, D = {0};
                 if (XS || XD) {
                     // accumulator row 8j + 4*hf + e is query qb*32 + that: four consecutive floats per j
-                    const float *ex = (const float *)(cur + L::EX) + qb * 32 + 4 * hf;
+                    const float *ex = (const float *)(cur + L::EX) + g0 + qb * 32 + 4 * hf;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         if (XS) {
@@ -495,7 +538,7 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
                         request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
                 }
                 RIB_FENCE();
-                if (!ALN && tile == ntiles - 1) mask_rows(S, tile * T + qb * 32, g.N, hf);
+                if (!ALN && tile == ntiles - 1) mask_rows(S, tile * T + g0 + qb * 32, g.N, hf);
                 uint32_t wp[8], wds[8];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -522,6 +565,19 @@ __global__ __launch_bounds__(T == 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
         c0 = c1, c1 = c2, c2 = r0;
     }
 
+    if (G > 1) {
+        float *const part = (float *)smem + lane;
+        if (grp > 0) {
+            give_sums(accK, part + (wave - own) * sums_of<DQK, false>());
+            give_sums(accV, part + (wave - own) * sums_of<DQK, false>() + 2 * L::RB * 1024);
+        }
+        __syncthreads();
+        if (grp > 0) return;
+        for (int j = 0; j < G - 1; ++j) {
+            take_sums(accK, part + (wave + j * own) * sums_of<DQK, false>());
+            take_sums(accV, part + (wave + j * own) * sums_of<DQK, false>() + 2 * L::RB * 1024);
+        }
+    }
     // (the streamed Q_aug rows carry scale * log2 e: undo the log2 e here)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
@@ -547,26 +603,31 @@ struct Args {
 };
 
 // Workgroups of `waves` waves, `nblk` of them per unit.
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT = 256>
+template <int DQK, int T, bool ALN, bool DQ, int G>
+size_t lds_of(const Geo &g, int waves)
+{
+    const size_t tiles = Lay<DQK, T>::bytes(waves), sums = (size_t)(G - 1) * (waves / G) * sums_of<DQK, DQ>() * sizeof(float);
+    return (tiles > sums ? tiles : sums) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+}
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT = 256, int G = 1>
 hipError_t launch_dkv(const Geo &g, int waves, int nblk, const Args &a)
 {
-    using L = Lay<DQK, T>;
-    const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+    // (the map stands behind the tiles: sums that reach past them come after its last use)
+    const size_t smem = lds_of<DQK, T, ALN, false, G>(g, waves);
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kern = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG, NT>;
+    auto kern = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG, NT, G>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v, a.ftab, a.fk, a.dout, a.lse,
                        a.delta, a.dk, a.dv, a.pk);
     return hipGetLastError();
 }
-template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG>
+template <int DQK, int T, bool XS, bool XD, bool ALN, int TINY, bool BIG, int NT = 256, int G = 1>
 hipError_t launch_dq(const Geo &g, int waves, int nblk, const Args &a)
 {
-    using L = Lay<DQK, T>;
-    const size_t smem = L::bytes(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+    const size_t smem = lds_of<DQK, T, ALN, true, G>(g, waves);
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kern = dq_kernel<DQK, T, XS, XD, ALN, TINY, BIG, 256>;
+    auto kern = dq_kernel<DQK, T, XS, XD, ALN, TINY, BIG, NT, G>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v, a.fq, a.fk, a.out, a.dout,
@@ -614,6 +675,29 @@ hipError_t launch_rows(const Geo &g, bool aln, int waves, int nblk, const Args &
                       : launch_pair<DQK, 32, XS, XD, false, TINY, false>(g, waves, nblk, a);
 }
 
+// The pair on a small grid, whose workgroups of four waves would leave CUs empty or with a wave a SIMD: eight waves, G groups
+// of which share the streamed side of 8 / G waves' stationary tokens; tiles of 32 G tokens, a block for each group.
+template <int DQK, bool XS, bool XD, bool ALN, int G>
+hipError_t launch_groups(const Geo &g, const Args &a)
+{
+    const int own = 8 / G, nblk = ((g.N + 63) / 64 + own - 1) / own;
+    const hipError_t e = launch_dq<DQK, 32 * G, XS, XD, ALN, kLong8, false, 512, G>(g, 8, nblk, a);
+    return e != hipSuccess ? e : launch_dkv<DQK, 32 * G, XS, XD, ALN, kLong8, false, 512, G>(g, 8, nblk, a);
+}
+
+// How many groups: where the grid is one round of the chip, four from 1024 tokens up (under that a wave's walk is short beside
+// the start and the sums at its end), two else.  Forward + backward, us, without / 2 / 4 groups: one 96 x 96 window, r = 34 557 / 480 /
+// 384, one 63 x 63 of 4 heads, d = r = 32 448 / 357 / 283, one 48 x 48 of 4 heads 133 / 123 / 117, 4 of 32 x 32, 2 images, 6
+// heads 80 / 80 / 76, one 32 x 32 of 2 heads 69 / 68 / 70, one 24 x 24 of 2 heads 58 / 51 / -, 4 of 25 x 25, 2 images, 4 heads 74 / 70 / 80.
+inline hipError_t groups_of(const Geo &g, int *groups)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    const int nb = (g.N + 63) / 64;
+    *groups = g.N >= 1024 && g.units * ((nb + 1) / 2) <= cus ? 4 : g.units * ((nb + 3) / 4) <= cus ? 2 : 1;
+    return e;
+}
+
 // Workgroup shape: up to 4 waves of 64 stationary tokens, an equal number in every workgroup of a
 // unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).  Images whose
 // offsets need more than 32 bits run the four-wave form with 64-bit offsets at every size.
@@ -637,8 +721,14 @@ hipError_t launch_width(const Geo &g, const Args &a)
         if (kind == kPairRib) return launch_rows<DQK, XS, XD, kPairRib>(g, aln, waves, nblk, a);
         if (kind == kNoRib) return launch_rows<DQK, XS, XD, kNoRib>(g, aln, waves, nblk, a);
     }
+    if (kind != kLong && kind != kLong8) return hipErrorInvalidValue;
+    int groups = 1;
+    const hipError_t e = groups_of(g, &groups);
+    if (e != hipSuccess) return e;
+    // (scalar token arithmetic needs whole tiles)
+    if (groups == 4) return aln && g.N % 128 == 0 ? launch_groups<DQK, XS, XD, true, 4>(g, a) : launch_groups<DQK, XS, XD, false, 4>(g, a);
+    if (groups == 2) return aln ? launch_groups<DQK, XS, XD, true, 2>(g, a) : launch_groups<DQK, XS, XD, false, 2>(g, a);
     if (kind == kLong8) return launch_rows<DQK, XS, XD, kLong8>(g, aln, waves, nblk, a);
-    if (kind != kLong) return hipErrorInvalidValue;
     return launch_rows<DQK, XS, XD, kLong>(g, aln, waves, nblk, a);
 }
 

@@ -315,7 +315,7 @@ __device__ __forceinline__ void request(Regs<DQK, TINY> &rg, const Geo &g, const
 #pragma unroll
     for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;                // the wave's first slot
-        if ((T == 64 && nt == 256) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
+        if ((T >= 64 && nt * M::SLOTS == T * M::LANES) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
             const int n0 = tile * T + slot / M::LANES;
             const uint32_t t = win.token<ALN, M::ROWS>(n0, l);
             rg.x[p] = get<TINY>(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
@@ -355,7 +355,7 @@ __device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, 
 #pragma unroll
     for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
-        if ((T == 64 && nt == 256) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
+        if ((T >= 64 && nt * M::SLOTS == T * M::LANES) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
             const int r0 = slot / M::LANES;                 // (uniform)
             Words<TINY> y = rg.y[p];
             if (!ALN && r0 + l >= left)

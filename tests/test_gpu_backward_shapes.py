@@ -72,3 +72,34 @@ def test_eight_wave_workgroups(oracle, d, r, M, s, B, ny, nx, heads):
     # dF sums windows, whose roundings add at random
     for name, a, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, ref):
         assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"] * (1.0 if name[1] != "F" else (B * ny * nx) ** 0.5), name
+
+
+@pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
+    (30, 18, 23, 4, 1, 1, 1, 1),        # 529 tokens, two groups: the third workgroup's rows end in its first wave
+    (30, 16, 24, 0, 1, 1, 2, 2),        # 576, whole tiles of 64
+    (32, 32, 31, 9, 1, 1, 1, 3),        # 961: the last tile a single token of the second group's block
+    (16, 14, 32, 0, 1, 1, 1, 2),        # 1024, four groups, whole tiles of 128
+    (30, 34, 33, 8, 1, 1, 1, 1),        # 1089: a last tile of 65
+    (30, 8, 40, 13, 1, 1, 1, 1),        # 1600 = 12.5 tiles, a window side that is a multiple of 8
+    (24, 24, 41, 0, 1, 1, 1, 2),        # 1681
+    (32, 16, 48, 5, 1, 1, 1, 2),        # 2304
+    (30, 34, 32, 0, 4, 2, 2, 2),        # 32 units: the last grid of one round in four groups
+    (30, 34, 32, 0, 3, 1, 11, 1),       # 33: two groups
+    (16, 16, 24, 7, 4, 3, 7, 1),        # 84 units: two groups
+    (16, 16, 24, 7, 1, 2, 43, 1),       # 86: none
+    (6, 4, 28, 0, 1, 1, 1, 1),          # rows of 8-byte pieces
+])
+def test_streamed_side_shared_by_groups(oracle, d, r, M, s, B, ny, nx, heads):
+    """Small grids, whose waves share the streamed side in two or four groups, around the rule's edges; run to run the same."""
+    import gpu_helpers as gh
+    wl = wk.custom(f"bwdg-d{d}r{r}m{M}", "bf16", B, ny * M, nx * M, heads, d, r, M, s, 8100 + 64 * M + d, backward=True)
+    x = wk.make_inputs(wl)
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t)
+    got = gh.gpu_bwd(wl, t, out, lse)
+    again = gh.gpu_bwd(wl, t, out, lse)
+    ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
+    for name, a, a2, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, again, ref):
+        assert bool((a == a2).all()), name
+        # dF sums windows, whose roundings add at random
+        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"] * (1.0 if name[1] != "F" else (B * ny * nx) ** 0.5), name
