@@ -104,26 +104,29 @@ __device__ __forceinline__ float sum16(const V &p)
     const float c = (p[8] + p[9]) + (p[10] + p[11]), d = (p[12] + p[13]) + (p[14] + p[15]);
     return (a + b) + (c + d);
 }
-constexpr int max_threads(int T, int QB) { return QB == 1 ? 512 : T == 64 ? 256 : 192; }
+constexpr int max_threads(int T, int QB, int G) { return QB == 1 || G > 1 ? 512 : T == 64 ? 256 : 192; }
 
 // One step is one 32x32 block s = (key block, query block): the score MFMAs of block s + 1 and the two
 // PV products of block s - 1 ride between the exponentials and packs of block s, in an order pinned
 // with scheduling fences (as in the streaming kernel).
-template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY>
-__global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort ? 3 : 2) void rows_fwd_kernel(
+//
+// G > 1: groups of waves share the streamed side of `waves / G` waves' queries (as in the backward pair): group `grp` takes its
+// block of every tile, and the sums, which have no stabiliser, are added through LDS.  The second walk is every wave's own.
+template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY, int G>
+__global__ __launch_bounds__(max_threads(T, QB, G), DQK <= 48 && TINY != kAnyShort && G == 1 ? 3 : 2) void rows_fwd_kernel(
     Geo g, int nblk, int force_max, const bf16_t *__restrict__ q, const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
     const bf16_t *__restrict__ fq, const bf16_t *__restrict__ fk, bf16_t *__restrict__ out, float *__restrict__ lse)
 {
     using L = Lay<DQK, T>;
-    constexpr int NB = T / 32, NS = QB * NB;
+    constexpr int NB = T / 32 / G, NS = QB * NB;            // key blocks of a tile: of this wave's group
     static_assert(NS % 2 == 0, "two score blocks alternate");
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    const int nt = T == 64 && QB == 2 ? 256 : (int)blockDim.x, waves = nt >> 6;
+    const int nt = G > 1 ? 512 : T == 64 && QB == 2 ? 256 : (int)blockDim.x, waves = nt >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
 
     // workgroups are dealt round-robin to the 8 XCDs: an XCD works on a contiguous range of (unit, block)
-    const int G = gridDim.x, per = G >> 3, rem = G & 7, xcd = blockIdx.x & 7;
+    const int wgs = gridDim.x, per = wgs >> 3, rem = wgs & 7, xcd = blockIdx.x & 7;
     const int logical = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
     const int u = logical / nblk, blk = logical - u * nblk;
     const int w = u / g.heads, hd = u - w * g.heads;
@@ -139,7 +142,8 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
     qs.xb = qs.yb = (const char *)(q + img * g.tstride + hd * g.d);
     qs.fb = (const char *)(fq + (int64_t)hd * g.N * g.r);
     ks.lse = ks.delta = qs.lse = qs.delta = nullptr;
-    const int n0 = (blk * waves + wave) * (QB * 32);
+    const int own = waves / G, grp = G == 1 ? 0 : wave / own, n0 = (blk * own + (G == 1 ? wave : wave % own)) * (QB * 32);
+    const int g0 = G == 1 ? 0 : grp * 32 * NB;              // the group's first row of a tile
     const int ntiles = (g.N + T - 1) / T;
     if (!ALN) __syncthreads();
 
@@ -169,7 +173,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
         lsum[qb] = 0.f;
         mrun[qb] = 0.f;         // what LSE adds to the denominator's log2
     }
-    const int tro = L::YR + tr_lane_offset<L::YS>(lane), ako = col * L::XS + 8 * hf;
+    const int tro = L::YR + tr_lane_offset<L::YS>(lane), ako = col * L::XS + 8 * hf, tro_g = tro + g0 * L::YS, ako_g = ako + g0 * L::XS;
     const f32x16 z = {0};
     // denominators: row 30 of O^T is register 14 of the upper lane half
     auto denominators = [&]() {
@@ -184,12 +188,12 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
         bf16x8 Ak[L::KS], At[2];
         f32x16 S[2];
         uint32_t P[2][8];
-        read_rows<L::KS>(Ak, smem + ako);
+        read_rows<L::KS>(Ak, smem + ako_g);
         S[0] = mfma(Ak[0], Qb[0][0], z);
 #pragma unroll
         for (int i = 1; i < L::KS; ++i) S[0] = mfma(Ak[i], Qb[0][i], S[0]);
         At[0] = At[1] = as_bf16x8(0u, 0u, 0u, 0u);      // (the first step's PV products add zero)
-        if (QB == 1) read_rows<L::KS>(Ak, smem + 32 * L::XS + ako);
+        if (QB == 1) read_rows<L::KS>(Ak, smem + 32 * L::XS + ako_g);
 #pragma unroll
         for (int i = 0; i < 8; ++i) P[1][i] = 0u;
         int c0 = 0, c1 = L::STAGE, c2 = 2 * L::STAGE;    // this tile's, the next tile's and the free stage
@@ -202,7 +206,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
                 float p[16];
                 RIB_FENCE();
                 S[ns] = mfma(Ak[0], Qb[qn][0], z);
-                if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + kb * 32, g.N, hf);
+                if (!ALN && tile == ntiles - 1) mask_rows(S[cs], tile * T + g0 + kb * 32, g.N, hf);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
                 P[cs][0] = pack_bf16(p[0], p[1]);
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
                 P[cs][5] = pack_bf16(p[10], p[11]);
                 if (turn) {     // K of the next key block (QB = 1: of the one after it)
                     const int kn = kb + (QB == 1 ? 2 : 1);
-                    read_rows<L::KS>(Ak, (kn < NB ? cur + kn * 32 * L::XS : nxt + (kn - NB) * 32 * L::XS) + ako);
+                    read_rows<L::KS>(Ak, (kn < NB ? cur + kn * 32 * L::XS : nxt + (kn - NB) * 32 * L::XS) + ako_g);
                 }
                 RIB_FENCE();
                 O[qn] = mfma(At[0], as_bf16x8(P[ns][0], P[ns][1], P[ns][2], P[ns][3]), O[qn]);
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
                 RIB_FENCE();
                 if (turn) {
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) At[i] = read_tr<L::YS>(cur + (kb * 32 + 16 * i) * L::YS, tro, 0);
+                    for (int i = 0; i < 2; ++i) At[i] = read_tr<L::YS>(cur + (kb * 32 + 16 * i) * L::YS, tro_g, 0);
                 }
                 if (s == NS - 1) request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 3 < ntiles ? tile + 3 : ntiles - 1, nt, wave);
             }
@@ -248,11 +252,35 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
         }
         O[QB - 1] = mfma(At[0], as_bf16x8(P[1][0], P[1][1], P[1][2], P[1][3]), O[QB - 1]);
         O[QB - 1] = mfma(At[1], as_bf16x8(P[1][4], P[1][5], P[1][6], P[1][7]), O[QB - 1]);
+        if constexpr (G > 1) {
+            // [wave][QB][17][64], behind the tiles and the map: a second walk needs the tiles' padding columns as they are
+            float *const part = (float *)((char *)smem + lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)8 * g.M)) + lane;
+            if (grp > 0) {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    float *const p = part + ((wave - own) * QB + qb) * 17 * 64;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) p[i * 64] = O[qb][i];
+                    if (SUM) p[16 * 64] = lsum[qb];
+                }
+            }
+            __syncthreads();
+            if (grp == 0) {
+                for (int j = 0; j < G - 1; ++j)
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) {
+                        const float *const p = part + ((wave + j * own) * QB + qb) * 17 * 64;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) O[qb][i] += p[i * 64];
+                        if (SUM) lsum[qb] += p[16 * 64];
+                    }
+            }
+        }
         denominators();
         bad = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
-            if (!((den[qb] >= 0x1p-60f) && (den[qb] <= 0x1p60f))) bad = true;
+            if (grp == 0 && !((den[qb] >= 0x1p-60f) && (den[qb] <= 0x1p60f))) bad = true;
     }
     // Cold path: the walk again with a running maximum, one key block at a time.  (Rows past the
     // window's end repeat its last row, so they ask for it only if that row does.)
@@ -272,7 +300,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
             request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
             __syncthreads();
 #pragma unroll 1
-            for (int kb = 0; kb < NB; ++kb) {
+            for (int kb = 0; kb < T / 32; ++kb) {
                 const int key0 = tile * T + kb * 32;
                 if (key0 >= g.N) break;
                 bf16x8 Ak[L::KS], At[2];
@@ -310,6 +338,7 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
         denominators();
     }
 
+    if (G > 1 && grp > 0) return;
     // Normalise and store straight from the accumulator layout: a lane holds, for one token, four groups of
     // four consecutive channels.
 #pragma unroll
@@ -344,12 +373,13 @@ __global__ __launch_bounds__(max_threads(T, QB), DQK <= 48 && TINY != kAnyShort 
     }
 }
 
-template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY>
+template <int DQK, int T, int QB, bool SUM, bool ALN, int TINY, int G = 1>
 hipError_t launch_one(const Geo &g, int waves, int nblk, const Args &a)
 {
-    const size_t smem = lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int));
+    const size_t smem = lds_bytes<DQK, T, QB>(waves) + (ALN ? 0 : (size_t)2 * g.M * sizeof(int)) +
+                        (size_t)(G - 1) * (waves / G) * QB * 17 * 64 * sizeof(float);
     if (smem > (size_t)kMaxDynLds) return hipErrorInvalidValue;
-    auto kern = rows_fwd_kernel<DQK, T, QB, SUM, ALN, TINY>;
+    auto kern = rows_fwd_kernel<DQK, T, QB, SUM, ALN, TINY, G>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.force_max, a.q, a.k, a.v,
@@ -376,6 +406,19 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
 {
     const Short kind = short_rows(g);
     const bool aln = g.M % 8 == 0;
+    if (g.N >= 1024 && (kind == kLong || kind == kLong8)) {
+        int cus = 0;
+        const hipError_t e = compute_units(&cus);
+        if (e != hipSuccess) return e;
+        // Four groups of two waves where that grid is one round of the chip and a wave's walk is long beside the sums at its end
+        // (us, 32 queries a wave / groups: one 96 x 96 window, d = r = 32 136 / 81, of 2 heads, r = 34 115 / 82, one 64 x 64 of 6 heads 50 / 35, one
+        // 48 x 48 of 4 heads 29.7 / 22.8, one 32 x 32 of 2 heads 15.9 / 14.3; one 24 x 24 of 2 heads 12.1 / 13.4, 128 units of 144 tokens 10.4 / 11.2).
+        // (Scalar token arithmetic needs whole tiles.)
+        const int nblk = (g.N + 127) / 128;
+        if (g.units * nblk <= cus)
+            return aln && g.N % 128 == 0 ? launch_one<DQK, 128, 2, SUM, true, kLong8, 4>(g, 8, nblk, a)
+                                         : launch_one<DQK, 128, 2, SUM, false, kLong8, 4>(g, 8, nblk, a);
+    }
     if (qb == 1 && (kind == kLong || kind == kLong8)) {
         const int nb = (g.N + 31) / 32, nblk = (nb + 7) / 8;
         int waves = (nb + nblk - 1) / nblk;

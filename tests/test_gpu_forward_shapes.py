@@ -59,3 +59,36 @@ def test_forward_shapes(oracle, d, r, M, s, ny, nx, many):
     (a, la), (b, lb) = (gh.gpu_fwd(wl, hot, flags=f, packed=False) for f in (0, rb.RIB_FLAG_FORCE_ROW_MAX))
     assert bool(torch.isfinite(a).all()) and bool(torch.isfinite(la).all())
     assert gh.max_abs(gh.host(a), gh.host(b)) <= gh.TOL["bf16"] and gh.max_abs(gh.host(la), gh.host(lb)) <= gh.TOL["bf16"]
+
+
+@pytest.mark.parametrize("flags", [0, rb.RIB_FLAG_FORCE_ROW_MAX], ids=["optimistic", "row-max"])
+@pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
+    (16, 14, 32, 3, 1, 1, 2, 2),        # whole tiles of 128; 32 columns
+    (30, 18, 33, 0, 1, 1, 1, 1),        # 1089: a last tile of 65, blocks without keys in two groups
+    (32, 16, 40, 9, 1, 1, 1, 1),        # 1600 = 12.5 tiles, fp32 sums
+    (30, 34, 45, 11, 1, 1, 1, 1),       # 2025, 64 columns
+    (30, 16, 32, 0, 4, 4, 2, 1),        # 32 units: the last grid of one round
+    (30, 16, 32, 0, 3, 1, 11, 1),       # 33: no groups
+    (6, 4, 36, 35, 1, 1, 1, 1),         # rows of 8-byte pieces
+])
+def test_streamed_side_shared_by_groups(oracle, d, r, M, s, B, ny, nx, heads, flags):
+    """Small grids, whose waves share the keys in four groups; then with one row whose logits need the second walk."""
+    import gpu_helpers as gh
+    wl = wk.custom(f"fwdg-d{d}r{r}m{M}", "bf16", B, ny * M, nx * M, heads, d, r, M, s, 8600 + 64 * M + d)
+    x = wk.make_inputs(wl)
+    g = geometry(oracle, wl)
+    O_ref, lse_ref = oracle.fwd(g, x["q"], x["k"], x["v"], x["f_q"], x["f_k"])
+    t = gh.device_inputs(wl, x)
+    out, lse = gh.gpu_fwd(wl, t, flags=flags)
+    out2, _ = gh.gpu_fwd(wl, t, flags=flags)
+    assert bool((out == out2).all())
+    assert gh.max_abs(gh.host(out), O_ref) <= gh.TOL["bf16"] and gh.max_abs(gh.host(lse), lse_ref) <= gh.TOL["bf16"]
+    if flags:
+        return
+    # q of one token 256 times as large (exact in bf16): its logits overflow exp2, and its workgroup walks again
+    import torch
+    t["q"][0, M // 2, M // 2] *= 256.0
+    got = gh.gpu_fwd(wl, t)[0]
+    ref = gh.gpu_fwd(wl, t, flags=rb.RIB_FLAG_FORCE_ROW_MAX)[0]
+    # both walks multiply the same operands; P and the sums differ by their rounding to 2^-8
+    assert bool(torch.isfinite(got).all()) and float((got.float() - ref.float()).abs().max()) <= gh.TOL["bf16"]
