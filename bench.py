@@ -31,10 +31,10 @@ PEAK_HBM_GBS = 8000.0
 # scaled by a plain copy of known size).  Where such a run of this very workload is committed under profiles/,
 # `traffic` carries its figure and `traffic_from_profile` says which file it comes from; otherwise `traffic` is null.
 PROFILED_TRAFFIC = {
-    "c5": {"forward": {"bytes": 250.3e6, "source": "profiles/c5_step_hbm_traffic.md"},
-           "backward": {"bytes": 1006.2e6, "source": "profiles/c5_step_hbm_traffic.md"},
-           "kernels": {"mfma_fwd_stream_kernel": 250.3e6, "dq_kernel": 444.2e6,
-                       "dkv_kernel": 447.9e6, "reduce_df_kernel": 114.1e6}},
+    "c5": {"forward": {"bytes": 250.0e6, "source": "profiles/c5_step_hbm_traffic.md"},
+           "backward": {"bytes": 1008.4e6, "source": "profiles/c5_step_hbm_traffic.md"},
+           "kernels": {"mfma_fwd_stream_kernel": 250.0e6, "dq_kernel": 441.4e6,
+                       "dkv_kernel": 452.9e6, "reduce_df_kernel": 114.1e6}},
 }
 
 
@@ -138,6 +138,8 @@ def kernel_flop(name, wl):
     per = 2.0 * wl.N * wl.N * wl.n_units
     if "fwd" in name:
         return wl.fwd_flop, "S, PV"
+    if "unit" in name:                  # the whole backward of a unit in one workgroup: nothing is made twice
+        return per * (5 * wl.d + 3 * wl.r), "S, dP, dV, dK_aug, dQ_aug"
     if "dkv" in name:
         return per * (4 * wl.d + 2 * wl.r), "S, dP, dV, dK_aug"
     if "dq" in name:

@@ -134,7 +134,8 @@ size_t rib_window_attn_bwd_workspace_bytes(const rib_params *p);
 /* Backward.  `out` and `lse` are the results of rib_window_attn_fwd on the same
  * inputs.  dq, dk, dv [B][H][W][C] (dense, dtype of q) and df_q, df_k
  * [heads][N][r] fp32 are OVERWRITTEN (df_* are sums over all images and
- * windows, reduced in a fixed order: results are run-to-run identical).
+ * windows, reduced in a fixed order: results are run-to-run identical; until the
+ * enqueued work is done df_q may hold intermediate values).
  * df_q / df_k may be NULL iff r == 0.  `workspace` is scratch for the duration
  * of the enqueued work; its contents afterwards are unspecified. */
 rib_status rib_window_attn_bwd(const rib_params *p,

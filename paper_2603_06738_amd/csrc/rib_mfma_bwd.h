@@ -23,16 +23,16 @@
 //   is one query).
 //
 //   What bounds them: neither pipe by itself.  By counters (32 x 32 windows, d = 30, r = 16) the matrix pipe
-//   (11 MFMAs a 32x32 block in dkv, 9 in dq) is busy 34 / 35 % of the SIMD-cycles and the vector ALU (95 / 76
-//   instructions a block, of which exp2, multiplies and packs are 48 / 40) 43 / 44 %; for 44 / 38 % of its time a
+//   (11 MFMAs a 32x32 block in dkv, 9 in dq) is busy 36 / 36 % of the SIMD-cycles and the vector ALU (89 / 75
+//   instructions a block, of which exp2, multiplies and packs are 48 / 40) 42 / 45 %; for 44 / 39 % of its time a
 //   wave waits on its previous instruction, and only two waves of 256 registers share a SIMD.  What both pipes
-//   need less of is staging.  So the streamed
-//   tiles are kept as plain rows in LDS, written as 8-byte pieces, and the operands of the
+//   need less of is staging (a build without it is 14 to 20 % faster).  So the streamed
+//   tiles are kept as plain rows in LDS, written in 16-byte pieces, and the operands of the
 //   products that contract over tokens are read TRANSPOSED from the same rows
 //   (ds_read_b64_tr_b16): no transposed image, no byte permutes to build one.  One pair of kernels
-//   serves every window of 64 or more tokens: a last partial tile repeats the window's last token
+//   serves every window of more tokens than one workgroup holds (rib_mfma_unit.h), and of 64 and more where those do not: a last partial tile repeats the window's last token
 //   and masks its rows of S (the separate kernels for windows that were not whole 256-token blocks,
-//   with their predicated staging, took 656 us where these take 265 us: 24 x 24 windows, 8 x 96 x 96
+//   with their predicated staging, took 656 us where these take about 280 us: 24 x 24 windows, 8 x 96 x 96
 //   tokens, 6 heads, d = 30, r = 18).  Registers: with 64 columns the four-wave dkv spills 10 to 14 of them, dq 33 to 99 where
 //   the window side is no multiple of 8 (21 to 49 with 48 columns).
 //

@@ -11,12 +11,12 @@
 // dot products of the packed pairs cost half of that, but sum rounded values).  Probabilities are
 // rounded to bf16 (v_cvt_pk_bf16_f32, which issues like the byte-permute a truncation takes).
 //
-// What bounds it: the vector issue beside the MFMAs (32 x 32 windows: 52 vector instructions a 32x32 block, of
-// which exp2 and packs are 24, the vector ALU busy half of the cycles, the matrix pipe 30 %, and 42 % of a wave's
+// What bounds it: the vector issue beside the MFMAs (32 x 32 windows: 51 vector instructions a 32x32 block, of
+// which exp2 and packs are 24, the vector ALU busy half of the cycles, the matrix pipe 32 %, and 41 % of a wave's
 // time a wait on its previous instruction), under 600 tokens the start and end of a workgroup.  Three waves a SIMD
 // (168 registers) where the width allows, so that one workgroup's ends lie under another's loop; that
 // and whole-row staging took (us, with the kernels that served these windows before / with this one):
-// 144 tokens, 2304 units 70.6 / 35.1; 576 tokens, 768 units 125.6 / 66.0; 256 tokens, 3456 units
+// 144 tokens, 2304 units 70.6 / 32.7; 576 tokens, 768 units 125.6 / 66.0; 256 tokens, 3456 units
 // 74.9 / 70.7, 96 units 11.6 / 8.2; 2304 tokens, 192 units, d = r = 32 230 / 222; 2025 tokens, 96 units 122 / 80.
 //
 // The stabiliser is optimistic: no running maximum, a range check of every denominator afterwards,
