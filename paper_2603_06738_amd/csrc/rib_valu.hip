@@ -550,14 +550,16 @@ hipError_t launch_reduce_df(const Geo &g, const float *part_q, const float *part
     if (g.r == 0) return hipSuccess;
     const int64_t per_head = (int64_t)g.N * g.r;
     const int nwin = (int)(g.units / g.heads);
-    // 16 bytes a lane where the rows of every window (and the caller's dF) keep that alignment
+    // 16 bytes a lane where the rows of every window keep that alignment, and the caller's dF does.  The slices, and with them the
+    // order of the sums, come from the sizes alone: the same call gives the same bits wherever dF lies.
     const uintptr_t at = (uintptr_t)dfq | (uintptr_t)dfk;
-    const int vec = per_head % 4 == 0 && at % 16 == 0 ? 4 : per_head % 2 == 0 && at % 8 == 0 ? 2 : 1;
+    const int whole = per_head % 4 == 0 ? 4 : per_head % 2 == 0 ? 2 : 1;
+    const int vec = whole == 4 && at % 16 == 0 ? 4 : whole >= 2 && at % 8 == 0 ? 2 : 1;
     // Slices until the chip has two waves a SIMD: one slice / this rule / up to 16 until it has eight, us: 576 windows of 256
     // tokens, 6 heads, r = 18 50 / 25 / 25, 144 of 1024, r = 16 21 / 21 / 23, 128 of 576, r = 18 12.6 / 11.0 / 11.7 (the
     // partials of the first pass at 5 TB/s).  A slice of under eight windows has too few loads in flight.
     int slices = 1;
-    while (slices < 16 && per_head * g.heads * 2 / vec * slices < 128 * 1024 && nwin / (2 * slices) >= 8) slices *= 2;
+    while (slices < 16 && per_head * g.heads * 2 / whole * slices < 128 * 1024 && nwin / (2 * slices) >= 8) slices *= 2;
     const int64_t lanes = kThreads / slices * vec;
     const int blocks = (int)((per_head + lanes - 1) / lanes);
     const dim3 grid((unsigned)((int64_t)blocks * g.heads), 2);

@@ -34,3 +34,36 @@ def test_rib_gradient_sums(oracle, dtype, B, ny, nx, heads, d, r, M):
     for name, a, a2, b in zip(("dF_q", "dF_k"), got[3:], again[3:], ref[3:]):
         assert bool((a == a2).all()), name
         assert gh.max_abs(gh.host(a), b) <= tol, name
+
+
+@pytest.mark.parametrize("dtype,B,ny,nx,heads,d,r,M", [
+    ("bf16", 4, 4, 4, 4, 30, 16, 16),       # one kernel a unit; 64 windows: slices for whole rows and for 4 bytes a lane differ
+    ("bf16", 8, 2, 2, 4, 30, 16, 32),       # the pair, 128 units: past one round, rows and the f_q table in 16-byte pieces
+    ("bf16", 1, 2, 4, 1, 30, 34, 32),       # the pair in groups, a second RIB piece
+    ("bf16", 2, 6, 7, 2, 6, 6, 25),         # rows of 8-byte pieces
+    ("f32", 4, 3, 3, 5, 7, 3, 9),           # 243 values a head: 4 bytes a lane wherever dF lies
+    ("f32", 4, 4, 4, 3, 30, 16, 16),
+], ids=["unit", "pair", "groups", "short-rows", "odd", "f32"])
+def test_rib_gradients_do_not_depend_on_where_they_lie(dtype, B, ny, nx, heads, d, r, M):
+    """dF_q and dF_k at 16-, 8- and 4-byte aligned addresses of a flat buffer: the same bits, and nothing beside them written."""
+    import torch
+    import gpu_helpers as gh
+    from paper_2603_06738_amd import binding as rb
+    wl = wk.custom(f"df-at-m{M}r{r}", dtype, B, ny * M, nx * M, heads, d, r, M, 1, 3700 + M, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    p = rb.params_of(wl)
+    out, lse = gh.gpu_fwd(wl, t)
+    want = gh.gpu_bwd(wl, t, out, lse)
+    dq, dk, dv = (torch.empty_like(out) for _ in range(3))
+    n = wl.heads * wl.N * wl.r
+    for at_q, at_k in ((4, 4), (1, 1), (2, 2), (4, 3), (2, 4)):     # in values; the allocation itself is 16-byte aligned
+        flat = torch.full((2, (n // 8 + 2) * 8), 7.0, dtype=torch.float32, device=gh.DEV)
+        dfq, dfk = flat[0, at_q:at_q + n], flat[1, at_k:at_k + n]
+        rb.rib_window_attn_bwd(p, t["q"], t["k"], t["v"], t["f_q"], t["f_k"], out, t["d_out"], lse, dq, dk, dv, dfq, dfk,
+                               rb.alloc_workspace(p, gh.DEV))
+        torch.cuda.synchronize()
+        for name, a, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), (dq, dk, dv, dfq, dfk), want):
+            assert torch.equal(a.reshape(-1), b.reshape(-1)), (name, at_q, at_k)
+        rest = flat.clone()
+        rest[0, at_q:at_q + n], rest[1, at_k:at_k + n] = 7.0, 7.0
+        assert bool((rest == 7.0).all()), (at_q, at_k)
