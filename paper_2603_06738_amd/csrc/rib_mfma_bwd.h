@@ -429,6 +429,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
         if (grp > 0) give_sums(acc, part + (wave - own) * sums_of<DQK, true>());
         __syncthreads();
         if (grp > 0) return;
+#pragma unroll 1            // (several groups' sums in flight are spills: dkv 150 to 160 registers in four groups)
         for (int j = 0; j < G - 1; ++j) take_sums(acc, part + (wave + j * own) * sums_of<DQK, true>());
     }
     // Outputs straight from the accumulator layout: a lane holds, for one token, groups of four
@@ -573,6 +574,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
         }
         __syncthreads();
         if (grp > 0) return;
+#pragma unroll 1
         for (int j = 0; j < G - 1; ++j) {
             take_sums(accK, part + (wave + j * own) * sums_of<DQK, false>());
             take_sums(accV, part + (wave + j * own) * sums_of<DQK, false>() + 2 * L::RB * 1024);
@@ -685,10 +687,10 @@ hipError_t launch_groups(const Geo &g, const Args &a)
     return e != hipSuccess ? e : launch_dkv<DQK, 32 * G, XS, XD, ALN, kLong8, false, 512, G>(g, 8, nblk, a);
 }
 
-// How many groups: where the grid is one round of the chip, four from 1024 tokens up (under that a wave's walk is short beside
-// the start and the sums at its end), two else.  Forward + backward, us, without / 2 / 4 groups: one 96 x 96 window, r = 34 557 / 480 /
-// 384, one 63 x 63 of 4 heads, d = r = 32 448 / 357 / 283, one 48 x 48 of 4 heads 133 / 123 / 117, 4 of 32 x 32, 2 images, 6
-// heads 80 / 80 / 76, one 32 x 32 of 2 heads 69 / 68 / 70, one 24 x 24 of 2 heads 58 / 51 / -, 4 of 25 x 25, 2 images, 4 heads 74 / 70 / 80.
+// How many groups: where the grid is one round of the chip, four from 1024 tokens up, two else.  Backward, us, without / 2 / 4
+// groups: one 96 x 96 window, d = 30, r = 16 367 / 318 / 205, one 63 x 63 of 6 heads, d = r = 32 386 / 308 / 203, one 48 x 48 102 / 92 / 66,
+// one 32 x 32 53 / 52 / 41, 8 of 4 heads 57 / 55 / 46, one 24 x 24 45 / 37 / 40; but one 40 x 40, d = r = 32 (half a tile of 128 left over) 102 / 86 / 90,
+// one 25 x 25 53 / 51 / 40: the line at 1024 was drawn while the sums of four groups spilled, and is not the best one without.
 inline hipError_t groups_of(const Geo &g, int *groups)
 {
     int cus = 0;
