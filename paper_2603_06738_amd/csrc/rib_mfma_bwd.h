@@ -638,18 +638,25 @@ hipError_t launch_dq(const Geo &g, int waves, int nblk, const Args &a)
 }
 
 // Whether the dkv kernel runs in workgroups of eight waves.  A lane then holds one 8-byte piece of each row instead of 16
-// bytes, and it is the registers that count: with 64 columns the four-wave form spills 10 to 14 of them (us, four waves / eight,
+// bytes, and it is the registers that count: with 64 columns the four-wave form spills 4 to 14 of them (us, four waves / eight,
 // traced: 96 x 96 windows, r = 34 3089 / 2803, 64 x 64 2527 / 2282, 48 x 48, d = r = 32 537 / 512), with 48 and 32 none (64 x 64
-// windows, r = 16 1067 / 1089, 32 x 32 410 / 435), and no second workgroup runs beside one's start and end.  So: 64 columns;
-// windows that fill the larger workgroups to nine tenths (41 x 41, 27 blocks in 32: forward + backward 1638 / 1661); and grids of
-// two rounds and more that do not take more of them in the larger workgroups (fewer: a CU with four waves is faster
-// than half the CUs with eight).
+// windows, r = 16 1067 / 1089, 32 x 32 410 / 435), and no second workgroup runs beside one's start and end.  So: 64 columns,
+// grids of two rounds and more (fewer: a CU with four waves is faster than half the CUs with eight), and no more rounds
+// than four waves take, which are counted one workgroup a CU: a last round of those that fills only one of a CU's two
+// places costs about three quarters of one that fills both.  That is less than a round of eight waves, unless there are enough others
+// to make up for it: four with the 7 % of aligned sides (five where the larger workgroups are not filled to nine tenths), eight with the 3 % of
+// other sides.  (Backward, 6 heads, us, four / eight: 40 x 40, r = 34, 192 units, rounds of 6 and 3 451 / 442, 168 units, 5 and 3 387 / 406, 144 units, 4 and
+// 3 327 / 376, 240 units, 7 and 4 552 / 566; 32 x 32, 288 units, 5 and 3 284 / 294; d = r = 32, 48 x 48, 192 units, 7 and 4 819 / 791, 56 x 56, 168 units, 9
+// and 5 1356 / 1294; 45 x 45, r = 34, 216 units, 7 and 4 1049 / 1071.)
 inline hipError_t eight_waves(const Geo &g, bool *yes)
 {
     int cus = 0;
     const hipError_t e = compute_units(&cus);
+    *yes = false;
+    if (e != hipSuccess) return e;
     const int64_t nb = (g.N + 63) / 64, n8 = g.units * ((nb + 7) / 8), n4 = g.units * ((nb + 3) / 4);
-    *yes = e == hipSuccess && (nb + 7) / 8 * 72 <= nb * 80 && n8 >= 2 * cus && (n8 + cus - 1) / cus <= (n4 + 2 * cus - 1) / (2 * cus);
+    const int64_t r8 = (n8 + cus - 1) / cus, r4 = (n4 + cus - 1) / cus, enough = g.M % 8 != 0 ? 8 : (nb + 7) / 8 * 72 <= nb * 10 ? 4 : 5;
+    *yes = n8 >= 2 * cus && 2 * r8 <= r4 + (r8 >= enough ? 1 : 0);
     return e;
 }
 

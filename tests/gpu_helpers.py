@@ -67,3 +67,13 @@ def gather_unit(oracle, g, arr, unit):
     """[B,H,W,C] array -> the [N,d] block of one (window, head) unit, window-local order."""
     b, y, x, hd = oracle.unit_token_index(g, unit)
     return arr[b, y, x, hd * g.d:(hd + 1) * g.d]
+
+
+def kernels_of(call):
+    """Names of the kernels that `call` launches (empty where the profiler sees none)."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages() if e.device_time_total > 0]

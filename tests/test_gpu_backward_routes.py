@@ -1,0 +1,37 @@
+"""Which form of the backward pair a call runs on, by the names of the kernels it launches, where the rule between them was
+not what its comment says.  (Grids for a chip of 256 compute units.)"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2603_06738_amd import workloads as wk
+
+
+def dkv_threads(d, r, M, B, ny, nx, heads):
+    """Threads of the dkv kernel's workgroups and whether it stages 16-byte pieces (None: no profiler, other chip)."""
+    import re
+    import torch
+    import gpu_helpers as gh
+    wl = wk.custom("route", "bf16", B, ny * M, nx * M, heads, d, r, M, 3, 1, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    out, lse = gh.gpu_fwd(wl, t)
+    names = gh.kernels_of(lambda: gh.gpu_bwd(wl, t, out, lse))
+    if not names or torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        return None
+    found = [re.search(r"dkv_kernel<\d+, (\d+), .*?, (\d), (?:true|false), (\d+), (\d+)>", n) for n in names]
+    (m,) = [f for f in found if f]
+    return m.group(1), int(m.group(3)) if m.group(1) == "64" else 192, m.group(2) == "0"
+
+
+@pytest.mark.parametrize("d,r,M,B,ny,nx,heads,want", [
+    (30, 34, 40, 7, 2, 2, 6, 256),      # 25 blocks in 32, 3 rounds of eight waves against 5 of four
+    (30, 34, 40, 8, 2, 2, 6, 512),      # 3 against 6
+    (30, 34, 32, 12, 2, 2, 6, 256),     # 16 in 16: 3 against 5
+    (30, 34, 32, 16, 2, 2, 6, 512),     # 3 against 6
+    (32, 32, 48, 8, 2, 2, 6, 512),      # 36 in 40: 4 against 7
+    (30, 34, 45, 9, 2, 2, 6, 256),      # an odd side: 4 against 7
+])
+def test_eight_wave_dkv_where_it_takes_no_more_rounds(d, r, M, B, ny, nx, heads, want):
+    got = dkv_threads(d, r, M, B, ny, nx, heads)
+    if got is not None:
+        assert got[:2] == ("64", want), got
