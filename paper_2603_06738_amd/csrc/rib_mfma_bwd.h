@@ -671,7 +671,12 @@ hipError_t launch_pair(const Geo &g, int waves, int nblk, const Args &a)
         if ((e = eight_waves(g, &eight)) != hipSuccess) return e;
         if (eight) return launch_dkv<DQK, 64, XS, XD, ALN, kLong8, false, 512>(g, 8, ((g.N + 63) / 64 + 7) / 8, a);
     }
-    return launch_dkv<DQK, T, XS, XD, ALN, TINY, BIG>(g, waves, nblk, a);
+    // With 64 columns and an aligned side dkv has fewer spills in 8-byte pieces (four waves 4 to 8 registers, with 16 bytes 8 to 12; three
+    // waves with both extras in the C operand 13, 40) and is faster there (backward, 6 heads, d = r = 32, us, 8-byte / 16-byte: 40 x 40, 288 units 661 /
+    // 675, 24 x 24, 672 units 327 / 353); three waves else spill alike and are slower (24 x 24, r = 34, 936 units 514 / 456), odd sides too (41 x 41, 264 units
+    // 1013 / 993).
+    constexpr bool less = DQK == 64 && ALN && TINY == kLong && (T == 64 || (XS && XD));
+    return launch_dkv<DQK, T, XS, XD, ALN, less ? (int)kLong8 : TINY, BIG>(g, waves, nblk, a);
 }
 
 template <int DQK, bool XS, bool XD, int TINY>

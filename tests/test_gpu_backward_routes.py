@@ -35,3 +35,16 @@ def test_eight_wave_dkv_where_it_takes_no_more_rounds(d, r, M, B, ny, nx, heads,
     got = dkv_threads(d, r, M, B, ny, nx, heads)
     if got is not None:
         assert got[:2] == ("64", want), got
+
+
+@pytest.mark.parametrize("d,r,M,B,ny,nx,heads,tile,wide", [
+    (32, 32, 24, 16, 2, 2, 6, "32", False),     # aligned, both extras in the C operand, three waves
+    (30, 34, 24, 16, 2, 2, 6, "32", True),      # LSE alone
+    (32, 32, 40, 6, 2, 2, 6, "64", False),      # aligned, four waves
+    (32, 32, 41, 7, 2, 2, 6, "64", True),       # an odd side
+])
+def test_dkv_pieces_of_64_columns(d, r, M, B, ny, nx, heads, tile, wide):
+    """8-byte pieces where those of 16 bytes spill more."""
+    got = dkv_threads(d, r, M, B, ny, nx, heads)
+    if got is not None:
+        assert (got[0], got[2]) == (tile, wide), got
