@@ -636,6 +636,11 @@ hipError_t split_fwd(const Geo &g, int waves, int nblk, const float *q, const fl
 }
 template <int DA>
 int keys_blocks(const Geo &g) { return (g.N + 32 * split::Keys<DA>::QW - 1) / (32 * split::Keys<DA>::QW); }
+// Grids of one round (the figures stand at split::Keys) of windows that give more than half of the groups a block: under that the
+// idle ones only take part in the sums (64 tokens, d = 30, r = 16, 24 units, us, without groups / with: forward 9.0 / 9.8, backward 31.4 / 34.0; 81
+// tokens 10.5 / 10.3 and 36.1 / 35.5).
+template <int DA>
+bool keys_fit(const Geo &g, int cus) { return g.units * keys_blocks<DA>(g) <= cus && 2 * ((g.N + 31) / 32) > split::Keys<DA>::G; }
 template <int DA>
 hipError_t split_fwd_keys(const Geo &g, int nblk, const float *q, const float *k, const float *v, const float *fq, const float *fk,
                           float *out, float *lse, hipStream_t st)
@@ -685,8 +690,7 @@ hipError_t fwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, c
         int cus = 0, nblk = 0;
         const hipError_t e = compute_units(&cus);
         if (e != hipSuccess) return e;
-        nblk = keys_blocks<DA>(g);
-        if (g.units * nblk <= cus) return split_fwd_keys<DA>(g, nblk, q, k, v, fq, fk, out, lse, st);
+        if (keys_fit<DA>(g, cus)) return split_fwd_keys<DA>(g, keys_blocks<DA>(g), q, k, v, fq, fk, out, lse, st);
         const int waves = split_waves(g, cus, &nblk);
         return waves < 6 ? split_fwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, out, lse, st)
                          : split_fwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, out, lse, st);
@@ -709,10 +713,9 @@ hipError_t bwd_t(const Geo &g, const void *q_, const void *k_, const void *v_, c
         int cus = 0, nblk = 0;
         const hipError_t e = compute_units(&cus);
         if (e != hipSuccess) return e;
-        nblk = keys_blocks<DA>(g);
-        if (g.units * nblk <= cus)
-            return launch_split_bwd(split::dkv_keys_kernel<DA>, split::dq_keys_kernel<DA>, split::Keys<DA>::template lds<kXS>(), g, 8, nblk, q, k, v,
-                                    fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);
+        if (keys_fit<DA>(g, cus))
+            return launch_split_bwd(split::dkv_keys_kernel<DA>, split::dq_keys_kernel<DA>, split::Keys<DA>::template lds<kXS>(), g, 8,
+                                    keys_blocks<DA>(g), q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);
         const int waves = split_waves(g, cus, &nblk);
         return waves < 6 ? split_bwd<DA, 32>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st)
                          : split_bwd<DA, 64>(g, waves, nblk, q, k, v, fq, fk, dout, lse, delta, dq, dk, dv, pq, pk, st);

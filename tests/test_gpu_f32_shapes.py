@@ -230,3 +230,18 @@ def test_rows_done_again_stay_in_their_workgroup(tensor, B, heads):
         fin = torch.isfinite(b)
         # fp32 sums of up to 144 terms in another order: 144 * 2^-24 of the largest
         assert float((a[fin] - b[fin]).abs().max()) <= 3e-5 * max(1.0, float(b[fin].abs().max())), name
+
+
+@pytest.mark.parametrize("d,r,M,grouped", [
+    (30, 16, 8, False), (16, 14, 8, False),     # two blocks for four groups
+    (30, 16, 9, True),                          # three
+    (30, 34, 8, True),                          # 64 columns: two groups
+])
+def test_groups_only_where_most_have_a_block(d, r, M, grouped):
+    import gpu_helpers as gh
+    wl = wk.custom("f32-route", "f32", 2, 2 * M, M, 3, d, r, M, 1, 9940 + M + r, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    out, lse = gh.gpu_fwd(wl, t)
+    names = gh.kernels_of(lambda: gh.gpu_fwd(wl, t)) + gh.kernels_of(lambda: gh.gpu_bwd(wl, t, out, lse))
+    kinds = [any(k in n for n in names) for k in ("fwd_keys_kernel", "dq_keys_kernel", "dkv_keys_kernel")]
+    assert not names or kinds == [grouped] * 3, names
