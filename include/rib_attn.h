@@ -192,7 +192,7 @@ size_t rib_window_attn_gated_bwd_workspace_bytes(const rib_params *p);
  *     dO = dO' (.) G    (formed once, in the storage type, inside the workspace)
  *     dG = dO' (.) O    (written to dgate, [B][H][W][C], storage type)
  * followed by the backward of the plain operator with that dO; one pass over the
- * grid produces dO, dG and delta together.  out_raw is the UNGATED forward
+ * grid produces dO, dG and, where the kernels after it do not make it, delta.  out_raw is the UNGATED forward
  * output.  Arguments, errors and determinism otherwise as rib_window_attn_bwd. */
 rib_status rib_window_attn_gated_bwd(const rib_params *p,
                                      const void *q, const void *k, const void *v,

@@ -161,7 +161,7 @@ struct BwdWs {
 BwdWs bwd_ws_layout(const Geo &g);
 // Gated backward: the same scratch followed by one grid tensor for dO = dO' * gate.
 size_t gated_dout_bytes(const Geo &g, int dtype);
-// delta, dO = dO' * gate (into `dout`, storage type) and dgate = dO' * O in one pass.
+// dO = dO' * gate (into `dout`, storage type), dgate = dO' * O and, where `delta` is not null, delta in one pass.
 hipError_t launch_delta_gated(const Geo &g, int dtype, const void *out_raw, const void *dout_gated, const void *gate,
                               float *delta, void *dout, void *dgate, hipStream_t st);
 // delta[u][i] = dO[i].O[i] per head (dtype = RIB_F32 / RIB_BF16 storage of out, dout).

@@ -20,8 +20,11 @@ hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const voi
     a.delta = (float *)((char *)ws + l.delta_off);
     a.pq = (float *)((char *)ws + l.dfq_off);
     a.pk = (float *)((char *)ws + l.dfk_off);
+    // Units that one workgroup holds are done in one kernel (the figures stand in rib_mfma_unit.h), which makes delta of the
+    // rows it stages; rows of a pair or less and 64-bit offsets have forms in the pair only.
+    const bool one = g.N <= 512 && (rows::short_rows(g) == rows::kLong || rows::short_rows(g) == rows::kLong8) && rows_supported(g);
     if (g.gate) {
-        const hipError_t e = launch_delta_gated(g, RIB_BF16, out, dout, g.gate, a.delta, gated_dout, dgate, st);
+        const hipError_t e = launch_delta_gated(g, RIB_BF16, out, dout, g.gate, one ? nullptr : a.delta, gated_dout, dgate, st);
         if (e != hipSuccess) return e;
         dout = gated_dout;
     }
@@ -32,11 +35,9 @@ hipError_t launch_mfma_bwd(const Geo &g, const void *q, const void *k, const voi
     // the call's own dF_q output, which is written last, holds the scaled rows of f_q until then (2 of its 4 bytes a value)
     a.ftab = (bf16_t *)dfq;
     a.st = st;
-    // RIB rows of more than 32 values are staged by the 64-column kernels only.  Units that one workgroup holds are done
-    // in one kernel (the figures stand in rib_mfma_unit.h); rows of a pair or less and 64-bit offsets have forms in the pair only.
+    // (RIB rows of more than 32 values are staged by the 64-column kernels only)
     const int aug = g.d + g.r;
     const int width = aug <= 32 && g.d <= 30 ? 32 : aug <= 48 && g.r <= 32 ? 48 : 64;
-    const bool one = g.N <= 512 && (rows::short_rows(g) == rows::kLong || rows::short_rows(g) == rows::kLong8) && rows_supported(g);
     const hipError_t e = one ? (width == 32 ? unit::launch32(g, a) : width == 48 ? unit::launch48(g, a) : unit::launch64(g, a))
                              : (width == 32 ? bwd::launch32(g, a) : width == 48 ? bwd::launch48(g, a) : bwd::launch64(g, a));
     if (e != hipSuccess) return e;

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kThreads) void valu_delta_kernel(Geo g, int nchunk,
 
 // Gated variant (CLA, Eq. 9: O' = O * G): from the gradient dO' of the gated output,
 //   dO = dO' * G (rounded to the storage type, written for the main kernels),
-//   dG = dO' * O,      delta = dO . O   (with the rounded dO, as the main kernels see it).
+//   dG = dO' * O,      delta = dO . O   (with the rounded dO, as the main kernels see it; null where they make it themselves).
 // Same mapping of lanes to (token, head) slices as above, so every element of the grid is
 // written exactly once.
 template <typename T>
@@ -257,6 +257,7 @@ __global__ __launch_bounds__(kThreads) void valu_delta_gated_kernel(Geo g, int n
                 acc = fmaf(widen(d_o), o, acc);
             }
         }
+        if (delta == nullptr) continue;
 #pragma unroll
         for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
         const int nl = it * 16 + grp;

@@ -70,3 +70,22 @@ def test_unit_backward_gated_is_the_plain_one_of_the_gated_gradient(d, r, M, s):
     torch.cuda.synchronize()
     for name, a, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), (dq, dk, dv, dfq, dfk), ref):
         assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("M,made", [(16, False), (24, True)], ids=["one-kernel", "pair"])
+def test_gated_call_makes_delta_once(M, made):
+    """The pass over dO', gate and O writes delta into the workspace for the pair of kernels only."""
+    import torch
+    import gpu_helpers as gh
+    wl = wk.custom(f"unitd-m{M}", "bf16", 1, M, 2 * M, 2, 30, 16, M, 3, 9950 + M, backward=True)
+    t = gh.device_inputs(wl, wk.make_inputs(wl))
+    p = rb.params_of(wl)
+    out, lse = gh.gpu_fwd(wl, t)
+    dq, dk, dv, dg = (torch.empty_like(out) for _ in range(4))
+    dfq, dfk = (torch.empty((wl.heads, wl.N, wl.r), dtype=torch.float32, device=gh.DEV) for _ in range(2))
+    ws = torch.full((rb.rib_window_attn_gated_bwd_workspace_bytes(p),), 0x5A, dtype=torch.uint8, device=gh.DEV)
+    rb.rib_window_attn_gated_bwd(p, t["q"], t["k"], t["v"], t["f_q"], t["f_k"], torch.ones_like(out), out, t["d_out"], lse,
+                                 dq, dk, dv, dg, dfq, dfk, ws)
+    torch.cuda.synchronize()
+    delta = ws[:wl.n_units * wl.N * 4]          # (the workspace begins with it)
+    assert bool((delta == 0x5A).all()) == (not made)
