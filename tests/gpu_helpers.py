@@ -77,3 +77,60 @@ def kernels_of(call):
         call()
         torch.cuda.synchronize()
     return [e.key for e in prof.key_averages() if e.device_time_total > 0]
+
+
+def rel(a, b):
+    """2-norm of the difference over the 2-norm of the reference."""
+    a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
+    assert a.shape == b.shape and np.isfinite(a).all(), (a.shape, b.shape)
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+NAMES = ("O", "LSE", "dQ", "dK", "dV", "dF_q", "dF_k")
+
+
+def many_images(oracle, wl, images, packed=False, gated=False):
+    """Forward and backward of a batch of `images` that fills the chip, drawn from two images, so that the oracle computes
+    only those: (got, ref, names of the backward's kernels), got and ref as in NAMES (gated: and dG)."""
+    from dataclasses import replace
+
+    from paper_2603_06738_amd import workloads as wk
+    from helpers import geometry
+    two = replace(wl, B=2, backward=True)
+    x = wk.make_inputs(two)
+    grids = ["q", "k", "v", "d_out"]
+    rng = np.random.default_rng(wl.seed)
+    if gated:
+        x["gate"] = wk.round_to_bf16(rng.random(x["q"].shape, dtype=np.float32))
+        grids.append("gate")
+    pick = rng.permutation(np.arange(images) % 2)
+    g = geometry(oracle, replace(two, B=1))
+    refs = []
+    for i in (0, 1):
+        y = {n: a[i:i + 1] if n in grids else a for n, a in x.items()}
+        args = [y[n] for n in ("q", "k", "v", "f_q", "f_k")]
+        if gated:
+            o, _, lse = oracle.gated_fwd(g, *args, y["gate"])
+            refs.append((o, lse) + oracle.gated_bwd(g, *args, y["gate"], y["d_out"]))
+        else:
+            refs.append(oracle.fwd(g, *args) + oracle.bwd(g, *args, y["d_out"]))
+    def of_batch(name, parts):      # the RIB gradients are sums over the images
+        return sum(int((pick == i).sum()) * parts[i] for i in (0, 1)) if name[:2] == "dF" else np.concatenate([parts[i] for i in pick])
+
+    ref = [of_batch(name, parts) for name, parts in zip(NAMES + ("dG",), zip(*refs))]
+    full = replace(wl, B=images)
+    t = device_inputs(full, {n: a[pick] if n in grids else a for n, a in x.items()}, packed=packed)
+    if not gated:
+        out, lse = gpu_fwd(full, t, packed=packed)
+        got = []
+        names = kernels_of(lambda: got.extend(gpu_bwd(full, t, out, lse, packed=packed)))
+        return (out, lse, *got), ref, names
+    p = rb.params_of(full)
+    out, raw, dq, dk, dv, dg = (torch.full_like(t["d_out"], float("nan")) for _ in range(6))
+    lse = torch.full((full.n_windows, full.heads, full.N), float("nan"), dtype=torch.float32, device=DEV)
+    dfq, dfk = (torch.full((full.heads, full.N, full.r), float("nan"), dtype=torch.float32, device=DEV) for _ in range(2))
+    ws = torch.empty(rb.rib_window_attn_gated_bwd_workspace_bytes(p), dtype=torch.uint8, device=DEV)
+    rb.rib_window_attn_gated_fwd(p, t["q"], t["k"], t["v"], t["f_q"], t["f_k"], t["gate"], out, raw, lse)
+    names = kernels_of(lambda: rb.rib_window_attn_gated_bwd(p, t["q"], t["k"], t["v"], t["f_q"], t["f_k"], t["gate"], raw,
+                                                            t["d_out"], lse, dq, dk, dv, dg, dfq, dfk, ws))
+    return (out, lse, dq, dk, dv, dfq, dfk, dg), ref, names

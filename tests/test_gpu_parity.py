@@ -197,9 +197,10 @@ def test_config5_backward_full_size(oracle, gh):
 def test_paper_schedule_layers(oracle, gh, name):
     """The (head dim, rank, window) combinations of the paper's networks (Appendix,
     "Network implementation details"), with the paper's two scales: forward and
-    backward, every element, on ONE image of the scheduled workload (the kernels'
-    launch shape per window is the benchmark's; the batch only multiplies windows;
-    the 64- and 96-windows keep two heads so that the oracle finishes in seconds)."""
+    backward, every element, on ONE image of the scheduled workload (windows past 512
+    tokens: a grid of one round, whose waves share the streamed side; the kernels of
+    the whole batch are in test_gpu_large_grids.py; the 64- and 96-windows keep two
+    heads so that the oracle finishes in seconds)."""
     from dataclasses import replace
     wl = replace(wk.SCHEDULE[name], B=1)
     if wl.M >= 64:

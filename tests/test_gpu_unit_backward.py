@@ -29,6 +29,10 @@ SHAPES = [  # (d, r, M, shift, H / M, W / M)
     (16, 12, 20, 7, 1, 1),      # 400
     (30, 16, 21, 20, 1, 1),     # 441
     (32, 32, 22, 11, 1, 1),     # 484: the last wave's second block starts past the end
+    # the other combinations of width, extras, alignment and waves
+    (16, 16, 9, 0, 1, 1), (16, 16, 12, 5, 1, 1), (16, 16, 20, 0, 1, 1), (32, 8, 9, 1, 1, 1), (32, 8, 20, 0, 1, 1), (32, 8, 8, 3, 1, 1),
+    (30, 18, 20, 9, 1, 1), (32, 16, 8, 0, 1, 2), (32, 16, 16, 4, 1, 1), (24, 34, 9, 0, 1, 1), (24, 34, 12, 7, 1, 1), (24, 34, 8, 0, 1, 2),
+    (32, 24, 9, 2, 1, 1), (32, 24, 12, 0, 1, 1), (32, 24, 8, 5, 1, 1), (30, 34, 20, 0, 1, 1), (32, 32, 12, 6, 1, 1), (32, 32, 8, 0, 1, 2),
 ]
 
 
