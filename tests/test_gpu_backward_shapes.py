@@ -15,6 +15,8 @@ from paper_2603_06738_amd import binding as rb
 from paper_2603_06738_amd import workloads as wk
 from helpers import geometry
 
+REL = 1e-2      # roundings to bf16, of at most 2^-8 each, of Q_aug (through the logits), of P or dS and of the result: 2.6 times 2^-8
+
 SHAPES = [  # (d, r, M, shift, H / M, W / M)
     (16, 14, 8, 3, 1, 2),       # one 64-token block: the second wave idles; width 32, extras in columns
     (16, 16, 24, 12, 1, 1),     # 3 workgroups of 3 waves; width 32, LSE in the C operand
@@ -55,6 +57,16 @@ def test_backward_shapes(oracle, d, r, M, s, ny, nx, packed):
         assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"], name
 
 
+def check_gradients(got, again, ref):
+    """Run to run the same, every element within the parity tests' bound, and within REL in the 2-norm: gradients of few
+    channels and sums over windows are themselves not much larger than that bound."""
+    import gpu_helpers as gh
+    for name, a, a2, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, again, ref):
+        assert bool((a == a2).all()), name
+        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"], name
+        assert gh.rel(gh.host(a), b) <= REL, name
+
+
 @pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
     (30, 34, 32, 16, 8, 2, 2, 8),       # 64 columns, LSE in the C operand; two whole workgroups a unit
     (32, 32, 45, 3, 4, 2, 4, 4),        # both in the C operand; 2025 tokens: a partial last block and tile
@@ -68,10 +80,9 @@ def test_eight_wave_workgroups(oracle, d, r, M, s, B, ny, nx, heads):
     t = gh.device_inputs(wl, x)
     out, lse = gh.gpu_fwd(wl, t)
     got = gh.gpu_bwd(wl, t, out, lse)
+    again = gh.gpu_bwd(wl, t, out, lse)
     ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
-    # dF sums windows, whose roundings add at random
-    for name, a, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, ref):
-        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"] * (1.0 if name[1] != "F" else (B * ny * nx) ** 0.5), name
+    check_gradients(got, again, ref)
 
 
 @pytest.mark.parametrize("d,r,M,s,B,ny,nx,heads", [
@@ -88,6 +99,11 @@ def test_eight_wave_workgroups(oracle, d, r, M, s, B, ny, nx, heads):
     (16, 16, 24, 7, 4, 3, 7, 1),        # 84 units: two groups
     (16, 16, 24, 7, 1, 2, 43, 1),       # 86: none
     (6, 4, 28, 0, 1, 1, 1, 1),          # rows of 8-byte pieces
+    # the other combinations of width, extras and alignment, in two groups and in four
+    (16, 16, 25, 0, 1, 1, 1, 2), (32, 8, 25, 3, 1, 1, 1, 2), (32, 16, 25, 0, 1, 1, 1, 2), (24, 34, 25, 1, 1, 1, 1, 2),
+    (32, 24, 25, 0, 1, 1, 1, 2), (32, 24, 24, 5, 1, 1, 1, 2), (16, 14, 33, 0, 1, 1, 1, 1), (16, 16, 33, 2, 1, 1, 1, 1),
+    (32, 8, 33, 0, 1, 1, 1, 1), (32, 8, 32, 7, 1, 1, 1, 1), (32, 16, 33, 0, 1, 1, 1, 1), (24, 34, 33, 0, 1, 1, 1, 1),
+    (32, 24, 33, 9, 1, 1, 1, 1), (32, 24, 32, 0, 1, 1, 1, 1),
 ])
 def test_streamed_side_shared_by_groups(oracle, d, r, M, s, B, ny, nx, heads):
     """Small grids, whose waves share the streamed side in two or four groups, around the rule's edges; run to run the same."""
@@ -99,7 +115,4 @@ def test_streamed_side_shared_by_groups(oracle, d, r, M, s, B, ny, nx, heads):
     got = gh.gpu_bwd(wl, t, out, lse)
     again = gh.gpu_bwd(wl, t, out, lse)
     ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
-    for name, a, a2, b in zip(("dQ", "dK", "dV", "dF_q", "dF_k"), got, again, ref):
-        assert bool((a == a2).all()), name
-        # dF sums windows, whose roundings add at random
-        assert gh.max_abs(gh.host(a), b) <= gh.TOL["bf16"] * (1.0 if name[1] != "F" else (B * ny * nx) ** 0.5), name
+    check_gradients(got, again, ref)

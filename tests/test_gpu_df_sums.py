@@ -29,11 +29,12 @@ def test_rib_gradient_sums(oracle, dtype, B, ny, nx, heads, d, r, M):
     got = gh.gpu_bwd(wl, t, out, lse)
     again = gh.gpu_bwd(wl, t, out, lse)
     ref = oracle.bwd(geometry(oracle, wl), x["q"], x["k"], x["v"], x["f_q"], x["f_k"], x["d_out"])
-    # bf16: the bound of one window's gradient, times the square root of the number of windows whose roundings add at random
-    tol = gh.TOL["f32"] if dtype == "f32" else gh.TOL["bf16"] * (B * ny * nx) ** 0.5
     for name, a, a2, b in zip(("dF_q", "dF_k"), got[3:], again[3:], ref[3:]):
         assert bool((a == a2).all()), name
-        assert gh.max_abs(gh.host(a), b) <= tol, name
+        if dtype == "f32":
+            assert gh.max_abs(gh.host(a), b) <= gh.TOL["f32"], name
+        else:       # a window left out of 36 or 64 would be an eighth of the sum and more
+            assert gh.rel(gh.host(a), b) <= 1e-2, name
 
 
 @pytest.mark.parametrize("dtype,B,ny,nx,heads,d,r,M", [
