@@ -712,6 +712,16 @@ inline hipError_t groups_of(const Geo &g, int *groups)
     return e;
 }
 
+// Which widths and extras rows of a kind meet (short rows beside d = 32, and RIB rows of under 8 values, need few columns; those of
+// more than 32 values take 64).
+constexpr bool reached(int kind, int dqk, bool xs, bool xd)
+{
+    return kind == kAnyShort ? !xd && !(dqk == 48 && xs)
+           : kind == kPairRib ? dqk == 32 || (dqk == 48 && !xs && xd)
+           : kind == kNoRib   ? !xs && (dqk == 32 || (dqk == 48 && xd))
+           : kind == kLong8   ? !(dqk == 48 && xs) && !(dqk == 64 && xd) : true;
+}
+
 // Workgroup shape: up to 4 waves of 64 stationary tokens, an equal number in every workgroup of a
 // unit; workgroups under 4 waves stream tiles of 32 tokens (a lane stages at most two).  Images whose
 // offsets need more than 32 bits run the four-wave form with 64-bit offsets at every size.
@@ -723,16 +733,22 @@ hipError_t launch_width(const Geo &g, const Args &a)
     if (waves < 2) waves = 2;
     const Short kind = short_rows(g);
     const bool aln = g.M % 8 == 0;
-    if (!rows_supported(g))
-        return kind != kLong && kind != kLong8 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, true>(g, 4, nblk, a)
-               : aln                           ? launch_pair<DQK, 64, XS, XD, true, kLong8, true>(g, 4, nblk, a)
-                                               : launch_pair<DQK, 64, XS, XD, false, kLong8, true>(g, 4, nblk, a);
-    if (kind == kAnyShort)
-        return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, false>(g, waves, nblk, a)
-                          : launch_pair<DQK, 32, XS, XD, false, kAnyShort, false>(g, waves, nblk, a);
-    // (short RIB rows beside d >= 4: d + r <= 32, or d = 32)
-    if constexpr (DQK == 32 || (DQK == 48 && !XS && XD)) {
+    if (!rows_supported(g)) {
+        if (kind == kLong || kind == kLong8)
+            return aln ? launch_pair<DQK, 64, XS, XD, true, kLong8, true>(g, 4, nblk, a)
+                       : launch_pair<DQK, 64, XS, XD, false, kLong8, true>(g, 4, nblk, a);
+        if constexpr (reached(kAnyShort, DQK, XS, XD) || reached(kPairRib, DQK, XS, XD) || reached(kNoRib, DQK, XS, XD))
+            return launch_pair<DQK, 64, XS, XD, false, kAnyShort, true>(g, 4, nblk, a);
+    }
+    if constexpr (reached(kAnyShort, DQK, XS, XD)) {
+        if (kind == kAnyShort)
+            return waves == 4 ? launch_pair<DQK, 64, XS, XD, false, kAnyShort, false>(g, waves, nblk, a)
+                              : launch_pair<DQK, 32, XS, XD, false, kAnyShort, false>(g, waves, nblk, a);
+    }
+    if constexpr (reached(kPairRib, DQK, XS, XD)) {
         if (kind == kPairRib) return launch_rows<DQK, XS, XD, kPairRib>(g, aln, waves, nblk, a);
+    }
+    if constexpr (reached(kNoRib, DQK, XS, XD)) {
         if (kind == kNoRib) return launch_rows<DQK, XS, XD, kNoRib>(g, aln, waves, nblk, a);
     }
     if (kind != kLong && kind != kLong8) return hipErrorInvalidValue;
@@ -742,8 +758,10 @@ hipError_t launch_width(const Geo &g, const Args &a)
     // (scalar token arithmetic needs whole tiles)
     if (groups == 4) return aln && g.N % 128 == 0 ? launch_groups<DQK, XS, XD, true, 4>(g, a) : launch_groups<DQK, XS, XD, false, 4>(g, a);
     if (groups == 2) return aln ? launch_groups<DQK, XS, XD, true, 2>(g, a) : launch_groups<DQK, XS, XD, false, 2>(g, a);
-    if (kind == kLong8) return launch_rows<DQK, XS, XD, kLong8>(g, aln, waves, nblk, a);
-    return launch_rows<DQK, XS, XD, kLong>(g, aln, waves, nblk, a);
+    if constexpr (reached(kLong8, DQK, XS, XD)) {
+        if (kind == kLong8) return launch_rows<DQK, XS, XD, kLong8>(g, aln, waves, nblk, a);
+    }
+    return kind == kLong ? launch_rows<DQK, XS, XD, kLong>(g, aln, waves, nblk, a) : hipErrorInvalidValue;
 }
 
 // d + r within the padded width; columns carry LSE / delta wherever two are free.

@@ -406,6 +406,7 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
 {
     const Short kind = short_rows(g);
     const bool aln = g.M % 8 == 0;
+    constexpr bool short8 = !(DQK == 64 && SUM);    // (RIB rows of 4 or 6 values beside d = 32 fit 48 columns)
     if (g.N >= 1024 && (kind == kLong || kind == kLong8)) {
         int cus = 0;
         const hipError_t e = compute_units(&cus);
@@ -423,24 +424,30 @@ hipError_t launch_width(const Geo &g, int qb, const Args &a)
         const int nb = (g.N + 31) / 32, nblk = (nb + 7) / 8;
         int waves = (nb + nblk - 1) / nblk;
         if (waves < 4) waves = 4;
-        if (kind == kLong8)
-            return aln ? launch_one<DQK, 64, 1, SUM, true, kLong8>(g, waves, nblk, a)
-                       : launch_one<DQK, 64, 1, SUM, false, kLong8>(g, waves, nblk, a);
+        if constexpr (short8) {
+            if (kind == kLong8)
+                return aln ? launch_one<DQK, 64, 1, SUM, true, kLong8>(g, waves, nblk, a)
+                           : launch_one<DQK, 64, 1, SUM, false, kLong8>(g, waves, nblk, a);
+        }
         return aln ? launch_one<DQK, 64, 1, SUM, true, kLong>(g, waves, nblk, a)
                    : launch_one<DQK, 64, 1, SUM, false, kLong>(g, waves, nblk, a);
     }
     const int nb = (g.N + 63) / 64, nblk = (nb + 3) / 4;
     int waves = (nb + nblk - 1) / nblk;
     if (waves < 2) waves = 2;
-    if (kind == kAnyShort)
-        return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, kAnyShort>(g, waves, nblk, a)
-                          : launch_one<DQK, 32, 2, SUM, false, kAnyShort>(g, waves, nblk, a);
+    if constexpr (!SUM) {       // (d = 2)
+        if (kind == kAnyShort)
+            return waves == 4 ? launch_one<DQK, 64, 2, SUM, false, kAnyShort>(g, waves, nblk, a)
+                              : launch_one<DQK, 32, 2, SUM, false, kAnyShort>(g, waves, nblk, a);
+    }
     // (short RIB rows beside d >= 4: d + r <= 32, or d = 32)
     if constexpr (DQK == 32 || (DQK == 48 && SUM)) {
         if (kind == kPairRib) return launch_queries64<DQK, SUM, kPairRib>(g, aln, waves, nblk, a);
         if (kind == kNoRib) return launch_queries64<DQK, SUM, kNoRib>(g, aln, waves, nblk, a);
     }
-    if (kind == kLong8) return launch_queries64<DQK, SUM, kLong8>(g, aln, waves, nblk, a);
+    if constexpr (short8) {
+        if (kind == kLong8) return launch_queries64<DQK, SUM, kLong8>(g, aln, waves, nblk, a);
+    }
     if (kind != kLong) return hipErrorInvalidValue;
     return launch_queries64<DQK, SUM, kLong>(g, aln, waves, nblk, a);
 }

@@ -430,9 +430,8 @@ hipError_t launch_unit(const Geo &g, const Args &a)
 template <int DQK, bool XS, bool XD>
 hipError_t unit_width(const Geo &g, const Args &a)
 {
-    if (g.M % 8 == 0)
-        return g.N <= 128 ? launch_unit<DQK, XS, XD, true, 2>(g, a) : g.N <= 256 ? launch_unit<DQK, XS, XD, true, 4>(g, a)
-                                                                                  : launch_unit<DQK, XS, XD, true, 8>(g, a);
+    if (g.M % 8 == 0)       // (8 or 16)
+        return g.N <= 128 ? launch_unit<DQK, XS, XD, true, 2>(g, a) : launch_unit<DQK, XS, XD, true, 4>(g, a);
     return g.N <= 128 ? launch_unit<DQK, XS, XD, false, 2>(g, a) : g.N <= 256 ? launch_unit<DQK, XS, XD, false, 4>(g, a)
                                                                                : launch_unit<DQK, XS, XD, false, 8>(g, a);
 }

@@ -48,3 +48,27 @@ def test_dkv_pieces_of_64_columns(d, r, M, B, ny, nx, heads, tile, wide):
     got = dkv_threads(d, r, M, B, ny, nx, heads)
     if got is not None:
         assert (got[0], got[2]) == (tile, wide), got
+
+
+@pytest.mark.parametrize("M,B", [(9, 1), (24, 1), (24, 43), (33, 1)], ids=["unit", "groups", "pair", "four-groups"])
+@pytest.mark.parametrize("d", range(2, 33, 2))
+def test_every_rank_is_served(d, M, B):
+    """Every even rank beside every even head dimension, against the vector-ALU kernels: the forms are chosen by both."""
+    import torch
+    import gpu_helpers as gh
+    from paper_2603_06738_amd import binding as rb
+    for r in range(0, 65 - d, 2):
+        wl = wk.custom("rank", "bf16", B, M, M, 2, d, r, M, 1, 14000 + 64 * d + r, backward=True)
+        gen = torch.Generator(device=gh.DEV)
+        gen.manual_seed(wl.seed)
+        grid, feat = (B, M, M, 2 * d), (2, M * M, r)
+        t = {n: torch.randn(grid, generator=gen, device=gh.DEV).to(torch.bfloat16) for n in ("q", "k", "v", "d_out")}
+        t.update({n: (0.5 * torch.randn(feat, generator=gen, device=gh.DEV)).to(torch.bfloat16) for n in ("f_q", "f_k")})
+        res = []
+        for flags in (0, rb.RIB_FLAG_VECTOR_ONLY):
+            out, lse = gh.gpu_fwd(wl, t, flags=flags)
+            res.append((out, lse) + gh.gpu_bwd(wl, t, *(res[0][:2] if res else (out, lse)), flags=flags))
+        for name, a, b in zip(gh.NAMES, *res):
+            if a.numel():
+                # as the bound of test_gpu_large_grids.py; the vector kernels round their results to 2^-8 too
+                assert float((a.float() - b.float()).norm() / b.float().norm()) <= 1.4e-2, (name, r)
