@@ -259,7 +259,10 @@ template <int TINY, class Off>
 __device__ __forceinline__ Words<TINY> get(const char *base, Off off, bool one)
 {
     Words<TINY> v;
-    if (one) {
+    if constexpr (TINY == kAnyShort) {
+        const dword2 x = get8(base, off, one);
+        v.w[0] = x.x, v.w[1] = x.y;
+    } else if (one) {
         v.w[0] = *(const uint32_t *)(base + off);
 #pragma unroll
         for (int i = 1; i < Moved<TINY>::WORDS; ++i) v.w[i] = 0u;
@@ -271,7 +274,8 @@ __device__ __forceinline__ Words<TINY> get(const char *base, Off off, bool one)
 template <int TINY>
 __device__ __forceinline__ void put(bf16_t *dst, const Words<TINY> &v, bool one)
 {
-    if (one) *(uint32_t *)dst = v.w[0];
+    if constexpr (TINY == kAnyShort) put8(dst, dword2{v.w[0], v.w[1]}, one);
+    else if (one) *(uint32_t *)dst = v.w[0];
     else *(Words<TINY> *)dst = v;
 }
 template <int TINY>
@@ -298,6 +302,17 @@ __device__ __forceinline__ auto token_offset(uint32_t t, int64_t stride)
     else return (uint32_t)__umul24(t, (uint32_t)stride);
 }
 
+// Whether pass `p` of a tile's staging has rows for the wave whose first slot is `slot`.  Where the number of lanes is a constant
+// the pass is taken or left out as a whole, and no branch splits the blocks it rides in; elsewhere there is one comparison.
+template <int TINY, int T>
+__device__ __forceinline__ bool stages(int p, int nt, int slot)
+{
+    constexpr int slots = T * Moved<TINY>::LANES;
+    if (__builtin_constant_p(nt) && nt * (p + 1) <= slots) return true;
+    if (__builtin_constant_p(nt) && nt * p >= slots) return false;
+    return slot < slots;
+}
+
 template <int DQK, int TINY>
 struct Regs {
     static constexpr int S = Moved<TINY>::SLOTS;
@@ -315,8 +330,8 @@ __device__ __forceinline__ void request(Regs<DQK, TINY> &rg, const Geo &g, const
 #pragma unroll
     for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;                // the wave's first slot
-        if ((T >= 64 && nt * M::SLOTS == T * M::LANES) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
-            const int n0 = tile * T + slot / M::LANES;
+        if (stages<TINY, T>(p, nt, slot)) {
+            const int n0 = tile * T + (int)((uint32_t)slot / M::LANES);
             const uint32_t t = win.token<ALN, M::ROWS>(n0, l);
             rg.x[p] = get<TINY>(s.xb, token_offset<BIG>(t, s.xs) + 4u * pc.dc, pc.c1);
             rg.y[p] = get<TINY>(s.yb, token_offset<BIG>(t, s.ys) + 4u * pc.dc, pc.c1);
@@ -355,8 +370,8 @@ __device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, 
 #pragma unroll
     for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
-        if ((T >= 64 && nt * M::SLOTS == T * M::LANES) || (T == 64 && nt == 512 && M::LANES == 8 && p == 0) || slot < T * M::LANES) {
-            const int r0 = slot / M::LANES;                 // (uniform)
+        if (stages<TINY, T>(p, nt, slot)) {
+            const int r0 = (int)((uint32_t)slot / M::LANES);    // (uniform)
             Words<TINY> y = rg.y[p];
             if (!ALN && r0 + l >= left)
 #pragma unroll
