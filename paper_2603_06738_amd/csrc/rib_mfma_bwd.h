@@ -160,7 +160,7 @@ __device__ __forceinline__ void stat_stage(const StatRegs<DQK, WITH_O, TINY> &r,
             if (DQK == 64) fb = QDO ? scaled<TINY>(r.fb[p], sp) : r.fb[p];
             put<TINY>(fr + p * M::ROWS * L::XS, fa, pc.f1d);
             if (DQK == 64) put<TINY>(fr1 + p * M::ROWS * L::XS, fb, pc.f1d);
-            if (QDO && ftab) {
+            if (QDO && has_table(TINY) && ftab) {
                 const int n = n0 + p * M::ROWS + l, last = g.N - 1, nb = aln && n0 + p * M::ROWS > last - (M::ROWS - 1) ? last - (M::ROWS - 1) + l : n;
                 char *row = ftab + __umul24((uint32_t)(nb < last ? nb : last), (uint32_t)g.r * 2u);
                 put<TINY>((bf16_t *)(row + 4u * pc.f0), fa, pc.f1d);
@@ -310,8 +310,8 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
     }
     __syncthreads();
     init_pads<DQK, T, false, XS, XD>(g, smem, nt);
-    commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, g.N, nt, wave);
-    commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
+    commit<DQK, T, false, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, false, ALN, TINY, BIG>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
             for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(XS ? S[cs][i] + nl[qb] : S[cs][i]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) p[i] *= XD ? D[cs][i] + nd[qb] : D[cs][i];
-            if (s == 0) commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem + c2, 1.f, rows_left<T>(g, tile + 2), nt, wave);
+            if (s == 0) commit<DQK, T, false, XS, XD, ALN, TINY>(rg, g, smem + c2, 1.f, 1.f, rows_left<T>(g, tile + 2), nt, wave);
             RIB_FENCE();
 #pragma unroll
             for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dq_kernel(Geo g, int nb
     }
 }
 
-// dK, dV (+ dF_k partial).  `fq` is the dq kernel's table of scaled RIB rows (they are the same for every window, and
+// dK, dV (+ dF_k partial).  `fq` is, where has_table, the dq kernel's table of scaled RIB rows (they are the same for every window, and
 // scaling them while they are staged cost a tenth of the loop's vector instructions).  Same walk with the roles exchanged.  There are no registers for a second
 // pair of score blocks here, so the phases of a block alternate (the two waves of a SIMD fill each
 // other's): gradient MFMAs of the block before and score MFMAs, then exponentials, products, packs.
@@ -460,6 +460,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
 {
     RIB_BWD_SETUP
     constexpr int NB = T / 32 / G;          // query blocks of a tile: of this wave's group
+    const float sp2 = g.scale_p * kLog2e;
 
     Regs<DQK, TINY> rg, rg1;
     bf16x8 Kb[2][L::KS], Vb[2][L::VS];
@@ -472,8 +473,8 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
     }
     __syncthreads();
     init_pads<DQK, T, true, XS, XD>(g, smem, nt);
-    commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, g.N, nt, wave);
-    commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem, sc2, sp2, g.N, nt, wave);
+    commit<DQK, T, true, XS, XD, ALN, TINY>(rg1, g, smem + L::STAGE, sc2, sp2, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, true, ALN, TINY, BIG>(rg, g, win, qs, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(T >= 64 ? NT : 192, 2) void dkv_kernel(Geo g, int n
                         for (int mb = 0; mb < L::RB; ++mb)
                             Aqt[mb][i] = read_tr<L::XS>(cur + (qb * 32 + 16 * i) * L::XS, trx, 32 * mb);
                     }
-                    if (qb == 0) commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem + c2, sc2, rows_left<T>(g, tile + 2), nt, wave);
+                    if (qb == 0) commit<DQK, T, true, XS, XD, ALN, TINY>(rg, g, smem + c2, sc2, sp2, rows_left<T>(g, tile + 2), nt, wave);
                 } else {
                     read_rows<L::KS>(Aq, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::XS : nxt) + aqo);
                     read_rows<L::VS>(Ag, (qb + 1 < NB ? cur + (qb + 1) * 32 * L::YS : nxt) + ago);
@@ -620,7 +621,8 @@ hipError_t launch_dkv(const Geo &g, int waves, int nblk, const Args &a)
     auto kern = dkv_kernel<DQK, T, XS, XD, ALN, TINY, BIG, NT, G>;
     const hipError_t e = prepare_kernel((const void *)kern, nullptr);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v, a.ftab, a.fk, a.dout, a.lse,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.units * nblk)), dim3(waves * 64), smem, a.st, g, nblk, a.q, a.k, a.v,
+                       has_table(TINY) ? a.ftab : a.fq, a.fk, a.dout, a.lse,
                        a.delta, a.dk, a.dv, a.pk);
     return hipGetLastError();
 }

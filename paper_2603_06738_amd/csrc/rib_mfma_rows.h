@@ -159,8 +159,8 @@ __global__ __launch_bounds__(max_threads(T, QB, G), DQK <= 48 && TINY != kAnySho
     }
     __syncthreads();
     init_pads<DQK, T, false, true, SUM>(g, smem, nt);
-    commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem, 1.f, g.N, nt, wave);
-    commit<DQK, T, false, true, SUM, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
+    commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem, 1.f, 1.f, g.N, nt, wave);
+    commit<DQK, T, false, true, SUM, ALN, TINY>(rg1, g, smem + L::STAGE, 1.f, 1.f, ntiles > 1 ? g.N - T : g.N, nt, wave);
     request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, ntiles > 2 ? 2 : ntiles - 1, nt, wave);
     __syncthreads();
 
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(max_threads(T, QB, G), DQK <= 48 && TINY != kAnySho
                 for (int i = 4; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(S[cs][i]);
                 P[cs][2] = pack_bf16(p[4], p[5]);
                 P[cs][3] = pack_bf16(p[6], p[7]);
-                if (s == 0) commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem + c2, 1.f, rows_left<T>(g, tile + 2), nt, wave);
+                if (s == 0) commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, smem + c2, 1.f, 1.f, rows_left<T>(g, tile + 2), nt, wave);
                 RIB_FENCE();
 #pragma unroll
                 for (int i = 2; i < L::KS; ++i) S[ns] = mfma(Ak[i], Qb[qn][i], S[ns]);
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(max_threads(T, QB, G), DQK <= 48 && TINY != kAnySho
 #pragma unroll 1
         for (int tile = 0; tile < ntiles; ++tile) {     // two stages in turn, one barrier a tile
             bf16_t *cur = smem + (tile & 1) * L::STAGE;
-            commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, cur, 1.f, g.N - tile * T, nt, wave);
+            commit<DQK, T, false, true, SUM, ALN, TINY>(rg, g, cur, 1.f, 1.f, g.N - tile * T, nt, wave);
             request<DQK, T, false, ALN, TINY, false>(rg, g, win, ks, tile + 1 < ntiles ? tile + 1 : tile, nt, wave);
             __syncthreads();
 #pragma unroll 1

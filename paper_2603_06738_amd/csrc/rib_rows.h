@@ -224,6 +224,10 @@ struct Moved {
 };
 template <int TINY>
 using Words = typename Moved<TINY>::Words;
+// Whether the backward's dq kernel writes the scaled RIB rows of Q_aug out for dkv to stream.  A row of one pair costs more to
+// write and read back than to scale again (backward of 12 units of 9 x 9, d = 14, r = 2 19.3 us without / 20.0 with; d = 2, r = 34, 14 x 14 54.9 /
+// 63.2, where the table is spilled registers too).
+constexpr bool has_table(int tiny) { return tiny == kLong || tiny == kLong8; }
 struct Piece {
     int dc, f0, f1;                 // first dword of the content / RIB pieces
     bool c1, f1d, fnone;            // single-dword content / RIB rows, no RIB at all (uniform)
@@ -286,7 +290,7 @@ __device__ __forceinline__ Words<TINY> scaled(Words<TINY> v, float s)
     return v;
 }
 
-// Streamed operand pair of a unit.  QDO: X = q (strided; its RIB rows scaled already), Y = dO (dense), extras = LSE, delta.
+// Streamed operand pair of a unit.  QDO: X = q (strided; its RIB rows scaled already where there is a table), Y = dO (dense), extras = LSE, delta.
 // Otherwise X = k, Y = v (both strided), extras = ones.
 struct Stream {
     const char *xb, *yb, *fb;       // this image's and head's slices; this head's RIB table
@@ -356,10 +360,10 @@ __device__ __forceinline__ int rows_left(const Geo &g, int tile)
     const int left = g.N - tile * T;
     return left > 0 ? left : (g.N - 1) % T + 1;
 }
-// `sc`: what Q content is multiplied by (QDO).  `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
+// `sc`, `sp`: what Q content and, without a table of scaled rows, its RIB rows are multiplied by (QDO).  `left`: how many of the tile's rows lie inside the window.  The Y rows past it are zero, so that an
 // infinity in the repeated last token does not meet the zero P of a masked row.
 template <int DQK, int T, bool QDO, bool XS, bool XD, bool ALN, int TINY>
-__device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, bf16_t *S, float sc, int left, int nt, int wave)
+__device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, bf16_t *S, float sc, float sp, int left, int nt, int wave)
 {
     using L = Lay<DQK, T>;
     using M = Moved<TINY>;
@@ -367,20 +371,25 @@ __device__ __forceinline__ void commit(const Regs<DQK, TINY> &rg, const Geo &g, 
     const Piece pc = piece_of<TINY>(g, lane % M::LANES);
     bf16_t *xr = S + __mul24(l, L::XS) + 2 * pc.dc, *yr = S + L::YR + __mul24(l, L::YS) + 2 * pc.dc;
     bf16_t *fr = S + __mul24(l, L::XS) + g.d + 2 * pc.f0, *fr1 = S + __mul24(l, L::XS) + g.d + 2 * pc.f1;
+    constexpr bool scale = QDO && !has_table(TINY);
 #pragma unroll
     for (int p = 0; p < M::SLOTS; ++p) {
         const int slot = p * nt + wave * 64;
         if (stages<TINY, T>(p, nt, slot)) {
             const int r0 = (int)((uint32_t)slot / M::LANES);    // (uniform)
-            Words<TINY> y = rg.y[p];
+            Words<TINY> x = rg.x[p], y = rg.y[p], fa = rg.fa[p], fb = rg.fb[DQK == 64 ? p : 0];
+            if (scale) {        // (ahead of the branches on short rows: behind them it is 30 spilled registers with 64 columns)
+                x = scaled<TINY>(x, sc), fa = scaled<TINY>(fa, sp);
+                if (DQK == 64) fb = scaled<TINY>(fb, sp);
+            }
             if (!ALN && r0 + l >= left)
 #pragma unroll
                 for (int i = 0; i < M::WORDS; ++i) y.w[i] = 0u;
-            put<TINY>(xr + r0 * L::XS, QDO ? scaled<TINY>(rg.x[p], sc) : rg.x[p], pc.c1);
+            put<TINY>(xr + r0 * L::XS, QDO && !scale ? scaled<TINY>(x, sc) : x, pc.c1);
             put<TINY>(yr + r0 * L::YS, y, pc.c1);
             if (!pc.fnone) {
-                put<TINY>(fr + r0 * L::XS, rg.fa[p], pc.f1d);
-                if (DQK == 64) put<TINY>(fr1 + r0 * L::XS, rg.fb[p], pc.f1d);
+                put<TINY>(fr + r0 * L::XS, fa, pc.f1d);
+                if (DQK == 64) put<TINY>(fr1 + r0 * L::XS, fb, pc.f1d);
             }
         }
     }
