@@ -166,7 +166,8 @@ hipError_t launch_delta_gated(const Geo &g, int dtype, const void *out_raw, cons
                               float *delta, void *dout, void *dgate, hipStream_t st);
 // delta[u][i] = dO[i].O[i] per head (dtype = RIB_F32 / RIB_BF16 storage of out, dout).
 hipError_t launch_delta(const Geo &g, int dtype, const void *out, const void *dout, float *delta, hipStream_t st);
-// dF[hd][e] = sum over windows (ascending) of part[(w*heads + hd)][e].
+// dF[hd][e] = sum over windows of part[(w*heads + hd)][e]: up to 16 runs of consecutive windows, each in ascending order, then
+// the runs in ascending order.  How many runs depends on the sizes alone.
 hipError_t launch_reduce_df(const Geo &g, const float *part_q, const float *part_k, float *dfq, float *dfk,
                             hipStream_t st);
 

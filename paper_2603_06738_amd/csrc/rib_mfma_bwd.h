@@ -33,8 +33,9 @@
 //   serves every window of more tokens than one workgroup holds (rib_mfma_unit.h), and of 64 and more where those do not: a last partial tile repeats the window's last token
 //   and masks its rows of S (the separate kernels for windows that were not whole 256-token blocks,
 //   with their predicated staging, took 656 us where these take about 280 us: 24 x 24 windows, 8 x 96 x 96
-//   tokens, 6 heads, d = 30, r = 18).  Registers: with 64 columns the four-wave dkv spills 10 to 14 of them, dq 33 to 99 where
-//   the window side is no multiple of 8 (21 to 49 with 48 columns).
+//   tokens, 6 heads, d = 30, r = 18).  Registers spilled: none with 32 columns, and none with 48 where the window side
+//   is a multiple of 8.  With 64 dkv spills 4 to 13 (odd sides 9 to 26), in eight waves and in groups up to 12; dq, on sides that are no multiple of 8
+//   only, 17 to 45 with 48 columns and 29 to 69 with 64 (two-channel heads 95).
 //
 //   The last r columns of dQ_aug / dK_aug are this unit's contribution to dF_q /
 //   dF_k (Sec. 3.1: the RIB features are shared by all windows); they go to a
@@ -267,7 +268,8 @@ __device__ __forceinline__ void take_sums(f32x16 (&acc)[N][M], const float *part
     const int ntiles = (g.N + T - 1) / T;                                                                  \
     if (!ALN) __syncthreads();
 
-// dQ (+ dF_q partial).  A lane stages at most two tokens a tile: T = 64 with 4 waves (NT = 256 lanes; dkv also 8), T = 32 with 2 or 3.
+// dQ (+ dF_q partial).  A lane stages at most two tokens a tile: T = 64 with 4 waves (NT = 256 lanes; dkv also 8), T = 32 with 2 or 3;
+// in two groups of waves T = 64 and in four T = 128, with 8 (both kernels).
 //
 // One step is one 32x32 block s = (key block, query block); its instructions are written in the
 // order they should issue and pinned with scheduling fences: the 5 score MFMAs of block s + 1 and

@@ -16,13 +16,16 @@
 //
 // delta = dO . O is made by the 8 lanes that stage a query row, which have its dO words already.
 //
-// Workgroups of 2, 4 and 8 waves: up to 128, 256, 512 tokens.  246 to 256 registers, two waves a SIMD; up to 256 tokens
-// 61 to 81 KB of LDS, so that two workgroups share a CU.  What bounds it (16x16 windows, d = 30, r = 18; clk of
+// Workgroups of 2, 4 and 8 waves: up to 128, 256, 512 tokens.  246 to 256 registers, two waves a SIMD; spilled are none with 32
+// columns, up to 5 with 48 and up to 22 with 64 (two waves; up to 7 with four and eight).  LDS with 32 / 48 / 64 columns: 35 / 41 / 48 KB
+// up to 128 tokens, 60 / 70 / 80 KB up to 256, so that two workgroups share a CU, 109 / 127 / 146 KB up to 512.  What bounds it (16x16 windows, d = 30, r = 18; clk of
 // a workgroup, two on the CU): start 10 000, a tile 4 200 (dQ 1 500, scores and gradients 2 400, barrier 200; the SIMD's
 // MFMAs 1 800, the CU's LDS accesses 1 800), end 7 800.  Forward + backward, us, with the pair / here / here
 // with the sums of RIB gradients as they are now (d = 30 and 6 heads unless said): 16 images 96 x 96 of 16x16, r = 18 432 / 348 / 329; 96 x 96
 // of 12x12, r = 16 728 / 389 / 340 (144 tokens: the pair gives each wave a half-empty tile); 96 x 96 of 8x8, r = 16 595 / 462 / 344; 8
-// images 66 x 66 of 22x22, d = r = 32, 8 heads 331 / 239 / 223; one 22x22 window of 2 heads 60 / 55, one 8x8 25 / 20.  Past 512 tokens a second group of keys would need dQ kept
+// images 66 x 66 of 22x22, d = r = 32, 8 heads 331 / 239 / 223; one 22x22 window of 2 heads 60 / 55, one 8x8 25 / 20.  On grids of one round the pair shares its streamed side
+// in two groups of waves, and is slower all the same (backward, d = 30, r = 16, groups / here: one 16x16 window of 2 heads 27 / 20, one
+// 22x22 45 / 42, 32 of 17x17, 4 heads 43 / 33).  Past 512 tokens a second group of keys would need dQ kept
 // in memory between the two, and the pair's loops take no longer a block than this one's.
 #pragma once
 

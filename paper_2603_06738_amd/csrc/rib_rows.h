@@ -2,7 +2,8 @@
 // forward kernel for windows of any size): operand types, the LDS image of a streamed tile, the
 // window map, and the staging of a tile from the grid tensors into that image.
 //
-// A streamed tile lies in LDS as plain token rows, written as 16-byte pieces by 4 lanes a token (rows of under 8 values: 8 bytes, 8 lanes); the
+// A streamed tile lies in LDS as plain token rows, written as 16-byte pieces by 4 lanes a token (8 bytes, 8 lanes: rows of under 8 values, workgroups of
+// eight waves in which all stage, kernels whose registers 16 bytes would spill); the
 // operands of products that contract over tokens are read TRANSPOSED from the same rows
 // (ds_read_b64_tr_b16).  A last partial tile repeats the window's last token, with zeros in place of its
 // V / dO, and the kernels mask its rows of the scores.

@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kThreads) void valu_bwd_dkv_kernel(Geo g, int nblk,
 
 // dF[hd][e] = sum over windows w of part[(w*heads + hd)][e]; e over N*r, VEC of them a lane.  A workgroup's lanes are
 // `slices` groups that each sum a run of windows (eight loads in flight), added through LDS in ascending order: the
-// order is fixed by the sizes.
+// order is fixed by the sizes (VEC does not enter it).
 template <int VEC>
 __global__ __launch_bounds__(kThreads) void reduce_df_kernel(int64_t per_head, int heads, int blocks, int nwin, int slices, const float *__restrict__ part_q,
                                                              const float *__restrict__ part_k,
