@@ -9,7 +9,8 @@ from paper_2603_06738_amd import binding as rb
 from paper_2603_06738_amd import workloads as wk
 
 INF = float("inf")
-SHAPES = [(30, 16, 9), (32, 16, 9), (30, 34, 11), (16, 14, 13), (24, 0, 15), (30, 16, 17), (30, 18, 8), (30, 16, 24)]
+SHAPES = [(30, 16, 9), (32, 16, 9), (30, 34, 11), (16, 14, 13), (24, 0, 15), (30, 16, 17), (30, 18, 8), (30, 16, 24),
+          (30, 16, 33), (32, 16, 40), (30, 34, 41)]     # four groups of waves, blocks of the last tile past the window
 
 
 def both(wl, t, names, flags=0):
